@@ -47,7 +47,8 @@ struct ScanPlan {
 
 static ScanPlan plan_scan(int R, int V) {
   ScanPlan p;
-  p.threads = (R >= 256 || R <= 16) ? SCAN_SMALL : SCAN_BIG;  // measured on MI355X
+  // (rows of at most two small tiles: a sixteen-wave workgroup would leave most of its waves without a value)
+  p.threads = (R >= 256 || R <= 16 || V <= 2 * scan_tile(SCAN_SMALL)) ? SCAN_SMALL : SCAN_BIG;  // measured on MI355X
   const int tile = scan_tile(p.threads);
   const int n_tiles = (V + tile - 1) / tile;
   // few rows: slice them until the chip is full (measured best)
@@ -441,9 +442,14 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
     // the K-th largest of the workgroup's group maxima (K elements of the tile reach it), or of
     // this wave's 64 lane maxima; afterwards also the wave's own K-th entry once its list is full.
     if (tile == 0) {
-      if (K <= SCAN_GROUPS) {
-        // maxima of the waves, or of their rows of 16 lanes when there are fewer waves than K
-        const bool by_wave = K <= SCAN_WAVES;
+      // Groups that hold no value of the row have no maximum: counting them, the K-th largest of the
+      // maxima would be -inf and every value of a short row would be inserted one by one (17 rows of
+      // 1024 logits: 26.8 us; with the groups counted and four-wave workgroups see plan_scan).
+      const int n_here = min(V - tbase, SCAN_TILE);  // the tile's values; 4 neighbouring ones to a thread
+      const int waves_here = min((n_here + 255) >> 8, SCAN_WAVES), groups_here = min((n_here + 63) >> 6, SCAN_GROUPS);
+      if (K <= groups_here) {
+        // maxima of the waves, or of their rows of 16 lanes when fewer waves than K hold values
+        const bool by_wave = K <= waves_here;
         const int n_groups = by_wave ? SCAN_WAVES : SCAN_GROUPS;
         if (by_wave) {
           const float wm = wave_max(tm);
