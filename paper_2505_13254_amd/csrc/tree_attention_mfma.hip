@@ -181,13 +181,16 @@ __device__ __forceinline__ void wait_lds(int n) {  // n is a constant once the w
 // BIG: trees of more than MF_MAX_M rows may occur; the ancestor table comes from a.anc_tiles.
 // HALF: head dimension 64.  Two neighbouring KV heads of a token are 256 contiguous bytes, i.e. one
 // row of this kernel, and a.Hkv / a.G count such pairs and the 2 G query heads that read them.  A
-// query row is widened to 128 elements with zeros on the other head's side, so its scores see its own
-// KV head only; the second product yields both heads' values and the row's own half is stored.  The
-// matrix cores do twice the arithmetic; K and V are still read once, in whole 256-byte rows.
+// wave's rows all belong to one head of the pair, whose half of the 256-byte rows it multiplies; K and
+// V are read once, in whole rows.  (Query rows widened to 128 elements with zeros took twice the matrix
+// instructions: 32 query heads, trees of 21 to 97 rows on 700 to 6001 tokens, 26.2 us -> 20.3 us.)
 template <bool PAGED, bool ONCE, bool BIG, bool HALF>
 __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_max) {
   constexpr int Q_ROW_BYTES = HALF ? MF_ROW_BYTES / 2 : MF_ROW_BYTES;  // a row of Q and of O
-  constexpr int Q_LOADS = HALF ? 4 : 8;                                 // 16-byte loads of a lane's part of it
+  constexpr int NK = HALF ? 4 : 8;  // matrix instructions (and K fragments) of a 32-key score block
+  constexpr int NT = HALF ? 2 : 4;  // 32-column blocks of a head's output row
+  constexpr int STEPS = NK / 2;     // steps of two matrix instructions in a window
+  constexpr int EPS = 4 / STEPS;    // pairs of exponentials a step takes along
   static_assert(!(BIG && ONCE), "more than 256 tree rows are several row groups");
   static_assert(MF_NBUF * MF_ANC_SLICE == MF_MAX_M * 8, "the slice ring of large trees takes the place of the table");
   __shared__ __attribute__((aligned(16))) char lds_k[MF_NBUF][MF_TILE_BYTES];
@@ -281,7 +284,21 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     sp = x / n_rg_max;
     if (rg >= (G * M + MF_ROWS - 1) / MF_ROWS || sp >= n_sp) return;
   }
-  const int R = G * M;
+  // Rows.  The rows of a (pair of) KV head(s) are numbered head by head in blocks of 32, tree row by tree
+  // row inside a head: block b belongs to head b / nbh of the pair and holds its rows 32 (b % nbh) ...
+  // (HALF: a wave's rows all read the same head of the pair, so it multiplies that head's half of the
+  // 256-byte K and V rows only).  A row group is up to eight blocks.
+  const int Gh = HALF ? G >> 1 : G;      // query heads per KV head
+  const int Rh = Gh * M;                  // rows of a KV head
+  const int nbh = (Rh + 31) >> 5;
+  const int n_blk = HALF ? 2 * nbh : nbh;
+  constexpr int BLK_MAX = MF_ROWS / 32;
+  const int blk0 = rg * BLK_MAX;
+  const int blk_n = n_blk - blk0 < BLK_MAX ? n_blk - blk0 : BLK_MAX;  // blocks of this group
+  const int my_blk = blk0 + wave;
+  const bool wave_active = wave < blk_n;
+  const int hb = HALF && my_blk >= nbh ? 1 : 0;          // head of the pair
+  const int row_base = (my_blk - hb * nbh) * 32;          // of the head's rows
 
   const char* kp = static_cast<const char*>(h_k_prefix) + ((PAGED ? 0 : p0) * Hkv + g) * MF_ROW_BYTES;
   const char* vp = static_cast<const char*>(h_v_prefix) + ((PAGED ? 0 : p0) * Hkv + g) * MF_ROW_BYTES;
@@ -295,8 +312,13 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const int n_ptiles = (int)((k_hi - k_lo + MF_TILE - 1) / MF_TILE);
   // (large trees: tree rows behind the last row of this row group are on nobody's root path, their tiles are left out)
   int tree_keys = M;
-  if constexpr (BIG)
-    if ((rg + 1) * MF_ROWS < R) tree_keys = ((rg + 1) * MF_ROWS - 1) / G + 1;
+  if constexpr (BIG) {
+    const int last = blk0 + blk_n - 1;
+    if (!HALF || blk0 >= nbh || last < nbh) {  // (all of one head)
+      const int past = (last - (HALF && blk0 >= nbh ? nbh : 0)) * 32 + 32;  // first row behind the group
+      if (past < Rh) tree_keys = (past - 1) / Gh + 1;
+    }
+  }
   const int n_ttiles = last_split ? (tree_keys + MF_TILE - 1) / MF_TILE : 0;
   const int n_tiles = n_ptiles + n_ttiles;  // >= 1: a split holds prefix keys, or it is the last one
   const int n_full = (int)((k_hi - k_lo) / MF_TILE);  // leading tiles made of 64 prefix keys
@@ -320,9 +342,9 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   unsigned anc_lane_off = 0;
   if constexpr (BIG) {
     anc_tbl = h_anc + (size_t)(h_tree_shared ? 0 : n0) * 32;
-    int r = rg * MF_ROWS + wave * 32 + (lane >> 1);
-    r = r < R ? r : R - 1;
-    anc_lane_off = (unsigned)(((r / G) * 2 + (lane & 1)) * 4);
+    int r = row_base + (lane >> 1);
+    r = r < Rh ? r : Rh - 1;
+    anc_lane_off = (unsigned)(((r / Gh) * 2 + (lane & 1)) * 4);
   }
   // Paged caches: the pages of this split's tiles (at most 256) are staged in LDS; the requests
   // go out here, before the Q rows are asked for, so that waiting for them waits for nothing else.
@@ -407,11 +429,9 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // ---- set-up.  Its global reads (parent pointers, Q rows) are requested first and the first two
   // K/V tiles right behind them, so that HBM is busy while the ancestor table is built and Q is
   // converted.  (Loads return in order: waiting for the Q rows never waits for a tile.)
-  const int row_base = rg * MF_ROWS + wave * 32;
-  const bool wave_active = row_base < R;
-  // r / G for a row number r < 2^16 without the integer-division sequence: (r + 0.5) / G is at least
-  // 1 / (2 G) away from an integer, far more than the rounding of the float product
-  const float inv_G = 1.0f / (float)G;
+  // r / Gh for a row number r < 2^16 without the integer-division sequence: (r + 0.5) / Gh is at least
+  // 1 / (2 Gh) away from an integer, far more than the rounding of the float product
+  const float inv_G = 1.0f / (float)Gh;
   auto div_G = [&](int r) { return (int)(((float)r + 0.5f) * inv_G); };
   // These loads are inline assembly like the tile loads: the compiler does not see the tile loads, so
   // a load of its own would be waited for with vmcnt(0), i.e. together with every tile requested
@@ -423,20 +443,19 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     const int32_t* src = h_parent + (h_tree_shared ? 0 : n0) + (tid < M ? tid : 0);  // (one tree for all entries, or each its own)
     asm volatile("global_load_dword %0, %1, off" : "=v"(my_parent) : "v"(src) : "memory");
   }
-  uintx4 qraw[8];
+  uintx4 qraw[NK];
   int tree_row;
   bool row_real;
-  bool q_upper = false;  // HALF: this row's query head reads the second KV head of the pair
+  const int head0 = g * G + hb * Gh;  // first query head of this wave's KV head
   {
     const int r = row_base + col;
-    const int rc = r < R ? r : R - 1;
-    const int i = div_G(rc), gi = rc - i * G;
+    const int rc = r < Rh ? r : Rh - 1;
+    const int i = div_G(rc), gi = rc - i * Gh;
     tree_row = i;
-    row_real = r < R;
-    if constexpr (HALF) q_upper = 2 * gi >= G;
-    const char* qrow = static_cast<const char*>(h_q) + ((int64_t)(n0 + i) * Hq + g * G + gi) * Q_ROW_BYTES + half * 16;
+    row_real = r < Rh;
+    const char* qrow = static_cast<const char*>(h_q) + ((int64_t)(n0 + i) * Hq + head0 + gi) * Q_ROW_BYTES + half * 16;
 #pragma unroll
-    for (int kk = 0; kk < Q_LOADS; ++kk)
+    for (int kk = 0; kk < NK; ++kk)
       asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qraw[kk]) : "v"(qrow), "n"(32 * kk) : "memory");
   }
   issue(0);
@@ -445,7 +464,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // as large as the count waits for no less)
   const int first_tile_loads = 2 * MF_LOADS * (n_tiles < 2 ? n_tiles : 2);
   if constexpr (!BIG) {
-    wait_vm(Q_LOADS + first_tile_loads);  // the parent pointers are there (the Q loads and the tiles are younger)
+    wait_vm(NK + first_tile_loads);  // the parent pointers are there (the Q loads and the tiles are younger)
     asm volatile("" : "+v"(my_parent));
   }
 
@@ -472,19 +491,13 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   wait_vm(first_tile_loads);  // the Q rows are there (the tiles are younger)
   if constexpr (HALF) {
     asm volatile("" : "+v"(qraw[0]), "+v"(qraw[1]), "+v"(qraw[2]), "+v"(qraw[3]));
-    const uintx4 zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {  // the row's 64 elements on its own head's side, zeros on the other
-      qraw[4 + kk] = q_upper ? qraw[kk] : zero;
-      qraw[kk] = q_upper ? zero : qraw[kk];
-    }
   } else {
     asm volatile("" : "+v"(qraw[0]), "+v"(qraw[1]), "+v"(qraw[2]), "+v"(qraw[3]), "+v"(qraw[4]), "+v"(qraw[5]),
                  "+v"(qraw[6]), "+v"(qraw[7]));
   }
-  bf16x8 qf[8];
+  bf16x8 qf[NK];
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
+  for (int kk = 0; kk < NK; ++kk) {
     const bf16x8 raw = __builtin_bit_cast(bf16x8, qraw[kk]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -495,13 +508,13 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     }
   }
 
-  floatx16 acc[4];   // O^T: [d block of 32][16 values]: d = 32 tt + 8 (v / 4) + 4 half + v % 4
+  floatx16 acc[NT];  // O^T: [d block of 32][16 values]: d = 32 tt + 8 (v / 4) + 4 half + v % 4
   floatx16 negm;     // minus the reference maximum in all 16 slots: start value of a score block
   float m_ref = 0.f, l_sum = 0.f;
 #pragma unroll
   for (int v = 0; v < 16; ++v) negm[v] = 0.f;
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
 
@@ -510,19 +523,20 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // K: lane (col, half) reads chunk 2 kk + half of key row col.  V: the transposing read returns, to
   // lane l of a 16-lane group, element l % 4 of the 8-byte pieces addressed by lanes l / 4 + {0, 4,
   // 8, 12} of the group: lane (a = l % 4, j = l / 4) therefore addresses key j of the wanted four at
-  // columns 4a .. 4a+3; fragment f = 4 k2 + tt holds the 16 keys of contraction step k2 for the 32
-  // output columns of d block tt.
+  // columns 4a .. 4a+3; fragment f = NT k2 + tt holds the 16 keys of contraction step k2 for the 32
+  // output columns of d block tt.  (HALF: the second head's half of a row begins at chunk 8.)
   const int tr_a = lane & 3, tr_j = (lane >> 2) & 3, tr_dh = (lane >> 4) & 1;
-  const char* kl[8];
-  const char* vl[8][2];
+  const char* kl[NK];
+  const char* vl[NK][2];
+  const int chunk0 = 8 * hb;
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) kl[kk] = &lds_k[0][0] + swz(col, 2 * kk + half);
+  for (int kk = 0; kk < NK; ++kk) kl[kk] = &lds_k[0][0] + swz(col, chunk0 + 2 * kk + half);
 #pragma unroll
-  for (int f = 0; f < 8; ++f)
+  for (int f = 0; f < NK; ++f)
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-      const int key = 16 * (f >> 2) + 8 * r + 4 * half + tr_j;
-      vl[f][r] = &lds_v[0][0] + swz(key, 4 * (f & 3) + 2 * tr_dh + (tr_a >> 1)) + (tr_a & 1) * 8;
+      const int key = 16 * (f / NT) + 8 * r + 4 * half + tr_j;
+      vl[f][r] = &lds_v[0][0] + swz(key, chunk0 + 4 * (f % NT) + 2 * tr_dh + (tr_a >> 1)) + (tr_a & 1) * 8;
     }
   auto ldk = [&](int off, int kk) { return *reinterpret_cast<const bf16x8*>(kl[kk] + off); };
   auto ldv = [&](int off, int f) {
@@ -583,7 +597,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
 #pragma unroll
     for (int v = 0; v < 16; ++v) negm[v] = -m_ref;
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[tt][v] *= alpha;
   };
@@ -612,7 +626,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     for (int j = 0; j < 4; ++j) pack_pair(exp_pair(S, h, j), P, j);
   };
 
-  bf16x8 kf[8], vf[8];  // fragment registers: four of each are alive at any time
+  bf16x8 kf[NK], vf[NK];  // fragment registers: four of each are alive at any time
   // Score window: S_out = K(block at oq) Q^T, started from -m_ref, in four steps of two matrix
   // instructions.  A step first requests the fragments of the next step (the window's last step:
   // the first two V fragments of the block at ov, whose product window follows), waits for its own,
@@ -626,26 +640,31 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     floatx2 pp[4];
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int sN = j + MF_AHEAD;  // the step whose fragments are requested now (4, 5: product window)
-      if (sN < 4) {
+    for (int j = 0; j < STEPS; ++j) {
+      const int sN = j + MF_AHEAD;  // the step whose fragments are requested now (STEPS: the product window's first)
+      if (sN < STEPS) {
         kf[2 * sN] = ldk(oq, 2 * sN);
         kf[2 * sN + 1] = ldk(oq, 2 * sN + 1);
       } else {
-        vf[2 * (sN - 4)] = ldv(ov, 2 * (sN - 4));
-        vf[2 * (sN - 4) + 1] = ldv(ov, 2 * (sN - 4) + 1);
+        vf[2 * (sN - STEPS)] = ldv(ov, 2 * (sN - STEPS));
+        vf[2 * (sN - STEPS) + 1] = ldv(ov, 2 * (sN - STEPS) + 1);
       }
       int pending = 0;  // LDS reads requested after those of step j: K steps count 2, V steps 4
 #pragma unroll
-      for (int d = 1; d <= MF_AHEAD; ++d) pending += (j + d < 4) ? 2 : 4;
+      for (int d = 1; d <= MF_AHEAD; ++d) pending += (j + d < STEPS) ? 2 : 4;
       wait_lds(pending);
       S_out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[2 * j], qf[2 * j], j == 0 ? negm : S_out, 0, 0, 0);
-      pp[j] = exp_pair(S_in, h, j);
+#pragma unroll
+      for (int e = EPS * j; e < EPS * (j + 1); ++e) pp[e] = exp_pair(S_in, h, e);
       S_out = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[2 * j + 1], qf[2 * j + 1], S_out, 0, 0, 0);
-      if (j > 0) pack_pair(pp[j - 1], P, j - 1);
+      if (j > 0) {
+#pragma unroll
+        for (int e = EPS * (j - 1); e < EPS * j; ++e) pack_pair(pp[e], P, e);
+      }
       MF_PIN();
     }
-    pack_pair(pp[3], P, 3);
+#pragma unroll
+    for (int e = EPS * (STEPS - 1); e < 4; ++e) pack_pair(pp[e], P, e);
     __builtin_amdgcn_s_setprio(0);
   };
   // Product window: O^T += V^T(block at ov) P^T with P = (P0, P1), same step structure; its last
@@ -658,29 +677,39 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     const bf16x8 b0 = __builtin_bit_cast(bf16x8, P0), b1 = __builtin_bit_cast(bf16x8, P1);
     floatx2 pp[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < STEPS; ++j) {
       const int sN = j + MF_AHEAD;
-      if (sN < 4) {
+      if (sN < STEPS) {
         vf[2 * sN] = ldv(ov, 2 * sN);
         vf[2 * sN + 1] = ldv(ov, 2 * sN + 1);
       } else if (KF) {
-        kf[2 * (sN - 4)] = ldk(oq, 2 * (sN - 4));
-        kf[2 * (sN - 4) + 1] = ldk(oq, 2 * (sN - 4) + 1);
+        kf[2 * (sN - STEPS)] = ldk(oq, 2 * (sN - STEPS));
+        kf[2 * (sN - STEPS) + 1] = ldk(oq, 2 * (sN - STEPS) + 1);
       }
       if (KF) {
         int pending = 0;
 #pragma unroll
-        for (int d = 1; d <= MF_AHEAD; ++d) pending += (j + d < 4) ? 4 : 2;
+        for (int d = 1; d <= MF_AHEAD; ++d) pending += (j + d < STEPS) ? 4 : 2;
         wait_lds(pending);
       }
-      acc[(2 * j) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[2 * j], j < 2 ? b0 : b1, acc[(2 * j) & 3], 0, 0, 0);
-      if (EXP) pp[j] = exp_pair(S_in, h, j);
-      acc[(2 * j + 1) & 3] =
-          __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[2 * j + 1], j < 2 ? b0 : b1, acc[(2 * j + 1) & 3], 0, 0, 0);
-      if (EXP && j > 0) pack_pair(pp[j - 1], P, j - 1);
+      acc[(2 * j) % NT] =
+          __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[2 * j], 2 * j < NT ? b0 : b1, acc[(2 * j) % NT], 0, 0, 0);
+      if (EXP) {
+#pragma unroll
+        for (int e = EPS * j; e < EPS * (j + 1); ++e) pp[e] = exp_pair(S_in, h, e);
+      }
+      acc[(2 * j + 1) % NT] =
+          __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[2 * j + 1], 2 * j < NT ? b0 : b1, acc[(2 * j + 1) % NT], 0, 0, 0);
+      if (EXP && j > 0) {
+#pragma unroll
+        for (int e = EPS * (j - 1); e < EPS * j; ++e) pack_pair(pp[e], P, e);
+      }
       MF_PIN();
     }
-    if (EXP) pack_pair(pp[3], P, 3);
+    if (EXP) {
+#pragma unroll
+      for (int e = EPS * (STEPS - 1); e < 4; ++e) pack_pair(pp[e], P, e);
+    }
     __builtin_amdgcn_s_setprio(0);
   };
   const std::true_type YES{};
@@ -696,17 +725,17 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     // ---- first block: it always has a visible key (a prefix token, or the root), and its exact
     // maximum is the reference of the whole pass
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) kf[kk] = ldk(0, kk);
+    for (int kk = 0; kk < NK; ++kk) kf[kk] = ldk(0, kk);
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], kk == 0 ? negm : sA, 0, 0, 0);
+    for (int kk = 0; kk < NK; ++kk) sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], kk == 0 ? negm : sA, 0, 0, 0);
     if (n_plain < 1) mask_block(0, sA);
     {
       const float mx = row_max(sA);
 #pragma unroll
       for (int v = 0; v < 16; ++v) sA[v] -= mx;
       set_reference(mx);
-      exp_half(sA, 0, pa);
     }
+    exp_half(sA, 0, pa);
 #pragma unroll
     for (int kk = 0; kk < 2 * MF_AHEAD; ++kk) kf[kk] = ldk(blk_off(0, 1), kk);
     // ---- one trip per tile t (blocks 2t and 2t + 1, ring slot s = t % 4); the barrier in its
@@ -770,7 +799,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
 #pragma unroll
     for (int v = 0; v < 16; ++v) negm[v] = 0.f;
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[tt][v] = 0.f;
     issue(0);
@@ -783,7 +812,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       const int off = blk_off((blk >> 1) % MF_NBUF, blk & 1);
       floatx16 S;
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk)
+      for (int kk = 0; kk < NK; ++kk)
         S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ldk(off, kk), qf[kk], kk == 0 ? negm : S, 0, 0, 0);
       if (blk >= n_plain) mask_block(blk, S);
       const float mx = row_max(S);
@@ -802,8 +831,8 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       l_sum += l0 + l1;
       const bf16x8 b0 = __builtin_bit_cast(bf16x8, P0), b1 = __builtin_bit_cast(bf16x8, P1);
 #pragma unroll
-      for (int f = 0; f < 8; ++f)
-        acc[f & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ldv(off, f), f < 4 ? b0 : b1, acc[f & 3], 0, 0, 0);
+      for (int f = 0; f < NK; ++f)
+        acc[f % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ldv(off, f), f < NT ? b0 : b1, acc[f % NT], 0, 0, 0);
     }
     l_tot = l_sum + __shfl_xor(l_sum, 32);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -812,13 +841,14 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
 
   if (n_sp == 1) {
     // ---- results, sequence with a single split: normalised rows go out as bf16.  Each wave turns its
-    // 32 x 128 block around in LDS (the tile ring is free: every wave has passed the last barrier),
-    // so that a lane stores 16 contiguous bytes and a store instruction covers four whole rows.
-    constexpr int ST_ROW = MF_ROW_BYTES + 16;  // padded row: the 8-byte writes of 16 rows spread over all banks
+    // block around in LDS (the tile ring is free: every wave has passed the last barrier),
+    // so that a lane stores 16 contiguous bytes and a store instruction covers whole rows.
+    constexpr int CPR = 4 * NT;  // 16-byte chunks of a row
+    constexpr int ST_ROW = 64 * NT + 16;  // padded row: the 8-byte writes of 16 rows spread over all banks
     char* stage = wave < 4 ? lds_k[wave] : lds_v[wave - 4];
     const float inv = 1.f / l_tot;
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
         const int d0 = 32 * tt + 8 * b + 4 * half;
@@ -830,20 +860,19 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
         *reinterpret_cast<uint2*>(stage + col * ST_ROW + d0 * 2) = pk;
       }
     const int r = row_base + col;
-    if (h_lse && half == 0 && r < R) {
-      const int i = div_G(r), gi = r - i * G;
-      h_lse[(int64_t)(n0 + i) * Hq + g * G + gi] = (m_ref + __log2f(l_tot)) * MF_LN2;
+    if (h_lse && half == 0 && r < Rh) {
+      const int i = div_G(r), gi = r - i * Gh;
+      h_lse[(int64_t)(n0 + i) * Hq + head0 + gi] = (m_ref + __log2f(l_tot)) * MF_LN2;
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's staging writes are in LDS
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int row_l = 4 * j + (lane >> 4), chunk = lane & 15;
+    for (int j = 0; j < CPR / 2; ++j) {
+      const int row_l = (64 / CPR) * j + lane / CPR, chunk = lane % CPR;
       const int ro = row_base + row_l;
-      const int i = div_G(ro < R ? ro : 0), gi = ro - i * G;
-      // (HALF: the eight chunks on the side of the row's own KV head are its 64 output elements)
-      if (ro < R && (!HALF || (chunk >> 3) == (2 * gi >= G ? 1 : 0))) {
+      const int i = div_G(ro < Rh ? ro : 0), gi = ro - i * Gh;
+      if (ro < Rh) {
         const uint4 val = *reinterpret_cast<const uint4*>(stage + row_l * ST_ROW + chunk * 16);
-        char* dst = static_cast<char*>(h_o) + ((int64_t)(n0 + i) * Hq + g * G + gi) * Q_ROW_BYTES + (HALF ? chunk & 7 : chunk) * 16;
+        char* dst = static_cast<char*>(h_o) + ((int64_t)(n0 + i) * Hq + head0 + gi) * Q_ROW_BYTES + chunk * 16;
         // non-temporal: the rows start their way to memory now instead of waiting in L2 for the
         // write-back at the end of the kernel, when every workgroup's rows would go at once
         __builtin_nontemporal_store(__builtin_bit_cast(uintx4, val), reinterpret_cast<uintx4*>(dst));
@@ -852,20 +881,18 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   } else {
     // ---- this split's partial record: unnormalised accumulators, reference maximum, denominator
     const int r = row_base + col;
-    if (r < R) {
-      const int i = div_G(r), gi = r - i * G;
-      const int64_t row = (int64_t)(n0 + i) * Hq + g * G + gi;
-      constexpr int REC_D = HALF ? 64 : 128;  // a record: o[REC_D], m, l, two pad floats
+    if (r < Rh) {
+      const int i = div_G(r), gi = r - i * Gh;
+      const int64_t row = (int64_t)(n0 + i) * Hq + head0 + gi;
+      constexpr int REC_D = 32 * NT;  // a record: o[REC_D], m, l, two pad floats
       float* rec = h_part + (row * h_sp_max + sp) * (REC_D + ATTN_REC_PAD);
-      const int own = 2 * gi >= G ? 1 : 0;  // HALF: the side of the row's own KV head
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt)
+      for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           const int d0 = 32 * tt + 8 * b + 4 * half;
           float4 f = {acc[tt][4 * b], acc[tt][4 * b + 1], acc[tt][4 * b + 2], acc[tt][4 * b + 3]};
-          if (!HALF) *reinterpret_cast<float4*>(rec + d0) = f;
-          else if ((tt >> 1) == own) *reinterpret_cast<float4*>(rec + (d0 & 63)) = f;
+          *reinterpret_cast<float4*>(rec + d0) = f;
         }
       if (half == 0) {
         rec[REC_D] = m_ref * MF_LN2;

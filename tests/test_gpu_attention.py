@@ -260,7 +260,7 @@ def test_ragged_batches_with_large_trees(G, seed):
 @pytest.mark.parametrize("M,L", [(61, 300), (129, 1000), (300, 70), (9, 0), (64, 2100)])
 def test_head_dimension_64_in_bfloat16(G, M, L, hq, hkv):
     """bfloat16 with D = 64 runs on the matrix cores too: the kernel takes the KV heads in pairs (two heads of
-    a token are one 256-byte row) and widens each query row with zeros on the other head's side.  One and
+    a token are one 256-byte row); a wave's rows belong to one head of the pair.  One and
     several row groups, large trees, an empty prefix, a prefix cut into splits."""
     import paper_2505_13254_amd as hs
     w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=64)

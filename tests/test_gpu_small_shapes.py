@@ -33,3 +33,14 @@ def test_short_rows(G, R, V, K):
     assert np.array_equal(got["topk_idx"], want["topk_idx"])
     for k in ("ent_topk", "ent_full"):
         assert G.entropy_err(got[k], want[k]) <= 1.0, k
+
+
+@pytest.mark.parametrize("hq,hkv", [(4, 4), (8, 4), (6, 2)])
+@pytest.mark.parametrize("M", [1, 31, 32, 33, 128, 129, 257])
+def test_head_dimension_64_row_blocks(G, hq, hkv, M):
+    """Head dimension 64: the 32-row blocks of a pair of KV heads are numbered head by head, so a head's
+    last block may be short, and a row group may hold rows of one head or of both."""
+    from test_gpu_attention import _case, _compare, _random_parents
+    w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=64)
+    rs = np.random.RandomState(M)
+    _compare(G, _case(w, M, [_random_parents(rs, M, back=9), _random_parents(rs, 5)], [333, 64], "unit"), "bf16")
