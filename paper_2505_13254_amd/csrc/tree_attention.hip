@@ -305,6 +305,13 @@ constexpr float PLAN_ITEM_US = 10.f;
 // item's fixed cost: one layer of the 8B shape (32 tiles a head) takes 25.9 us cut into 4 x 8 tiles, 23.5 us
 // into 8 x 4 or 16 x 2, combine launch included.
 constexpr int PLAN_MIN_SPLIT_TILES = 2;
+// A launch of at most half as many items as compute units gives each item two workgroups of up to 128 rows,
+// in which two waves share a row block and take every other 32 keys: 0.65 us a tile instead of 1.03 on an
+// otherwise idle chip (33 and 126 tiles a workgroup, 244 rows: 43.9 and 140 us -> 31.2 and 91 us).  The fixed
+// 10 us of an item and a combine launch of 3.5 us + its records at 4.5 TB/s were fitted to the same sweeps
+// (one layer of 2048 and of 8000 tokens, 1 to 33 splits; within 2 us of all of them).
+constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2;
+constexpr float PLAN_NARROW_TILE_US = 0.65f;
 constexpr int PLAN_MIN_SPLIT_TOKENS = PLAN_MIN_SPLIT_TILES * 64;
 static inline float plan_tile_us(int waves) { return 1.25f + 0.04f * (float)waves; }
 
@@ -362,18 +369,18 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   // Unequal items (a ragged batch): the makespan of each candidate is found by replaying the
   // hardware's dispatch, which hands the next workgroup in index order to the first compute unit
   // that falls free (list scheduling).  Equal items (the layers of one step) run in whole rounds.
-  static const int targets[] = {1 << 20, 192, 160, 128, 112, 96, 80, 72, 64, 56, 48, 40, 32, 24, 16, 8, 4, 2};
+  static const int targets[] = {1 << 20, 192, 160, 128, 112, 96, 80, 72, 64, 56, 48, 40, 32, 24, 16, 12, 8, 6, 4, 2};
   // Cuts finer than eight tiles are candidates only while eight-tile items would leave compute units idle
   // (a launch of one or two layers): such an item is mostly its fixed cost.
   int64_t coarse_items = 0;
   for (int i = 0; i < n; ++i) coarse_items += (int64_t)a.Hkv * seqs[i].rg * (seqs[i].tiles / 8 > 0 ? seqs[i].tiles / 8 : 1);
-  const int n_targets = (int)(sizeof(targets) / sizeof(targets[0])) - (coarse_items < PLAN_CUS ? 0 : 2);
+  const int n_targets = (int)(sizeof(targets) / sizeof(targets[0])) - (coarse_items < PLAN_CUS ? 0 : 3);
   ListPlan best{0.f, 0};
   static thread_local std::vector<float> item_cost, cu_free;  // (kept between calls: no allocation in the steady state)
   for (int ti = 0; ti < n_targets; ++ti) {
     const int target = targets[ti];
     double total = 0.0, rec_bytes = 0.0;
-    float mx = 0.f, mn = 1e30f;
+    float mx = 0.f, mn = 1e30f, mx_narrow = 0.f;
     int64_t items = 0;
     int ord[ATTN_TBL];
     float seq_cost[ATTN_TBL];
@@ -387,10 +394,16 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       total += (double)a.Hkv * nsp * ((q.rg - 1) * one + one_last);
       items += (int64_t)a.Hkv * nsp * q.rg;
       if (big > mx) mx = big;
+      mx_narrow = std::max(mx_narrow, PLAN_ITEM_US + (float)(per + q.ttiles) * PLAN_NARROW_TILE_US);
       if (one_last < mn) mn = one_last;
       if (nsp > 1) rec_bytes += (double)q.M * a.Hq * nsp * ((a.half ? 64 : 128) + ATTN_REC_PAD) * 4 * 2;  // written, then read
       ord[i] = i;
       seq_cost[i] = (float)per * plan_tile_us(q.waves0);
+    }
+    if (items <= PLAN_NARROW_ITEMS) {  // every workgroup has a compute unit: the longest item decides
+      const float est = mx_narrow + (rec_bytes > 0.0 ? 3.5f + (float)(rec_bytes / 4.5e6) : 0.f);
+      if (best.target == 0 || est < best.est_us) best = ListPlan{est, target};
+      continue;
     }
     // (no schedule ends before the work divided by the compute units, nor before its longest item: a
     // candidate whose bound is no better than the best estimate so far needs no replay)
@@ -471,6 +484,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   }
   a.n_tbl = n;
   a.n_items = (int)first;
+  a.narrow = first <= PLAN_NARROW_ITEMS ? 1 : 0;
   a.sp_max = sp_max;
   return true;
 }
@@ -482,7 +496,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
 struct PlanMemo {
   std::vector<int64_t> key;  // everything the plan is a function of; empty: unused slot
   bool ok;
-  int n_tbl, n_items, sp_max;
+  int n_tbl, n_items, narrow, sp_max;
   SeqEntry tbl[ATTN_TBL];
 };
 constexpr int PLAN_MEMO_SLOTS = 4;
@@ -512,6 +526,7 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
       if (m.ok) {
         a.n_tbl = m.n_tbl;
         a.n_items = m.n_items;
+        a.narrow = m.narrow;
         a.sp_max = m.sp_max;
         memcpy(a.tbl, m.tbl, sizeof(SeqEntry) * (size_t)m.n_tbl);
       }
@@ -523,6 +538,7 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
   if (m.ok) {
     m.n_tbl = a.n_tbl;
     m.n_items = a.n_items;
+    m.narrow = a.narrow;
     m.sp_max = a.sp_max;
     memcpy(m.tbl, a.tbl, sizeof(SeqEntry) * (size_t)a.n_tbl);
   }
@@ -668,7 +684,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   a.block_table = block_table; a.max_blocks = max_blocks;
   a.B = B; a.Hq = Hq; a.Hkv = mfma ? kv_units : Hkv; a.G = mfma ? g_unit : Hq / Hkv; a.half = mfma && pairs ? 1 : 0; a.scale = scale;
   a.o = o; a.lse = lse; a.part = static_cast<float*>(workspace);
-  a.n_tbl = 0; a.n_items = 0; a.anc_tiles = nullptr;
+  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.anc_tiles = nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // the workspace query bounds the splits of a sequence the same way
   const int64_t sp_bound = total_prefix / PLAN_MIN_SPLIT_TOKENS + 1;

@@ -220,19 +220,19 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   float* const h_lse = a.lse;
   float* const h_part = a.part;
   const float h_scale = a.scale;
-  const int h_sp_max = a.sp_max, h_n_tbl = a.n_tbl, h_tree_shared = a.tree_shared;
+  const int h_sp_max = a.sp_max, h_n_tbl = a.n_tbl, h_tree_shared = a.tree_shared, h_narrow = a.narrow;
   const int G = a.G, Hkv = a.Hkv, Hq = a.Hq;
   asm volatile("" : "+v"(t0_lo), "+v"(t0_hi));  // (keeps the request here instead of inside the branch that uses it)
   asm volatile("" ::"s"(h_q), "s"(h_k_prefix), "s"(h_v_prefix), "s"(h_k_tree), "s"(h_v_tree), "s"(h_parent), "s"(h_o),
                "s"(h_lse), "s"(h_part), "s"(h_scale), "s"(h_sp_max), "s"(h_n_tbl), "s"(G), "s"(Hkv), "s"(Hq),
-               "s"(n_rg_max), "s"(h_tree_shared));
+               "s"(n_rg_max), "s"(h_tree_shared), "s"(h_narrow));
   int n0, M, g, rg, sp, n_sp, tiles_per_split;
   int64_t p0, L;
   if (h_n_tbl > 0) {
     // Work-list launch: the table of sequences sits in the kernel arguments; lane l fetches entry
     // l (and l + 64), a ballot finds the entry whose item range holds this workgroup, and its
     // fields are read from that lane: one memory round trip, no dependent offset loads.
-    const int x = blockIdx.x;
+    const int x = blockIdx.x, item = x >> h_narrow;  // (narrow launches: two workgroups to an item of the table)
     unsigned f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int base = 0; base < h_n_tbl; base += 64) {
       const int idx = base + lane;
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
         lo = *reinterpret_cast<const uintx4*>(&a.tbl[idx]);
         hi = *(reinterpret_cast<const uintx4*>(&a.tbl[idx]) + 1);
       }
-      const unsigned long long below = __ballot((int)lo[0] <= x);  // entries are in rising first_item order
+      const unsigned long long below = __ballot((int)lo[0] <= item);  // entries are in rising first_item order
       if (below == 0ull) break;
       const int e = __builtin_popcountll(below) - 1;
 #pragma unroll
@@ -262,8 +262,8 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     p0 = (int64_t)(((unsigned long long)f[5] << 32) | f[4]);
     tiles_per_split = (int)f[6];
     n_sp = (int)(short)(f[7] & 0xffffu);
-    const int n_rg = (int)(short)(f[7] >> 16);
-    int local = x - (int)f[0];
+    const int n_rg = (int)(short)(f[7] >> 16) << h_narrow;
+    int local = x - ((int)f[0] << h_narrow);
     g = local % Hkv;
     local /= Hkv;
     rg = local % n_rg;
@@ -287,16 +287,27 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // Rows.  The rows of a (pair of) KV head(s) are numbered head by head in blocks of 32, tree row by tree
   // row inside a head: block b belongs to head b / nbh of the pair and holds its rows 32 (b % nbh) ...
   // (HALF: a wave's rows all read the same head of the pair, so it multiplies that head's half of the
-  // 256-byte K and V rows only).  A row group is up to eight blocks.
+  // 256-byte K and V rows only).  A row group is up to eight blocks, in narrow launches up to four.
   const int Gh = HALF ? G >> 1 : G;      // query heads per KV head
   const int Rh = Gh * M;                  // rows of a KV head
   const int nbh = (Rh + 31) >> 5;
   const int n_blk = HALF ? 2 * nbh : nbh;
-  constexpr int BLK_MAX = MF_ROWS / 32;
-  const int blk0 = rg * BLK_MAX;
-  const int blk_n = n_blk - blk0 < BLK_MAX ? n_blk - blk0 : BLK_MAX;  // blocks of this group
-  const int my_blk = blk0 + wave;
-  const bool wave_active = wave < blk_n;
+  const int blk_max = (MF_ROWS / 32) >> h_narrow;  // (eight, narrow launches: four)
+  const int blk0 = rg * blk_max;
+  const int blk_n = n_blk - blk0 < blk_max ? n_blk - blk0 : blk_max;  // blocks of this group
+  if (blk_n <= 0) return;  // (narrow: an item of at most 128 rows needs one of its two workgroups)
+  // Narrow launches have compute units to spare and are bound by each workgroup's own pace: the
+  // four blocks' waves alone, one to a SIMD, would have nothing to hide their chains of dependent
+  // steps behind.  There two waves share a row block, one takes the even 32-key blocks of the
+  // tiles, the other the odd ones, and their results meet in LDS at the end: `kpar` is the wave's key
+  // parity, `pair_shift` tells how far apart the two waves are.  (Groups of at most four blocks in
+  // launches that fill the chip are bound by HBM at 1.25 us a tile either way, and sharing made them
+  // run ahead of the other row groups of their keys, out of reach of the L2 copies: 0.8 % slower.)
+  const bool ksplit = h_narrow != 0;
+  const int pair_shift = !ksplit ? 3 : blk_n <= 1 ? 0 : blk_n == 2 ? 1 : 2;
+  const int my_blk = blk0 + (wave & ((1 << pair_shift) - 1));
+  const int kpar = wave >> pair_shift;    // (without sharing: 0)
+  const bool wave_active = my_blk < blk0 + blk_n && kpar < 2;
   const int hb = HALF && my_blk >= nbh ? 1 : 0;          // head of the pair
   const int row_base = (my_blk - hb * nbh) * 32;          // of the head's rows
 
@@ -735,6 +746,54 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       for (int v = 0; v < 16; ++v) sA[v] -= mx;
       set_reference(mx);
     }
+    if (ksplit) {
+      // ---- two waves to a row block: this one takes 32-key block `kpar` of every tile.  Both start from
+      // the first block's maximum, so their sums need no rescaling when they meet.
+      //   window 1: scores of tile t+1  | second half of tile t
+      //   window 2: product of tile t   | first half of tile t+1
+      // The barrier that lets tile t + 1 in stands at the start of the trip; every wave has finished tile
+      // t - 1 by then.
+      const int kofs = kpar * MF_BLOCK_BYTES;
+      if (kpar != 0) {
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk)
+          sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ldk(kofs, kk), qf[kk], kk == 0 ? negm : sA, 0, 0, 0);
+        if (n_plain < 2) mask_block(1, sA);
+      }
+      exp_half(sA, 0, pa);
+      auto trip = [&](int t, int s, floatx16& S_cur, floatx16& S_next, uintx4& P_cur, uintx4& P_next, auto masked) {
+        constexpr bool MASKED = decltype(masked)::value;
+        const int s1 = (s + 1) % MF_NBUF;
+        if (MASKED) {
+          next_arrival(t);
+        } else {
+          asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * MF_LOADS) : "memory");
+          issue_full(t + 3, (s + 3) % MF_NBUF);
+        }
+#pragma unroll
+        for (int kk = 0; kk < 2 * MF_AHEAD; ++kk) kf[kk] = ldk(blk_off(s1, 0) + kofs, kk);
+        win_qk(blk_off(s1, 0) + kofs, blk_off(s, 0) + kofs, S_next, S_cur, 1, pb);
+        if (MASKED && 2 * (t + 1) + kpar >= n_plain) mask_block(2 * (t + 1) + kpar, S_next);
+        win_pv(blk_off(s, 0) + kofs, 0, P_cur, pb, S_next, 0, P_next, YES, NO);
+      };
+      int t = 0;
+      for (; t + 6 < n_full; t += 4) {
+        trip(t, 0, sA, sB, pa, pc, NO);
+        trip(t + 1, 1, sB, sA, pc, pa, NO);
+        trip(t + 2, 2, sA, sB, pa, pc, NO);
+        trip(t + 3, 3, sB, sA, pc, pa, NO);
+      }
+      for (; t + 1 < n_tiles; ++t) {
+        trip(t, t % MF_NBUF, sA, sB, pa, pc, YES);
+        sA = sB;
+        pa = pc;
+      }
+      const int off = blk_off(t % MF_NBUF, 0) + kofs;
+      exp_half(sA, 1, pb);
+#pragma unroll
+      for (int f = 0; f < 2 * MF_AHEAD; ++f) vf[f] = ldv(off, f);
+      win_pv(off, 0, pa, pb, sA, 0, pc, NO, NO);
+    } else {
     exp_half(sA, 0, pa);
 #pragma unroll
     for (int kk = 0; kk < 2 * MF_AHEAD; ++kk) kf[kk] = ldk(blk_off(0, 1), kk);
@@ -781,6 +840,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       for (int f = 0; f < 2 * MF_AHEAD; ++f) vf[f] = ldv(blk_off(s, 1), f);
       win_pv(blk_off(s, 1), 0, pc, pb, sB, 0, pa, NO, NO);
     }
+    }
     l_sum = l0 + l1;
   } else {
     // no rows: this wave only moves tiles and meets the barriers
@@ -808,7 +868,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     for (int blk = 0; blk < n_blocks; ++blk) {
       // the barrier of next_arrival also keeps any wave from reading tile t + 1 before all of it is there
       if ((blk & 1) && blk + 1 < n_blocks) next_arrival(blk >> 1);
-      if (!wave_active) continue;
+      if (!wave_active || kpar != 0) continue;  // (of two waves that share a row block the first does it all)
       const int off = blk_off((blk >> 1) % MF_NBUF, blk & 1);
       floatx16 S;
 #pragma unroll
@@ -837,69 +897,117 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     l_tot = l_sum + __shfl_xor(l_sum, 32);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   }
-  if (!wave_active) return;
-
-  if (n_sp == 1) {
-    // ---- results, sequence with a single split: normalised rows go out as bf16.  Each wave turns its
-    // block around in LDS (the tile ring is free: every wave has passed the last barrier),
-    // so that a lane stores 16 contiguous bytes and a store instruction covers whole rows.
-    constexpr int CPR = 4 * NT;  // 16-byte chunks of a row
-    constexpr int ST_ROW = 64 * NT + 16;  // padded row: the 8-byte writes of 16 rows spread over all banks
-    char* stage = wave < 4 ? lds_k[wave] : lds_v[wave - 4];
-    const float inv = 1.f / l_tot;
+  if (ksplit) {
+    // ---- the two waves of a row block swap halves of their columns through the (now free) tile ring:
+    // each ends up with the sums of NT / 2 column blocks, kept in acc[0 .. NT / 2), and the denominator.
+    // A wave's 8 NT KB of floats lie 16 bytes to a lane, so both sides move whole 1 KB pieces.
+    float* const ex = reinterpret_cast<float*>(wave < 4 ? &lds_k[0][0] : &lds_v[0][0]);  // (each 64 KB: four waves)
+    if (wave_active) {
+      if (kpar != 0) {
 #pragma unroll
-    for (int tt = 0; tt < NT; ++tt)
+        for (int tt = 0; tt < NT / 2; ++tt) {
+          const floatx16 x = acc[tt];
+          acc[tt] = acc[tt + NT / 2];
+          acc[tt + NT / 2] = x;
+        }
+      }
+#pragma unroll
+      for (int tt = 0; tt < NT / 2; ++tt)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          float4 f = {acc[tt + NT / 2][4 * b], acc[tt + NT / 2][4 * b + 1], acc[tt + NT / 2][4 * b + 2], acc[tt + NT / 2][4 * b + 3]};
+          *reinterpret_cast<float4*>(ex + (wave & 3) * 4096 + (tt * 4 + b) * 256 + lane * 4) = f;
+        }
+      ex[(wave & 3) * 4096 + 2048 + lane] = l_tot;
+      if (kpar == 0) ex[(wave & 3) * 4096 + 2112 + lane] = m_ref;  // (the exact path moves the first wave's reference only)
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const int other = wave ^ (1 << pair_shift);  // (a wave without rows reads some wave's piece and drops it)
+    const float* const from = reinterpret_cast<const float*>(other < 4 ? &lds_k[0][0] : &lds_v[0][0]) + (other & 3) * 4096;
+#pragma unroll
+    for (int tt = 0; tt < NT / 2; ++tt)
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        const int d0 = 32 * tt + 8 * b + 4 * half;
-        floatx2 f01 = {acc[tt][4 * b] * inv, acc[tt][4 * b + 1] * inv};
-        floatx2 f23 = {acc[tt][4 * b + 2] * inv, acc[tt][4 * b + 3] * inv};
-        uint2 pk;
-        pk.x = __builtin_bit_cast(unsigned, __builtin_convertvector(f01, bf16x2));
-        pk.y = __builtin_bit_cast(unsigned, __builtin_convertvector(f23, bf16x2));
-        *reinterpret_cast<uint2*>(stage + col * ST_ROW + d0 * 2) = pk;
+        const float4 f = *reinterpret_cast<const float4*>(from + (tt * 4 + b) * 256 + lane * 4);
+        acc[tt][4 * b] += f.x;
+        acc[tt][4 * b + 1] += f.y;
+        acc[tt][4 * b + 2] += f.z;
+        acc[tt][4 * b + 3] += f.w;
       }
-    const int r = row_base + col;
-    if (h_lse && half == 0 && r < Rh) {
-      const int i = div_G(r), gi = r - i * Gh;
-      h_lse[(int64_t)(n0 + i) * Hq + head0 + gi] = (m_ref + __log2f(l_tot)) * MF_LN2;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's staging writes are in LDS
+    l_tot += from[2048 + lane];
+    if (kpar != 0) m_ref = from[2112 + lane];
+    // (every wave has its sums before the staging below reuses the ring)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  }
+  if (!wave_active) return;
+
+  // `NB` column blocks (acc[0 .. NB)) of this wave's 32 rows, from column col0 of the head's row on
+  auto write_out = [&](auto nb, int col0) {
+    constexpr int NB = decltype(nb)::value;
+    constexpr int CPR = 4 * NB;  // 16-byte chunks of a row
+    if (n_sp == 1) {
+      // ---- results, sequence with a single split: normalised rows go out as bf16.  Each wave turns its
+      // block around in LDS (the tile ring is free: every wave has passed the last barrier),
+      // so that a lane stores 16 contiguous bytes and a store instruction covers whole rows.
+      constexpr int ST_ROW = 64 * NB + 16;  // padded row: the 8-byte writes of 16 rows spread over all banks
+      char* stage = wave < 4 ? lds_k[wave] : lds_v[wave - 4];
+      const float inv = 1.f / l_tot;
 #pragma unroll
-    for (int j = 0; j < CPR / 2; ++j) {
-      const int row_l = (64 / CPR) * j + lane / CPR, chunk = lane % CPR;
-      const int ro = row_base + row_l;
-      const int i = div_G(ro < Rh ? ro : 0), gi = ro - i * Gh;
-      if (ro < Rh) {
-        const uint4 val = *reinterpret_cast<const uint4*>(stage + row_l * ST_ROW + chunk * 16);
-        char* dst = static_cast<char*>(h_o) + ((int64_t)(n0 + i) * Hq + head0 + gi) * Q_ROW_BYTES + chunk * 16;
-        // non-temporal: the rows start their way to memory now instead of waiting in L2 for the
-        // write-back at the end of the kernel, when every workgroup's rows would go at once
-        __builtin_nontemporal_store(__builtin_bit_cast(uintx4, val), reinterpret_cast<uintx4*>(dst));
-      }
-    }
-  } else {
-    // ---- this split's partial record: unnormalised accumulators, reference maximum, denominator
-    const int r = row_base + col;
-    if (r < Rh) {
-      const int i = div_G(r), gi = r - i * Gh;
-      const int64_t row = (int64_t)(n0 + i) * Hq + head0 + gi;
-      constexpr int REC_D = 32 * NT;  // a record: o[REC_D], m, l, two pad floats
-      float* rec = h_part + (row * h_sp_max + sp) * (REC_D + ATTN_REC_PAD);
-#pragma unroll
-      for (int tt = 0; tt < NT; ++tt)
+      for (int tt = 0; tt < NB; ++tt)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           const int d0 = 32 * tt + 8 * b + 4 * half;
-          float4 f = {acc[tt][4 * b], acc[tt][4 * b + 1], acc[tt][4 * b + 2], acc[tt][4 * b + 3]};
-          *reinterpret_cast<float4*>(rec + d0) = f;
+          floatx2 f01 = {acc[tt][4 * b] * inv, acc[tt][4 * b + 1] * inv};
+          floatx2 f23 = {acc[tt][4 * b + 2] * inv, acc[tt][4 * b + 3] * inv};
+          uint2 pk;
+          pk.x = __builtin_bit_cast(unsigned, __builtin_convertvector(f01, bf16x2));
+          pk.y = __builtin_bit_cast(unsigned, __builtin_convertvector(f23, bf16x2));
+          *reinterpret_cast<uint2*>(stage + col * ST_ROW + d0 * 2) = pk;
         }
-      if (half == 0) {
-        rec[REC_D] = m_ref * MF_LN2;
-        rec[REC_D + 1] = l_tot;
+      const int r = row_base + col;
+      if (h_lse && half == 0 && r < Rh && col0 == 0) {
+        const int i = div_G(r), gi = r - i * Gh;
+        h_lse[(int64_t)(n0 + i) * Hq + head0 + gi] = (m_ref + __log2f(l_tot)) * MF_LN2;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's staging writes are in LDS
+#pragma unroll
+      for (int j = 0; j < CPR / 2; ++j) {
+        const int row_l = (64 / CPR) * j + lane / CPR, chunk = lane % CPR;
+        const int ro = row_base + row_l;
+        const int i = div_G(ro < Rh ? ro : 0), gi = ro - i * Gh;
+        if (ro < Rh) {
+          const uint4 val = *reinterpret_cast<const uint4*>(stage + row_l * ST_ROW + chunk * 16);
+          char* dst = static_cast<char*>(h_o) + ((int64_t)(n0 + i) * Hq + head0 + gi) * Q_ROW_BYTES + col0 * 2 + chunk * 16;
+          // non-temporal: the rows start their way to memory now instead of waiting in L2 for the
+          // write-back at the end of the kernel, when every workgroup's rows would go at once
+          __builtin_nontemporal_store(__builtin_bit_cast(uintx4, val), reinterpret_cast<uintx4*>(dst));
+        }
+      }
+    } else {
+      // ---- this split's partial record: unnormalised accumulators, reference maximum, denominator
+      const int r = row_base + col;
+      if (r < Rh) {
+        const int i = div_G(r), gi = r - i * Gh;
+        const int64_t row = (int64_t)(n0 + i) * Hq + head0 + gi;
+        constexpr int REC_D = 32 * NT;  // a record: o[REC_D], m, l, two pad floats
+        float* rec = h_part + (row * h_sp_max + sp) * (REC_D + ATTN_REC_PAD);
+#pragma unroll
+        for (int tt = 0; tt < NB; ++tt)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const int d0 = col0 + 32 * tt + 8 * b + 4 * half;
+            float4 f = {acc[tt][4 * b], acc[tt][4 * b + 1], acc[tt][4 * b + 2], acc[tt][4 * b + 3]};
+            *reinterpret_cast<float4*>(rec + d0) = f;
+          }
+        if (half == 0 && col0 == 0) {
+          rec[REC_D] = m_ref * MF_LN2;
+          rec[REC_D + 1] = l_tot;
+        }
       }
     }
-  }
+  };
+  if (ksplit) write_out(std::integral_constant<int, NT / 2>{}, kpar * (16 * NT));
+  else write_out(std::integral_constant<int, NT>{}, 0);
 }
 
 // `ev_start` / `ev_stop` (may be NULL): HIP events attached to this dispatch; the runtime stamps them
@@ -908,8 +1016,8 @@ hs_status attn_mfma_launch(const AttnArgs& a, int max_tree_rows, hipStream_t str
                            hipEvent_t ev_stop) {
   const int n_rg_max = (a.G * max_tree_rows + MF_ROWS - 1) / MF_ROWS;
   dim3 grid((unsigned)(a.Hkv * n_rg_max * a.sp_max), (unsigned)a.B);
-  if (a.n_tbl > 0) grid = dim3((unsigned)a.n_items, 1u);
-  const bool once = n_rg_max == 1;  // every (sequence, head) is one row group: its keys have one reader
+  if (a.n_tbl > 0) grid = dim3((unsigned)a.n_items << a.narrow, 1u);
+  const bool once = n_rg_max == 1 && a.narrow == 0;  // every (sequence, head) is one row group: its keys have one reader
   const bool big = max_tree_rows > MF_MAX_M;
   const dim3 block(MF_THREADS);
   if (big) {

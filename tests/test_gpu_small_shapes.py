@@ -44,3 +44,20 @@ def test_head_dimension_64_row_blocks(G, hq, hkv, M):
     w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=64)
     rs = np.random.RandomState(M)
     _compare(G, _case(w, M, [_random_parents(rs, M, back=9), _random_parents(rs, 5)], [333, 64], "unit"), "bf16")
+
+
+@pytest.mark.parametrize("variant", ["unit", "hot", "cold"])
+@pytest.mark.parametrize("D,hq,hkv,M,L", [
+    (128, 2, 2, 1, 0), (128, 2, 2, 1, 31), (128, 2, 2, 32, 64), (128, 2, 2, 33, 65), (128, 2, 2, 65, 129), (128, 4, 2, 64, 33),
+    (128, 8, 2, 32, 1025), (128, 8, 2, 33, 97), (128, 8, 2, 64, 4000), (128, 8, 2, 75, 448), (128, 2, 1, 300, 200),
+    (64, 4, 4, 17, 130), (64, 8, 2, 33, 1000), (64, 4, 2, 129, 63)])
+def test_launches_that_leave_compute_units_to_spare(G, D, hq, hkv, M, L, variant):
+    """Few work items: two workgroups to an item, two waves to a row block, each on every other 32 keys.
+    One to four row blocks in a workgroup, a second workgroup without rows, last tiles with one or two
+    32-key blocks, prefixes in one and in several splits, the exact second pass."""
+    from test_gpu_attention import _case, _compare, _random_parents
+    if variant == "cold" and (L < 64 or M < 2):
+        pytest.skip("the planted rows and keys need two rows and 64 keys")
+    w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
+    rs = np.random.RandomState(M + L)
+    _compare(G, _case(w, M, [_random_parents(rs, M, back=9)], [L], variant), "bf16", big_scores=variant != "unit")
