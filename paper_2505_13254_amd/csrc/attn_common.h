@@ -29,12 +29,33 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {  // round to nearest, t
   return (bf16_t)(u >> 16);
 }
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+// Four neighbouring elements as float32, at any element's address (the type's alignment is an
+// element's; global memory takes wide accesses at any address).
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned short bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));
 template <typename T>
-__device__ __forceinline__ float load_elem(const T* p);
+__device__ __forceinline__ float4 load4(const T* p);
 template <>
-__device__ __forceinline__ float load_elem<float>(const float* p) { return *p; }
+__device__ __forceinline__ float4 load4<float>(const float* p) {
+  const float4_any f = *reinterpret_cast<const float4_any*>(p);
+  return make_float4(f[0], f[1], f[2], f[3]);
+}
 template <>
-__device__ __forceinline__ float load_elem<bf16_t>(const bf16_t* p) { return bf16_to_f32(*p); }
+__device__ __forceinline__ float4 load4<bf16_t>(const bf16_t* p) {
+  const bf16x4_any f = *reinterpret_cast<const bf16x4_any*>(p);
+  return make_float4(bf16_to_f32(f[0]), bf16_to_f32(f[1]), bf16_to_f32(f[2]), bf16_to_f32(f[3]));
+}
+template <typename T>
+__device__ __forceinline__ void store4(T* p, float4 v);
+template <>
+__device__ __forceinline__ void store4<float>(float* p, float4 v) {
+  *reinterpret_cast<float4_any*>(p) = float4_any{v.x, v.y, v.z, v.w};
+}
+template <>
+__device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float4 v) {
+  *reinterpret_cast<bf16x4_any*>(p) = bf16x4_any{f32_to_bf16(v.x), f32_to_bf16(v.y), f32_to_bf16(v.z), f32_to_bf16(v.w)};
+}
 
 template <typename T>
 __device__ __forceinline__ void store_elem(T* p, float v);
@@ -98,13 +119,6 @@ __device__ __forceinline__ int64_t prefix_len_of(const AttnArgs& a, int s) {
 __host__ __device__ __forceinline__ int splits_of(int64_t L, int split_len) {
   int n = (int)((L + split_len - 1) / split_len);
   return n < 1 ? 1 : n;
-}
-
-// Is tree row j on the root path of tree row i (j == i or an ancestor)?  par: local parents.
-__device__ __forceinline__ bool on_root_path(const int* par, int i, int j) {
-  int a = i;
-  while (a > j) a = par[a];
-  return a == j;
 }
 
 }  // namespace hs

@@ -2,8 +2,8 @@
 // (Section 2.2: the pruned tree is verified in one pass with tree-mask attention).
 //
 // This file holds the entry point, the launch planning, the float32 / any-shape kernel
-// (k_attn_generic: vector ALU, K/V tiles staged through LDS, 16 rows per workgroup) and the
-// split combine (k_attn_combine).  bfloat16 with head dimension 128 goes to the MFMA kernel in
+// (k_attn_generic: float32 matrix instructions, 16 rows per workgroup, keys shared out to its waves)
+// and the split combine (k_attn_combine).  bfloat16 with head dimension 128 goes to the MFMA kernel in
 // tree_attention_mfma.hip.
 #include <stdlib.h>
 #include <string.h>
@@ -21,24 +21,47 @@ hs_status attn_mfma_launch(const AttnArgs& a, int max_tree_rows, hipStream_t str
 bool attn_mfma_supported(int D, hs_dtype dt, int max_tree_rows, float scale);
 size_t attn_mfma_table_bytes(int max_tree_rows, int64_t NN);
 
-constexpr int GEN_THREADS = 256;
-constexpr int GEN_ROWS = 16;  // rows per workgroup (4 per wave)
-constexpr int GEN_TILE = 64;  // keys per tile (one per lane)
+constexpr int GEN_THREADS = 512;
+constexpr int GEN_WAVES = GEN_THREADS / 64;
+constexpr int GEN_ROWS = 16;  // rows per workgroup
+constexpr int GEN_TILE = 64;  // tokens of a page
 constexpr int MAX_TREE_ROWS = 1024;
 
+// ---- float32, and every bfloat16 call that the matrix-core kernel of the other file does not take.
+//
+// One workgroup = 16 query rows of one (sequence, KV head, key split); its eight waves share out the
+// split's keys in groups of 16 (GPI groups to a wave and trip) and their partial softmaxes meet in LDS at
+// the end.  What bounds these calls is latency: there are few rows, so a workgroup's own chain of trips
+// counts, and keys are spread over waves before they are spread over workgroups, which would need the
+// combine launch.  Both products run on the float32 matrix instruction (v_mfma_f32_16x16x4_f32: full
+// float32 multiply-adds), transposed so that a lane holds scores of one row:
+//     S^T[key, row] = K[key, :] . Q[row, :]      A = K, B = Q: lane (i = l % 16, h = l / 16) holds row i,
+//                                                elements 4 (4 c + h) + e of step 4 c + e
+//     O^T[d, row] += V^T[d, key] P^T[key, row]   B = P: score register v of lane (i, h) is key 4 h + v of
+//                                                row i, which is the B operand of step v as it stands
+// The contraction order is free, so K, Q and V go from global memory into operand registers 16 bytes at
+// a time and nothing is staged in LDS; output column block b holds columns i * D / 16 + b.
+// (One row group of four rows per wave on the vector ALUs, K and V staged through LDS, five LDS reads to
+// four multiply-adds: three sequences of 100 to 1500 tokens, 8 heads of 64, 17 to 40 rows: 84 us a call; now 23.
+// One of 16384 tokens, 32 heads of 128 on 8, 61 rows: 2048 us a call; now 218.)
 template <typename T, int D>
 __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
-  __shared__ float Ks[GEN_TILE][D + 1];
-  __shared__ float Vs[GEN_TILE][D];
-  __shared__ float Qs[GEN_ROWS][D];
-  __shared__ float Ps[GEN_THREADS / 64][4][GEN_TILE];
+  constexpr int NQ = D / 16;            // 16-byte (float32) pieces of a lane's part of a K, Q or V row group
+  constexpr int GPI = D == 64 ? 2 : 1;  // key groups of a wave's trip
+  constexpr int DPL = D / 16;           // output columns of a lane's row (and column blocks)
+  constexpr int ANC_WORDS = MAX_TREE_ROWS / 32;
   __shared__ int par[MAX_TREE_ROWS];
+  __shared__ unsigned anc[GEN_ROWS][ANC_WORDS + 1];
+  __shared__ float o_part[GEN_WAVES][GEN_ROWS][D + 4];
+  __shared__ float m_part[GEN_WAVES][GEN_ROWS], l_part[GEN_WAVES][GEN_ROWS];
 
   const int s = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n0 = a.node_offsets[s];
   const int M = a.node_offsets[s + 1] - n0;
-  const int64_t p0 = a.block_table != nullptr ? 0 : a.prefix_offsets[s];
+  const bool paged = a.block_table != nullptr;  // prefix tiles are pages of GEN_TILE tokens
+  const int64_t p0 = paged ? 0 : a.prefix_offsets[s];
   const int64_t L = prefix_len_of(a, s);
   if (M <= 0) return;
   const int G = a.G, Hkv = a.Hkv, Hq = a.Hq;
@@ -53,128 +76,197 @@ __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
   if (rb >= n_rb || sp >= n_sp) return;
 
   const T* q = static_cast<const T*>(a.q);
-  const bool paged = a.block_table != nullptr;  // prefix tiles are pages of GEN_TILE tokens
-  const T* kp = static_cast<const T*>(a.k_prefix) + (paged ? 0 : p0) * Hkv * D;
-  const T* vp = static_cast<const T*>(a.v_prefix) + (paged ? 0 : p0) * Hkv * D;
-  const T* kt = static_cast<const T*>(a.k_tree) + (int64_t)n0 * Hkv * D;
-  const T* vt = static_cast<const T*>(a.v_tree) + (int64_t)n0 * Hkv * D;
+  const T* kp = static_cast<const T*>(a.k_prefix) + (p0 * Hkv + g) * D;
+  const T* vp = static_cast<const T*>(a.v_prefix) + (p0 * Hkv + g) * D;
+  const T* kt = static_cast<const T*>(a.k_tree) + ((int64_t)n0 * Hkv + g) * D;
+  const T* vt = static_cast<const T*>(a.v_tree) + ((int64_t)n0 * Hkv + g) * D;
+  const int64_t tok = (int64_t)Hkv * D;  // elements from one token's row of this head to the next one's
 
-  for (int i = tid; i < M; i += GEN_THREADS) par[i] = a.parent[(a.tree_shared ? 0 : n0) + i];
-  const int r0 = rb * GEN_ROWS;
-  for (int e = tid; e < GEN_ROWS * D; e += GEN_THREADS) {
-    const int rr = e / D, d = e - rr * D;
-    const int r = r0 + rr;
-    float v = 0.f;
-    if (r < R) {
-      const int i = r / G, gi = r - i * G;
-      v = load_elem<T>(q + ((int64_t)(n0 + i) * Hq + g * G + gi) * D + d);
-    }
-    Qs[rr][d] = v;
-  }
-
-  constexpr int DPL = D / 64;  // output elements per lane
-  float m_run[4], l_run[4], acc[4][DPL];
-#pragma unroll
-  for (int rr = 0; rr < 4; ++rr) {
-    m_run[rr] = -HS_INF;
-    l_run[rr] = 0.f;
-#pragma unroll
-    for (int dd = 0; dd < DPL; ++dd) acc[rr][dd] = 0.f;
-  }
-
+  const bool last_split = sp == n_sp - 1;
   const int64_t k_lo = (int64_t)sp * a.split_len;
-  const int64_t k_hi = (sp == n_sp - 1) ? L : k_lo + a.split_len;
-  const int n_prefix_tiles = (int)((k_hi - k_lo + GEN_TILE - 1) / GEN_TILE);
-  const int n_tree_tiles = (sp == n_sp - 1) ? (M + GEN_TILE - 1) / GEN_TILE : 0;
+  const int64_t k_hi = last_split ? L : k_lo + a.split_len;
+  const int n_pg = (int)((k_hi - k_lo + 15) >> 4);      // groups of 16 prefix keys, the last one may be short
+  const int n_groups = n_pg + (last_split ? (M + 15) >> 4 : 0);
 
-  for (int t = 0; t < n_prefix_tiles + n_tree_tiles; ++t) {
-    const bool tree = t >= n_prefix_tiles;
-    const int64_t base = tree ? (int64_t)(t - n_prefix_tiles) * GEN_TILE : k_lo + (int64_t)t * GEN_TILE;
-    const int64_t limit = tree ? M : k_hi;
-    const T* ksrc = tree ? kt : kp;
-    const T* vsrc = tree ? vt : vp;
-    // where the tile's first key lives: in place, or in the page the block table names
-    const int64_t where = (!tree && paged) ? (int64_t)a.block_table[(int64_t)s * a.max_blocks + base / GEN_TILE] * GEN_TILE
-                                           : base;
-    __syncthreads();  // previous tile fully consumed (and Qs / par written, first time)
-    for (int e = tid; e < GEN_TILE * D; e += GEN_THREADS) {
-      const int j = e / D, d = e - j * D;
-      const int64_t key = base + j;
-      float kv = 0.f, vv = 0.f;
-      if (key < limit) {
-        kv = load_elem<T>(ksrc + ((where + j) * Hkv + g) * D + d);
-        vv = load_elem<T>(vsrc + ((where + j) * Hkv + g) * D + d);
+  const int i16 = lane & 15, h = lane >> 4;
+  const int r0 = rb * GEN_ROWS;
+  const int r = r0 + i16 < R ? r0 + i16 : R - 1;        // this lane's row (rows past the end repeat the last one)
+  const int node = r / G;
+  const int64_t qrow = (int64_t)(n0 + node) * Hq + g * G + (r - node * G);
+
+  // a key group's operands: K pieces (key i16) and V pieces (keys 4 h + v, columns i16 * DPL ...)
+  struct Frag {
+    float4 k[NQ], v[NQ];
+  };
+  auto load_group = [&](int grp, Frag& f) {
+    const bool tree = grp >= n_pg;
+    const int64_t first = tree ? (int64_t)(grp - n_pg) * 16 : k_lo + (int64_t)grp * 16;
+    const int rows = (int)((tree ? (int64_t)M : k_hi) - first);  // >= 1; keys past the end repeat the last one
+    // where the group's first key lives: in place, or in the page the block table names
+    const int64_t where = (!tree && paged) ? (int64_t)a.block_table[(int64_t)s * a.max_blocks + first / GEN_TILE] * GEN_TILE + first % GEN_TILE
+                                           : first;
+    const T* kb = (tree ? kt : kp) + where * tok;
+    const T* vb = (tree ? vt : vp) + where * tok;
+    const T* krow = kb + (i16 < rows ? i16 : rows - 1) * tok + 4 * h;
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) f.k[c] = load4<T>(krow + 16 * c);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int key = 4 * h + v;
+      const T* vrow = vb + (key < rows ? key : rows - 1) * tok + i16 * DPL;
+#pragma unroll
+      for (int c = 0; c < DPL / 4; ++c) f.v[v * (DPL / 4) + c] = load4<T>(vrow + 4 * c);
+    }
+  };
+
+  Frag cur[GPI], nxt[GPI];
+  const int stride = GEN_WAVES * GPI;
+  int grp = wave * GPI;
+#pragma unroll
+  for (int u = 0; u < GPI; ++u)
+    if (grp + u < n_groups) load_group(grp + u, cur[u]);
+
+  float4 qf[NQ];
+#pragma unroll
+  for (int c = 0; c < NQ; ++c) qf[c] = load4<T>(q + qrow * D + 16 * c + 4 * h);
+
+  // ---- the rows' root paths as bit sets over the tree rows
+  if (last_split) {
+    const int32_t* parent = a.parent + (a.tree_shared ? 0 : n0);
+    for (int i = tid; i < M; i += GEN_THREADS) par[i] = parent[i];
+    for (int e = tid; e < GEN_ROWS * (ANC_WORDS + 1); e += GEN_THREADS) (&anc[0][0])[e] = 0u;
+    __syncthreads();
+    if (tid < GEN_ROWS) {  // (lane tid of the first wave: its own row)
+      for (int j = node; j >= 0;) {
+        anc[tid][j >> 5] |= 1u << (j & 31);
+        const int up = par[j];
+        j = up < j ? up : -1;  // (a malformed tree cannot keep the walk from ending)
       }
-      Ks[j][d] = kv;
-      Vs[j][d] = vv;
     }
     __syncthreads();
-
-    // scores of this wave's 4 rows against the tile's 64 keys (lane = key)
-    float sc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int d = 0; d < D; ++d) {
-      const float kv = Ks[lane][d];
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) sc[rr] = fmaf(Qs[wave * 4 + rr][d], kv, sc[rr]);
-    }
-    const int64_t key = base + lane;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int r = r0 + wave * 4 + rr;
-      bool ok = key < limit && r < R;
-      if (ok && tree) ok = on_root_path(par, r / G, (int)key);
-      const float sv = ok ? sc[rr] * a.scale : -HS_INF;
-      float mx = sv;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-      const float m_new = fmaxf(m_run[rr], mx);
-      float pj = 0.f, alpha = 1.f;
-      if (m_new != -HS_INF) {
-        pj = __expf(sv - m_new);
-        alpha = __expf(m_run[rr] - m_new);  // 0 when nothing was seen before
-      }
-      float ps = pj;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) ps += __shfl_xor(ps, off);
-      l_run[rr] = l_run[rr] * alpha + ps;
-      m_run[rr] = m_new;
-#pragma unroll
-      for (int dd = 0; dd < DPL; ++dd) acc[rr][dd] *= alpha;
-      Ps[wave][rr][lane] = pj;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int j = 0; j < GEN_TILE; ++j) {
-#pragma unroll
-      for (int dd = 0; dd < DPL; ++dd) {
-        const float vv = Vs[j][lane + 64 * dd];
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) acc[rr][dd] = fmaf(Ps[wave][rr][j], vv, acc[rr][dd]);
-      }
-    }
   }
 
-  // write the result (sequences with one split) or this split's partial record
+  floatx4 acc[DPL];
+  float m_run = -HS_INF, l_run = 0.f;  // m_run: of the row (all four lanes of it); l_run: of this lane's keys
 #pragma unroll
-  for (int rr = 0; rr < 4; ++rr) {
-    const int r = r0 + wave * 4 + rr;
-    if (r >= R) continue;
-    const int i = r / G, gi = r - i * G;
+  for (int b = 0; b < DPL; ++b) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  for (; grp < n_groups; grp += stride) {
+#pragma unroll
+    for (int u = 0; u < GPI; ++u)
+      if (grp + stride + u < n_groups) load_group(grp + stride + u, nxt[u]);
+
+    floatx4 S[GPI];
+    float mx = -HS_INF;
+#pragma unroll
+    for (int u = 0; u < GPI; ++u) {
+      if (GPI > 1 && grp + u >= n_groups) {
+        S[u] = floatx4{-HS_INF, -HS_INF, -HS_INF, -HS_INF};
+        continue;
+      }
+      // (two chains: consecutive instructions of one accumulator wait for each other)
+      floatx4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+      for (int c = 0; c < NQ; ++c) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur[u].k[c].x, qf[c].x, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur[u].k[c].y, qf[c].y, s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur[u].k[c].z, qf[c].z, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur[u].k[c].w, qf[c].w, s1, 0, 0, 0);
+      }
+      const bool tree = grp + u >= n_pg;
+      const int64_t first = tree ? (int64_t)(grp + u - n_pg) * 16 : k_lo + (int64_t)(grp + u) * 16;
+      // bit v: key 4 h + v of the group counts for this lane's row
+      unsigned ok = 0xfu;
+      if (tree) ok = anc[i16][(int)first >> 5] >> (((int)first & 31) + 4 * h);  // (bits past the tree are zero)
+      else if (first + 16 > k_hi) {
+        const int left = (int)(k_hi - first) - 4 * h;
+        ok = left >= 4 ? 0xfu : left > 0 ? (1u << left) - 1u : 0u;
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        S[u][v] = ((ok >> v) & 1u) ? (s0[v] + s1[v]) * a.scale : -HS_INF;
+        mx = fmaxf(mx, S[u][v]);
+      }
+    }
+    // the row's maximum moves only when a score of this trip lies above it
+    if (__ballot(mx > m_run) != 0ull) {
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = m_new == -HS_INF ? 1.f : __expf(m_run - m_new);  // 0 when nothing was seen before
+      l_run *= alpha;
+#pragma unroll
+      for (int b = 0; b < DPL; ++b) acc[b] *= alpha;
+      m_run = m_new;
+    }
+#pragma unroll
+    for (int u = 0; u < GPI; ++u) {
+      if (GPI > 1 && grp + u >= n_groups) continue;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float p = S[u][v] == -HS_INF ? 0.f : __expf(S[u][v] - m_run);
+        l_run += p;
+#pragma unroll
+        for (int c = 0; c < DPL / 4; ++c) {
+          const float4 vv = cur[u].v[v * (DPL / 4) + c];
+          acc[4 * c + 0] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv.x, p, acc[4 * c + 0], 0, 0, 0);
+          acc[4 * c + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv.y, p, acc[4 * c + 1], 0, 0, 0);
+          acc[4 * c + 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv.z, p, acc[4 * c + 2], 0, 0, 0);
+          acc[4 * c + 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv.w, p, acc[4 * c + 3], 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < GPI; ++u) cur[u] = nxt[u];
+  }
+
+  // ---- the waves' parts meet: register b of value vv is column (4 h + vv) * DPL + b of row i16
+  l_run += __shfl_xor(l_run, 16);
+  l_run += __shfl_xor(l_run, 32);
+  if (h == 0) {
+    m_part[wave][i16] = m_run;
+    l_part[wave][i16] = l_run;
+  }
+#pragma unroll
+  for (int vv = 0; vv < 4; ++vv)
+#pragma unroll
+    for (int c = 0; c < DPL / 4; ++c)
+      *reinterpret_cast<float4*>(&o_part[wave][i16][(4 * h + vv) * DPL + 4 * c]) =
+          make_float4(acc[4 * c][vv], acc[4 * c + 1][vv], acc[4 * c + 2][vv], acc[4 * c + 3][vv]);
+  __syncthreads();
+  constexpr int PIECES = GEN_ROWS * D / 4;  // four columns to a thread
+  for (int e = tid; e < PIECES; e += GEN_THREADS) {
+    const int rr = e / (D / 4), d = (e - rr * (D / 4)) * 4;
+    if (r0 + rr >= R) continue;
+    float m = m_part[0][rr];
+#pragma unroll
+    for (int w = 1; w < GEN_WAVES; ++w) m = fmaxf(m, m_part[w][rr]);
+    float l = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < GEN_WAVES; ++w) {
+      const float mw = m_part[w][rr];
+      const float f = mw == -HS_INF ? 0.f : __expf(mw - m);  // (a wave without a visible key: weight 0)
+      const float4 ow = *reinterpret_cast<const float4*>(&o_part[w][rr][d]);
+      l = fmaf(l_part[w][rr], f, l);
+      o.x = fmaf(ow.x, f, o.x);
+      o.y = fmaf(ow.y, f, o.y);
+      o.z = fmaf(ow.z, f, o.z);
+      o.w = fmaf(ow.w, f, o.w);
+    }
+    // the result (sequences with one split) or this split's partial record
+    const int i = (r0 + rr) / G, gi = r0 + rr - i * G;
     const int64_t row = (int64_t)(n0 + i) * Hq + g * G + gi;
     if (n_sp == 1) {
-      T* out = static_cast<T*>(a.o) + row * D;
-      const float inv = 1.f / l_run[rr];
-#pragma unroll
-      for (int dd = 0; dd < DPL; ++dd) store_elem<T>(out + lane + 64 * dd, acc[rr][dd] * inv);
-      if (a.lse && lane == 0) a.lse[row] = m_run[rr] + __logf(l_run[rr]);
+      const float inv = 1.f / l;
+      store4<T>(static_cast<T*>(a.o) + row * D + d, make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv));
+      if (a.lse && d == 0) a.lse[row] = m + __logf(l);
     } else {
       float* rec = a.part + (row * a.sp_max + sp) * (D + ATTN_REC_PAD);
-#pragma unroll
-      for (int dd = 0; dd < DPL; ++dd) rec[lane + 64 * dd] = acc[rr][dd];
-      if (lane == 0) {
-        rec[D] = m_run[rr];
-        rec[D + 1] = l_run[rr];
+      *reinterpret_cast<float4*>(rec + d) = o;
+      if (d == 0) {
+        rec[D] = m;
+        rec[D + 1] = l;
       }
     }
   }
@@ -252,6 +344,8 @@ __global__ __launch_bounds__(64 * CMB_ROWS) void k_attn_combine(AttnArgs a, int6
   if (a.lse && lane == 0) a.lse[row] = m + __logf(l);
 }
 
+constexpr int PLAN_CUS = 256;
+
 struct AttnPlan {
   int split_len, sp_max, n_rb_max, max_rows;
   int64_t max_L;
@@ -261,7 +355,7 @@ struct AttnPlan {
 // Chooses the split length from the host copies of the offsets: enough workgroups to fill the
 // chip, but splits long enough that partial records stay small next to the K/V they summarise.
 static AttnPlan plan_attention(const int32_t* hno, const int64_t* hpo, const int64_t* hlens, int B, int Hq, int Hkv,
-                               int rows_per_wg, int target_wgs) {
+                               int rows_per_wg) {
   AttnPlan p{};
   int max_M = 0;
   int64_t max_L = 0, sum_L = 0;
@@ -281,7 +375,9 @@ static AttnPlan plan_attention(const int32_t* hno, const int64_t* hpo, const int
   if (p.n_rb_max < 1) p.n_rb_max = 1;
   // workgroups without splitting: one per (sequence, head, row block); split until the target is met
   const int64_t base_wgs = (int64_t)B * Hkv * p.n_rb_max;
-  int64_t want = base_wgs > 0 ? (target_wgs + base_wgs - 1) / base_wgs : 1;  // splits per average sequence
+  // (a workgroup per compute unit: float32, four sequences of 200 to 2000 tokens, 8 heads of 128 on 2, up to 64
+  // rows, 128 workgroups unsplit: 42.7 us with splits for 512 workgroups, 32.4 us with splits for 256)
+  int64_t want = base_wgs > 0 ? (PLAN_CUS + base_wgs - 1) / base_wgs : 1;  // splits per average sequence
   if (want < 1) want = 1;
   const int64_t mean_L = B > 0 ? sum_L / B : 0;
   int64_t len = (mean_L + want - 1) / want;
@@ -299,7 +395,6 @@ static AttnPlan plan_attention(const int32_t* hno, const int64_t* hpo, const int
 // is longest-processing-time-first scheduling.  The cost model (microseconds, fitted to
 // measurements on MI355X) only has to rank alternatives: an item costs a fixed part plus a
 // per-tile part that grows with the number of waves that have rows.
-constexpr int PLAN_CUS = 256;
 constexpr float PLAN_ITEM_US = 10.f;
 // Splits of at least 128 tokens (the workspace bound relies on it).  A launch of few workgroups is mostly an
 // item's fixed cost: one layer of the 8B shape (32 tiles a head) takes 25.9 us cut into 4 x 8 tiles, 23.5 us
@@ -693,7 +788,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   AttnPlan plan{};
   if (!(mfma && plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap))) {
     a.n_tbl = 0;
-    plan = plan_attention(host_node_offsets, host_prefix_offsets, host_prefix_lens, B, Hq, a.Hkv, mfma ? 0 : GEN_ROWS, mfma ? 256 : 1024);
+    plan = plan_attention(host_node_offsets, host_prefix_offsets, host_prefix_lens, B, Hq, a.Hkv, mfma ? 0 : GEN_ROWS);
     while (plan.sp_max > sp_cap) {
       plan.split_len *= 2;
       plan.sp_max = splits_of(plan.max_L, plan.split_len);

@@ -61,3 +61,41 @@ def test_launches_that_leave_compute_units_to_spare(G, D, hq, hkv, M, L, variant
     w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
     rs = np.random.RandomState(M + L)
     _compare(G, _case(w, M, [_random_parents(rs, M, back=9)], [L], variant), "bf16", big_scores=variant != "unit")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,hq,hkv,M,L,offset", [
+    (64, 3, 3, 1, 0, 0), (64, 3, 3, 16, 15, 0), (64, 6, 3, 17, 16, 1), (64, 3, 1, 33, 511, 0), (64, 3, 3, 5, 1040, 3),
+    (128, 3, 3, 1, 1, 0), (128, 6, 3, 16, 17, 0), (128, 3, 1, 47, 513, 1), (128, 3, 3, 1024, 40, 0)])
+def test_attention_of_any_shape_and_address(G, dtype, D, hq, hkv, M, L, offset):
+    """The kernel for float32 and for what the bfloat16 matrix kernel refuses (an odd number of KV heads of
+    64, arrays off a 16-byte boundary): groups of 16 keys that end short, fewer groups than waves, split
+    prefixes, the largest tree, arrays that start `offset` elements off."""
+    import paper_2505_13254_amd as hs
+    from oracle import pipeline
+    from test_gpu_attention import _case, _random_parents
+    if dtype == "bf16" and D == 128 and offset == 0:
+        offset = 1  # (an aligned array would go to the other kernel)
+    w = W.small(W.WORKLOADS[2 if dtype == "bf16" else 1], Hq=hq, Hkv=hkv, D=D)
+    rs = np.random.RandomState(M + L)
+    step = _case(w, M, [_random_parents(rs, M, back=9), _random_parents(rs, 2)], [L, 64], "unit")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def off(x):
+        x = np.ascontiguousarray(x)  # (bfloat16 values come as their bits)
+        t = torch.from_numpy(x.view(np.int16)).view(dt) if dtype == "bf16" else torch.from_numpy(x)
+        flat = torch.zeros(x.size + offset, dtype=dt, device="cuda:0")
+        flat[offset:] = t.flatten().to("cuda:0")
+        return flat[offset:].view(x.shape)
+
+    q, kp, vp, kt, vt = (off(step[n]) for n in ("q", "k_prefix", "v_prefix", "k_tree", "v_tree"))
+    no, po = torch.from_numpy(step["node_offsets"]), torch.from_numpy(step["prefix_offsets"])
+    o, lse = hs.hs_tree_attention(q, kp, vp, kt, vt, torch.from_numpy(step["parent"]).to("cuda:0"), no.to("cuda:0"),
+                                  po.to("cuda:0"), no, po, step["scale"], want_lse=True)
+    assert hs.hs_tree_attention_last_kernel() == 2
+    want_o, want_lse = pipeline.attention_out(step)
+    # float32 arithmetic throughout: up to 1088 terms a row, each rounded at 2^-24 of values of order 1 (the
+    # bfloat16 result is rounded once more, to 2^-9 of it)
+    tol = 2e-6 + (2.0 ** -8 * np.abs(want_o) if dtype == "bf16" else 1e-5 * np.abs(want_o).max())
+    assert np.all(np.abs(o.float().cpu().numpy() - want_o) <= tol)
+    assert np.abs(lse.cpu().numpy() - want_lse).max() <= 2e-5
