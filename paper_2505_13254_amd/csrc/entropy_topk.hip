@@ -22,21 +22,24 @@
 #include <limits.h>
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "hs_common.h"
 
 namespace hs {
 
-// The row scan is built for two workgroup sizes.  Sixteen waves: fewest slices to merge, best
-// for a few dozen rows.  Four waves, several workgroups per compute unit: the workgroups' set-up,
-// merge and write-out phases overlap with other workgroups' streaming, best for many rows (and
-// for very few, where a row is cut into many short slices anyway).
+// The row scan is built for two workgroup sizes.  Sixteen waves: fewest slices to merge, best for a few
+// dozen rows.  Four waves, several workgroups per compute unit: the workgroups' set-up, merge and
+// write-out phases overlap with other workgroups' streaming, best for many rows (and for very few,
+// where a row is cut into many short slices anyway).
 constexpr int SCAN_BIG = 1024, SCAN_SMALL = 256;
 constexpr int SCAN_VPT = 16;                        // values per thread per tile (4 x float4)
 constexpr int scan_tile(int threads) { return threads * SCAN_VPT; }  // logits per workgroup tile
 constexpr int FIN_THREADS = 256;
 constexpr int FIN_CAP = HS_MAX_TOPK * HS_MAX_TOPK;  // candidates the merge of 64 slices can face
 constexpr int MAX_SPLITS = 64;                       // slices per row (one list head per lane)
-constexpr int SCAN_TARGET_WGS = 256;                 // rows are sliced until about one 16-wave workgroup per compute unit exists
+constexpr int SCAN_BIG_WGS = 256;                    // rows are sliced until about so many workgroups exist
+constexpr int SCAN_SMALL_WGS = 600;
 constexpr float LOG2E = 1.4426950408889634f;
 
 struct ScanPlan {
@@ -47,18 +50,52 @@ struct ScanPlan {
 
 static ScanPlan plan_scan(int R, int V) {
   ScanPlan p;
-  // (rows of at most two small tiles: a sixteen-wave workgroup would leave most of its waves without a value)
-  p.threads = (R >= 256 || R <= 16 || V <= 2 * scan_tile(SCAN_SMALL)) ? SCAN_SMALL : SCAN_BIG;  // measured on MI355X
+  // Sixteen waves for 17 rows up to eight million logits.  (Cold inputs, K = 10, microseconds a call, best slicing
+  // of sixteen / four waves: 61 rows of 128256 19.6 / 19.9, 129 of 32000 14.9 / 16.0; 97 of 128256 24.9 / 23.3, 300
+  // of 128256 54 / 40, 10 of 128256 14.2 / 12.9.  Rows of at most two small tiles would leave most of sixteen
+  // waves without a value.)
+  p.threads = (R <= 16 || (int64_t)R * V > (8 << 20) || V <= 2 * scan_tile(SCAN_SMALL)) ? SCAN_SMALL : SCAN_BIG;
   const int tile = scan_tile(p.threads);
   const int n_tiles = (V + tile - 1) / tile;
-  // few rows: slice them until the chip is full (measured best)
-  int want = SCAN_TARGET_WGS * (SCAN_BIG / p.threads) / (R > 0 ? R : 1);
+  // (97 rows in 6 slices 23.3 us, in 11 27.5, in 3 26.3; 300 in 2 40.4, in 1 42.1, in 3 43.2.  A merge of more than
+  // 16 slices pays for the first few rows only: 10 rows in 16 slices 12.9 us, in 32 14.7; 1 row 12.1 and 11.3.)
+  int want = (p.threads == SCAN_BIG ? SCAN_BIG_WGS : SCAN_SMALL_WGS) / (R > 0 ? R : 1);
+  if (R > 4 && want > 16) want = 16;
   if (want > n_tiles) want = n_tiles;
   if (want > MAX_SPLITS) want = MAX_SPLITS;
   if (want < 1) want = 1;
   p.tiles_per_wg = (n_tiles + want - 1) / want;
   p.splits = (n_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg;
   return p;
+}
+
+// Floats as unsigned numbers in the same order.
+__device__ __forceinline__ unsigned ordered_bits(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v + 0.f);
+  return u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+}
+// Value of an ordered-float number (the upper half of a key); numbers below -inf's stand for -inf.
+__device__ __forceinline__ float ordered_value(unsigned u) {
+  return __builtin_bit_cast(float, max(u, 0x007fffffu) ^ ((u >> 31) ? 0x80000000u : 0xffffffffu));
+}
+// Lanes below this one in a mask.
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+}
+// A pair as one unsigned number: larger key = better pair (larger value, then lower index); never 0.
+// (-0 and +0 are the same value; NaN never gets here: it passes no comparison with a threshold.)
+__device__ __forceinline__ unsigned long long pair_key(float v, int i) {
+  return ((unsigned long long)ordered_bits(v) << 32) | (0xffffffffu - (unsigned)i);
+}
+// The pair of a key (0: an unused entry, worse than every pair).
+__device__ __forceinline__ void pair_of(unsigned long long k, float& v, int& i) {
+  v = ordered_value((unsigned)(k >> 32));
+  i = k == 0ull ? INT_MAX : (int)(0xffffffffu - (unsigned)k);
+}
+// The key of lane l, in scalar registers.
+__device__ __forceinline__ unsigned long long lane_key(unsigned long long k, int l) {
+  return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(k >> 32), l) << 32) |
+         (unsigned)__builtin_amdgcn_readlane((int)k, l);
 }
 
 // Rank of this lane's pair among the pairs of lanes 0 .. n-1 (number of them holding a better pair).
@@ -72,17 +109,13 @@ __device__ __forceinline__ int wave_rank(float v, int i, int n) {
   return r;
 }
 
-// The value of the lane to the left (lane 0 receives 0): a DPP move shifted by one lane across the wave.
-__device__ __forceinline__ int from_left(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x138, 0xf, 0xf, true); }
-
-// Inserts the wave-uniform pair (xv, xi) into the sorted list held one entry per lane.
-__device__ __forceinline__ void list_insert(float xv, int xi, float& lv, int& li) {
-  const bool beats = better(xv, xi, lv, li);  // false ... false true ... true along the lanes
-  const int left_beaten = from_left(beats ? 1 : 0);
-  const float left_v = __builtin_bit_cast(float, from_left(__builtin_bit_cast(int, lv)));
-  const int left_i = from_left(li);
-  lv = beats ? (left_beaten ? left_v : xv) : lv;
-  li = beats ? (left_beaten ? left_i : xi) : li;
+// Inserts the wave-uniform key x into the sorted list held one entry per lane (largest first).
+__device__ __forceinline__ void list_insert(unsigned long long x, unsigned long long& list) {
+  // the left neighbour's entry (lane 0: one that nothing beats)
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(-1, (int)list, 0x138, 0xf, 0xf, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(-1, (int)(list >> 32), 0x138, 0xf, 0xf, false);
+  const unsigned long long left = ((unsigned long long)hi << 32) | lo;
+  list = x > list ? (x > left ? left : x) : list;
 }
 
 // Maximum of each row of 16 lanes; lane 15 of a row holds it.
@@ -120,47 +153,36 @@ __device__ __forceinline__ Stats stats_wave_sum(Stats a, float inv_t) {
 // Scratch of the merges (shared memory).
 template <int CAP>
 struct MergeScratch {
-  float cv[CAP];  // candidates
-  int ci[CAP];
-  int rank[CAP];
-  float ov[HS_MAX_TOPK];  // the K best of them, in order
-  int oi[HS_MAX_TOPK];
+  unsigned long long key[CAP];         // candidates (pair_key; 0: none)
+  unsigned long long best[HS_MAX_TOPK];  // the K best of them, in order (0: fewer than K)
   int cnt;
-  float thr_v;
-  int thr_i;
   Stats total;
 };
 
-// Ranks the candidates sm.cv/ci[0, n) by counting (the order is strict: ranks are a permutation) and
-// leaves those of rank < K, in order, in sm.ov / sm.oi.  With fewer candidates than threads a
-// candidate's opponents are shared out among P threads, which add up their counts in LDS.
-// Called by all `nthreads` threads (a power of two); sm.rank[0, n) must be zero on entry (a barrier
-// before the call); ends with a barrier.
+// Ranks the candidates sm.key[0, n) by counting (keys differ, zeros aside: ranks are a permutation) and
+// leaves those of rank < K, in order, in sm.best (zero on entry).  A wave takes a run of candidates, one
+// to a lane, and 64 opponents at a time, one to a lane: a candidate's key goes to a scalar register, one
+// comparison and a count of the ballot's bits follow, and no step waits for LDS.  (A loop over LDS, one
+// dependent read to an opponent, and counts added up by LDS atomics before: 8 us to 7.4 from a
+// workgroup's start to its slice's result.)  Called by all `nthreads` threads; ends with a barrier.
 template <int CAP>
 __device__ __forceinline__ void rank_candidates(MergeScratch<CAP>& sm, int n, int K, int tid, int nthreads) {
-  int shift = 0;  // P = 2^shift threads per candidate
-  while (n > 0 && (n << (shift + 1)) <= nthreads) ++shift;
-  const int P = 1 << shift;
-  const int chunk = (n + P - 1) >> shift;
-  for (int base = 0; base < n; base += nthreads) {  // one trip unless n > nthreads
-    const int a = base + (tid >> shift), part = tid & (P - 1);
-    if (a < n) {
-      const float av = sm.cv[a];
-      const int ai = sm.ci[a];
-      const int b0 = part * chunk, b1 = (b0 + chunk < n) ? b0 + chunk : n;
-      int r = 0;
-      for (int b = b0; b < b1; ++b) r += better(sm.cv[b], sm.ci[b], av, ai) ? 1 : 0;
-      if (P > 1) atomicAdd(&sm.rank[a], r);
-      else sm.rank[a] = r;
+  const int lane = tid & 63;
+  const int n_waves = nthreads >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int per = (n + n_waves - 1) / n_waves;
+  const int lo = wave * per, hi = min(n, lo + per);
+  for (int c0 = lo; c0 < hi; c0 += 64) {  // one trip unless a wave has more than 64 candidates
+    const int cn = min(64, hi - c0);
+    const unsigned long long mine = lane < cn ? sm.key[c0 + lane] : 0ull;
+    int rank = 0;
+    for (int o = 0; o < n; o += 64) {
+      const unsigned long long opp = o + lane < n ? sm.key[o + lane] : 0ull;
+      for (int j = 0; j < cn; ++j) {
+        const int above = __popcll(__ballot(opp > lane_key(mine, j)));
+        rank += lane == j ? above : 0;
+      }
     }
-  }
-  __syncthreads();
-  for (int a = tid; a < n; a += nthreads) {
-    const int r = sm.rank[a];
-    if (r < K) {
-      sm.ov[r] = sm.cv[a];
-      sm.oi[r] = sm.ci[a];
-    }
+    if (mine != 0ull && rank < K) sm.best[rank] = mine;
   }
   __syncthreads();
 }
@@ -170,37 +192,31 @@ __device__ __forceinline__ void rank_candidates(MergeScratch<CAP>& sm, int n, in
 // launch use to hand their slices' results to each other: a fence that reaches the other XCDs
 // would write back and invalidate a whole L2, and cost the scan several times its own duration.
 __device__ __forceinline__ float ld_dev(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ int ld_dev(const int* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ unsigned long long ld_dev(const unsigned long long* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void st_dev(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void st_dev(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_dev(unsigned long long* p, unsigned long long v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// Merges S <= 64 slices of a row: statistics st[s] (m, s1, t) and sorted K-lists pv/pi[s * K + k].
+// Merges S <= 64 slices of a row: statistics st[s] (m, s1, t) and sorted K-lists pk[s * K + k] of keys.
 // COHERENT: the slices were written by other workgroups of the same launch (ld_dev).
-// Leaves the row's statistics in sm.total and its K best pairs, in order, in sm.ov / sm.oi.
-// Called by all `nthreads` threads of the workgroup (tid 0..nthreads-1); ends with a barrier.
+// Leaves the row's statistics in sm.total and its K best pairs, in order, in sm.best.
+// Called by all `nthreads` threads of the workgroup (tid 0..nthreads-1) after a barrier; ends with a barrier.
 // Everything the merge reads from memory is requested at once (one trip, which is most of its
 // time when the slices come from other workgroups): the lists by all threads, the statistics by the
-// last wave.  Then the K-th best list head becomes a threshold (with at least K lists), which only
-// a few entries pass, and those are ranked by counting.
+// last wave.  Then the K-th best list head becomes a threshold (with at least K lists; every wave finds
+// it for itself), which only a few entries pass, and those are ranked by counting.
 template <bool COHERENT, int CAP>
-__device__ __forceinline__ void merge_slices(const float4* st, const float* pv, const int* pi, int S, int K,
-                                             float inv_t, MergeScratch<CAP>& sm, int tid, int nthreads) {
+__device__ __forceinline__ void merge_slices(const float4* st, const unsigned long long* pk, int S, int K, float inv_t,
+                                             MergeScratch<CAP>& sm, int tid, int nthreads) {
   const int lane = tid & 63;
-  __shared__ float head_v[MAX_SPLITS];
-  __shared__ int head_i[MAX_SPLITS];
+  __shared__ unsigned long long head[MAX_SPLITS];
   constexpr int PER = 4;  // entries a thread keeps in registers (a trip covers PER x nthreads of the S x K)
   const int n_all = S * K;
-  float ev[PER];
-  int ei[PER];
+  unsigned long long ek[PER];
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     const int e = tid + q * nthreads;
-    ev[q] = -HS_INF;
-    ei[q] = INT_MAX;
-    if (e < n_all) {
-      ev[q] = COHERENT ? ld_dev(pv + e) : pv[e];
-      ei[q] = COHERENT ? ld_dev(pi + e) : pi[e];
-    }
+    ek[q] = 0ull;
+    if (e < n_all) ek[q] = COHERENT ? ld_dev(pk + e) : pk[e];
   }
   Stats a = stats_empty();
   const bool stats_wave = tid >= nthreads - 64;
@@ -213,63 +229,33 @@ __device__ __forceinline__ void merge_slices(const float4* st, const float* pv, 
       a = Stats{f.x, f.y, f.z};
     }
   }
-  for (int e = tid; e < n_all; e += nthreads) sm.rank[e] = 0;
   if (tid == 0) sm.cnt = 0;
+  if (tid < HS_MAX_TOPK) sm.best[tid] = 0ull;
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     const int e = tid + q * nthreads;
-    if (e < n_all && e % K == 0) {
-      head_v[e / K] = ev[q];
-      head_i[e / K] = ei[q];
-    }
+    if (e < n_all && e % K == 0) head[e / K] = ek[q];
   }
+  __syncthreads();
+  // threshold: the K-th best list head when there are at least K lists, else "every entry passes"
+  unsigned long long thr = 1ull;
+  if (S >= K) {
+    const unsigned long long hk = lane < S ? head[lane] : 0ull;
+    int rank = 0;
+    for (int l = 0; l < S; ++l) rank += lane_key(hk, l) > hk ? 1 : 0;
+    const unsigned long long who = __ballot(rank == K - 1 && hk != 0ull);
+    if (who != 0ull) thr = lane_key(hk, __ffsll((long long)who) - 1);
+  }
+  auto admit = [&](unsigned long long k) {
+    if (k >= thr) sm.key[atomicAdd(&sm.cnt, 1)] = k;  // (order of arrival does not matter; at most S * K <= CAP entries)
+  };
+#pragma unroll
+  for (int q = 0; q < PER; ++q) admit(ek[q]);
+  for (int e = tid + PER * nthreads; e < n_all; e += nthreads)  // (more entries than PER x nthreads: the rest)
+    admit(COHERENT ? ld_dev(pk + e) : pk[e]);
   if (stats_wave) {
     a = stats_wave_sum(a, inv_t);
     if (lane == 0) sm.total = a;
-  }
-  __syncthreads();
-  if (tid < 64) {
-    // threshold: the K-th best list head when there are at least K lists, else "everything passes"
-    float tv = -HS_INF;
-    int ti = INT_MAX;
-    if (S >= K) {
-      const float hv = lane < S ? head_v[lane] : -HS_INF;
-      const int hi = lane < S ? head_i[lane] : INT_MAX;
-      int r = wave_rank(hv, hi, S);
-      unsigned long long who = __ballot(r == K - 1 && lane < S);
-      if (who != 0ull) {
-        int src = __ffsll((long long)who) - 1;
-        tv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, hv), src));
-        ti = __builtin_amdgcn_readlane(hi, src);
-      }
-    }
-    if (lane == 0) {
-      sm.thr_v = tv;
-      sm.thr_i = ti;
-    }
-  }
-  __syncthreads();
-  {
-    const float tv = sm.thr_v;
-    const int ti = sm.thr_i;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      if (ei[q] != INT_MAX && !better(tv, ti, ev[q], ei[q])) {  // (INT_MAX: an unused list entry, or none)
-        int pos = atomicAdd(&sm.cnt, 1);  // order of arrival does not matter: ranks are computed below
-        sm.cv[pos] = ev[q];               // (at most S * K <= CAP entries)
-        sm.ci[pos] = ei[q];
-      }
-    }
-    // (more entries than PER x nthreads: the rest in further trips)
-    for (int e = tid + PER * nthreads; e < n_all; e += nthreads) {
-      float v = COHERENT ? ld_dev(pv + e) : pv[e];
-      int i = COHERENT ? ld_dev(pi + e) : pi[e];
-      if (i != INT_MAX && !better(tv, ti, v, i)) {
-        int pos = atomicAdd(&sm.cnt, 1);
-        sm.cv[pos] = v;
-        sm.ci[pos] = i;
-      }
-    }
   }
   __syncthreads();
   rank_candidates(sm, sm.cnt, K, tid, nthreads);
@@ -285,25 +271,26 @@ __device__ __forceinline__ void write_row(const MergeScratch<CAP>& sm, int64_t r
   const int lane = tid;
   const float m = sm.total.m, s1 = sm.total.s1, t = sm.total.t;
   const float l1p = log1pf(s1);
+  float ov;
+  int oi;
+  pair_of(lane < K ? sm.best[lane] : 0ull, ov, oi);
   if (lane < K) {
-    topk_idx[row * K + lane] = sm.oi[lane];
-    topk_logp[row * K + lane] = (sm.ov[lane] - m) * inv_t - l1p;
+    topk_idx[row * K + lane] = oi;
+    topk_logp[row * K + lane] = (ov - m) * inv_t - l1p;
   }
   // Top-K probabilities renormalised over the K: weights relative to the best one (lane = entry);
   // entropy = ln(1 + sum w) - sum(w a) / (1 + sum w), every term of one sign
+  const float best = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ov)));
   float w = 0.f, wa = 0.f;
   if (lane >= 1 && lane < K) {
-    const float a = (sm.ov[lane] - sm.ov[0]) * inv_t;
+    const float a = (ov - best) * inv_t;
     if (a > -100.f) {
       w = expf(a);
       wa = w * a;
     }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    w += __shfl_xor(w, off);
-    wa += __shfl_xor(wa, off);
-  }
+  w = wave_sum(w);
+  wa = wave_sum(wa);
   if (lane == 0) {
     ent_topk[row] = log1pf(w) - wa / (1.f + w);
     if (ent_full) ent_full[row] = l1p - t / (1.f + s1);
@@ -324,7 +311,7 @@ template <bool VEC, int SCAN_THREADS, bool FUSED, int NBUF, bool STATS>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restrict__ logits, int64_t row_stride,
                                                             int V, int K, float inv_t, int tiles_per_wg,
                                                             float4* __restrict__ part_stats,
-                                                            float* __restrict__ part_val, int* __restrict__ part_idx,
+                                                            unsigned long long* __restrict__ part_key,
                                                             int32_t* __restrict__ topk_idx,
                                                             float* __restrict__ topk_logp,
                                                             float* __restrict__ ent_topk,
@@ -344,29 +331,27 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
   constexpr int SCAN_CAP = (FUSED && SCAN_WAVES * HS_MAX_TOPK < FUSED_CAP) ? FUSED_CAP : SCAN_WAVES * HS_MAX_TOPK;
   __shared__ float4 wave_st[SCAN_WAVES];
   __shared__ float group_maxima[SCAN_GROUPS];
+  __shared__ __attribute__((aligned(16))) float lane_vals[SCAN_WAVES][64 * SCAN_VPT];  // values of the lanes that reach the threshold
+  __shared__ int lane_ids[SCAN_WAVES][64];
   __shared__ MergeScratch<SCAN_CAP> sm;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (uniform for the compiler too)
   const int split = blockIdx.x, S = gridDim.x, row = blockIdx.y;
   // (rows from rows1 on may lie in a second array)
   const float* __restrict__ x = (logits2 != nullptr && src_row >= rows1) ? logits2 + (src_row - rows1) * row_stride
                                                                          : logits + src_row * row_stride;
 
-  // this wave's K best pairs so far, best first, entry l in lane l; the rest holds a pair that
-  // loses against every real one
-  float lv = -HS_INF;
-  int li = INT_MAX;
-  // statistics are kept in the log2 domain while scanning: y = (x - m) * c, c = log2(e) / T
-  const float c = inv_t * LOG2E;
-  float m = -HS_INF, s1 = 0.f, t2 = 0.f;
+  // this wave's K best pairs so far, best first, entry l in lane l as a key (0: none yet); `floor_key` is
+  // what a pair has to beat to join them, `thr` what its value has to reach
+  unsigned long long best = 0ull, floor_key = 0ull;
   float thr = -HS_INF;
-  int thr_i = INT_MAX;  // among elements equal to thr only those with a lower index can still enter the list
-  if (tid == 0) sm.cnt = 0;
-  if (tid < HS_MAX_TOPK) {  // a slice with fewer than K elements leaves the rest of its list unused
-    sm.ov[tid] = -HS_INF;
-    sm.oi[tid] = INT_MAX;
-  }
-  __syncthreads();
+  // Statistics in the log2 domain, y = (x - ref) * c with c = log2(e) / T, relative to the maximum of all the
+  // values this wave has seen: s1 and t2 are this lane's sums of 2^y and 2^y y over its values, one
+  // instance of the maximum held out of them.
+  const float c = inv_t * LOG2E;
+  float ref = -HS_INF, s1 = 0.f, t2 = 0.f;
+  if (tid < HS_MAX_TOPK) sm.best[tid] = 0ull;  // (a slice with fewer than K elements leaves the rest unused)
 
   auto load_tile = [&](int tile, float (&v)[SCAN_VPT]) {
     const int tbase = (split * tiles_per_wg + tile) * SCAN_TILE;
@@ -405,43 +390,74 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
   n_full = n_full < 0 ? 0 : (n_full > n_my ? n_my : n_full);
 
   // One tile: statistics of this thread's 16 values, threshold, insertion of the few values that
-  // reach it.
-  auto process = [&](const float (&v)[SCAN_VPT], int tile) {
+  // reach it.  The arithmetic of the statistics bounds the scan of many rows, so the tile without a new
+  // maximum, nearly every one, does five instructions to a value and no more.  (With the maximum held out
+  // per lane every tile searched for it and paid eight: one four-wave workgroup scanned a row of 128256
+  // logits in 38.9 us, now 28.6; 896 rows took 98.8 us, now 92.5, which is 5 TB/s.)
+  auto process = [&](const float (&v)[SCAN_VPT], int tile, auto is_first) __attribute__((always_inline)) {
+    constexpr bool FIRST = decltype(is_first)::value;
     const int tbase = (split * tiles_per_wg + tile) * SCAN_TILE;
-#define HS_IDX(jj) (tbase + (((jj) >> 2) * SCAN_THREADS + tid) * 4 + ((jj)&3))
 
-    // ---- softmax statistics of this thread's values
     float tm = fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7])));
     tm = fmaxf(tm, fmaxf(fmaxf(fmaxf(v[8], v[9]), fmaxf(v[10], v[11])), fmaxf(fmaxf(v[12], v[13]), fmaxf(v[14], v[15]))));
-    int skip = -1;
-    if (STATS && tm > m) {
+    if (STATS) {
+      float st = 0.f, tt = 0.f;  // the tile's sums
+      if (FIRST || __ballot(tm > ref) != 0ull) {
+        // a new maximum (FIRST: or no value at all): the sums so far move to it, the old one joins them
+        const float wm = wave_max(tm);
+        if (wm != -HS_INF) {
+          const int leader = __ffsll((long long)__ballot(tm == wm)) - 1;
+          if (!FIRST && ref != -HS_INF) {
+            const float d2 = (ref - wm) * c;
+            const float e = exp2_fast(d2);
+            const float w = s1 + (lane == leader ? 1.f : 0.f);
+            t2 = e * (t2 + d2 * w);
+            s1 = e * w;
+          }
+          ref = wm;
+          int skip = -1;  // the instance that is held out: the leader's first
+          if (lane == leader) {
 #pragma unroll
-      for (int jj = SCAN_VPT - 1; jj >= 0; --jj) skip = (v[jj] == tm) ? jj : skip;  // first instance of the max
-      if (m != -HS_INF) {
-        const float d2 = (m - tm) * c;
-        const float e = exp2_fast(d2);
-        const float w = 1.f + s1;
-        t2 = e * (t2 + d2 * w);
-        s1 = e * w;
-      }
-      m = tm;
-    }
-    if (STATS && tm != -HS_INF) {
+            for (int jj = SCAN_VPT - 1; jj >= 0; --jj) skip = (v[jj] == wm) ? jj : skip;
+          }
 #pragma unroll
-      for (int jj = 0; jj < SCAN_VPT; ++jj) {
-        // x - m first: exact near the maximum (an fma with a rounded m * c would leave the maximum's
-        // own y slightly off zero and put that into t2); the clamp keeps 0 * -inf out of t2
-        const float y = fmaxf((v[jj] - m) * c, -1e30f);
-        const float e = exp2_fast(y);
-        t2 = fmaf(e, y, t2);
-        s1 += (jj == skip) ? 0.f : e;
+          for (int jj = 0; jj < SCAN_VPT; ++jj) {
+            // x - ref first: exact near the maximum (an fma with a rounded ref * c would leave the maximum's
+            // own y slightly off zero and put that into t2); the clamp keeps 0 * -inf out of t2
+            const float y = fmaxf((v[jj] - ref) * c, -1e30f);
+            const float e = exp2_fast(y);
+            tt = fmaf(e, y, tt);
+            st += (jj == skip) ? 0.f : e;
+          }
+        }
+      } else if (ref != -HS_INF) {
+#pragma unroll
+        for (int jj = 0; jj < SCAN_VPT; ++jj) {
+          const float y = (v[jj] - ref) * c;
+          const float e = exp2_fast(y);
+          tt = fmaf(e, y, tt);
+          st += e;
+        }
+        if (__ballot(!(tt == tt)) != 0ull) {  // masked logits among them (0 * -inf): the tile again, clamped
+          st = 0.f;
+          tt = 0.f;
+#pragma unroll
+          for (int jj = 0; jj < SCAN_VPT; ++jj) {
+            const float y = fmaxf((v[jj] - ref) * c, -1e30f);
+            const float e = exp2_fast(y);
+            tt = fmaf(e, y, tt);
+            st += e;
+          }
+        }
       }
+      s1 += st;
+      t2 += tt;
     }
 
     // ---- threshold (a value): no element below it can be among the row's K best.  First tile:
     // the K-th largest of the workgroup's group maxima (K elements of the tile reach it), or of
     // this wave's 64 lane maxima; afterwards also the wave's own K-th entry once its list is full.
-    if (tile == 0) {
+    if (FIRST) {
       // Groups that hold no value of the row have no maximum: counting them, the K-th largest of the
       // maxima would be -inf and every value of a short row would be inserted one by one (17 rows of
       // 1024 logits: 26.8 us; with the groups counted and four-wave workgroups see plan_scan).
@@ -470,85 +486,90 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
         thr = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, tm), __ffsll((long long)who) - 1));
       }
     }
-    // the wave's own K-th entry, once it is at least as good as the threshold, replaces it as a
-    // (value, index) pair: an element that equals it in value enters only with a lower index
-    // (rows of equal logits would otherwise send every element through the insertion)
-    auto tighten = [&]() {
-      const float kv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, lv), K - 1));
-      if (kv >= thr) {
-        thr = kv;
-        thr_i = __builtin_amdgcn_readlane(li, K - 1);  // INT_MAX while the list is not full
-      }
-    };
-    tighten();
 
-    // ---- insert the elements that reach the threshold (skipped when no lane's maximum does)
-    if (__ballot(tm >= thr) != 0ull) {
+    // ---- insert the elements that reach the threshold.  A lane whose maximum does puts its 16 values into
+    // LDS; 64 of them at a time, one to a lane, are then compared with the list's worst entry, and what
+    // beats it is inserted.  (One copy of the insertion for the whole tile, not one for each register: short
+    // scans wait for their instructions more than for anything else, 10 rows in 16 slices 13.9 us to 12.9.)  (The floor is a pair: of equal values only lower indices beat it, or rows of
+    // equal logits would send every element through the insertion.)
+    const unsigned long long lanes = __ballot(tm >= thr);
+    if (lanes != 0ull) {
+      float* const vals = lane_vals[wave];
+      if (tm >= thr) {
+        const int at = lanes_below(lanes);
 #pragma unroll
-      for (int jj = 0; jj < SCAN_VPT; ++jj) {
-        if (__ballot(v[jj] >= thr) != 0ull) {
-          const int idx = HS_IDX(jj);
-          unsigned long long todo = __ballot(v[jj] > thr || (v[jj] == thr && idx < thr_i));
-          while (todo != 0ull) {
-            const int src = __ffsll((long long)todo) - 1;
-            todo &= todo - 1ull;
-            const float xv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[jj]), src));
-            const int xi = __builtin_amdgcn_readlane(idx, src);
-            list_insert(xv, xi, lv, li);
-          }
-          tighten();
+        for (int j = 0; j < 4; ++j)
+          *reinterpret_cast<float4*>(vals + at * SCAN_VPT + j * 4) = make_float4(v[j * 4], v[j * 4 + 1], v[j * 4 + 2], v[j * 4 + 3]);
+        lane_ids[wave][at] = lane;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (other lanes' values; LDS keeps a wave's order)
+      const int n = __popcll(lanes) * SCAN_VPT;
+      for (int e0 = 0; e0 < n; e0 += 64) {
+        unsigned long long key = 0ull;
+        if (e0 + lane < n) {
+          const float x = vals[e0 + lane];
+          const int jj = lane & (SCAN_VPT - 1), from = lane_ids[wave][(e0 + lane) / SCAN_VPT];
+          const int idx = tbase + (((jj >> 2) * SCAN_THREADS) + wave * 64 + from) * 4 + (jj & 3);
+          // (rows end inside a tile: what lies past the end is no value)
+          if (x >= thr && idx < V) key = pair_key(x, idx);
+        }
+        for (unsigned long long todo = __ballot(key > floor_key); todo != 0ull; todo &= __ballot(key > floor_key)) {
+          const int src = __ffsll((long long)todo) - 1;
+          todo &= todo - 1ull;
+          list_insert(lane_key(key, src), best);
+          floor_key = lane_key(best, K - 1);  // (0 while the list is not full)
         }
       }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (floor_key != 0ull) thr = fmaxf(thr, ordered_value((unsigned)(floor_key >> 32)));
     }
-#undef HS_IDX
   };
   // NBUF register buffers, NBUF - 1 tiles in flight: the loads of tile t + NBUF - 1 are requested
   // before tile t is processed (what is in flight bounds the bandwidth).  The steady-state loop
   // requests without a condition, so that the wait before a tile's values counts exactly the younger
   // tiles; the last tiles run through the guarded copy below.
   float buf[NBUF][SCAN_VPT];
-  // (whole tiles by the unconditional loads: the guarded ones wait for each other)
+  const std::true_type YES{};
+  const std::false_type NO{};
+  int tile = 1;
+  if (n_full >= 2 * NBUF) {
+    // (requested without a condition as well: a wait counts only loads that are pending on every path to it)
 #pragma unroll
-  for (int b = 0; b < NBUF - 1; ++b) {
-    if (b < n_full) load_full_tile(b, buf[b]);
-    else if (b < n_my) load_tile(b, buf[b]);
-  }
-  int tile = 0;
-  for (; tile + 2 * NBUF - 2 < n_full; tile += NBUF) {
+    for (int b = 0; b < NBUF; ++b) load_full_tile(b, buf[b]);
+    process(buf[0], 0, YES);
+    for (; tile + 2 * NBUF - 2 < n_full; tile += NBUF) {
+#pragma unroll
+      for (int b = 0; b < NBUF; ++b) {
+        load_full_tile(tile + b + NBUF - 1, buf[b]);
+        process(buf[(b + 1) % NBUF], tile + b, NO);
+      }
+    }
+  } else {
+    // (whole tiles by the unconditional loads: the guarded ones wait for each other)
 #pragma unroll
     for (int b = 0; b < NBUF; ++b) {
-      load_full_tile(tile + b + NBUF - 1, buf[(b + NBUF - 1) % NBUF]);
-      process(buf[b], tile + b);
+      if (b < n_full) load_full_tile(b, buf[b]);
+      else if (b < n_my) load_tile(b, buf[b]);
     }
+    if (n_my > 0) process(buf[0], 0, YES);
   }
   for (; tile < n_my; tile += NBUF) {
 #pragma unroll
     for (int b = 0; b < NBUF; ++b) {
       if (tile + b < n_my) {
-        if (tile + b + NBUF - 1 < n_my) load_tile(tile + b + NBUF - 1, buf[(b + NBUF - 1) % NBUF]);
-        process(buf[b], tile + b);
+        if (tile + b + NBUF - 1 < n_my) load_tile(tile + b + NBUF - 1, buf[b]);
+        process(buf[(b + 1) % NBUF], tile + b, NO);
       }
     }
   }
 
   // ---- the waves' statistics and the real entries of their lists meet in LDS
   if (STATS) {
-    Stats st{m, s1, t2 * 0.6931471805599453f};  // back to natural-log units
-    st = stats_wave_sum(st, inv_t);
-    if (lane == 0) wave_st[wave] = make_float4(st.m, st.s1, st.t, 0.f);
+    // (the maximum is the whole wave's: plain sums; t back in natural-log units)
+    const float ws = wave_sum(s1), wt = wave_sum(t2);
+    if (lane == 0) wave_st[wave] = make_float4(ref, ws, wt * 0.6931471805599453f, 0.f);
   }
-  {
-    const bool real = lane < K && li != INT_MAX;  // a list's real entries come first
-    const int n_w = __popcll(__ballot(real));
-    int base = 0;
-    if (lane == 0) base = atomicAdd(&sm.cnt, n_w);  // (zeroed at the start, a barrier ago)
-    base = __builtin_amdgcn_readfirstlane(base);
-    if (real) {
-      sm.cv[base + lane] = lv;
-      sm.ci[base + lane] = li;
-      sm.rank[base + lane] = 0;
-    }
-  }
+  if (lane < K) sm.key[wave * K + lane] = best;
   __syncthreads();
   if (STATS && tid < 64) {
     Stats a = stats_empty();
@@ -559,18 +580,20 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
     a = stats_wave_sum(a, inv_t);
     if (lane == 0) sm.total = a;
   }
-  rank_candidates(sm, sm.cnt, K, tid, SCAN_THREADS);  // (its first barrier also publishes sm.total)
+  rank_candidates(sm, SCAN_WAVES * K, K, tid, SCAN_THREADS);  // (its barrier also publishes sm.total)
   static_assert(STATS || !FUSED, "rows are finished by the caller of a scan without statistics");
   if (S == 1) {
     if (STATS) write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
-    else if (tid < K) topk_idx[row * K + tid] = sm.oi[tid];
+    else if (tid < K) {
+      float ov;
+      int oi;
+      pair_of(sm.best[tid], ov, oi);
+      topk_idx[row * K + tid] = oi;
+    }
   } else {
     const int64_t slot = (int64_t)row * S + split;
     if (!FUSED) {
-      if (tid < K) {
-        part_val[slot * K + tid] = sm.ov[tid];
-        part_idx[slot * K + tid] = sm.oi[tid];
-      }
+      if (tid < K) part_key[slot * K + tid] = sm.best[tid];
       if (STATS && tid == 0) part_stats[slot] = make_float4(sm.total.m, sm.total.s1, sm.total.t, 0.f);
     } else {
       __shared__ int is_last;
@@ -578,10 +601,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
       // they are acknowledged (vmcnt) the ticket is drawn.  The workgroup that draws the last one
       // finds every slice of the row written.
       if (tid < 64) {
-        if (tid < K) {
-          st_dev(part_val + slot * K + tid, sm.ov[tid]);
-          st_dev(part_idx + slot * K + tid, sm.oi[tid]);
-        }
+        if (tid < K) st_dev(part_key + slot * K + tid, sm.best[tid]);
         if (tid < 3) st_dev(reinterpret_cast<float*>(part_stats + slot) + tid, tid == 0 ? sm.total.m : tid == 1 ? sm.total.s1 : sm.total.t);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (tid == 0) {
@@ -593,8 +613,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
       }
       __syncthreads();
       if (is_last) {
-        merge_slices<true>(part_stats + (int64_t)row * S, part_val + (int64_t)row * S * K, part_idx + (int64_t)row * S * K,
-                           S, K, inv_t, sm, tid, SCAN_THREADS);
+        merge_slices<true>(part_stats + (int64_t)row * S, part_key + (int64_t)row * S * K, S, K, inv_t, sm, tid, SCAN_THREADS);
         write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
       }
     }
@@ -608,8 +627,7 @@ __global__ __launch_bounds__(256) void k_fill_zero(uint4* __restrict__ p, size_t
 }
 
 __global__ __launch_bounds__(FIN_THREADS) void k_scan_finalize(const float4* __restrict__ part_stats,
-                                                               const float* __restrict__ part_val,
-                                                               const int* __restrict__ part_idx, int S, int K,
+                                                               const unsigned long long* __restrict__ part_key, int S, int K,
                                                                float inv_t, int32_t* __restrict__ topk_idx,
                                                                float* __restrict__ topk_logp,
                                                                float* __restrict__ ent_topk,
@@ -622,7 +640,7 @@ __global__ __launch_bounds__(FIN_THREADS) void k_scan_finalize(const float4* __r
   const int64_t row = blockIdx.x;
   if (row_active != nullptr && row_active[row] == 0) return;
   if (row_index != nullptr && row_index[row] < 0) return;
-  merge_slices<false>(part_stats + row * S, part_val + row * S * K, part_idx + row * S * K, S, K, inv_t, sm, tid, FIN_THREADS);
+  merge_slices<false>(part_stats + row * S, part_key + row * S * K, S, K, inv_t, sm, tid, FIN_THREADS);
   write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
 }
 
@@ -630,7 +648,7 @@ size_t row_topk_workspace(int R, int V, int K) {
   if (R <= 0) return 0;
   ScanPlan p = plan_scan(R, V);
   size_t n = (size_t)R * p.splits;
-  return TICKET_BYTES + align_up(n * sizeof(float4), 256) + 2 * align_up(n * K * sizeof(float), 256);
+  return TICKET_BYTES + align_up(n * sizeof(float4), 256) + align_up(n * K * sizeof(unsigned long long), 256);
 }
 
 hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V, int K, float temperature,
@@ -646,8 +664,7 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
   // of the workspace, whatever the shape, so that calls of different shapes can share a prepared one
   unsigned* tickets = c.take<unsigned>(TICKET_BYTES / sizeof(unsigned));
   float4* part_stats = c.take<float4>(n);
-  float* part_val = c.take<float>(n * K);
-  int* part_idx = c.take<int>(n * K);
+  unsigned long long* part_key = c.take<unsigned long long>(n * K);
   const float inv_t = 1.0f / temperature;
   const bool vec = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && (row_stride % 4 == 0) &&
                    (reinterpret_cast<uintptr_t>(logits2) % 16 == 0);
@@ -656,7 +673,7 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
   const bool fused = prepared && slices == nullptr && p.splits > 1 && p.splits * K <= FUSED_CAP;
 #define HS_SCAN_LAUNCH(VEC, T, F, ST)                                                                                     \
   hipLaunchKernelGGL((k_scan_rows<VEC, T, F, 3, ST>), grid, dim3(T), 0, stream, logits, row_stride, V, K, inv_t, p.tiles_per_wg, \
-                     part_stats, part_val, part_idx, topk_idx, topk_logp, ent_topk, ent_full, lse, row_active, row_index, logits2, rows1, tickets)
+                     part_stats, part_key, topk_idx, topk_logp, ent_topk, ent_full, lse, row_active, row_index, logits2, rows1, tickets)
   if (slices != nullptr && slices->pairs_only) {
     if (p.threads == SCAN_BIG) {
       if (vec) HS_SCAN_LAUNCH(true, SCAN_BIG, false, false);
@@ -683,13 +700,11 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
 #undef HS_SCAN_LAUNCH
   hs_status st = launch_status("row scan");
   if (slices != nullptr) {
-    slices->val = part_val;
-    slices->idx = part_idx;
+    slices->key = part_key;
     slices->count = p.splits;
   }
   if (st != HS_OK || p.splits == 1 || slices != nullptr || fused) return st;
-  hipLaunchKernelGGL(k_scan_finalize, dim3(R), dim3(FIN_THREADS), 0, stream, part_stats, part_val, part_idx,
-                     p.splits, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, row_active, row_index);
+  hipLaunchKernelGGL(k_scan_finalize, dim3(R), dim3(FIN_THREADS), 0, stream, part_stats, part_key, p.splits, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, row_active, row_index);
   return launch_status("row scan merge");
 }
 

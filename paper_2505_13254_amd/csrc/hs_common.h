@@ -37,9 +37,9 @@ struct Carver {
 // Row scan shared by hs_draft_entropy_topk and hs_verify_accept (defined in entropy_topk.hip).
 size_t row_topk_workspace(int R, int V, int K);
 // `slices` (may be NULL): when the rows had to be cut into slices, the merge launch is left to the
-// caller, who receives the per-slice results instead: entry (row * count + slice) * K + k of
-// val / idx is the slice's k-th best pair (an unused entry has index INT_MAX).  count == 1 means
-// the outputs were written in full.
+// caller, who receives the per-slice results instead: entry (row * count + slice) * K + k of `key` is
+// the slice's k-th best pair as one number: of two keys the larger is the better pair, the lower half
+// is 2^32 - 1 - index, 0 is an unused entry.  count == 1 means the outputs were written in full.
 // `row_active` (device, may be NULL): one byte per row; a row whose byte is 0 is neither read nor
 // written.  `row_index` (device, may be NULL): result row r is computed from logits row
 // row_index[r]; a negative entry leaves row r's results as they are.  `logits2` (may be NULL):
@@ -47,8 +47,7 @@ size_t row_topk_workspace(int R, int V, int K);
 // `prepared`: the workspace was cleared by hs_workspace_prepare and has since been used by completed
 // calls of this kind only; rows cut into slices are then merged by the scan's own launch.
 struct ScanSlices {
-  const float* val;
-  const int32_t* idx;
+  const unsigned long long* key;
   int count;
   bool pairs_only = false;  // in: the caller wants the slices' best pairs only, no softmax statistics
 };

@@ -45,12 +45,11 @@ constexpr float FIX_SCALE = 0x1p62f;   // probabilities are summed as 64-bit int
 constexpr double FIX_UNIT = 0x1p-62;   // the sums do not depend on the order of their terms
 
 // ----------------------------------------------------------------------------------- greedy
-// With n_slices > 1 the target rows' argmax arrives as one (value, index) pair per row slice
-// (the row scan's merge launch is folded into this kernel): the best pair under (value
-// descending, index ascending) is the row's argmax, stored in `arg` for the walk.
+// With n_slices > 1 the target rows' argmax arrives as one pair per row slice (the row scan's merge
+// launch is folded into this kernel): the slice's largest key is the row's argmax, stored in `arg` for
+// the walk.
 __global__ __launch_bounds__(GR_THREADS) void k_accept_greedy(int32_t* __restrict__ arg,
-                                                              const float* __restrict__ slice_val,
-                                                              const int32_t* __restrict__ slice_idx, int n_slices,
+                                                              const unsigned long long* __restrict__ slice_key, int n_slices,
                                                               const int32_t* __restrict__ token,
                                                               const int32_t* __restrict__ parent,
                                                               const int32_t* __restrict__ node_offsets,
@@ -83,16 +82,9 @@ __global__ __launch_bounds__(GR_THREADS) void k_accept_greedy(int32_t* __restric
   if (n_slices > 1) {
     for (int i = tid; i < n; i += GR_THREADS) {
       const int64_t base = (int64_t)(o + i) * n_slices;
-      float bv = slice_val[base];
-      int bi = slice_idx[base];
-      for (int q = 1; q < n_slices; ++q) {
-        const float v = slice_val[base + q];
-        const int x = slice_idx[base + q];
-        if (better(v, x, bv, bi)) {
-          bv = v;
-          bi = x;
-        }
-      }
+      unsigned long long best = 0ull;
+      for (int q = 0; q < n_slices; ++q) best = max(best, slice_key[base + q]);
+      const int bi = best != 0ull ? (int)(0xffffffffu - (unsigned)best) : INT_MAX;
       arg[o + i] = bi;
       if (staged) l_arg[i] = bi;
     }
@@ -1003,7 +995,7 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
              workspace_bytes);
   int32_t *t_arg = nullptr, *d_arg = nullptr;
   float *t_lz = nullptr, *d_lz = nullptr;
-  hs::ScanSlices slices{nullptr, nullptr, 1};
+  hs::ScanSlices slices{nullptr, 1};
   slices.pairs_only = true;  // (the greedy walk needs the rows' argmax and nothing else)
   hs::ChainOut chain{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   hs::BucketWs bk{};  // (all NULL: no sorted residual)
@@ -1042,7 +1034,7 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     if (r != HS_OK) return r;
   }
   if (!stochastic) {
-    hipLaunchKernelGGL(hs::k_accept_greedy, dim3(B), dim3(hs::GR_THREADS), 0, st, t_arg, slices.val, slices.idx,
+    hipLaunchKernelGGL(hs::k_accept_greedy, dim3(B), dim3(hs::GR_THREADS), 0, st, t_arg, slices.key,
                        slices.count, token, parent, node_offsets, max_depth, accept_len, accept_path, bonus_token);
     return hs::launch_status("accept (greedy)");
   }
