@@ -98,8 +98,19 @@ def _check(status: int, where: str):
         raise HsError(status, where, lib().hs_last_error().decode())
 
 
+# The short calls are bound by what happens here: addresses go to ctypes as plain integers (the declared
+# argument types convert them), the current stream's handle is asked for without building a Stream object,
+# and host arrays that already have the right type are passed as they are (one attention call 17.6 us of host
+# time with objects and copies, 13 us now).
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else _vp(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _host(t: torch.Tensor, dtype) -> torch.Tensor:
+    """`t` as a contiguous CPU tensor of type dtype."""
+    if t.dtype is dtype and t.device.type == "cpu" and t.is_contiguous():
+        return t
+    return t.to(dtype=dtype, device="cpu").contiguous()
 
 
 def _dev(t: torch.Tensor, dtype, name: str) -> torch.Tensor:
@@ -108,9 +119,10 @@ def _dev(t: torch.Tensor, dtype, name: str) -> torch.Tensor:
     return t
 
 
-def _stream(stream) -> _vp:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return _vp(s.cuda_stream)
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def workspace(nbytes: int, device) -> Optional[torch.Tensor]:
@@ -191,9 +203,8 @@ def hs_tree_prune(parent: torch.Tensor, logc: torch.Tensor, node_offsets: torch.
                    out_offsets=torch.empty(B + 1, dtype=torch.int32, device=dev),
                    out_src=torch.empty(max(NN, 1), dtype=torch.int32, device=dev),
                    out_parent=torch.empty(max(NN, 1), dtype=torch.int32, device=dev))
-    need = lib().hs_tree_prune_workspace(B, NN)
     if ws is None:
-        ws = workspace(need, dev)
+        ws = workspace(lib().hs_tree_prune_workspace(B, NN), dev)
     tail = (_ptr(d_max), _ptr(theta), _ptr(max_nodes), _ptr(out["depth"]), _ptr(out["cumlogp"]), _ptr(out["keep"]),
             _ptr(out["out_offsets"]), _ptr(out["out_src"]), _ptr(out["out_parent"]),
             _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream))
@@ -321,8 +332,8 @@ def hs_tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, parent, node_offset
         _dev(t, q.dtype, name)
     _dev(parent, torch.int32, "parent"); _dev(node_offsets, torch.int32, "node_offsets")
     _dev(prefix_offsets, torch.int64, "prefix_offsets")
-    hno = host_node_offsets.to(dtype=torch.int32, device="cpu").contiguous()
-    hpo = host_prefix_offsets.to(dtype=torch.int64, device="cpu").contiguous()
+    hno = _host(host_node_offsets, torch.int32)
+    hpo = _host(host_prefix_offsets, torch.int64)
     NN, Hq, D = q.shape
     Hkv = k_tree.shape[1]
     B = hno.numel() - 1
@@ -331,11 +342,10 @@ def hs_tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, parent, node_offset
         out = torch.empty_like(q)
     if want_lse and lse is None:
         lse = torch.empty((NN, Hq), dtype=torch.float32, device=dev)
-    need = lib().hs_tree_attention_workspace(B, NN, int(hpo[-1]), Hq, Hkv, D, dt)
     if ws is None:
-        ws = workspace(need, dev)
+        ws = workspace(lib().hs_tree_attention_workspace(B, NN, int(hpo[-1]), Hq, Hkv, D, dt), dev)
     head = (_ptr(q), _ptr(k_prefix), _ptr(v_prefix), _ptr(k_tree), _ptr(v_tree), _ptr(parent),
-            _ptr(node_offsets), _ptr(prefix_offsets), _vp(hno.data_ptr()), _vp(hpo.data_ptr()))
+            _ptr(node_offsets), _ptr(prefix_offsets), hno.data_ptr(), hpo.data_ptr())
     tail = (B, Hq, Hkv, D, dt, float(scale), _ptr(out), _ptr(lse), _ptr(ws), 0 if ws is None else ws.numel(),
             _stream(stream))
     if shared_tree:
@@ -346,8 +356,8 @@ def hs_tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, parent, node_offset
         st = lib().hs_tree_attention(*head, *tail)
     else:
         _dev(prefix_lens, torch.int64, "prefix_lens")
-        hl = host_prefix_lens.to(dtype=torch.int64, device="cpu").contiguous()
-        st = lib().hs_tree_attention_lens(*head, _ptr(prefix_lens), _vp(hl.data_ptr()), *tail)
+        hl = _host(host_prefix_lens, torch.int64)
+        st = lib().hs_tree_attention_lens(*head, _ptr(prefix_lens), hl.data_ptr(), *tail)
     _check(st, "hs_tree_attention")
     return out, lse
 
@@ -364,8 +374,8 @@ def hs_tree_attention_paged(q, k_pages, v_pages, k_tree, v_tree, parent, node_of
         _dev(t, q.dtype, name)
     _dev(parent, torch.int32, "parent"); _dev(node_offsets, torch.int32, "node_offsets")
     _dev(block_table, torch.int32, "block_table"); _dev(prefix_lens, torch.int64, "prefix_lens")
-    hno = host_node_offsets.to(dtype=torch.int32, device="cpu").contiguous()
-    hl = host_prefix_lens.to(dtype=torch.int64, device="cpu").contiguous()
+    hno = _host(host_node_offsets, torch.int32)
+    hl = _host(host_prefix_lens, torch.int64)
     NN, Hq, D = q.shape
     Hkv = k_tree.shape[1]
     B = hno.numel() - 1
@@ -376,12 +386,11 @@ def hs_tree_attention_paged(q, k_pages, v_pages, k_tree, v_tree, parent, node_of
         out = torch.empty_like(q)
     if want_lse and lse is None:
         lse = torch.empty((NN, Hq), dtype=torch.float32, device=dev)
-    need = lib().hs_tree_attention_workspace(B, NN, int(hl.sum()), Hq, Hkv, D, dt)
     if ws is None:
-        ws = workspace(need, dev)
+        ws = workspace(lib().hs_tree_attention_workspace(B, NN, int(hl.sum()), Hq, Hkv, D, dt), dev)
     st = lib().hs_tree_attention_paged(_ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(k_tree), _ptr(v_tree), _ptr(parent),
-                                       _ptr(node_offsets), _vp(hno.data_ptr()), _ptr(block_table), block_table.shape[1],
-                                       k_pages.shape[1], _ptr(prefix_lens), _vp(hl.data_ptr()), B, Hq, Hkv, D, dt,
+                                       _ptr(node_offsets), hno.data_ptr(), _ptr(block_table), block_table.shape[1],
+                                       k_pages.shape[1], _ptr(prefix_lens), hl.data_ptr(), B, Hq, Hkv, D, dt,
                                        float(scale), _ptr(out), _ptr(lse), _ptr(ws), 0 if ws is None else ws.numel(),
                                        _stream(stream))
     _check(st, "hs_tree_attention_paged")
@@ -457,9 +466,8 @@ def hs_verify_accept(target_logits, draft_logits, token, parent, node_offsets, m
         out = dict(accept_len=torch.empty(B, dtype=torch.int32, device=dev),
                    accept_path=torch.empty((B, max_depth), dtype=torch.int32, device=dev),
                    bonus_token=torch.empty(B, dtype=torch.int32, device=dev))
-    need = lib().hs_verify_accept_workspace_mode(B, NN, V, int(mode))
     if ws is None:
-        ws = workspace(need, dev)
+        ws = workspace(lib().hs_verify_accept_workspace_mode(B, NN, V, int(mode)), dev)
     st = lib().hs_verify_accept(_ptr(target_logits), _ptr(draft_logits), row_stride, _ptr(token), _ptr(parent),
                                 _ptr(node_offsets), B, NN, V, int(mode), float(temperature), _ptr(uniforms),
                                 int(max_depth), _ptr(out["accept_len"]), _ptr(out["accept_path"]),
