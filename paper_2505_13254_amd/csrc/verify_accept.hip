@@ -12,10 +12,9 @@
 //               max(p(v) - beta_j q(v), 0) for every token not yet rejected (beta_j a scalar that
 //               accumulates Z_i / (1 - sum of rejected q)), and frozen at its value of the time
 //               for a rejected token; only its normaliser is needed per rejection.  A node with
-//               one child gets it from one cooperative pass over its two vocabulary rows; for a
-//               node with several children the tokens with p > q are first sorted by p / q into
-//               buckets with their sums (three kernels on the whole chip), after which every
-//               normaliser of the chain is two suffix sums plus the tokens of three buckets.  One
+//               children has the tokens with p > q sorted by p / q into buckets with their sums (one
+//               kernel on the whole chip), after which every normaliser of its chain is two
+//               suffix sums plus, from the second rejection on, the tokens of three buckets.  One
 //               workgroup per node with children runs that node's chain of rejections ahead of
 //               the walk, all nodes in parallel (k_accept_chain), and leaves each child's pair of
 //               current probabilities; the walk itself (k_accept_walk, one workgroup per sequence) then
@@ -37,10 +36,10 @@ constexpr int AC_MAX_ROWS = 8192;   // 64-token rows of the CDF search held in L
 constexpr int BR_SLICES = 16;     // workgroups per tree row that sum the bonus distribution's rows ahead of the walk
 constexpr int BR_THREADS = 512;
 constexpr int BK_NODES = 4096;      // calls with up to this many tree rows get the sorted residual (below)
-constexpr int BK_SLICES = 16;       // vocabulary slices per row in the kernels that build it
+constexpr int BK_SLICES = 16;       // vocabulary slices per row, each sorted by itself
 constexpr int BK_N = 256;           // buckets of the ratio p / q: BK_PER_OCTAVE per factor of two, from 1 upwards
-constexpr int BK_THREADS = 256;     // (one thread per bucket in the scan)
-constexpr float BK_PER_OCTAVE = 16.f;
+constexpr int BK_THREADS = 256;     // (one thread per bucket)
+constexpr float BK_PER_OCTAVE = 32.f;
 constexpr float FIX_SCALE = 0x1p62f;   // probabilities are summed as 64-bit integers in units of 2^-62:
 constexpr double FIX_UNIT = 0x1p-62;   // the sums do not depend on the order of their terms
 
@@ -177,6 +176,16 @@ __device__ __forceinline__ double row16_sum(double x) {
   return x;
 }
 
+// Sum over the lanes of a wave, in every lane, by DPP moves.
+__device__ __forceinline__ double wave_sum_dpp(double x) {
+  x = row16_sum(x);  // lanes 15, 31, 47, 63
+  const int lo = __double2loint(x), hi = __double2hiint(x);
+  double t = __hiloint2double(__builtin_amdgcn_readlane(hi, 15), __builtin_amdgcn_readlane(lo, 15));
+#pragma unroll
+  for (int l = 31; l < 64; l += 16) t += __hiloint2double(__builtin_amdgcn_readlane(hi, l), __builtin_amdgcn_readlane(lo, l));
+  return t;
+}
+
 __device__ __forceinline__ double wave_incl_scan(double v, int lane) {
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -268,29 +277,26 @@ __device__ __forceinline__ int gather_children(const int32_t* __restrict__ paren
 
 // ------------------------------------------------------------------ the sorted residual
 // Along a node's chain of rejections only beta changes: F(beta) = sum_v max(p(v) - beta q(v), 0),
-// taken at an increasing sequence of beta >= 1 that is not known in advance.  A token contributes
-// p - beta q while its ratio p / q exceeds beta and nothing afterwards.  So, for every node with
-// at least two children, three small kernels that run on the whole chip sort the tokens with
-// p > q by their ratio into BK_N buckets (a counting sort: count per vocabulary slice and bucket,
-// scan, scatter) and keep, per bucket, the sums of p and of q.  F(beta) is then
+// taken at an increasing sequence of beta >= 1 that is not known in advance, but for the first:
+// 1.  A token contributes p - beta q while its ratio p / q exceeds beta and nothing afterwards.  So, for
+// every node with children, a kernel that runs on the whole chip sorts the tokens with p > q of each
+// vocabulary slice by their ratio into BK_N buckets (a counting sort inside a workgroup, the slice
+// read twice) and keeps, per bucket, the sums of p and of q.  F(1) is the sum of all of them, F(beta)
 //     sum over the buckets well above beta of (P_b - beta Q_b)      two suffix sums, read once
 //   + sum over the tokens of the three buckets around beta of max(p - beta q, 0)
 // which is what k_accept_chain evaluates per rejection: a few thousand pairs instead of two
-// vocabulary rows.  A token's bucket is floor(BK_PER_OCTAVE * log2(p / q)), taken from the two
+// vocabulary rows.  (Sorted across slices, with a scan and a second pass over the rows in launches of
+// their own: 23.6 us for a 61-row tree; now 16.3.)  A token's bucket is floor(BK_PER_OCTAVE * log2(p / q)), taken from the two
 // exponent arguments (p = exp2(a_p)): the rounding of that difference is many orders below a
 // bucket's width, and one bucket to either side of beta's own is still treated token by token, so
 // no token is ever taken for live or dead by its bucket alone when it is not.  All sums are 64-bit
 // integers in units of 2^-62 (LDS and per-slice partial sums), so neither the order in which the
 // lanes' atomic additions arrive nor the order of the tokens inside a bucket changes a result.
 struct BucketWs {
-  uint32_t* count;            // [NN][BK_SLICES][BK_N] live tokens per (slice, bucket); after the scan: first position
-  unsigned long long* psum;   // [NN][BK_SLICES][BK_N] their p, summed
-  unsigned long long* qsum;   // [NN][BK_SLICES][BK_N] their q
-  uint32_t* start;            // [NN][BK_N + 1] first position of a bucket in `pairs` (ascending ratio)
-  unsigned long long* sp;     // [NN][BK_N + 1] sum of p over the buckets >= b
-  unsigned long long* sq;     // [NN][BK_N + 1] sum of q over them
-  float2* pairs;              // [NN][V] (p, q) of the live tokens, bucket by bucket
-  int32_t* nk;                // [NN] number of children the chain will try
+  uint32_t* start;            // [NN][BK_SLICES][BK_N + 1] first position in `pairs` of a slice's buckets (ascending ratio)
+  unsigned long long* psum;   // [NN][BK_SLICES][BK_N] sum of p over a slice's bucket
+  unsigned long long* qsum;   // [NN][BK_SLICES][BK_N] sum of q over it
+  float2* pairs;              // [NN][V] (p, q) of the live tokens, slice by slice, bucket by bucket
 };
 
 __device__ __forceinline__ int bucket_of(float ap, float aq) {
@@ -298,175 +304,157 @@ __device__ __forceinline__ int bucket_of(float ap, float aq) {
 }
 __device__ __forceinline__ unsigned long long to_fixed(float x) { return (unsigned long long)(x * FIX_SCALE); }
 
-// Sequence, local row and number of children to try of global row g (all threads; one barrier).
-struct NodeRef {
-  int o, n, cur, nk;
-};
-__device__ __forceinline__ NodeRef node_ref(int g, const int32_t* __restrict__ parent,
-                                            const int32_t* __restrict__ node_offsets, int B, int max_depth,
-                                            int* lds_count) {
-  int lo = 0, hi = B;  // sequence of this row: last s with node_offsets[s] <= g
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (node_offsets[mid] <= g) lo = mid; else hi = mid;
-  }
-  NodeRef r;
-  r.o = node_offsets[lo];
-  r.n = node_offsets[lo + 1] - r.o;
-  r.cur = g - r.o;
-  r.nk = 0;
-  if (r.cur >= r.n) return r;  // (an empty sequence before this row's: cannot happen, offsets are monotone)
-  int depth = 0;
-  for (int j = parent[r.o + r.cur]; j >= 0; j = parent[r.o + j]) ++depth;
-  if (threadIdx.x == 0) *lds_count = 0;
-  __syncthreads();
-  if (depth < max_depth) {
-    int c = 0;
-    for (int i = 1 + threadIdx.x; i < r.n; i += blockDim.x) c += parent[r.o + i] == r.cur ? 1 : 0;
-    if (c) atomicAdd(lds_count, c);
-  }
-  __syncthreads();
-  r.nk = *lds_count < AC_MAX_KIDS ? *lds_count : AC_MAX_KIDS;
-  return r;
-}
-
-// grid (BK_SLICES, NN).  SCATTER false: counts and sums of slice blockIdx.x of row blockIdx.y;
-// SCATTER true (after k_bucket_scan): the same pass again, now placing every live pair.
-template <bool SCATTER>
-__global__ __launch_bounds__(BK_THREADS) void k_bucket_pass(
-    const float* __restrict__ target, const float* __restrict__ draft, int64_t row_stride,
-    const int32_t* __restrict__ parent, const int32_t* __restrict__ node_offsets, int B, int V, float inv_t,
-    int max_depth, const int32_t* __restrict__ t_arg, const float* __restrict__ t_lz,
-    const int32_t* __restrict__ d_arg, const float* __restrict__ d_lz, BucketWs ws) {
-  __shared__ unsigned cnt[BK_N];  // SCATTER: the next free position of each bucket
+// grid (BK_SLICES, NN): sorts slice blockIdx.x of row blockIdx.y.  n_tried[g]: children that row g's
+// chain tries.
+__global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restrict__ target, const float* __restrict__ draft,
+                                                            int64_t row_stride, int V, float inv_t,
+                                                            const int32_t* __restrict__ n_tried, const int32_t* __restrict__ t_arg,
+                                                            const float* __restrict__ t_lz, const int32_t* __restrict__ d_arg,
+                                                            const float* __restrict__ d_lz, BucketWs ws) {
+  static_assert(BK_THREADS == BK_N, "a thread per bucket");
+  __shared__ unsigned cnt[BK_N];  // tokens of a bucket; then its next free position
   __shared__ unsigned long long ps[BK_N], qs[BK_N];
-  __shared__ int n_kids;
-  const int slice = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
-  int nk;
-  if (SCATTER) {
-    nk = ws.nk[g];
-  } else {
-    nk = node_ref(g, parent, node_offsets, B, max_depth, &n_kids).nk;
-    if (slice == 0 && tid == 0) ws.nk[g] = nk;
-  }
-  if (nk < 2) return;  // a single rejection is one plain pass of the chain kernel
-  const int64_t slot = ((int64_t)g * BK_SLICES + slice) * BK_N;
-  for (int b = tid; b < BK_N; b += BK_THREADS) {
-    cnt[b] = SCATTER ? ws.count[slot + b] : 0u;
-    ps[b] = 0ull;
-    qs[b] = 0ull;
-  }
+  __shared__ unsigned wave_total[BK_N / 64];
+  const int slice = blockIdx.x, g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nk = n_tried[g];
+  if (nk == 0) return;
+  cnt[tid] = 0u;
+  ps[tid] = 0ull;
+  qs[tid] = 0ull;
   const float* p_row = target + (int64_t)g * row_stride;
   const float* q_row = draft + (int64_t)g * row_stride;
   const RowView p(p_row, p_row[t_arg[g]], t_lz[g], inv_t);
   const RowView q(q_row, q_row[d_arg[g]], d_lz[g], inv_t);
-  float2* __restrict__ pairs = ws.pairs + (int64_t)g * V;
+  const int n4 = V >> 2;
+  const int per = (n4 + BK_SLICES - 1) / BK_SLICES;
+  const int i0 = min(n4, slice * per), i1 = min(n4, i0 + per);
+  const int tail = slice == BK_SLICES - 1 ? V & 3 : 0;  // the last V % 4 tokens are the last slice's
+  const float4* __restrict__ px = reinterpret_cast<const float4*>(p_row);
+  const float4* __restrict__ qx = reinterpret_cast<const float4*>(q_row);
+  auto each_token = [&](auto token) {
+#pragma unroll 2
+    for (int i = i0 + tid; i < i1; i += BK_THREADS) {
+      const float4 fp = px[i], fq = qx[i];
+      token(fp.x, fq.x);
+      token(fp.y, fq.y);
+      token(fp.z, fq.z);
+      token(fp.w, fq.w);
+    }
+    if (tid < tail) token(p_row[(n4 << 2) + tid], q_row[(n4 << 2) + tid]);
+  };
   __syncthreads();
-  auto token = [&](float xp, float xq) {
+  each_token([&](float xp, float xq) {
     const float ap = p.arg(xp), aq = q.arg(xq);
     const float pv = exp2_fast(ap), qv = exp2_fast(aq);
     if (pv > qv) {  // live at beta = 1, where every chain starts
       const int b = bucket_of(ap, aq);
-      if (SCATTER) {
-        pairs[atomicAdd(&cnt[b], 1u)] = make_float2(pv, qv);
-      } else {
-        atomicAdd(&cnt[b], 1u);
-        atomicAdd(&ps[b], to_fixed(pv));
-        atomicAdd(&qs[b], to_fixed(qv));
-      }
+      atomicAdd(&cnt[b], 1u);
+      atomicAdd(&ps[b], to_fixed(pv));
+      atomicAdd(&qs[b], to_fixed(qv));
     }
-  };
-  const int n4 = V >> 2;
-  const int per = (n4 + BK_SLICES - 1) / BK_SLICES;
-  const int i1 = min(n4, (slice + 1) * per);
-  const float4* __restrict__ px = reinterpret_cast<const float4*>(p_row);
-  const float4* __restrict__ qx = reinterpret_cast<const float4*>(q_row);
-#pragma unroll 2
-  for (int i = slice * per + tid; i < i1; i += BK_THREADS) {
-    const float4 fp = px[i], fq = qx[i];
-    token(fp.x, fq.x);
-    token(fp.y, fq.y);
-    token(fp.z, fq.z);
-    token(fp.w, fq.w);
-  }
-  if (slice == BK_SLICES - 1) {  // the last V % 4 tokens
-    const int v = (n4 << 2) + tid;
-    if (v < V) token(p_row[v], q_row[v]);
-  }
-  if (!SCATTER) {
-    __syncthreads();
-    for (int b = tid; b < BK_N; b += BK_THREADS) {
-      ws.count[slot + b] = cnt[b];
-      ws.psum[slot + b] = ps[b];
-      ws.qsum[slot + b] = qs[b];
-    }
-  }
-}
-
-// grid NN, one thread per bucket: per-slice counts become first positions, bucket totals become
-// the suffix sums the chain reads.
-__global__ __launch_bounds__(BK_N) void k_bucket_scan(BucketWs ws) {
-  __shared__ unsigned s_cnt[BK_N];
-  __shared__ unsigned long long s_p[BK_N], s_q[BK_N];
-  const int g = blockIdx.x, b = threadIdx.x;
-  if (ws.nk[g] < 2) return;
-  unsigned off[BK_SLICES], total = 0u;
-  unsigned long long tp = 0ull, tq = 0ull;
-#pragma unroll
-  for (int sl = 0; sl < BK_SLICES; ++sl) {
-    const int64_t at = ((int64_t)g * BK_SLICES + sl) * BK_N + b;
-    off[sl] = total;
-    total += ws.count[at];
-    tp += ws.psum[at];
-    tq += ws.qsum[at];
-  }
-  s_cnt[b] = total;
-  s_p[b] = tp;
-  s_q[b] = tq;
+  });
   __syncthreads();
-  // inclusive prefix counts (ascending) and inclusive suffix sums (descending), log-step
-  for (int d = 1; d < BK_N; d <<= 1) {
-    const unsigned c = b >= d ? s_cnt[b - d] : 0u;
-    const unsigned long long ap = b + d < BK_N ? s_p[b + d] : 0ull, aq = b + d < BK_N ? s_q[b + d] : 0ull;
-    __syncthreads();
-    s_cnt[b] += c;
-    s_p[b] += ap;
-    s_q[b] += aq;
-    __syncthreads();
-  }
-  const unsigned first = s_cnt[b] - total;
-#pragma unroll
-  for (int sl = 0; sl < BK_SLICES; ++sl) ws.count[((int64_t)g * BK_SLICES + sl) * BK_N + b] = first + off[sl];
-  const int64_t row = (int64_t)g * (BK_N + 1);
-  ws.start[row + b] = first;
-  ws.sp[row + b] = s_p[b];
-  ws.sq[row + b] = s_q[b];
-  if (b == BK_N - 1) {
-    ws.start[row + BK_N] = first + total;
-    ws.sp[row + BK_N] = 0ull;
-    ws.sq[row + BK_N] = 0ull;
-  }
+  const int64_t slot = (int64_t)g * BK_SLICES + slice;
+  ws.psum[slot * BK_N + tid] = ps[tid];
+  ws.qsum[slot * BK_N + tid] = qs[tid];
+  if (nk < 2) return;  // (a single rejection needs the sums alone)
+  const unsigned mine = cnt[tid];
+  const unsigned incl = (unsigned)wave_prefix_sum((int)mine);
+  if (lane == 63) wave_total[wave] = incl;
+  __syncthreads();
+  unsigned first = (unsigned)i0 * 4u + incl - mine;
+  for (int w = 0; w < wave; ++w) first += wave_total[w];
+  ws.start[slot * (BK_N + 1) + tid] = first;
+  if (tid == BK_N - 1) ws.start[slot * (BK_N + 1) + BK_N] = first + mine;
+  cnt[tid] = first;
+  __syncthreads();
+  float2* __restrict__ pairs = ws.pairs + (int64_t)g * V;
+  each_token([&](float xp, float xq) {  // (the slice again, from the caches)
+    const float ap = p.arg(xp), aq = q.arg(xq);
+    const float pv = exp2_fast(ap), qv = exp2_fast(aq);
+    if (pv > qv) pairs[atomicAdd(&cnt[bucket_of(ap, aq)], 1u)] = make_float2(pv, qv);
+  });
 }
 
-// A row's bucket tables, staged in LDS once per chain (the chain is serial: what it reads per
-// rejection should not be a round trip to memory).
+// Sums of 64-bit integers over the lanes of a wave by DPP moves of their halves: inclusive prefix sums ...
+__device__ __forceinline__ unsigned long long wave_prefix_sum(unsigned long long x) {
+#define HS_DPP_STEP(ctrl, rows, banks)                                                                                       \
+  x += ((unsigned long long)(unsigned)__builtin_amdgcn_update_dpp(0, (int)(x >> 32), ctrl, rows, banks, false) << 32) |     \
+       (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, banks, false)
+  HS_DPP_STEP(0x111, 0xf, 0xf);  // row_shr:1
+  HS_DPP_STEP(0x112, 0xf, 0xf);  // row_shr:2
+  HS_DPP_STEP(0x114, 0xf, 0xe);  // row_shr:4
+  HS_DPP_STEP(0x118, 0xf, 0xc);  // row_shr:8
+  HS_DPP_STEP(0x142, 0xa, 0xf);  // row_bcast:15
+  HS_DPP_STEP(0x143, 0xc, 0xf);  // row_bcast:31
+#undef HS_DPP_STEP
+  return x;
+}
+// ... and the last lane's, in every lane: the sum.
+__device__ __forceinline__ unsigned long long wave_total(unsigned long long x) {
+  x = wave_prefix_sum(x);
+  return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(x >> 32), 63) << 32) |
+         (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+
+// A row's bucket tables in LDS, made once per chain from the slices' (the chain is serial: what it reads
+// per rejection should not be a round trip to memory).
 struct BucketTables {
-  unsigned start[BK_N + 1];
-  unsigned long long sp[BK_N + 1], sq[BK_N + 1];
+  unsigned start[BK_SLICES][BK_N + 1];
+  unsigned long long sp[BK_N + 1], sq[BK_N + 1];  // sums of p and of q over the buckets >= b
 };
-__device__ __forceinline__ void load_bucket_tables(const BucketWs& ws, int g, BucketTables& t) {
-  const int64_t row = (int64_t)g * (BK_N + 1);
-  for (int b = threadIdx.x; b <= BK_N; b += blockDim.x) {
-    t.start[b] = ws.start[row + b];
-    t.sp[b] = ws.sp[row + b];
-    t.sq[b] = ws.sq[row + b];
+// (all AC_THREADS threads; no barrier at the end)
+__device__ __forceinline__ void load_bucket_tables(const BucketWs& ws, int g, bool with_starts, BucketTables& t) {
+  constexpr int PARTS = AC_THREADS / BK_N, PER = BK_SLICES / PARTS;
+  static_assert(PARTS * BK_N == AC_THREADS && PER * PARTS == BK_SLICES, "a thread per bucket and group of slices");
+  __shared__ unsigned long long part_p[PARTS][BK_N], part_q[PARTS][BK_N], wave_p[BK_N / 64], wave_q[BK_N / 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t first = (int64_t)g * BK_SLICES;
+  {
+    const int b = tid % BK_N, part = tid / BK_N;
+    unsigned long long tp = 0ull, tq = 0ull;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      tp += ws.psum[(first + part * PER + k) * BK_N + b];
+      tq += ws.qsum[(first + part * PER + k) * BK_N + b];
+    }
+    part_p[part][b] = tp;
+    part_q[part][b] = tq;
+  }
+  if (with_starts)
+    for (int e = tid; e < BK_SLICES * (BK_N + 1); e += AC_THREADS) (&t.start[0][0])[e] = ws.start[first * (BK_N + 1) + e];
+  __syncthreads();
+  unsigned long long ip = 0ull, iq = 0ull;
+  const int b = BK_N - 1 - tid;  // (from the top: prefix sums over the threads are suffix sums over the buckets)
+  if (tid < BK_N) {
+#pragma unroll
+    for (int k = 0; k < PARTS; ++k) {
+      ip += part_p[k][b];
+      iq += part_q[k][b];
+    }
+    ip = wave_prefix_sum(ip);
+    iq = wave_prefix_sum(iq);
+    if (lane == 63) {
+      wave_p[tid >> 6] = ip;
+      wave_q[tid >> 6] = iq;
+    }
+  }
+  __syncthreads();
+  if (tid < BK_N) {
+    for (int w = 0; w < (tid >> 6); ++w) {
+      ip += wave_p[w];
+      iq += wave_q[w];
+    }
+    t.sp[b] = ip;
+    t.sq[b] = iq;
+    if (tid == 0) t.sp[BK_N] = t.sq[BK_N] = 0ull;
   }
 }
 
 // What the first wave hands to the others for one rejection, and what they hand back.
 struct BucketStep {
   double beta;
-  int lo, hi;                          // positions in `pairs` of the tokens to take one by one
+  int b_lo, b_hi;                      // buckets whose tokens are taken one by one
   unsigned long long part[AC_WAVES];   // their terms, summed per wave
 };
 
@@ -478,42 +466,82 @@ __device__ __forceinline__ void near_buckets(double beta, int& b_lo, int& b_hi) 
   b_hi = own + 2 < BK_N ? own + 2 : BK_N;
 }
 
-// The terms max(p - beta q, 0) of pairs [lo, hi), all threads of the workgroup, summed per wave into
-// step.part.  They are formed in float64 and summed as integers in units of 2^-52 (the fraction
-// bits of 1 + term, term < 1): the order of the pairs inside a bucket, which the scatter's atomic
+// The terms max(p - beta q, 0) of the pairs in buckets [b_lo, b_hi), a slice to a wave, summed per wave
+// into step.part.  They are formed in float64 and summed as integers in units of 2^-52 (the fraction
+// bits of 1 + term, term < 1): the order of the pairs inside a bucket, which the sort's atomic
 // additions decide, does not reach the result.
-__device__ __forceinline__ void near_terms(const float2* __restrict__ pairs, BucketStep& step) {
-  const int tid = threadIdx.x;
+__device__ __forceinline__ void near_terms(const float2* __restrict__ pairs, const BucketTables& t, BucketStep& step) {
+  static_assert(AC_WAVES == BK_SLICES, "a slice to a wave");
+  constexpr int AHEAD = 8;  // pairs a lane requests together: one trip to memory for about 500 pairs of a slice
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const double beta = step.beta;
-  const int hi = step.hi;
+  const int lo = (int)t.start[wave][step.b_lo], hi = (int)t.start[wave][step.b_hi];
   unsigned long long acc = 0ull;
-#pragma unroll 4
-  for (int i = step.lo + tid; i < hi; i += AC_THREADS) {
-    const float2 e = pairs[i];
-    const double term = fmin(fmax((double)e.x - beta * (double)e.y, 0.0), 0x1.fffffffffffffp-1);
-    acc += (unsigned long long)__double_as_longlong(1.0 + term) & 0xfffffffffffffull;
-  }
+  for (int i = lo + lane; i < hi; i += 64 * AHEAD) {
+    float2 e[AHEAD];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-  if ((tid & 63) == 0) step.part[tid >> 6] = acc;
+    for (int u = 0; u < AHEAD; ++u) e[u] = i + 64 * u < hi ? pairs[i + 64 * u] : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const double term = fmin(fmax((double)e[u].x - beta * (double)e[u].y, 0.0), 0x1.fffffffffffffp-1);
+      acc += (unsigned long long)__double_as_longlong(1.0 + term) & 0xfffffffffffffull;
+    }
+  }
+  acc = wave_total(acc);
+  if (lane == 0) step.part[wave] = acc;
 }
 
-// One workgroup per sequence: the rows the scan of [target rows ; draft rows] has to read: every
-// target row (wanted[row] = 1) and the draft rows of the rows that are somebody's parent
-// (has_child = wanted + NN; nobody reads the draft row of a row without children).
-__global__ __launch_bounds__(GR_THREADS) void k_mark_parents(const int32_t* __restrict__ parent,
-                                                             const int32_t* __restrict__ node_offsets, int NN,
-                                                             uint8_t* __restrict__ wanted) {
+// One workgroup per sequence, ahead of everything else: what the tree says about each row.
+//   wanted    the rows the scan of [target rows ; draft rows] has to read: every target row
+//             (wanted[row] = 1) and the draft rows of the rows that are somebody's parent
+//             (wanted[NN + row]; nobody reads the draft row of a row without children)
+//   n_tried   children that the row's chain tries: none below the last level that may be accepted
+//   tickets   the scan's counters of these rows, cleared (its slices are merged by its own launch)
+// (Every later kernel used to walk from its row to the root for the depth, a chain of global reads.)
+__global__ __launch_bounds__(GR_THREADS) void k_tree_rows(const int32_t* __restrict__ parent,
+                                                          const int32_t* __restrict__ node_offsets, int NN, int max_depth,
+                                                          uint8_t* __restrict__ wanted, int32_t* __restrict__ n_tried,
+                                                          unsigned* __restrict__ tickets) {
+  __shared__ int l_par[GR_LDS_ROWS], l_kids[GR_LDS_ROWS];
   const int s = blockIdx.x, tid = threadIdx.x;
   const int o = node_offsets[s];
   const int n = node_offsets[s + 1] - o;
-  uint8_t* __restrict__ has_child = wanted + NN;
+  const bool staged = n <= GR_LDS_ROWS;
+  if (s == (int)gridDim.x - 1)
+    for (int g = o + n + tid; g < NN; g += GR_THREADS) {  // rows behind the last sequence: nobody's
+      wanted[g] = 0;
+      wanted[NN + g] = 0;
+      n_tried[g] = 0;
+      tickets[g] = 0u;
+      tickets[NN + g] = 0u;
+    }
   for (int i = tid; i < n; i += GR_THREADS) {
     wanted[o + i] = 1;
-    has_child[o + i] = 0;
+    tickets[o + i] = 0u;
+    tickets[NN + o + i] = 0u;
+    if (staged) {
+      l_par[i] = parent[o + i];
+      l_kids[i] = 0;
+    } else {
+      n_tried[o + i] = 0;
+    }
   }
   __syncthreads();
-  for (int i = 1 + tid; i < n; i += GR_THREADS) has_child[o + parent[o + i]] = 1;
+  for (int i = 1 + tid; i < n; i += GR_THREADS) {
+    if (staged) atomicAdd(&l_kids[l_par[i]], 1);
+    else atomicAdd(&n_tried[o + parent[o + i]], 1);
+  }
+  __syncthreads();
+  for (int i = tid; i < n; i += GR_THREADS) {
+    int depth = 0;
+    if (staged)
+      for (int j = l_par[i]; j >= 0; j = l_par[j]) ++depth;
+    else
+      for (int j = parent[o + i]; j >= 0; j = parent[o + j]) ++depth;
+    const int kids = staged ? l_kids[i] : __hip_atomic_load(&n_tried[o + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wanted[NN + o + i] = kids > 0 ? 1 : 0;
+    n_tried[o + i] = depth < max_depth ? min(kids, AC_MAX_KIDS) : 0;
+  }
 }
 
 // What the stochastic walk needs from a node's chain of rejections.
@@ -523,7 +551,7 @@ struct ChainOut {
   double* child_frozen;  // [NN] its weight in the residual after its own rejection
   double* node_beta;     // [NN] beta and normaliser after all of the node's children were rejected
   double* node_Z;
-  int32_t* n_tried;      // [NN] number of children the node's chain tried (0: the node's residual is p itself)
+  int32_t* n_tried;      // [NN] number of children the node's chain tries (0: the node's residual is p itself)
   double* bonus_rows;    // [NN][ceil(V / 64)] row sums of the residual a bonus token would be drawn from
                          // if the walk stopped at the node (NULL: the walk sums the rows of its stop node)
 };
@@ -584,7 +612,7 @@ __device__ __forceinline__ void bonus_row_sums(const RowView& p, const RowView& 
 __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
     const float* __restrict__ target, const float* __restrict__ draft, int64_t row_stride,
     const int32_t* __restrict__ token, const int32_t* __restrict__ parent, const int32_t* __restrict__ node_offsets,
-    int B, int V, float inv_t, int max_depth, const int32_t* __restrict__ t_arg, const float* __restrict__ t_lz,
+    int B, int V, float inv_t, const int32_t* __restrict__ t_arg, const float* __restrict__ t_lz,
     const int32_t* __restrict__ d_arg, const float* __restrict__ d_lz, ChainOut out, BucketWs bk) {
   __shared__ int kids[AC_MAX_KIDS];
   __shared__ int kids_sorted[AC_MAX_KIDS];
@@ -607,26 +635,24 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
   // (row statistics first: these loads do not depend on the tree)
   const float p_lz = t_lz[g], q_lz = d_lz[g];
   const int p_arg = t_arg[g], q_arg = d_arg[g];
-  int depth = 0;
-  for (int j = parent[o + cur]; j >= 0; j = parent[o + j]) ++depth;
-  const int nk = gather_children(parent, o, n, cur, depth < max_depth, kids, kids_sorted, &n_kids);
-  if (tid == 0) out.n_tried[g] = nk;
+  const int nk = out.n_tried[g];
   const float* p_row = target + (int64_t)g * row_stride;
   const RowView p(p_row, p_row[p_arg], p_lz, inv_t);
   if (nk == 0) {
     // no chain to run: this workgroup sums the rows of p, the distribution a bonus token is drawn from
-    // if the walk stops here (done long before the longest chain of the launch)
+    // if the walk stops here (done before the longest chain of the launch: with these rows left to
+    // k_bonus_rows that kernel took 10.3 us instead of 5.7 and this one no less)
     const int n_rows = (V + 63) / 64;
     if (out.bonus_rows != nullptr) bonus_row_sums(p, p, false, 0.0, V, 0, n_rows, out.bonus_rows + (int64_t)g * n_rows);
     return;
   }
+  gather_children(parent, o, n, cur, true, kids, kids_sorted, &n_kids);
   const float* q_row = draft + (int64_t)g * row_stride;
   const RowView q(q_row, q_row[q_arg], q_lz, inv_t);
   // every child's token and its two probabilities, fetched side by side: the chain below is serial,
   // and a round trip to memory per step would dominate it
-  // the sorted residual (bk.pairs may be NULL) exists for the rows with at least two children
-  const bool sorted = bk.pairs != nullptr && nk >= 2;
-  if (sorted) load_bucket_tables(bk, g, tables);
+  const bool sorted = bk.pairs != nullptr;  // there is a sorted residual
+  if (sorted) load_bucket_tables(bk, g, nk >= 2, tables);
   if (tid < nk) {
     const int x = token[o + kids_sorted[tid]];
     kid_p[tid] = p.prob(x);
@@ -638,40 +664,63 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
   if (sorted) {
     // The first wave keeps the chain's scalars; the others only help with the tokens around beta.
     // (Sixteen waves that all repeat the scalar part take issue slots from one another: 4 us a step.)
+    // A step is a chain of its own, a division, two barriers and a trip to memory, so whatever is not
+    // part of it is left for later or for other lanes: lane j keeps what child j's probabilities are
+    // made of, the rejected tokens' corrections are a lane each, sums travel by DPP moves.  (61 rows, chains of
+    // ten: 2.2 us a step, most of it the trip to memory, and 0.6 for the first; 2.6 and a trip before.)
     const bool lead = tid < 64;
+    const int lane = tid & 63;
+    double my_px = 0.0, my_qx = 0.0, my_Z = 1.0, my_rem = 1.0;
     for (int j = 0; j < nk; ++j) {
       int b_hi = 0;
       if (lead) {
-        const int c = kids_sorted[j];
-        const double px = (double)kid_p[j];
-        const double qx = (double)kid_q[j];
-        const double pc = fmax(px - beta * qx, 0.0) / Z;  // current p(x)
-        const double qc = qx / (1.0 - sumq);              // current q(x)
-        beta += Z / (1.0 - sumq);
+        const double px = (double)kid_p[j], qx = (double)kid_q[j];
+        const double rem = 1.0 - sumq;
+        if (lane == (j & 63)) {
+          my_px = fmax(px - beta * qx, 0.0);  // current p(x), times Z
+          my_qx = qx;                         // current q(x), times rem
+          my_Z = Z;
+          my_rem = rem;
+        }
+        beta += Z / rem;
         sumq += qx;
-        const double frozen = fmax(px - beta * qx, 0.0);
-        int b_lo;
-        near_buckets(beta, b_lo, b_hi);
-        rej_w[j] = frozen;  // (every lane of the wave stores the same value; LDS keeps a wave's order)
-        if (tid == 0) {
-          out.child_p[o + c] = pc;
-          out.child_q[o + c] = qc;
-          out.child_frozen[o + c] = frozen;
-          step.beta = beta;
-          step.lo = (int)tables.start[b_lo];
-          step.hi = (int)tables.start[b_hi];
+        rej_w[j] = fmax(px - beta * qx, 0.0);  // (every lane of the wave stores the same value; LDS keeps a wave's order)
+        if ((j & 63) == 63 || j == nk - 1) {
+          const int i = (j & ~63) + lane;
+          if (i <= j) {
+            const int c = kids_sorted[i];
+            out.child_p[o + c] = my_px / my_Z;
+            out.child_q[o + c] = my_qx / my_rem;
+            out.child_frozen[o + c] = rej_w[i];
+          }
+        }
+        if (j > 0) {
+          int b_lo;
+          near_buckets(beta, b_lo, b_hi);
+          if (tid == 0) {
+            step.beta = beta;
+            step.b_lo = b_lo;
+            step.b_hi = b_hi;
+          }
         }
       }
-      __syncthreads();
-      near_terms(pairs, step);
-      __syncthreads();
+      if (j > 0) {  // (beta = 1 at the first rejection: every sorted token is live)
+        __syncthreads();
+        near_terms(pairs, tables, step);
+        __syncthreads();
+      }
       if (lead) {
-        unsigned long long near = 0ull;
-        for (int w = 0; w < AC_WAVES; ++w) near += step.part[w];
-        double F = ((double)tables.sp[b_hi] - beta * (double)tables.sq[b_hi]) * FIX_UNIT + (double)near * 0x1p-52;
+        double F;
+        if (j == 0) {
+          F = (double)(tables.sp[0] - tables.sq[0]) * FIX_UNIT;
+        } else {
+          const unsigned long long near = wave_total(lane < AC_WAVES ? step.part[lane] : 0ull);
+          F = ((double)tables.sp[b_hi] - beta * (double)tables.sq[b_hi]) * FIX_UNIT + (double)near * 0x1p-52;
+        }
         // a rejected token's weight is frozen: its live term leaves the sum
-        for (int i = 0; i <= j; ++i) F += rej_w[i] - fmax((double)kid_p[i] - beta * (double)kid_q[i], 0.0);
-        Z = F;
+        double fix = 0.0;
+        for (int i = lane; i <= j; i += 64) fix += rej_w[i] - fmax((double)kid_p[i] - beta * (double)kid_q[i], 0.0);
+        Z = F + wave_sum_dpp(fix);
       }
     }
   } else {
@@ -947,19 +996,14 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
 // takes them.
 static size_t bucket_workspace(int NN, int V, Carver* c, BucketWs* ws) {
   if (NN > BK_NODES) return 0;
-  const size_t n_sb = (size_t)NN * BK_SLICES * BK_N, n_b = (size_t)NN * (BK_N + 1);
+  const size_t n_sb = (size_t)NN * BK_SLICES * BK_N, n_st = (size_t)NN * BK_SLICES * (BK_N + 1);
   if (c != nullptr) {
-    ws->count = c->take<uint32_t>(n_sb);
+    ws->start = c->take<uint32_t>(n_st);
     ws->psum = c->take<unsigned long long>(n_sb);
     ws->qsum = c->take<unsigned long long>(n_sb);
-    ws->start = c->take<uint32_t>(n_b);
-    ws->sp = c->take<unsigned long long>(n_b);
-    ws->sq = c->take<unsigned long long>(n_b);
     ws->pairs = c->take<float2>((size_t)NN * V);
-    ws->nk = c->take<int32_t>(NN);
   }
-  return align_up(n_sb * 4, 256) + 2 * align_up(n_sb * 8, 256) + align_up(n_b * 4, 256) + 2 * align_up(n_b * 8, 256) +
-         align_up((size_t)NN * V * sizeof(float2), 256) + align_up((size_t)NN * 4, 256);
+  return align_up(n_st * 4, 256) + 2 * align_up(n_sb * 8, 256) + align_up((size_t)NN * V * sizeof(float2), 256);
 }
 
 // Bytes of the row sums k_bonus_rows leaves for the walk (0 beyond BK_NODES rows: the walk then sums
@@ -1051,9 +1095,13 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     if (mode == HS_ACCEPT_STOCHASTIC) {
       // one scan over [target rows ; draft rows]; draft rows are read where a row has children, and
       // nowhere else
-      hipLaunchKernelGGL(hs::k_mark_parents, dim3(B), dim3(hs::GR_THREADS), 0, st, parent, node_offsets, NN, wanted);
+      hipLaunchKernelGGL(hs::k_tree_rows, dim3(B), dim3(hs::GR_THREADS), 0, st, parent, node_offsets, NN, max_depth, wanted,
+                         chain.n_tried, static_cast<unsigned*>(scan_ws));
+      r = hs::launch_status("accept (tree rows)");
+      if (r != HS_OK) return r;
+      // (the rows' counters are clear: the scan merges its slices itself)
       r = hs::row_topk_launch(target_logits, row_stride, 2 * NN, V, 1, T, t_arg, t_lz, t_ent, nullptr, nullptr,
-                              scan_ws, st, nullptr, wanted, nullptr, draft_logits, NN);
+                              scan_ws, st, nullptr, wanted, nullptr, draft_logits, NN, true);
     } else {
       // greedy: the merge of the row slices is done by the accept kernel (one launch less)
       r = hs::row_topk_launch(target_logits, row_stride, NN, V, 1, T, t_arg, t_lz, t_ent, nullptr, nullptr, scan_ws,
@@ -1072,22 +1120,16 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
                         reinterpret_cast<uintptr_t>(target_logits) % 16 == 0 &&
                         reinterpret_cast<uintptr_t>(draft_logits) % 16 == 0;
     if (sorted) {
-      const dim3 grid(hs::BK_SLICES, NN);
-      hipLaunchKernelGGL(hs::k_bucket_pass<false>, grid, dim3(hs::BK_THREADS), 0, st, target_logits, draft_logits,
-                         row_stride, parent, node_offsets, B, V, 1.0f / temperature, max_depth, t_arg, t_lz, d_arg,
-                         d_lz, bk);
-      hipLaunchKernelGGL(hs::k_bucket_scan, dim3(NN), dim3(hs::BK_N), 0, st, bk);
-      hipLaunchKernelGGL(hs::k_bucket_pass<true>, grid, dim3(hs::BK_THREADS), 0, st, target_logits, draft_logits,
-                         row_stride, parent, node_offsets, B, V, 1.0f / temperature, max_depth, t_arg, t_lz, d_arg,
-                         d_lz, bk);
+      hipLaunchKernelGGL(hs::k_bucket_sort, dim3(hs::BK_SLICES, NN), dim3(hs::BK_THREADS), 0, st, target_logits, draft_logits,
+                         row_stride, V, 1.0f / temperature, chain.n_tried, t_arg, t_lz, d_arg, d_lz, bk);
       hs_status r = hs::launch_status("accept (sorted residual)");
       if (r != HS_OK) return r;
     } else {
       bk.pairs = nullptr;
     }
     hipLaunchKernelGGL(hs::k_accept_chain, dim3(NN), dim3(hs::AC_THREADS), 0, st, target_logits, draft_logits,
-                       row_stride, token, parent, node_offsets, B, V, 1.0f / temperature, max_depth, t_arg, t_lz,
-                       d_arg, d_lz, chain, bk);
+                       row_stride, token, parent, node_offsets, B, V, 1.0f / temperature, t_arg, t_lz, d_arg, d_lz,
+                       chain, bk);
     hs_status r = hs::launch_status("accept (rejection chains)");
     if (r != HS_OK) return r;
     if (chain.bonus_rows != nullptr) {

@@ -99,3 +99,30 @@ def test_attention_of_any_shape_and_address(G, dtype, D, hq, hkv, M, L, offset):
     tol = 2e-6 + (2.0 ** -8 * np.abs(want_o) if dtype == "bf16" else 1e-5 * np.abs(want_o).max())
     assert np.all(np.abs(o.float().cpu().numpy() - want_o) <= tol)
     assert np.abs(lse.cpu().numpy() - want_lse).max() <= 2e-5
+
+
+@pytest.mark.parametrize("sizes,spare", [([1], 2), ([5, 3], 3), ([1030], 0), ([1100, 4], 5)])
+def test_ratio_rule_on_large_trees_and_spare_rows(G, sizes, spare):
+    """Sampling with the draft's ratio rule: trees beyond the 1024 rows that are staged in LDS, and rows
+    behind the last sequence (what pruning into arrays with spare capacity leaves), which nobody scans."""
+    import paper_2505_13254_amd as hs
+    from test_gpu_entropy_prune_accept import _accept_equal, _random_accept_case
+    rs = np.random.RandomState(sum(sizes))
+    V, D, done = 4100, 5, 0
+    for attempt in range(60):
+        case = _random_accept_case(rs, sizes, V, 1, 1.0, D)
+        if case is None:
+            continue
+        target, draft, token, parent, offs, u, base = case
+        NN = len(token)
+        rows = np.full((spare, V), np.nan, np.float32)
+        fill = np.full(spare, 0x7fffffff, np.int32)
+        out = hs.hs_verify_accept(G.dev(np.concatenate([target, rows])), G.dev(np.concatenate([draft, rows])),
+                                  G.dev(np.concatenate([token, fill]), torch.int32), G.dev(np.concatenate([parent, fill]), torch.int32),
+                                  G.dev(offs, torch.int32), 1, 1.0,
+                                  G.dev(np.concatenate([u[:NN], np.zeros(spare), u[NN:]]), torch.float32), D)
+        _accept_equal({k: G.host(v) for k, v in out.items()}, base)
+        done += 1
+        if done == 4:
+            break
+    assert done == 4
