@@ -107,6 +107,7 @@ struct AttnArgs {
   int n_tbl;       // > 0: work-list launch (1-D grid over the items of tbl[0 .. n_tbl)); 0: grid.y = sequence
   int n_items;
   int narrow;      // work-list launches: 1 = two workgroups to an item, one for each 128 of its up to 256 rows
+  int cmb_row0;    // first tree row that the merge of the splits looks at
   alignas(16) SeqEntry tbl[ATTN_TBL];  // (lanes fetch their entry with 16-byte loads)
 };
 static_assert(offsetof(AttnArgs, tbl) % 16 == 0, "16-byte loads of the table entries");

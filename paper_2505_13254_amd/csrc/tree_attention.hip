@@ -278,7 +278,7 @@ constexpr int CMB_ROWS = 4;  // rows (waves) per workgroup
 template <typename T, int D>
 __global__ __launch_bounds__(64 * CMB_ROWS) void k_attn_combine(AttnArgs a, int64_t n_rows) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * CMB_ROWS + (threadIdx.x >> 6);  // node_global * Hq + h
+  const int64_t row = (int64_t)a.cmb_row0 * a.Hq + (int64_t)blockIdx.x * CMB_ROWS + (threadIdx.x >> 6);  // node_global * Hq + h
   if (row >= n_rows) return;
   const int node = (int)(row / a.Hq);
   int n_sp;
@@ -413,7 +413,22 @@ static inline float plan_tile_us(int waves) { return 1.25f + 0.04f * (float)wave
 struct ListPlan {
   float est_us;
   int target;
+  int tail, cuts;  // the last `tail` entries have each of their splits cut into `cuts` once more (0, 1: none)
 };
+
+// Equal entries whose items do not fill whole rounds of the compute units: the entries that spill into the
+// last round can be cut finer, so that their items fill the chip.  When do `q` items of cost c and, behind
+// them, `m` items of cost s end?
+static inline float plan_two_sizes(int64_t q, float c, int64_t m, float s) {
+  const int64_t k = q / PLAN_CUS, r = q % PLAN_CUS;        // k whole rounds, then r compute units have one more
+  const int64_t early = (PLAN_CUS - r) * (int64_t)(c / s);  // small items that end while they do
+  const float full = (float)(k + (r > 0 ? 1 : 0)) * c;
+  if (m <= early) {
+    const float end = (float)k * c + (float)((m + PLAN_CUS - r - 1) / (PLAN_CUS - r)) * s;
+    return end > full ? end : full;
+  }
+  return (float)(k + 1) * c + (float)((m - early + PLAN_CUS - 1) / PLAN_CUS) * s;
+}
 
 // Splits of a sequence of `tiles` prefix tiles when items should hold about `target` tiles.
 static inline int plan_splits(int tiles, int target, int sp_cap, bool paged = false) {
@@ -470,7 +485,9 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   int64_t coarse_items = 0;
   for (int i = 0; i < n; ++i) coarse_items += (int64_t)a.Hkv * seqs[i].rg * (seqs[i].tiles / 8 > 0 ? seqs[i].tiles / 8 : 1);
   const int n_targets = (int)(sizeof(targets) / sizeof(targets[0])) - (coarse_items < PLAN_CUS ? 0 : 3);
-  ListPlan best{0.f, 0};
+  bool equal = true;  // entries of one size
+  for (int i = 1; i < n; ++i) equal = equal && seqs[i].M == seqs[0].M && seqs[i].tiles == seqs[0].tiles;
+  ListPlan best{0.f, 0, 0, 1};
   static thread_local std::vector<float> item_cost, cu_free;  // (kept between calls: no allocation in the steady state)
   for (int ti = 0; ti < n_targets; ++ti) {
     const int target = targets[ti];
@@ -497,8 +514,31 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     }
     if (items <= PLAN_NARROW_ITEMS) {  // every workgroup has a compute unit: the longest item decides
       const float est = mx_narrow + (rec_bytes > 0.0 ? 3.5f + (float)(rec_bytes / 4.5e6) : 0.f);
-      if (best.target == 0 || est < best.est_us) best = ListPlan{est, target};
+      if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1};
       continue;
+    }
+    // Equal entries, a last round that is not full: its entries cut finer.  (Layers of
+    // the 8B head layout in one call: 33 of 2048 tokens and 61 rows, 264 items for 256 compute units, 112 us
+    // uncut and 91 with the last layer in eight; 38 of 6000 tokens and 33 rows 242 and 189; 129 rows on 4096
+    // tokens, 40 layers and heads, 730 and 707.)
+    if (equal && n > 1 && items > PLAN_CUS && items % PLAN_CUS != 0) {
+      const Seq& q = seqs[0];
+      int nsp, per;
+      plan_cut(q.tiles, target, sp_cap, a.block_table != nullptr, &nsp, &per);
+      const int64_t entry_items = items / n;
+      const int tail = (int)((items % PLAN_CUS + entry_items - 1) / entry_items);
+      for (int cuts = 2; cuts <= 8 && tail < n; cuts *= 2) {
+        const int per2 = (per + cuts - 1) / cuts;
+        const int nsp2 = (q.tiles + per2 - 1) / per2;
+        if (per2 < 2 * PLAN_MIN_SPLIT_TILES || nsp2 > sp_cap) break;
+        const float c = PLAN_ITEM_US + (float)(per + q.ttiles) * plan_tile_us(q.waves0);
+        const float small = PLAN_ITEM_US + (float)(per2 + q.ttiles) * plan_tile_us(q.waves0);
+        const double rec = (double)q.M * a.Hq * ((a.half ? 64 : 128) + ATTN_REC_PAD) * 4 * 2 *
+                           ((double)tail * nsp2 + (nsp > 1 ? (double)(n - tail) * nsp : 0.0));
+        const float est = plan_two_sizes(entry_items * (n - tail), c, entry_items / nsp * nsp2 * tail, small) +
+                          4.f + (float)(rec / 2.5e6);
+        if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, tail, cuts};
+      }
     }
     // (no schedule ends before the work divided by the compute units, nor before its longest item: a
     // candidate whose bound is no better than the best estimate so far needs no replay)
@@ -546,7 +586,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       est = end;
     }
     est += combine_us;
-    if (best.target == 0 || est < best.est_us) best = ListPlan{est, target};
+    if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1};
   }
   // the table: sequences by falling cost of an item
   int order[ATTN_TBL];
@@ -555,6 +595,10 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   for (int i = 0; i < n; ++i) {
     const Seq& q = seqs[i];
     plan_cut(q.tiles, best.target, sp_cap, a.block_table != nullptr, &nsp_of[i], &per_of[i]);
+    if (i >= n - best.tail) {
+      per_of[i] = (per_of[i] + best.cuts - 1) / best.cuts;
+      nsp_of[i] = (q.tiles + per_of[i] - 1) / per_of[i];
+    }
     cost[i] = (float)per_of[i] * plan_tile_us(q.waves0);
     order[i] = i;
   }
@@ -577,6 +621,9 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     if (nsp_of[i] > sp_max) sp_max = nsp_of[i];
     if (first >= (int64_t)1 << 30) return false;
   }
+  a.cmb_row0 = hno[seqs[n - 1].s + 1];  // (rows before the first entry with several splits need no merge)
+  for (int i = n - 1; i >= 0; --i)
+    if (nsp_of[i] > 1) a.cmb_row0 = hno[seqs[i].s];
   a.n_tbl = n;
   a.n_items = (int)first;
   a.narrow = first <= PLAN_NARROW_ITEMS ? 1 : 0;
@@ -591,7 +638,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
 struct PlanMemo {
   std::vector<int64_t> key;  // everything the plan is a function of; empty: unused slot
   bool ok;
-  int n_tbl, n_items, narrow, sp_max;
+  int n_tbl, n_items, narrow, sp_max, cmb_row0;
   SeqEntry tbl[ATTN_TBL];
 };
 constexpr int PLAN_MEMO_SLOTS = 4;
@@ -623,6 +670,7 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
         a.n_items = m.n_items;
         a.narrow = m.narrow;
         a.sp_max = m.sp_max;
+        a.cmb_row0 = m.cmb_row0;
         memcpy(a.tbl, m.tbl, sizeof(SeqEntry) * (size_t)m.n_tbl);
       }
       return m.ok;
@@ -635,6 +683,7 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
     m.n_items = a.n_items;
     m.narrow = a.narrow;
     m.sp_max = a.sp_max;
+    m.cmb_row0 = a.cmb_row0;
     memcpy(m.tbl, a.tbl, sizeof(SeqEntry) * (size_t)a.n_tbl);
   }
   return m.ok;
@@ -779,7 +828,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   a.block_table = block_table; a.max_blocks = max_blocks;
   a.B = B; a.Hq = Hq; a.Hkv = mfma ? kv_units : Hkv; a.G = mfma ? g_unit : Hq / Hkv; a.half = mfma && pairs ? 1 : 0; a.scale = scale;
   a.o = o; a.lse = lse; a.part = static_cast<float*>(workspace);
-  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.anc_tiles = nullptr;
+  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.cmb_row0 = 0; a.anc_tiles = nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // the workspace query bounds the splits of a sequence the same way
   const int64_t sp_bound = total_prefix / PLAN_MIN_SPLIT_TOKENS + 1;
@@ -788,6 +837,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   AttnPlan plan{};
   if (!(mfma && plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap))) {
     a.n_tbl = 0;
+    a.cmb_row0 = 0;
     plan = plan_attention(host_node_offsets, host_prefix_offsets, host_prefix_lens, B, Hq, a.Hkv, mfma ? 0 : GEN_ROWS);
     while (plan.sp_max > sp_cap) {
       plan.split_len *= 2;
@@ -855,7 +905,8 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   }
   if (a.sp_max > 1) {
     const int64_t n_rows = (int64_t)NN * Hq;
-    dim3 grid((unsigned)((n_rows + CMB_ROWS - 1) / CMB_ROWS)), block(64 * CMB_ROWS);
+    const int64_t merged = n_rows - (int64_t)a.cmb_row0 * Hq;
+    dim3 grid((unsigned)((merged + CMB_ROWS - 1) / CMB_ROWS)), block(64 * CMB_ROWS);
     if (dt == HS_F32 && D == 64) hipLaunchKernelGGL((k_attn_combine<float, 64>), grid, block, 0, st, a, n_rows);
     else if (dt == HS_F32) hipLaunchKernelGGL((k_attn_combine<float, 128>), grid, block, 0, st, a, n_rows);
     else if (D == 64) hipLaunchKernelGGL((k_attn_combine<bf16_t, 64>), grid, block, 0, st, a, n_rows);

@@ -126,3 +126,18 @@ def test_ratio_rule_on_large_trees_and_spare_rows(G, sizes, spare):
         if done == 4:
             break
     assert done == 4
+
+
+@pytest.mark.parametrize("D,hq,hkv,M,L,B", [(128, 8, 8, 9, 1500, 33), (128, 8, 4, 40, 833, 70), (64, 8, 8, 5, 2100, 66)])
+def test_equal_entries_that_spill_into_another_round(G, D, hq, hkv, M, L, B):
+    """A few items more than compute units, all alike: the last entries are cut into splits, the others
+    are written directly and the merge starts behind them."""
+    import paper_2505_13254_amd as hs
+    from test_gpu_attention import _case, _compare, _random_parents
+    w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
+    rs = np.random.RandomState(B)
+    step = _case(w, B, [_random_parents(rs, M, back=9) for _ in range(B)], [L] * B, "unit")
+    totals, per = hs.hs_tree_attention_plan(torch.from_numpy(step["node_offsets"]), torch.from_numpy(step["prefix_offsets"]),
+                                            hq, hkv, D, hs.HS_BF16)
+    assert per[0][0] == 1 and per[B - 1][0] > 1 and totals[2] == per[B - 1][0]
+    _compare(G, step, "bf16")
