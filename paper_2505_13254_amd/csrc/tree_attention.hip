@@ -452,8 +452,10 @@ static inline void plan_cut(int tiles, int target, int sp_cap, bool paged, int* 
 }
 
 // Fills a.tbl / a.n_tbl / a.n_items / a.sp_max.  Returns false when the batch does not fit the table.
+// lean: the plan for a workspace that does not hold the usual one's records (fewer cuts, hence fewer
+// records): no finer last round, and a launch of few items is cut as if each had one workgroup.
 static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, const int64_t* hlens, int B,
-                          int sp_cap) {
+                          int sp_cap, bool lean) {
   struct Seq {
     int s, M, tiles, rg, waves0, waves_last, ttiles;
   };
@@ -491,6 +493,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   static thread_local std::vector<float> item_cost, cu_free;  // (kept between calls: no allocation in the steady state)
   for (int ti = 0; ti < n_targets; ++ti) {
     const int target = targets[ti];
+    if (lean && (target == 12 || target == 6)) continue;
     double total = 0.0, rec_bytes = 0.0;
     float mx = 0.f, mn = 1e30f, mx_narrow = 0.f;
     int64_t items = 0;
@@ -512,7 +515,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       ord[i] = i;
       seq_cost[i] = (float)per * plan_tile_us(q.waves0);
     }
-    if (items <= PLAN_NARROW_ITEMS) {  // every workgroup has a compute unit: the longest item decides
+    if (items <= PLAN_NARROW_ITEMS && !lean) {  // every workgroup has a compute unit: the longest item decides
       const float est = mx_narrow + (rec_bytes > 0.0 ? 3.5f + (float)(rec_bytes / 4.5e6) : 0.f);
       if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1};
       continue;
@@ -521,7 +524,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     // the 8B head layout in one call: 33 of 2048 tokens and 61 rows, 264 items for 256 compute units, 112 us
     // uncut and 91 with the last layer in eight; 38 of 6000 tokens and 33 rows 242 and 189; 129 rows on 4096
     // tokens, 40 layers and heads, 730 and 707.)
-    if (equal && n > 1 && items > PLAN_CUS && items % PLAN_CUS != 0) {
+    if (equal && !lean && n > 1 && items > PLAN_CUS && items % PLAN_CUS != 0) {
       const Seq& q = seqs[0];
       int nsp, per;
       plan_cut(q.tiles, target, sp_cap, a.block_table != nullptr, &nsp, &per);
@@ -645,14 +648,15 @@ constexpr int PLAN_MEMO_SLOTS = 4;
 constexpr int PLAN_MEMO_MAX_B = 1024;  // larger batches (at most 96 of their entries non-empty) are planned every time
 
 static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* hpo, const int64_t* hlens, int B,
-                               int sp_cap) {
-  if (B > PLAN_MEMO_MAX_B) return plan_worklist(a, hno, hpo, hlens, B, sp_cap);
+                               int sp_cap, bool lean) {
+  if (B > PLAN_MEMO_MAX_B) return plan_worklist(a, hno, hpo, hlens, B, sp_cap, lean);
   static thread_local PlanMemo memo[PLAN_MEMO_SLOTS];
   static thread_local unsigned next_slot = 0;
   static thread_local std::vector<int64_t> key;
   key.clear();
   key.push_back(B);
   key.push_back(sp_cap);
+  key.push_back(lean ? 1 : 0);
   key.push_back(a.G);
   key.push_back(a.Hkv);
   key.push_back(a.half);
@@ -676,7 +680,7 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
       return m.ok;
     }
   PlanMemo& m = memo[next_slot++ % PLAN_MEMO_SLOTS];
-  m.ok = plan_worklist(a, hno, hpo, hlens, B, sp_cap);
+  m.ok = plan_worklist(a, hno, hpo, hlens, B, sp_cap, lean);
   m.key = key;
   if (m.ok) {
     m.n_tbl = a.n_tbl;
@@ -835,7 +839,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   const int sp_cap = (int)(sp_bound < 2 ? 2 : sp_bound > 64 ? 64 : sp_bound);
 
   AttnPlan plan{};
-  if (!(mfma && plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap))) {
+  if (!(mfma && plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, false))) {
     a.n_tbl = 0;
     a.cmb_row0 = 0;
     plan = plan_attention(host_node_offsets, host_prefix_offsets, host_prefix_lens, B, Hq, a.Hkv, mfma ? 0 : GEN_ROWS);
@@ -852,7 +856,12 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
     a.split_len = 0; a.n_rb_max = 1;
   }
   const size_t table_bytes = mfma ? align_up(attn_mfma_table_bytes(max_M, NN), 256) : 0;
-  const size_t need = part_bytes(NN, Hq, D, a.sp_max) + table_bytes;
+  size_t need = part_bytes(NN, Hq, D, a.sp_max) + table_bytes;
+  // a workspace that is too small for this plan may still hold the one with fewer cuts
+  if (a.n_tbl > 0 && !plan_only && a.sp_max > 1 && (workspace == nullptr || workspace_bytes < need)) {
+    plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, true);
+    need = part_bytes(NN, Hq, D, a.sp_max) + table_bytes;
+  }
   if (table_bytes != 0 && workspace != nullptr)
     a.anc_tiles = reinterpret_cast<const unsigned*>(static_cast<const char*>(workspace) + part_bytes(NN, Hq, D, a.sp_max));
   if (plan_only) {

@@ -141,3 +141,27 @@ def test_equal_entries_that_spill_into_another_round(G, D, hq, hkv, M, L, B):
                                             hq, hkv, D, hs.HS_BF16)
     assert per[0][0] == 1 and per[B - 1][0] > 1 and totals[2] == per[B - 1][0]
     _compare(G, step, "bf16")
+
+
+def test_a_workspace_without_room_for_the_finer_last_round(G):
+    """The same launch with no room for records runs uncut; a launch that is cut in any plan (one sequence
+    of few heads) is refused."""
+    import paper_2505_13254_amd as hs
+    from test_gpu_attention import _case, _random_parents
+    for D, hq, hkv, M, L, B in [(128, 8, 8, 9, 1500, 33), (64, 8, 8, 5, 1000, 66), (128, 8, 4, 40, 833, 70), (128, 8, 4, 9, 4000, 1)]:
+        w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
+        rs = np.random.RandomState(B)
+        step = _case(w, B, [_random_parents(rs, M, back=9) for _ in range(B)], [L] * B, "unit")
+        no, po = (torch.from_numpy(np.asarray(step[k])) for k in ("node_offsets", "prefix_offsets"))
+        args = [G.dev_store(step[k]) for k in ("q", "k_prefix", "v_prefix", "k_tree", "v_tree")]
+        args += [G.dev(step["parent"], torch.int32), no.cuda(), po.cuda(), no, po, float(step["scale"])]
+        small = torch.empty(256, dtype=torch.uint8, device="cuda")
+        if B == 1:
+            with pytest.raises(hs.HsError):
+                hs.hs_tree_attention(*args, ws=small)
+            continue
+        want, _ = G.run_attention(step)
+        got, _ = hs.hs_tree_attention(*args, ws=small)
+        # both sum in float32 and round weights and results to bfloat16: at most a unit each, 2^-8 of the
+        # values that are averaged
+        assert np.abs(G.host(got) - want).max() <= 2.0 ** -7 * np.abs(G.host(args[2])).max()
