@@ -22,6 +22,7 @@
 #include <limits.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "hs_common.h"
@@ -644,10 +645,14 @@ __global__ __launch_bounds__(FIN_THREADS) void k_scan_finalize(const float4* __r
   write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
 }
 
+// What a scan of up to R rows can need: fewer rows are cut into more slices each, but never into more than
+// SCAN_SMALL_WGS in all unless the rows themselves are more, so a workspace made for R rows holds fewer too.
 size_t row_topk_workspace(int R, int V, int K) {
   if (R <= 0) return 0;
-  ScanPlan p = plan_scan(R, V);
-  size_t n = (size_t)R * p.splits;
+  static_assert(SCAN_BIG_WGS <= SCAN_SMALL_WGS, "the bound on the slices of a call");
+  const int tile = scan_tile(SCAN_SMALL);
+  const int64_t most = std::min((V + tile - 1) / tile, MAX_SPLITS);
+  const size_t n = (size_t)std::max<int64_t>(R, std::min<int64_t>(R * most, SCAN_SMALL_WGS));
   return TICKET_BYTES + align_up(n * sizeof(float4), 256) + align_up(n * K * sizeof(unsigned long long), 256);
 }
 

@@ -118,6 +118,18 @@ def test_accept_workspace_depends_on_the_mode(lib):
     assert va(d, d, 128256, d, d, d, 1, 61, 128256, 0, 1.0, d, 6, d, d, d, d, greedy - 256, None) == 4
 
 
+@pytest.mark.parametrize("V", [1024, 8000, 32000, 50257, 128256, 262144])
+def test_a_workspace_for_many_rows_holds_fewer(lib, V):
+    """Callers size a workspace for their largest step: the queries never fall as rows are added."""
+    f = lib.hs_draft_entropy_topk_workspace
+    f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int32] * 3
+    qm = lib.hs_verify_accept_workspace_mode
+    qm.restype, qm.argtypes = ctypes.c_size_t, [ctypes.c_int32] * 3 + [ctypes.c_int]
+    for need in [lambda r: f(r, V, 10), lambda r: qm(1, r, V, 0), lambda r: qm(1, r, V, 1)]:
+        sizes = [need(r) for r in range(1, 700)]
+        assert sizes == sorted(sizes)
+
+
 def test_adaptive_policy_on_the_host_matches_the_worked_table(lib):
     """hs_adaptive_policy (host arithmetic only) against the hand-worked Section 4.3 table of the figure example."""
     f = lib.hs_adaptive_policy
