@@ -471,7 +471,7 @@ hs_status hs_time_next_attention(void* start_event, void* stop_event);
  * Which kernel the calling thread's last hs_tree_attention / _lens / _paged / _shared_tree call
  * launched: 1 = the matrix-core kernel (bfloat16; D = 128, or D = 64 with an even number of KV heads;
  * 16-byte aligned tensors; G * rows < 65536 for G = Hq / Hkv, twice that at D = 64),
- * 2 = the vector-ALU kernel (everything else),
+ * 2 = the any-shape kernel (everything else; float32 matrix instructions),
  * 0 = none (no such call yet, an empty batch, or the call failed before its launch). */
 int32_t hs_tree_attention_last_kernel(void);
 

@@ -507,7 +507,7 @@ def hs_tree_attention_plan(host_node_offsets, host_prefix_offsets, Hq, Hkv, D, d
 
 
 def hs_tree_attention_last_kernel() -> int:
-    """1: this thread's last tree-attention call ran on the matrix cores, 2: on the vector ALUs, 0: it launched nothing."""
+    """1: this thread's last tree-attention call ran the bfloat16 matrix-core kernel, 2: the any-shape kernel, 0: it launched nothing."""
     return int(lib().hs_tree_attention_last_kernel())
 
 

@@ -271,7 +271,7 @@ def test_head_dimension_64_in_bfloat16(G, M, L, hq, hkv):
 
 def test_head_dimension_64_ragged_batches(G):
     """D = 64 through the ragged work-list launch: several sequences, splits, all input variants; an odd
-    number of KV heads cannot be paired and runs on the vector ALUs."""
+    number of KV heads cannot be paired and runs on the any-shape kernel."""
     import paper_2505_13254_amd as hs
     rs = np.random.RandomState(64)
     for it in range(10):
