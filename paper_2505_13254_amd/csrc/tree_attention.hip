@@ -406,7 +406,20 @@ constexpr int PLAN_MIN_SPLIT_TILES = 2;
 // 10 us of an item and a combine launch of 3.5 us + its records at 4.5 TB/s were fitted to the same sweeps
 // (one layer of 2048 and of 8000 tokens, 1 to 33 splits; within 2 us of all of them).
 constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2;
-constexpr float PLAN_NARROW_TILE_US = 0.65f;
+// Such a launch draws less from HBM, so it is compared with launches of one workgroup to each compute unit
+// (129 to 256 items) at the pace those have on a chip that is not full, and has to be estimated PLAN_NARROW_GAIN
+// better (several row groups read the same keys: PLAN_NARROW_GAIN_RG).  12 layers of 6000 tokens, 48 rows a head:
+// 57 us as 192 items, 77 as 96 narrow ones; 244 rows a head: 100 and 85.
+constexpr float PLAN_NARROW_GAIN = 0.93f, PLAN_NARROW_GAIN_RG = 0.9f;
+static inline float plan_narrow_tile_us(int64_t items, int waves) {
+  return 0.65f + (waves > 4 && items > 72 ? 0.004f * (float)(items - 72) : 0.f);
+}
+static inline float plan_round_tile_us(int64_t items, int waves) {
+  const float idle = 0.85f + 0.13f * (float)std::max(0, waves - 4);                  // up to 192 items
+  const float full = std::max(idle, std::min(1.6f, 1.15f + 0.12f * (float)(waves - 2)));  // 256 items
+  return idle + (full - idle) * (float)std::max<int64_t>(0, items - 192) / 64.f;
+}
+static inline float plan_round_item_us(int waves) { return waves > 4 ? 10.f : 8.f; }
 constexpr int PLAN_MIN_SPLIT_TOKENS = PLAN_MIN_SPLIT_TILES * 64;
 static inline float plan_tile_us(int waves) { return 1.25f + 0.04f * (float)waves; }
 
@@ -495,7 +508,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     const int target = targets[ti];
     if (lean && (target == 12 || target == 6)) continue;
     double total = 0.0, rec_bytes = 0.0;
-    float mx = 0.f, mn = 1e30f, mx_narrow = 0.f;
+    float mx = 0.f, mn = 1e30f;
     int64_t items = 0;
     int ord[ATTN_TBL];
     float seq_cost[ATTN_TBL];
@@ -509,14 +522,25 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       total += (double)a.Hkv * nsp * ((q.rg - 1) * one + one_last);
       items += (int64_t)a.Hkv * nsp * q.rg;
       if (big > mx) mx = big;
-      mx_narrow = std::max(mx_narrow, PLAN_ITEM_US + (float)(per + q.ttiles) * PLAN_NARROW_TILE_US);
       if (one_last < mn) mn = one_last;
       if (nsp > 1) rec_bytes += (double)q.M * a.Hq * nsp * ((a.half ? 64 : 128) + ATTN_REC_PAD) * 4 * 2;  // written, then read
       ord[i] = i;
       seq_cost[i] = (float)per * plan_tile_us(q.waves0);
     }
-    if (items <= PLAN_NARROW_ITEMS && !lean) {  // every workgroup has a compute unit: the longest item decides
-      const float est = mx_narrow + (rec_bytes > 0.0 ? 3.5f + (float)(rec_bytes / 4.5e6) : 0.f);
+    if (items <= PLAN_CUS && !lean) {  // every workgroup has a compute unit: the longest item decides
+      const bool narrow = items <= PLAN_NARROW_ITEMS;
+      float longest = 0.f;
+      bool groups = false;
+      for (int i = 0; i < n; ++i) {
+        const Seq& q = seqs[i];
+        int nsp, per;
+        plan_cut(q.tiles, target, sp_cap, a.block_table != nullptr, &nsp, &per);
+        const float tile = narrow ? plan_narrow_tile_us(items, q.waves0) : plan_round_tile_us(items, q.waves0);
+        longest = std::max(longest, plan_round_item_us(q.waves0) + (float)(per + q.ttiles) * tile);
+        groups = groups || q.rg > 1;
+      }
+      float est = longest + (rec_bytes > 0.0 ? 3.5f + (float)(rec_bytes / 4.5e6) : 0.f);
+      if (narrow) est /= groups ? PLAN_NARROW_GAIN_RG : PLAN_NARROW_GAIN;
       if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1};
       continue;
     }
