@@ -785,6 +785,9 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
     const int32_t* __restrict__ t_arg, const float* __restrict__ t_lz, const int32_t* __restrict__ d_arg,
     const float* __restrict__ d_lz, ChainOut chain, int32_t* __restrict__ accept_len,
     int32_t* __restrict__ accept_path, int32_t* __restrict__ bonus_token) {
+  // Every wave reads these while it tries a level's children, at its own pace: they are written between the
+  // barriers ahead of that loop only.  A next level's writes come behind the barriers of gather_children, and
+  // what is made after the loop, the corrections of a bonus draw, has an array of its own.
   __shared__ int kids[AC_MAX_KIDS];
   __shared__ int kids_sorted[AC_MAX_KIDS];
   __shared__ int n_kids;
@@ -792,6 +795,7 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
   __shared__ double rej_w[AC_MAX_KIDS];  // frozen weight of each rejected token
   __shared__ float kid_u[AC_MAX_KIDS];    // the child's uniform
   __shared__ double kid_a[AC_MAX_KIDS], kid_b[AC_MAX_KIDS];  // its current p(x) (and q(x) under the ratio rule)
+  __shared__ double rej_fix[AC_MAX_KIDS];  // bonus draw: what a rejected token's frozen weight changes in its row sum
   __shared__ double rowsum[AC_MAX_ROWS];
   __shared__ double chunk_tot[AC_MAX_ROWS / 64];  // sums of 64 rows
   __shared__ int chunk_last[AC_MAX_ROWS / 64];
@@ -912,10 +916,10 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
       bonus_row_sums(p, q, sub_q, beta, V, 0, n_rows, rowsum);
     }
     // (every rejected token's correction by a thread of its own: one trip to memory for all of them)
-    if (tid < n_rej) kid_a[tid] = rej_w[tid] - token_weight(p, q, sub_q, beta, rej_tok[tid]);
+    if (tid < n_rej) rej_fix[tid] = rej_w[tid] - token_weight(p, q, sub_q, beta, rej_tok[tid]);
     __syncthreads();
     if (tid == 0)
-      for (int i = 0; i < n_rej; ++i) rowsum[rej_tok[i] >> 6] += kid_a[i];
+      for (int i = 0; i < n_rej; ++i) rowsum[rej_tok[i] >> 6] += rej_fix[i];
     __syncthreads();
     // two levels: the sixteen waves sum chunks of 64 rows side by side, one wave then looks for the
     // chunk, the row inside it and the token inside the row

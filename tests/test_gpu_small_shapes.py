@@ -165,3 +165,47 @@ def test_a_workspace_without_room_for_the_finer_last_round(G):
         # both sum in float32 and round weights and results to bfloat16: at most a unit each, 2^-8 of the
         # values that are averaged
         assert np.abs(G.host(got) - want).max() <= 2.0 ** -7 * np.abs(G.host(args[2])).max()
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("n_kids", [1, 63, 65, 250])
+def test_bonus_draws_after_many_rejections(G, mode, n_kids):
+    """Bonus draws at the root and at a node below it with up to 250 rejected children, whose corrections are
+    made by one to four waves while others may still be trying the children: the checker's tokens, and the
+    same ones on every call."""
+    import paper_2505_13254_amd as hs
+    from oracle import verify_accept
+    from test_gpu_entropy_prune_accept import _accept_equal
+    rs = np.random.RandomState(n_kids + mode)
+    V, done = 8192, 0
+    for attempt in range(40):
+        # sequence 0: all children of the root are rejected; sequence 1: the root's only child is accepted and
+        # all of its children are rejected (the target gives a rejected token a fraction of the draft's share)
+        parent = np.concatenate([[-1], [0] * n_kids, [-1, 0], [1] * n_kids]).astype(np.int32)
+        offs = np.asarray([0, n_kids + 1, 2 * n_kids + 3], np.int32)
+        NN = len(parent)
+        draft = (rs.normal(size=(NN, V)) * 2).astype(np.float32)
+        target = (0.9 * draft + 0.5 * rs.normal(size=(NN, V))).astype(np.float32)
+        token = np.zeros(NN, np.int32)
+        for node, first in ((0, 1), (n_kids + 2, n_kids + 3)):
+            token[first:first + n_kids] = np.argsort(-draft[node], kind="stable")[:n_kids]
+            target[node, token[first:first + n_kids]] -= 3.0
+        target[n_kids + 1, token[n_kids + 2]] += 30.0
+        u = np.concatenate([0.9 + 0.0999 * rs.rand(NN), rs.rand(2)]).astype(np.float32)
+        want = verify_accept(target, draft, token, parent, offs, mode, 1.0, u, 4)
+        assert list(want["accept_len"]) == [0, 1]
+        near = []
+        for sgn in (-1.0, 1.0):  # (a draw at the edge of a token's interval may fall to either side)
+            un = u.astype(np.float64)
+            un[NN:] = np.clip(un[NN:] + sgn * 1e-5, 0.0, 1.0 - 1e-12)
+            near.append(verify_accept(target, draft, token, parent, offs, mode, 1.0, un, 4)["bonus_token"])
+        if not all(np.array_equal(b, want["bonus_token"]) for b in near):
+            continue
+        args = [G.dev(target), G.dev(draft), G.dev(token, torch.int32), G.dev(parent, torch.int32), G.dev(offs, torch.int32), mode,
+                1.0, G.dev(u, torch.float32), 4]
+        for rep in range(4):
+            _accept_equal({k: G.host(v) for k, v in hs.hs_verify_accept(*args).items()}, want)
+        done += 1
+        if done == 3:
+            break
+    assert done == 3
