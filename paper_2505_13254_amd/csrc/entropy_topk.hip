@@ -230,13 +230,10 @@ __device__ __forceinline__ void merge_slices(const float4* st, const unsigned lo
       a = Stats{f.x, f.y, f.z};
     }
   }
+  // (the heads by loads of their own: the S x K entries may be more than the threads hold in registers)
+  if (tid < S) head[tid] = COHERENT ? ld_dev(pk + (int64_t)tid * K) : pk[(int64_t)tid * K];
   if (tid == 0) sm.cnt = 0;
   if (tid < HS_MAX_TOPK) sm.best[tid] = 0ull;
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int e = tid + q * nthreads;
-    if (e < n_all && e % K == 0) head[e / K] = ek[q];
-  }
   __syncthreads();
   // threshold: the K-th best list head when there are at least K lists, else "every entry passes"
   unsigned long long thr = 1ull;

@@ -209,3 +209,27 @@ def test_bonus_draws_after_many_rejections(G, mode, n_kids):
         if done == 3:
             break
     assert done == 3
+
+
+@pytest.mark.parametrize("R,V,K", [(1, 262144, 16), (1, 262144, 17), (4, 262144, 20), (1, 262144, 64), (4, 256000, 40), (3, 151936, 30)])
+def test_merge_of_many_slices_and_long_lists(G, R, V, K):
+    """Few rows of a large vocabulary: up to 64 slices of 4096, more list entries than the merge keeps in
+    registers (K = 16: just as many).  A row's K best values lie in its last K slices, one in each, falling
+    from slice to slice, so that the merge's threshold is the very last slice's best."""
+    import paper_2505_13254_amd as hs
+    rs = np.random.RandomState(V + K)
+    x = (rs.randn(R, V) * 2 - 100.0).astype(np.float32)
+    n_slices = -(-V // 4096)
+    for r in range(R):
+        for i in range(K):
+            sl = n_slices - K + i
+            x[r, sl * 4096 + rs.randint(min(4096, V - sl * 4096))] = 40.0 - 0.25 * i
+    want, xd = draft_entropy_topk(x, K, 1.0), G.dev(x)
+    ws = hs.workspace(hs.lib().hs_draft_entropy_topk_workspace(R, V, K), G.DEV)
+    hs.hs_workspace_prepare(ws)
+    for fused in (True, False):
+        for rep in range(3):
+            got = {k: G.host(v) for k, v in hs.hs_draft_entropy_topk(xd, K, 1.0, ws=ws, fused=fused).items()}
+            assert np.array_equal(got["topk_idx"], want["topk_idx"]), (fused, rep)
+            for k in ("ent_topk", "ent_full"):
+                assert G.entropy_err(got[k], want[k]) <= 1.0, k
