@@ -160,30 +160,45 @@ struct MergeScratch {
   Stats total;
 };
 
-// Ranks the candidates sm.key[0, n) by counting (keys differ, zeros aside: ranks are a permutation) and
-// leaves those of rank < K, in order, in sm.best (zero on entry).  A wave takes a run of candidates, one
-// to a lane, and 64 opponents at a time, one to a lane: a candidate's key goes to a scalar register, one
-// comparison and a count of the ballot's bits follow, and no step waits for LDS.  (A loop over LDS, one
-// dependent read to an opponent, and counts added up by LDS atomics before: 8 us to 7.4 from a
-// workgroup's start to its slice's result.)  Called by all `nthreads` threads; ends with a barrier.
+// A key that at least K entries of S <= 64 sorted lists reach, so that nothing below it is among the K best:
+// with r = ceil(K / S), the ceil(K / r)-th largest of the lists' r-th entries (1, which every entry
+// reaches, when fewer lists are that long).  `rth`: list s's r-th entry in lane s < S, 0 in the other lanes.
+__device__ __forceinline__ int threshold_depth(int S, int K) { return (K + S - 1) / S; }
+__device__ __forceinline__ unsigned long long lists_threshold(unsigned long long rth, int S, int K) {
+  const int r = threshold_depth(S, K), m = (K + r - 1) / r;
+  int rank = 0;
+  for (int l = 0; l < S; ++l) rank += lane_key(rth, l) > rth ? 1 : 0;
+  const unsigned long long who = __ballot(rank == m - 1 && rth != 0ull);
+  return who != 0ull ? lane_key(rth, __ffsll((long long)who) - 1) : 1ull;
+}
+
+// Ranks those of the candidates sm.key[0, n) that reach `thr` (>= 1) by counting (keys differ, zeros aside:
+// ranks are a permutation) and leaves those of rank < K, in order, in sm.best (zero on entry).  A wave takes a
+// run of candidates, one to a lane, and 64 opponents at a time, one to a lane: a candidate's key goes to a scalar
+// register, one comparison and a count of the ballot's bits follow, and no step waits for LDS.  (A loop over
+// LDS, one dependent read to an opponent, and counts added up by LDS atomics before: 8 us to 7.4 from a
+// workgroup's start to its slice's result.  Without the threshold every wave went through all 64 places of
+// its list for K = 64: 17 rows of 12000 logits 107 us.)  Called by all `nthreads` threads; ends with a barrier.
 template <int CAP>
-__device__ __forceinline__ void rank_candidates(MergeScratch<CAP>& sm, int n, int K, int tid, int nthreads) {
+__device__ __forceinline__ void rank_candidates(MergeScratch<CAP>& sm, int n, int K, unsigned long long thr, int tid, int nthreads) {
   const int lane = tid & 63;
   const int n_waves = nthreads >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int per = (n + n_waves - 1) / n_waves;
   const int lo = wave * per, hi = min(n, lo + per);
   for (int c0 = lo; c0 < hi; c0 += 64) {  // one trip unless a wave has more than 64 candidates
-    const int cn = min(64, hi - c0);
-    const unsigned long long mine = lane < cn ? sm.key[c0 + lane] : 0ull;
+    const unsigned long long mine = lane < hi - c0 ? sm.key[c0 + lane] : 0ull;
+    const unsigned long long ranked = __ballot(mine >= thr);
+    if (ranked == 0ull) continue;
     int rank = 0;
     for (int o = 0; o < n; o += 64) {
       const unsigned long long opp = o + lane < n ? sm.key[o + lane] : 0ull;
-      for (int j = 0; j < cn; ++j) {
+      for (unsigned long long left = ranked; left != 0ull; left &= left - 1ull) {
+        const int j = __ffsll((long long)left) - 1;
         const int above = __popcll(__ballot(opp > lane_key(mine, j)));
         rank += lane == j ? above : 0;
       }
     }
-    if (mine != 0ull && rank < K) sm.best[rank] = mine;
+    if (mine >= thr && rank < K) sm.best[rank] = mine;
   }
   __syncthreads();
 }
@@ -203,13 +218,14 @@ __device__ __forceinline__ void st_dev(unsigned long long* p, unsigned long long
 // Called by all `nthreads` threads of the workgroup (tid 0..nthreads-1) after a barrier; ends with a barrier.
 // Everything the merge reads from memory is requested at once (one trip, which is most of its
 // time when the slices come from other workgroups): the lists by all threads, the statistics by the
-// last wave.  Then the K-th best list head becomes a threshold (with at least K lists; every wave finds
-// it for itself), which only a few entries pass, and those are ranked by counting.
+// last wave.  Then the lists' heads (fewer lists than K: their r-th entries) give a threshold, which every wave
+// finds for itself; only a few entries pass it, and those are ranked by counting.  (With a threshold for at least
+// K lists only, one row of 128256 logits in 32 slices took 957 us for K = 64.)
 template <bool COHERENT, int CAP>
 __device__ __forceinline__ void merge_slices(const float4* st, const unsigned long long* pk, int S, int K, float inv_t,
                                              MergeScratch<CAP>& sm, int tid, int nthreads) {
   const int lane = tid & 63;
-  __shared__ unsigned long long head[MAX_SPLITS];
+  __shared__ unsigned long long rth[MAX_SPLITS];
   constexpr int PER = 4;  // entries a thread keeps in registers (a trip covers PER x nthreads of the S x K)
   const int n_all = S * K;
   unsigned long long ek[PER];
@@ -230,20 +246,15 @@ __device__ __forceinline__ void merge_slices(const float4* st, const unsigned lo
       a = Stats{f.x, f.y, f.z};
     }
   }
-  // (the heads by loads of their own: the S x K entries may be more than the threads hold in registers)
-  if (tid < S) head[tid] = COHERENT ? ld_dev(pk + (int64_t)tid * K) : pk[(int64_t)tid * K];
+  // (by loads of their own: the S x K entries may be more than the threads hold in registers)
+  if (tid < S) {
+    const unsigned long long* e = pk + (int64_t)tid * K + threshold_depth(S, K) - 1;
+    rth[tid] = COHERENT ? ld_dev(e) : *e;
+  }
   if (tid == 0) sm.cnt = 0;
   if (tid < HS_MAX_TOPK) sm.best[tid] = 0ull;
   __syncthreads();
-  // threshold: the K-th best list head when there are at least K lists, else "every entry passes"
-  unsigned long long thr = 1ull;
-  if (S >= K) {
-    const unsigned long long hk = lane < S ? head[lane] : 0ull;
-    int rank = 0;
-    for (int l = 0; l < S; ++l) rank += lane_key(hk, l) > hk ? 1 : 0;
-    const unsigned long long who = __ballot(rank == K - 1 && hk != 0ull);
-    if (who != 0ull) thr = lane_key(hk, __ffsll((long long)who) - 1);
-  }
+  const unsigned long long thr = lists_threshold(lane < S ? rth[lane] : 0ull, S, K);
   auto admit = [&](unsigned long long k) {
     if (k >= thr) sm.key[atomicAdd(&sm.cnt, 1)] = k;  // (order of arrival does not matter; at most S * K <= CAP entries)
   };
@@ -256,7 +267,7 @@ __device__ __forceinline__ void merge_slices(const float4* st, const unsigned lo
     if (lane == 0) sm.total = a;
   }
   __syncthreads();
-  rank_candidates(sm, sm.cnt, K, tid, nthreads);
+  rank_candidates(sm, sm.cnt, K, thr, tid, nthreads);
 }
 
 // Writes a row's results from its merged statistics and Top-K list (first wave of the workgroup).
@@ -578,7 +589,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
     a = stats_wave_sum(a, inv_t);
     if (lane == 0) sm.total = a;
   }
-  rank_candidates(sm, SCAN_WAVES * K, K, tid, SCAN_THREADS);  // (its barrier also publishes sm.total)
+  // (lists that fit one wave of opponents are ranked whole: the threshold would cost what it saves)
+  unsigned long long list_thr = 1ull;
+  if (SCAN_WAVES * K > 64)
+    list_thr = lists_threshold(lane < SCAN_WAVES ? sm.key[lane * K + threshold_depth(SCAN_WAVES, K) - 1] : 0ull, SCAN_WAVES, K);
+  rank_candidates(sm, SCAN_WAVES * K, K, list_thr, tid, SCAN_THREADS);  // (its barrier also publishes sm.total)
   static_assert(STATS || !FUSED, "rows are finished by the caller of a scan without statistics");
   if (S == 1) {
     if (STATS) write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);

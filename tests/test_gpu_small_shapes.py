@@ -233,3 +233,27 @@ def test_merge_of_many_slices_and_long_lists(G, R, V, K):
             assert np.array_equal(got["topk_idx"], want["topk_idx"]), (fused, rep)
             for k in ("ent_topk", "ent_full"):
                 assert G.entropy_err(got[k], want[k]) <= 1.0, k
+
+
+@pytest.mark.parametrize("K", [1, 5, 16, 17, 33, 64])
+@pytest.mark.parametrize("R,V", [(20, 12000), (20, 40000), (3, 12000), (2, 140000)])
+def test_lists_of_unequal_length(G, R, V, K):
+    """The merges' threshold with more and with fewer lists than K: the row's best all in one wave's lanes, spread
+    evenly, tied, rising, and rows with fewer unmasked logits than K."""
+    rs = np.random.RandomState(V + K)
+    x = (rs.randn(R, V) * 3).astype(np.float32)
+    x[0, 256:320] += 50.0
+    x[1, :: V // 70] += 50.0
+    if R > 2:
+        x[2] = np.round(x[2])
+    if R > 6:
+        x[3] = -np.inf
+        x[3, rs.permutation(V)[:K // 2 + 1]] = 1.0
+        x[4] = np.sort(x[4])
+        x[5, :-K] = -np.inf
+        x[6] = 0.5
+    want = draft_entropy_topk(x, K, 1.0)
+    got = G.run_entropy(x, K, 1.0)
+    assert np.array_equal(got["topk_idx"], want["topk_idx"])
+    for k in ("ent_topk", "ent_full"):
+        assert G.entropy_err(got[k], want[k]) <= 1.0, k
