@@ -360,6 +360,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
   // instance of the maximum held out of them.
   const float c = inv_t * LOG2E;
   float ref = -HS_INF, s1 = 0.f, t2 = 0.f;
+  bool masked = false;  // a masked logit has been met: the wave's sums are clamped from there on
   if (tid < HS_MAX_TOPK) sm.best[tid] = 0ull;  // (a slice with fewer than K elements leaves the rest unused)
 
   auto load_tile = [&](int tile, float (&v)[SCAN_VPT]) {
@@ -440,22 +441,28 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
           }
         }
       } else if (ref != -HS_INF) {
-#pragma unroll
-        for (int jj = 0; jj < SCAN_VPT; ++jj) {
-          const float y = (v[jj] - ref) * c;
-          const float e = exp2_fast(y);
-          tt = fmaf(e, y, tt);
-          st += e;
-        }
-        if (__ballot(!(tt == tt)) != 0ull) {  // masked logits among them (0 * -inf): the tile again, clamped
+        auto sums = [&](auto clamped) {
           st = 0.f;
           tt = 0.f;
 #pragma unroll
           for (int jj = 0; jj < SCAN_VPT; ++jj) {
-            const float y = fmaxf((v[jj] - ref) * c, -1e30f);
+            const float x = (v[jj] - ref) * c;
+            const float y = decltype(clamped)::value ? fmaxf(x, -1e30f) : x;
             const float e = exp2_fast(y);
             tt = fmaf(e, y, tt);
             st += e;
+          }
+        };
+        if (!masked) {
+          sums(std::false_type{});
+          masked = __ballot(!(tt == tt)) != 0ull;  // masked logits among them (0 * -inf)
+        }
+        if (masked) {
+          if (__ballot(tm != -HS_INF) != 0ull) {
+            sums(std::true_type{});
+          } else {
+            st = 0.f;
+            tt = 0.f;
           }
         }
       }

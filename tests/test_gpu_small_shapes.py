@@ -257,3 +257,32 @@ def test_lists_of_unequal_length(G, R, V, K):
     assert np.array_equal(got["topk_idx"], want["topk_idx"])
     for k in ("ent_topk", "ent_full"):
         assert G.entropy_err(got[k], want[k]) <= 1.0, k
+
+
+@pytest.mark.parametrize("T", [1.0, 0.7])
+@pytest.mark.parametrize("R,V", [(1, 128259), (10, 40000), (51, 50257), (300, 12000)])
+def test_masked_logits_at_any_place(G, R, V, T):
+    """Rows whose first -inf comes in the first tile, in a later one or at the end, one masked logit, whole
+    tiles of them between tiles with values, all but a few: a wave that has met one changes how it sums."""
+    rs = np.random.RandomState(R + V)
+    x = (rs.randn(R, V) * 2).astype(np.float32)
+    for r in range(R):
+        kind = r % 6 if R > 1 else 3
+        if kind == 0:
+            x[r, V // 3] = -np.inf
+        elif kind == 1:
+            x[r, 4096 * rs.randint(1, 3):] = -np.inf
+        elif kind == 2:
+            x[r, rs.rand(V) < 0.5] = -np.inf
+        elif kind == 3:  # (blocks of the smaller and of the larger tile)
+            x[r, np.repeat(rs.rand(-(-V // 4096)) < 0.6, 4096)[:V]] = -np.inf
+            x[r, rs.permutation(V)[:20]] = 3.0
+        elif kind == 4:
+            x[r, rs.permutation(V)[:V - 12]] = -np.inf
+        else:
+            x[r, V - 1] = -np.inf
+    want = draft_entropy_topk(x, 10, T)
+    got = G.run_entropy(x, 10, T)
+    assert np.array_equal(got["topk_idx"], want["topk_idx"])
+    for k in ("ent_topk", "ent_full"):
+        assert G.entropy_err(got[k], want[k]) <= 1.0, k
