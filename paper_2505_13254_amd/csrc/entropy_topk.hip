@@ -172,22 +172,21 @@ __device__ __forceinline__ unsigned long long lists_threshold(unsigned long long
   return who != 0ull ? lane_key(rth, __ffsll((long long)who) - 1) : 1ull;
 }
 
-// Ranks those of the candidates sm.key[0, n) that reach `thr` (>= 1) by counting (keys differ, zeros aside:
-// ranks are a permutation) and leaves those of rank < K, in order, in sm.best (zero on entry).  A wave takes a
-// run of candidates, one to a lane, and 64 opponents at a time, one to a lane: a candidate's key goes to a scalar
-// register, one comparison and a count of the ballot's bits follow, and no step waits for LDS.  (A loop over
-// LDS, one dependent read to an opponent, and counts added up by LDS atomics before: 8 us to 7.4 from a
-// workgroup's start to its slice's result.  Without the threshold every wave went through all 64 places of
-// its list for K = 64: 17 rows of 12000 logits 107 us.)  Called by all `nthreads` threads; ends with a barrier.
+// Ranks the candidates sm.key[0, n) by counting (keys differ, zeros aside: ranks are a permutation) and
+// leaves those of rank < K, in order, in sm.best (zero on entry).  A wave takes a run of candidates, one to a lane, and
+// 64 opponents at a time, one to a lane: a candidate's key goes to a scalar register, one comparison and a count of the
+// ballot's bits follow, and no step waits for LDS.  (A loop over LDS, one dependent read to an opponent, and counts
+// added up by LDS atomics before: 8 us to 7.4 from a workgroup's start to its slice's result.)  Called by all
+// `nthreads` threads; ends with a barrier.
 template <int CAP>
-__device__ __forceinline__ void rank_candidates(MergeScratch<CAP>& sm, int n, int K, unsigned long long thr, int tid, int nthreads) {
+__device__ __forceinline__ void rank_candidates(MergeScratch<CAP>& sm, int n, int K, int tid, int nthreads) {
   const int lane = tid & 63;
   const int n_waves = nthreads >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int per = (n + n_waves - 1) / n_waves;
   const int lo = wave * per, hi = min(n, lo + per);
   for (int c0 = lo; c0 < hi; c0 += 64) {  // one trip unless a wave has more than 64 candidates
     const unsigned long long mine = lane < hi - c0 ? sm.key[c0 + lane] : 0ull;
-    const unsigned long long ranked = __ballot(mine >= thr);
+    const unsigned long long ranked = __ballot(mine != 0ull);
     if (ranked == 0ull) continue;
     int rank = 0;
     for (int o = 0; o < n; o += 64) {
@@ -198,7 +197,7 @@ __device__ __forceinline__ void rank_candidates(MergeScratch<CAP>& sm, int n, in
         rank += lane == j ? above : 0;
       }
     }
-    if (mine >= thr && rank < K) sm.best[rank] = mine;
+    if (mine != 0ull && rank < K) sm.best[rank] = mine;
   }
   __syncthreads();
 }
@@ -267,7 +266,7 @@ __device__ __forceinline__ void merge_slices(const float4* st, const unsigned lo
     if (lane == 0) sm.total = a;
   }
   __syncthreads();
-  rank_candidates(sm, sm.cnt, K, thr, tid, nthreads);
+  rank_candidates(sm, sm.cnt, K, tid, nthreads);
 }
 
 // Writes a row's results from its merged statistics and Top-K list (first wave of the workgroup).
@@ -585,8 +584,27 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
     const float ws = wave_sum(s1), wt = wave_sum(t2);
     if (lane == 0) wave_st[wave] = make_float4(ref, ws, wt * 0.6931471805599453f, 0.f);
   }
-  if (lane < K) sm.key[wave * K + lane] = best;
+  // Lists that fit one wave of opponents are ranked whole.  Of longer ones only the entries that reach a threshold
+  // join, a wave's in one piece (ranked whole, or with the threshold but from the lists' places, K = 40: 40 rows of
+  // 16384 logits 49 and 21 us, 15 now; 200 rows 51 and 23, 17 now).
+  __shared__ unsigned long long rth[SCAN_WAVES];
+  const bool whole = SCAN_WAVES * K <= 64;
+  if (whole) {
+    if (lane < K) sm.key[wave * K + lane] = best;
+  } else {
+    if (lane == threshold_depth(SCAN_WAVES, K) - 1) rth[wave] = best;
+    if (tid == 0) sm.cnt = 0;
+  }
   __syncthreads();
+  if (!whole) {
+    const unsigned long long list_thr = lists_threshold(lane < SCAN_WAVES ? rth[lane] : 0ull, SCAN_WAVES, K);
+    const bool joins = lane < K && best >= list_thr;  // (a list's first entries)
+    const int n_joins = __popcll(__ballot(joins));
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&sm.cnt, n_joins);
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (joins) sm.key[base + lane] = best;
+  }
   if (STATS && tid < 64) {
     Stats a = stats_empty();
     if (lane < SCAN_WAVES) {
@@ -596,11 +614,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
     a = stats_wave_sum(a, inv_t);
     if (lane == 0) sm.total = a;
   }
-  // (lists that fit one wave of opponents are ranked whole: the threshold would cost what it saves)
-  unsigned long long list_thr = 1ull;
-  if (SCAN_WAVES * K > 64)
-    list_thr = lists_threshold(lane < SCAN_WAVES ? sm.key[lane * K + threshold_depth(SCAN_WAVES, K) - 1] : 0ull, SCAN_WAVES, K);
-  rank_candidates(sm, SCAN_WAVES * K, K, list_thr, tid, SCAN_THREADS);  // (its barrier also publishes sm.total)
+  if (!whole) __syncthreads();
+  rank_candidates(sm, whole ? SCAN_WAVES * K : sm.cnt, K, tid, SCAN_THREADS);  // (its barrier also publishes sm.total)
   static_assert(STATS || !FUSED, "rows are finished by the caller of a scan without statistics");
   if (S == 1) {
     if (STATS) write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
