@@ -39,8 +39,8 @@ constexpr int scan_tile(int threads) { return threads * SCAN_VPT; }  // logits p
 constexpr int FIN_THREADS = 256;
 constexpr int FIN_CAP = HS_MAX_TOPK * HS_MAX_TOPK;  // candidates the merge of 64 slices can face
 constexpr int MAX_SPLITS = 64;                       // slices per row (one list head per lane)
-constexpr int SCAN_BIG_WGS = 256;                    // rows are sliced until about so many workgroups exist
-constexpr int SCAN_SMALL_WGS = 600;
+constexpr int SCAN_BIG_WGS = 256;                    // rows are sliced until about so many sixteen-wave workgroups exist ...
+constexpr int SCAN_FINE_WGS = 600;                   // ... or four-wave ones (where they are: see plan_scan)
 constexpr float LOG2E = 1.4426950408889634f;
 
 struct ScanPlan {
@@ -49,22 +49,34 @@ struct ScanPlan {
   int tiles_per_wg;  // tiles each of them scans
 };
 
-static ScanPlan plan_scan(int R, int V) {
+// Cold inputs, K = 10, microseconds a call, best slicing of sixteen / four waves:
+//   17 rows of 8193  10.5 / 11.0    97 of 32000 13.6 / 15.5    66 of 128256 21.5 / 21.8   200 of 128256 27.4 / 31.1
+//   17 rows of 8000   9.5 /  9.5   256 of 32000 16.2 / 18.9   280 of 128256 48.7 / 40.3   600 of   8193 25.9 / 17.2
+// From 257 rows on sixteen-wave workgroups need a second round; rows of one small tile would leave most of sixteen
+// waves without a value (17 rows of 1000: 12.1 / 7.9), and so would rows of two, but the first threshold of four waves
+// comes from 16 groups only (40 rows of 8000, K = 40: 15.8 / 20.4).
+// Slices: 256 workgroups of sixteen waves (97 rows of 100000: 1 slice 21.6, 2 24.1, 3 28.3; 66 of 128256: 24.2, 23.3,
+// 21.5); for more than 256 rows none, or two of many tiles (300 of 50257: 1 slice 32.9, 2 34.7; 300 of 151936, merged by the
+// scan's launch: 43.9 and 41.1; 400 of 128256 42.4 and 50.3); for up to 16 rows as many as there are tiles, but a
+// merge of more than 16 pays for the first few rows only (10 rows of 128256 in 16 slices 12.9, in 32 14.7; 1 row 12.1
+// and 11.3), and one slice takes three tiles in the time of a merge (16 rows of 4097: 8.7 and 12.5, of 8000: 9.5
+// and 10.9).
+// `sparse`: a good part of the rows will be left out (row_active), so that large scans have room for workgroups of four
+// waves in more slices (61 rows and their 20 parents of 128256 logits, K = 1, the ratio rule's whole call: 67.8 us,
+// 69.7 by the rule for full scans).
+static ScanPlan plan_scan(int R, int V, int K, bool sparse) {
   ScanPlan p;
-  // Sixteen waves for 17 rows up to eight million logits.  (Cold inputs, K = 10, microseconds a call, best slicing
-  // of sixteen / four waves: 61 rows of 128256 19.6 / 19.9, 129 of 32000 14.9 / 16.0; 97 of 128256 24.9 / 23.3, 300
-  // of 128256 54 / 40, 10 of 128256 14.2 / 12.9.  Rows of at most two small tiles would leave most of sixteen
-  // waves without a value.)
-  p.threads = (R <= 16 || (int64_t)R * V > (8 << 20) || V <= 2 * scan_tile(SCAN_SMALL)) ? SCAN_SMALL : SCAN_BIG;
+  const int small_tiles = (V + scan_tile(SCAN_SMALL) - 1) / scan_tile(SCAN_SMALL);
+  const bool fine = sparse && R <= SCAN_BIG_WGS && (int64_t)R * V > (8 << 20);
+  p.threads = (R <= 16 || R > SCAN_BIG_WGS || small_tiles == 1 || (small_tiles == 2 && K <= 16) || fine) ? SCAN_SMALL : SCAN_BIG;
   const int tile = scan_tile(p.threads);
   const int n_tiles = (V + tile - 1) / tile;
-  // (97 rows in 6 slices 23.3 us, in 11 27.5, in 3 26.3; 300 in 2 40.4, in 1 42.1, in 3 43.2.  A merge of more than
-  // 16 slices pays for the first few rows only: 10 rows in 16 slices 12.9 us, in 32 14.7; 1 row 12.1 and 11.3.)
-  int want = (p.threads == SCAN_BIG ? SCAN_BIG_WGS : SCAN_SMALL_WGS) / (R > 0 ? R : 1);
-  if (R > 4 && want > 16) want = 16;
+  int want = 1;
+  if (p.threads == SCAN_BIG) want = SCAN_BIG_WGS / R;
+  else if (n_tiles > 3 && R <= 16) want = R <= 4 ? MAX_SPLITS : 16;
+  else if (fine) want = std::min(16, SCAN_FINE_WGS / R);
+  else if (n_tiles >= 24 && R <= SCAN_FINE_WGS / 2) want = 2;
   if (want > n_tiles) want = n_tiles;
-  if (want > MAX_SPLITS) want = MAX_SPLITS;
-  if (want < 1) want = 1;
   p.tiles_per_wg = (n_tiles + want - 1) / want;
   p.splits = (n_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg;
   return p;
@@ -679,15 +691,21 @@ __global__ __launch_bounds__(FIN_THREADS) void k_scan_finalize(const float4* __r
   write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
 }
 
-// What a scan of up to R rows can need: fewer rows are cut into more slices each, but never into more than
-// SCAN_SMALL_WGS in all unless the rows themselves are more, so a workspace made for R rows holds fewer too.
-size_t row_topk_workspace(int R, int V, int K) {
-  if (R <= 0) return 0;
-  static_assert(SCAN_BIG_WGS <= SCAN_SMALL_WGS, "the bound on the slices of a call");
-  const int tile = scan_tile(SCAN_SMALL);
-  const int64_t most = std::min((V + tile - 1) / tile, MAX_SPLITS);
-  const size_t n = (size_t)std::max<int64_t>(R, std::min<int64_t>(R * most, SCAN_SMALL_WGS));
+// Bytes for the slices' results of a call.
+static size_t slots_bytes(size_t n, int K) {
   return TICKET_BYTES + align_up(n * sizeof(float4), 256) + align_up(n * K * sizeof(unsigned long long), 256);
+}
+
+// What any scan of up to R rows can need: fewer rows are cut into more slices each (see plan_scan).
+size_t row_topk_workspace(int R, int V, int K, bool sparse) {
+  if (R <= 0) return 0;
+  const int64_t small = (V + scan_tile(SCAN_SMALL) - 1) / scan_tile(SCAN_SMALL);
+  const int64_t big = (V + scan_tile(SCAN_BIG) - 1) / scan_tile(SCAN_BIG);
+  int64_t n = std::max({(int64_t)R, std::min(R, 4) * std::min<int64_t>(small, MAX_SPLITS), std::min(R, 16) * std::min<int64_t>(small, 16),
+                        std::min<int64_t>(R * big, SCAN_BIG_WGS)});
+  if (sparse) n = std::max(n, std::min<int64_t>(R * std::min<int64_t>(small, 16), SCAN_FINE_WGS));
+  if (R > SCAN_BIG_WGS && small >= 24) n = std::max(n, std::min<int64_t>(2 * R, SCAN_FINE_WGS));
+  return slots_bytes((size_t)n, K);
 }
 
 hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V, int K, float temperature,
@@ -696,7 +714,7 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
                           const int32_t* row_index, const float* logits2, int rows1, bool prepared) {
   // (rows are the grid's second dimension)
   HS_REQUIRE(R <= 65535, HS_ERR_UNSUPPORTED, "row scan: %d rows in one call (at most 65535)", R);
-  ScanPlan p = plan_scan(R, V);
+  ScanPlan p = plan_scan(R, V, K, row_active != nullptr);
   Carver c(workspace);
   size_t n = (size_t)R * p.splits;
   // one counter per row, zero in a prepared workspace and left at zero; always the same leading part
@@ -751,7 +769,7 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
 
 extern "C" size_t hs_draft_entropy_topk_workspace(int32_t R, int32_t V, int32_t K) {
   if (R <= 0 || V <= 0 || K <= 0 || K > HS_MAX_TOPK) return 0;
-  return hs::row_topk_workspace(R, V, K);
+  return hs::row_topk_workspace(R, V, K, false);
 }
 
 static hs_status entropy_topk_impl(const float* logits, int64_t row_stride, const int32_t* row_index, int32_t R,
@@ -767,7 +785,7 @@ static hs_status entropy_topk_impl(const float* logits, int64_t row_stride, cons
   HS_REQUIRE(temperature > 0.f, HS_ERR_SHAPE, "hs_draft_entropy_topk: temperature must be positive");
   if (R == 0) return HS_OK;
   HS_REQUIRE(logits && topk_idx && topk_logp && ent_topk, HS_ERR_NULL, "hs_draft_entropy_topk: NULL argument");
-  size_t need = hs::row_topk_workspace(R, V, K);
+  const size_t need = hs::row_topk_workspace(R, V, K, false);
   HS_REQUIRE(workspace && workspace_bytes >= need && reinterpret_cast<uintptr_t>(workspace) % 256 == 0,
              HS_ERR_WORKSPACE, "hs_draft_entropy_topk: workspace needs %zu bytes, 256-byte aligned (got %zu)", need,
              workspace_bytes);

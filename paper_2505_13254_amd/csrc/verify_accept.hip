@@ -1016,22 +1016,25 @@ static size_t bonus_rows_bytes(int NN, int V) {
   return NN <= BK_NODES ? align_up((size_t)NN * ((V + 63) / 64) * sizeof(double), 256) : 0;
 }
 
+// Bytes of a call besides the scan's workspace, which comes last.
+static size_t accept_arrays_bytes(int NN, int V, bool ratio) {
+  // per row: argmax, -ln Z and an unused Top-1 entropy, for the target and for the draft rows (the
+  // two sets back to back: the ratio rule scans [target rows ; draft rows] in one launch)
+  const size_t sets = 3 * align_up((size_t)2 * NN * sizeof(float), 256);
+  // five doubles per row: what the rejection chains hand to the walk; two bytes per row: rows to scan
+  const size_t chain = 5 * align_up((size_t)NN * sizeof(double), 256) + align_up((size_t)2 * NN, 256);
+  // the sorted residual belongs to the ratio rule alone, and so do the children counts and the bonus
+  // distribution's row sums of every tree row
+  const size_t sorted = ratio ? bucket_workspace(NN, V, nullptr, nullptr) + align_up((size_t)NN * sizeof(int32_t), 256) + bonus_rows_bytes(NN, V) : 0;
+  return sets + chain + sorted;
+}
+
 }  // namespace hs
 
 extern "C" size_t hs_verify_accept_workspace_mode(int32_t B, int32_t NN, int32_t V, hs_accept_mode mode) {
   if (B <= 0 || NN <= 0 || V <= 0) return 0;
-  // per row: argmax, -ln Z and an unused Top-1 entropy, for the target and for the draft rows (the
-  // two sets back to back: the ratio rule scans [target rows ; draft rows] in one launch)
-  const size_t sets = 3 * hs::align_up((size_t)2 * NN * sizeof(float), 256);
-  // five doubles per row: what the rejection chains hand to the walk; two bytes per row: rows to scan
-  const size_t chain = 5 * hs::align_up((size_t)NN * sizeof(double), 256) + hs::align_up((size_t)2 * NN, 256);
-  // the sorted residual belongs to the ratio rule alone, and so does the scan of twice the rows
-  const bool ratio = mode == HS_ACCEPT_STOCHASTIC;
-  size_t sorted = ratio ? hs::bucket_workspace(NN, V, nullptr, nullptr) : 0;
-  // the ratio rule's children counts, and the bonus distribution's row sums of every tree row
-  if (ratio) sorted += hs::align_up((size_t)NN * sizeof(int32_t), 256) + hs::bonus_rows_bytes(NN, V);
-  const size_t scan1 = hs::row_topk_workspace(NN, V, 1), scan2 = ratio ? hs::row_topk_workspace(2 * NN, V, 1) : 0;
-  return sets + chain + sorted + (scan1 > scan2 ? scan1 : scan2);
+  const bool ratio = mode == HS_ACCEPT_STOCHASTIC;  // (it scans twice the rows)
+  return hs::accept_arrays_bytes(NN, V, ratio) + hs::row_topk_workspace(ratio ? 2 * NN : NN, V, 1, ratio);
 }
 
 extern "C" size_t hs_verify_accept_workspace(int32_t B, int32_t NN, int32_t V) {
@@ -1065,7 +1068,8 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
                  "hs_verify_accept: stochastic modes support V <= %d", hs::AC_MAX_ROWS * 64);
     }
   }
-  const size_t need = hs_verify_accept_workspace_mode(B, NN, V, mode);
+  const bool ratio = mode == HS_ACCEPT_STOCHASTIC;
+  const size_t need = NN > 0 ? hs::accept_arrays_bytes(NN, V, ratio) + hs::row_topk_workspace(ratio ? 2 * NN : NN, V, 1, ratio) : 0;
   HS_REQUIRE(need == 0 || (workspace && workspace_bytes >= need && reinterpret_cast<uintptr_t>(workspace) % 256 == 0),
              HS_ERR_WORKSPACE, "hs_verify_accept: workspace needs %zu bytes, 256-byte aligned (got %zu)", need,
              workspace_bytes);
