@@ -28,9 +28,10 @@
  * Conventions that hold for every call
  *   - Pointers are DEVICE pointers unless the parameter name starts with host_.  The caller owns
  *     every buffer; the library allocates and frees nothing, and keeps nothing after a call.
- *   - Scratch memory comes from the caller: `workspace` must hold at least the bytes the matching
- *     *_workspace query returns for the same shape arguments and must be 256-byte aligned.
- *     A smaller or NULL workspace (when the query is non-zero) gives HS_ERR_WORKSPACE.
+ *   - Scratch memory comes from the caller: `workspace` must be 256-byte aligned, and the bytes the
+ *     matching *_workspace query returns for the same shape arguments are always enough (row scan and
+ *     accept walk: for calls of fewer rows too).  A call may need less than its query says; a workspace
+ *     that does not hold what the call needs, or a NULL one, gives HS_ERR_WORKSPACE.
  *   - A call only enqueues kernels on `stream` (a hipStream_t; NULL = the default stream) and
  *     returns.  Results are valid once the caller has synchronised that stream.  No call
  *     synchronises the device, and none records a memset, so calls may be captured in a HIP graph.
@@ -61,7 +62,7 @@ typedef enum {
   HS_ERR_NULL = 1,        /* a required pointer is NULL                                  */
   HS_ERR_SHAPE = 2,       /* a size is negative, zero where it may not be, or inconsistent */
   HS_ERR_UNSUPPORTED = 3, /* a valid request this build has no kernel for                */
-  HS_ERR_WORKSPACE = 4,   /* workspace NULL, misaligned or smaller than the query says   */
+  HS_ERR_WORKSPACE = 4,   /* workspace NULL, misaligned or too small for the call         */
   HS_ERR_RUNTIME = 5      /* the HIP runtime refused a launch                            */
 } hs_status;
 

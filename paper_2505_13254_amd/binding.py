@@ -16,6 +16,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libheterospec.so")
 
 HS_F32, HS_BF16 = 0, 1
+HS_ERR_WORKSPACE = 4
 HS_ACCEPT_GREEDY, HS_ACCEPT_STOCHASTIC, HS_ACCEPT_STOCHASTIC_POINTMASS = 0, 1, 2
 HS_PSTAR_CUMULATIVE, HS_PSTAR_LOCAL = 0, 1
 HS_MAX_TOPK = 64
@@ -170,9 +171,10 @@ def hs_draft_entropy_topk(logits: torch.Tensor, K: int, temperature: float = 1.0
     tail = (_ptr(out["topk_idx"]), _ptr(out["topk_logp"]), _ptr(out["ent_topk"]), _ptr(out.get("ent_full")),
             _ptr(out.get("lse")), _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream))
     if fused:
-        if ws is None or ws.numel() < need:
+        st = HS_ERR_WORKSPACE if ws is None else lib().hs_draft_entropy_topk_fused(
+            _ptr(logits), stride, _ptr(row_index), R, V, K, float(temperature), *tail)
+        if st == HS_ERR_WORKSPACE and (ws is None or ws.numel() < need):
             raise ValueError("the fused call needs a prepared workspace of at least %d bytes" % need)
-        st = lib().hs_draft_entropy_topk_fused(_ptr(logits), stride, _ptr(row_index), R, V, K, float(temperature), *tail)
     elif row_index is None:
         st = lib().hs_draft_entropy_topk(_ptr(logits), stride, R, V, K, float(temperature), *tail)
     else:

@@ -696,7 +696,12 @@ static size_t slots_bytes(size_t n, int K) {
   return TICKET_BYTES + align_up(n * sizeof(float4), 256) + align_up(n * K * sizeof(unsigned long long), 256);
 }
 
-// What any scan of up to R rows can need: fewer rows are cut into more slices each (see plan_scan).
+// What the scan of R rows needs ...
+size_t row_topk_need(int R, int V, int K, bool sparse) {
+  return R <= 0 ? 0 : slots_bytes((size_t)R * plan_scan(R, V, K, sparse).splits, K);
+}
+
+// ... and what any scan of up to R rows can need: fewer rows are cut into more slices each (see plan_scan).
 size_t row_topk_workspace(int R, int V, int K, bool sparse) {
   if (R <= 0) return 0;
   const int64_t small = (V + scan_tile(SCAN_SMALL) - 1) / scan_tile(SCAN_SMALL);
@@ -785,7 +790,7 @@ static hs_status entropy_topk_impl(const float* logits, int64_t row_stride, cons
   HS_REQUIRE(temperature > 0.f, HS_ERR_SHAPE, "hs_draft_entropy_topk: temperature must be positive");
   if (R == 0) return HS_OK;
   HS_REQUIRE(logits && topk_idx && topk_logp && ent_topk, HS_ERR_NULL, "hs_draft_entropy_topk: NULL argument");
-  const size_t need = hs::row_topk_workspace(R, V, K, false);
+  const size_t need = hs::row_topk_need(R, V, K, false);
   HS_REQUIRE(workspace && workspace_bytes >= need && reinterpret_cast<uintptr_t>(workspace) % 256 == 0,
              HS_ERR_WORKSPACE, "hs_draft_entropy_topk: workspace needs %zu bytes, 256-byte aligned (got %zu)", need,
              workspace_bytes);

@@ -35,9 +35,10 @@ struct Carver {
 };
 
 // Row scan shared by hs_draft_entropy_topk and hs_verify_accept (defined in entropy_topk.hip).
-// row_topk_workspace never falls as R grows (a workspace for R rows holds fewer).
+// row_topk_workspace never falls as R grows (a workspace for R rows holds fewer); a call asks for row_topk_need.
 // sparse: with `row_active`.
 size_t row_topk_workspace(int R, int V, int K, bool sparse);
+size_t row_topk_need(int R, int V, int K, bool sparse);
 // `slices` (may be NULL): when the rows had to be cut into slices, the merge launch is left to the
 // caller, who receives the per-slice results instead: entry (row * count + slice) * K + k of `key` is
 // the slice's k-th best pair as one number: of two keys the larger is the better pair, the lower half

@@ -286,3 +286,55 @@ def test_masked_logits_at_any_place(G, R, V, T):
     assert np.array_equal(got["topk_idx"], want["topk_idx"])
     for k in ("ent_topk", "ent_full"):
         assert G.entropy_err(got[k], want[k]) <= 1.0, k
+
+
+@pytest.mark.parametrize("R,V,K,slices", [(97, 128256, 10, 2), (51, 128256, 10, 4), (200, 50257, 10, 1), (40, 8000, 40, 1), (97, 8000, 10, 1),
+                                          (16, 12000, 3, 1), (10, 128256, 10, 16), (600, 8193, 10, 1), (260, 131072, 10, 2)])
+def test_a_workspace_for_the_slices_of_the_call(G, R, V, K, slices):
+    """A call asks for the slices that its own rows are cut into (a statistics record of 16 bytes and K keys of
+    8 each, behind the 65536 counters), not for what smaller calls could need, and is refused without them."""
+    import paper_2505_13254_amd as hs
+    up = lambda n: -(-n // 256) * 256
+    need = 4 * 65536 + up(R * slices * 16) + up(R * slices * K * 8)
+    x = (np.random.RandomState(R).randn(R, V) * 2).astype(np.float32)
+    want, xd = draft_entropy_topk(x, K, 1.0), G.dev(x)
+    guard = torch.full((need + 4096,), 77, dtype=torch.uint8, device=G.DEV)
+    ws = guard[:need]
+    hs.hs_workspace_prepare(ws)
+    for fused in (True, False):
+        got = {k: G.host(v) for k, v in hs.hs_draft_entropy_topk(xd, K, 1.0, ws=ws, fused=fused).items()}
+        assert np.array_equal(got["topk_idx"], want["topk_idx"])
+        for k in ("ent_topk", "ent_full"):
+            assert G.entropy_err(got[k], want[k]) <= 1.0, k
+    assert bool((guard[need:] == 77).all())
+    with pytest.raises(hs.HsError):
+        hs.hs_draft_entropy_topk(xd, K, 1.0, ws=ws[:need - 256])
+
+
+def test_accept_workspaces_hold_every_smaller_call(G):
+    """A workspace made for the largest tree serves all smaller ones in every mode, and nothing is written behind it."""
+    import paper_2505_13254_amd as hs
+    from test_gpu_entropy_prune_accept import _accept_equal
+    from oracle import verify_accept
+    rs = np.random.RandomState(3)
+    V, top = 50257, 140
+    for mode in (0, 1, 2):
+        need = hs.lib().hs_verify_accept_workspace_mode(1, top, V, mode)
+        guard = torch.full((need + 4096,), 77, dtype=torch.uint8, device=G.DEV)
+        for NN in (1, 2, 5, 9, 17, 64, 129, top):
+            target = (rs.normal(size=(NN, V)) * 3).astype(np.float32)
+            draft = (target + rs.normal(size=(NN, V))).astype(np.float32)
+            parent = np.asarray([-1] + [(i - 1) // 3 for i in range(1, NN)], np.int32)
+            token = np.zeros(NN, np.int32)
+            for i in range(1, NN):  # (one of the likely tokens of the parent's row, another for each sibling)
+                token[i] = np.argsort(-target[parent[i]], kind="stable")[(i - 1) % 3]
+            offs = np.asarray([0, NN], np.int32)
+            u = np.concatenate([rs.rand(NN), [0.5]]).astype(np.float32)
+            args = [G.dev(target), G.dev(draft), G.dev(token, torch.int32), G.dev(parent, torch.int32), G.dev(offs, torch.int32), mode, 1.0,
+                    G.dev(u, torch.float32), 6]
+            near = [verify_accept(target, draft, token, parent, offs, mode, 1.0, np.clip(u.astype(np.float64) + d, 0.0, 1.0 - 1e-12), 6)
+                    for d in (-1e-5, 0.0, 1e-5)]
+            got = {k: G.host(v) for k, v in hs.hs_verify_accept(*args, ws=guard[:need]).items()}
+            if all(np.array_equal(n[k], near[1][k]) for n in near for k in near[1] if k in got):
+                _accept_equal(got, near[1])
+        assert bool((guard[need:] == 77).all())
