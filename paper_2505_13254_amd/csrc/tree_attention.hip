@@ -400,26 +400,27 @@ constexpr float PLAN_ITEM_US = 10.f;
 // item's fixed cost: one layer of the 8B shape (32 tiles a head) takes 25.9 us cut into 4 x 8 tiles, 23.5 us
 // into 8 x 4 or 16 x 2, combine launch included.
 constexpr int PLAN_MIN_SPLIT_TILES = 2;
-// A launch of at most half as many items as compute units gives each item two workgroups of up to 128 rows,
-// in which two waves share a row block and take every other 32 keys: 0.65 us a tile instead of 1.03 on an
-// otherwise idle chip (33 and 126 tiles a workgroup, 244 rows: 43.9 and 140 us -> 31.2 and 91 us).  The fixed
-// 10 us of an item and a combine launch of 3.5 us + its records at 4.5 TB/s were fitted to the same sweeps
-// (one layer of 2048 and of 8000 tokens, 1 to 33 splits; within 2 us of all of them).
+// A launch of at most half as many items as compute units can give each item two workgroups of up to 128 rows,
+// in which two waves share a row block and take every other 32 keys ("narrow"): 0.65 us a tile instead of 1.05 on
+// an otherwise idle chip for items of more than 128 rows (33 and 126 tiles a workgroup, 244 rows: 43.9 and 140 us
+// -> 31.2 and 91 us).
 constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2;
-// Such a launch draws less from HBM, so it is compared with launches of one workgroup to each compute unit
-// (129 to 256 items) at the pace those have on a chip that is not full, and has to be estimated PLAN_NARROW_GAIN
-// better (several row groups read the same keys: PLAN_NARROW_GAIN_RG).  12 layers of 6000 tokens, 48 rows a head:
-// 57 us as 192 items, 77 as 96 narrow ones; 244 rows a head: 100 and 85.
-constexpr float PLAN_NARROW_GAIN = 0.93f, PLAN_NARROW_GAIN_RG = 0.9f;
-static inline float plan_narrow_tile_us(int64_t items, int waves) {
-  return 0.65f + (waves > 4 && items > 72 ? 0.004f * (float)(items - 72) : 0.f);
+// Launches that give every item a compute unit of its own, either way: the longest item decides.  A tile costs
+// the more the more K/V streams are read at a time, and above 128 rows, where two waves share a SIMD, the matrix
+// instructions' time at least; up to 128 rows two waves to a row block gain nothing, and cost more to start and
+// to end.  Measured per tile with 28 / 115 / 180 / 230 streams: narrow 0.70, 0.87; else up to 128 rows 0.71, 0.82,
+// 0.97, 1.11; 256 rows 1.1, 1.2, 1.6, 1.65, at D = 64 0.75 to 1.1.  The constants are those that chose the best of
+// all cuts in 2499 random launches (1 to 48 entries, 60 to 12000 tokens, 1 to 300 rows, five head layouts, both head
+// dimensions; 1.4 % above each launch's best cut on average), which makes them higher than the times: the estimates
+// of fuller launches that they are compared with are high as well.  (Every launch of up to 128 items narrow, with
+// flat costs a tile: 2.0 %; 3 entries of 2344 tokens, 66 rows, 40 heads 49.0 us, now and without narrow launches 39.4;
+// one of 8945 tokens, 130 rows 68 and 55; without narrow launches 9.9 % on average.)
+static inline float plan_own_cu_us(bool narrow, bool half, int waves, int tiles, float streams) {
+  const float item = waves > 4 ? 12.f : narrow && waves > 2 ? 8.4f : 6.5f;
+  float tile = narrow ? 0.88f + 0.0029f * streams : 1.07f + 0.0018f * streams;
+  if (!narrow && waves > 4) tile = std::max(tile, half ? 1.35f : 1.5f);
+  return item + (float)tiles * tile;
 }
-static inline float plan_round_tile_us(int64_t items, int waves) {
-  const float idle = 0.85f + 0.13f * (float)std::max(0, waves - 4);                  // up to 192 items
-  const float full = std::max(idle, std::min(1.6f, 1.15f + 0.12f * (float)(waves - 2)));  // 256 items
-  return idle + (full - idle) * (float)std::max<int64_t>(0, items - 192) / 64.f;
-}
-static inline float plan_round_item_us(int waves) { return waves > 4 ? 10.f : 8.f; }
 constexpr int PLAN_MIN_SPLIT_TOKENS = PLAN_MIN_SPLIT_TILES * 64;
 static inline float plan_tile_us(int waves) { return 1.25f + 0.04f * (float)waves; }
 
@@ -427,6 +428,7 @@ struct ListPlan {
   float est_us;
   int target;
   int tail, cuts;  // the last `tail` entries have each of their splits cut into `cuts` once more (0, 1: none)
+  int narrow;      // two workgroups to an item
 };
 
 // Equal entries whose items do not fill whole rounds of the compute units: the entries that spill into the
@@ -466,7 +468,7 @@ static inline void plan_cut(int tiles, int target, int sp_cap, bool paged, int* 
 
 // Fills a.tbl / a.n_tbl / a.n_items / a.sp_max.  Returns false when the batch does not fit the table.
 // lean: the plan for a workspace that does not hold the usual one's records (fewer cuts, hence fewer
-// records): no finer last round, and a launch of few items is cut as if each had one workgroup.
+// records): no finer last round, no two workgroups to an item.
 static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, const int64_t* hlens, int B,
                           int sp_cap, bool lean) {
   struct Seq {
@@ -502,7 +504,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   const int n_targets = (int)(sizeof(targets) / sizeof(targets[0])) - (coarse_items < PLAN_CUS ? 0 : 3);
   bool equal = true;  // entries of one size
   for (int i = 1; i < n; ++i) equal = equal && seqs[i].M == seqs[0].M && seqs[i].tiles == seqs[0].tiles;
-  ListPlan best{0.f, 0, 0, 1};
+  ListPlan best{0.f, 0, 0, 1, 0};
   static thread_local std::vector<float> item_cost, cu_free;  // (kept between calls: no allocation in the steady state)
   for (int ti = 0; ti < n_targets; ++ti) {
     const int target = targets[ti];
@@ -527,21 +529,29 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       ord[i] = i;
       seq_cost[i] = (float)per * plan_tile_us(q.waves0);
     }
-    if (items <= PLAN_CUS && !lean) {  // every workgroup has a compute unit: the longest item decides
-      const bool narrow = items <= PLAN_NARROW_ITEMS;
-      float longest = 0.f;
-      bool groups = false;
+    const float combine_us = rec_bytes > 0.0 ? 4.f + (float)(rec_bytes / 2.5e6) : 0.f;  // the combine launch, ~2.5 TB/s
+    if (items <= PLAN_CUS && !lean) {  // every item has a compute unit of its own
+      int longest = 0;     // tiles of an item
+      double streamed = 0.0;  // tiles of all items, row groups of the same keys as one
       for (int i = 0; i < n; ++i) {
         const Seq& q = seqs[i];
         int nsp, per;
         plan_cut(q.tiles, target, sp_cap, a.block_table != nullptr, &nsp, &per);
-        const float tile = narrow ? plan_narrow_tile_us(items, q.waves0) : plan_round_tile_us(items, q.waves0);
-        longest = std::max(longest, plan_round_item_us(q.waves0) + (float)(per + q.ttiles) * tile);
-        groups = groups || q.rg > 1;
+        longest = std::max(longest, per + q.ttiles);
+        streamed += (double)a.Hkv * nsp * (per + q.ttiles);
       }
-      float est = longest + (rec_bytes > 0.0 ? 3.5f + (float)(rec_bytes / 4.5e6) : 0.f);
-      if (narrow) est /= groups ? PLAN_NARROW_GAIN_RG : PLAN_NARROW_GAIN;
-      if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1};
+      const float streams = (float)(streamed / longest);  // read at a time while the longest item runs
+      for (int narrow = 0; narrow <= (items <= PLAN_NARROW_ITEMS ? 1 : 0); ++narrow) {
+        float est = 0.f;
+        for (int i = 0; i < n; ++i) {
+          const Seq& q = seqs[i];
+          int nsp, per;
+          plan_cut(q.tiles, target, sp_cap, a.block_table != nullptr, &nsp, &per);
+          est = std::max(est, plan_own_cu_us(narrow != 0, a.half != 0, q.waves0, per + q.ttiles, streams));
+        }
+        est += combine_us;
+        if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1, narrow};
+      }
       continue;
     }
     // Equal entries, a last round that is not full: its entries cut finer.  (Layers of
@@ -564,12 +574,11 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
                            ((double)tail * nsp2 + (nsp > 1 ? (double)(n - tail) * nsp : 0.0));
         const float est = plan_two_sizes(entry_items * (n - tail), c, entry_items / nsp * nsp2 * tail, small) +
                           4.f + (float)(rec / 2.5e6);
-        if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, tail, cuts};
+        if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, tail, cuts, 0};
       }
     }
     // (no schedule ends before the work divided by the compute units, nor before its longest item: a
     // candidate whose bound is no better than the best estimate so far needs no replay)
-    const float combine_us = rec_bytes > 0.0 ? 4.f + (float)(rec_bytes / 2.5e6) : 0.f;  // the combine launch, ~2.5 TB/s
     {
       const float floor_us = (float)(total / PLAN_CUS) > mx ? (float)(total / PLAN_CUS) : mx;
       if (best.target != 0 && floor_us + combine_us >= best.est_us) continue;
@@ -613,7 +622,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       est = end;
     }
     est += combine_us;
-    if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1};
+    if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1, 0};
   }
   // the table: sequences by falling cost of an item
   int order[ATTN_TBL];
@@ -653,7 +662,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     if (nsp_of[i] > 1) a.cmb_row0 = hno[seqs[i].s];
   a.n_tbl = n;
   a.n_items = (int)first;
-  a.narrow = first <= PLAN_NARROW_ITEMS ? 1 : 0;
+  a.narrow = best.narrow;
   a.sp_max = sp_max;
   return true;
 }

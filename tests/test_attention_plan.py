@@ -76,6 +76,15 @@ def test_a_single_layer_is_cut_finer_than_a_launch_that_fills_the_chip():
     assert all(r[1] >= 8 for r in per4)
 
 
+@pytest.mark.parametrize("B,M,L,H,D", [(3, 66, 2344, 40, 128), (16, 29, 8715, 8, 128)])
+def test_few_long_items_are_cut_until_the_chip_is_full(B, M, L, H, D):
+    """Up to 128 items of many tiles are bound by the K/V streams in flight, however many workgroups an item
+    gets: they are cut until most compute units have one."""
+    totals, per = _plan([M] * B, [L] * B, 32 if H == 8 else H, H, D=D)
+    _check_work_list([M] * B, [L] * B, 32 if H == 8 else H, H, D, totals, per)
+    assert 160 <= totals[1] <= 256 and totals[5] == 1
+
+
 def test_plans_are_remembered_per_input_not_per_call_order():
     """The library keeps its last few plans: the same inputs give the same plan whatever was planned in
     between (more shapes than it keeps), and inputs that differ in one length, one tree size, the head layout,
