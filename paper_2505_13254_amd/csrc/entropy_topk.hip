@@ -41,6 +41,7 @@ constexpr int FIN_CAP = HS_MAX_TOPK * HS_MAX_TOPK;  // candidates the merge of 6
 constexpr int MAX_SPLITS = 64;                       // slices per row (one list head per lane)
 constexpr int SCAN_BIG_WGS = 256;                    // rows are sliced until about so many sixteen-wave workgroups exist ...
 constexpr int SCAN_FINE_WGS = 600;                   // ... or four-wave ones (where they are: see plan_scan)
+constexpr int SCAN_CUT_WGS = 1024;                   // ... of more than 256 rows
 constexpr float LOG2E = 1.4426950408889634f;
 
 struct ScanPlan {
@@ -61,22 +62,38 @@ struct ScanPlan {
 // merge of more than 16 pays for the first few rows only (10 rows of 128256 in 16 slices 12.9, in 32 14.7; 1 row 12.1
 // and 11.3), and one slice takes three tiles in the time of a merge (16 rows of 4097: 8.7 and 12.5, of 8000: 9.5
 // and 10.9).
-// `sparse`: a good part of the rows will be left out (row_active), so that large scans have room for workgroups of four
-// waves in more slices (61 rows and their 20 parents of 128256 logits, K = 1, the ratio rule's whole call: 67.8 us,
+// `rows.sparse`: a good part of the rows will be left out (row_active), so that large scans have room for workgroups of
+// four waves in more slices (61 rows and their 20 parents of 128256 logits, K = 1, the ratio rule's whole call: 67.8 us,
 // 69.7 by the rule for full scans).
-static ScanPlan plan_scan(int R, int V, int K, bool sparse) {
+// Rows that are not 16-byte aligned are read a value at a time, which only more workgroups make up for; slices whose
+// merge is the caller's (rows.pairs_only) cost no launch.  So the argmax scan takes 257 rows and more in three slices,
+// or two, as long as 1024 workgroups allow (277 rows of 50257: 1 slice 31.2, 2 28.7, 3 26.0; 305 of 187620, aligned: 57.1,
+// 50.5, 48.9; aligned rows from about 360 on gain nothing, 421 to 520 of 32000 or 50256 would lose 3 %), three-tile
+// rows in three slices (2 of 11379: 8.8, 7.0), and the full scan up to 341 long rows in three (301 of 132058: 70.8, 53.2;
+// shorter ones break even) and up to 16 rows in up to 256 slices altogether (7 of 137847: 17.1 in 12 slices each, 15.0 in
+// 34).
+static ScanPlan plan_scan(int R, int V, int K, const ScanRows& rows) {
   ScanPlan p;
   const int small_tiles = (V + scan_tile(SCAN_SMALL) - 1) / scan_tile(SCAN_SMALL);
-  const bool fine = sparse && R <= SCAN_BIG_WGS && (int64_t)R * V > (8 << 20);
+  const bool fine = rows.sparse && R <= SCAN_BIG_WGS && (int64_t)R * V > (8 << 20);
   p.threads = (R <= 16 || R > SCAN_BIG_WGS || small_tiles == 1 || (small_tiles == 2 && K <= 16) || fine) ? SCAN_SMALL : SCAN_BIG;
   const int tile = scan_tile(p.threads);
   const int n_tiles = (V + tile - 1) / tile;
   int want = 1;
-  if (p.threads == SCAN_BIG) want = SCAN_BIG_WGS / R;
-  else if (n_tiles > 3 && R <= 16) want = R <= 4 ? MAX_SPLITS : 16;
-  else if (fine) want = std::min(16, SCAN_FINE_WGS / R);
-  else if (n_tiles >= 24 && R <= SCAN_FINE_WGS / 2) want = 2;
+  if (p.threads == SCAN_BIG) {
+    want = SCAN_BIG_WGS / R;
+  } else if (R <= 16) {
+    if (n_tiles > (rows.pairs_only && !rows.aligned ? 1 : 3)) want = R <= 4 ? MAX_SPLITS : rows.pairs_only || rows.aligned ? 16 : SCAN_BIG_WGS / R;
+  } else if (fine) {
+    want = std::min(16, SCAN_FINE_WGS / R);
+  } else if (R > SCAN_BIG_WGS) {
+    const int cut = std::min(3, SCAN_CUT_WGS / R);  // (three up to 341 rows, two up to 512)
+    if (rows.pairs_only && (cut == 3 || (n_tiles >= 24 && (!rows.aligned || R <= 360)))) want = cut;
+    else if (!rows.aligned && !rows.sparse && cut == 3 && n_tiles >= 16) want = cut;
+    else if (n_tiles >= 24 && R <= SCAN_FINE_WGS / 2) want = 2;
+  }
   if (want > n_tiles) want = n_tiles;
+  if (want < 1) want = 1;
   p.tiles_per_wg = (n_tiles + want - 1) / want;
   p.splits = (n_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg;
   return p;
@@ -697,8 +714,8 @@ static size_t slots_bytes(size_t n, int K) {
 }
 
 // What the scan of R rows needs ...
-size_t row_topk_need(int R, int V, int K, bool sparse) {
-  return R <= 0 ? 0 : slots_bytes((size_t)R * plan_scan(R, V, K, sparse).splits, K);
+size_t row_topk_need(int R, int V, int K, const ScanRows& rows) {
+  return R <= 0 ? 0 : slots_bytes((size_t)R * plan_scan(R, V, K, rows).splits, K);
 }
 
 // ... and what any scan of up to R rows can need: fewer rows are cut into more slices each (see plan_scan).
@@ -706,10 +723,10 @@ size_t row_topk_workspace(int R, int V, int K, bool sparse) {
   if (R <= 0) return 0;
   const int64_t small = (V + scan_tile(SCAN_SMALL) - 1) / scan_tile(SCAN_SMALL);
   const int64_t big = (V + scan_tile(SCAN_BIG) - 1) / scan_tile(SCAN_BIG);
-  int64_t n = std::max({(int64_t)R, std::min(R, 4) * std::min<int64_t>(small, MAX_SPLITS), std::min(R, 16) * std::min<int64_t>(small, 16),
+  int64_t n = std::max({(int64_t)R, std::min(R, 4) * std::min<int64_t>(small, MAX_SPLITS), std::min<int64_t>(std::min(R, 16) * small, SCAN_BIG_WGS),
                         std::min<int64_t>(R * big, SCAN_BIG_WGS)});
   if (sparse) n = std::max(n, std::min<int64_t>(R * std::min<int64_t>(small, 16), SCAN_FINE_WGS));
-  if (R > SCAN_BIG_WGS && small >= 24) n = std::max(n, std::min<int64_t>(2 * R, SCAN_FINE_WGS));
+  if (R > SCAN_BIG_WGS) n = std::max(n, std::min<int64_t>(R * std::min<int64_t>(small, 3), SCAN_CUT_WGS));
   return slots_bytes((size_t)n, K);
 }
 
@@ -719,7 +736,8 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
                           const int32_t* row_index, const float* logits2, int rows1, bool prepared) {
   // (rows are the grid's second dimension)
   HS_REQUIRE(R <= 65535, HS_ERR_UNSUPPORTED, "row scan: %d rows in one call (at most 65535)", R);
-  ScanPlan p = plan_scan(R, V, K, row_active != nullptr);
+  const ScanRows rows{scan_aligned(logits, logits2, row_stride), row_active != nullptr, slices != nullptr && slices->pairs_only};
+  ScanPlan p = plan_scan(R, V, K, rows);
   Carver c(workspace);
   size_t n = (size_t)R * p.splits;
   // one counter per row, zero in a prepared workspace and left at zero; always the same leading part
@@ -728,8 +746,7 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
   float4* part_stats = c.take<float4>(n);
   unsigned long long* part_key = c.take<unsigned long long>(n * K);
   const float inv_t = 1.0f / temperature;
-  const bool vec = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && (row_stride % 4 == 0) &&
-                   (reinterpret_cast<uintptr_t>(logits2) % 16 == 0);
+  const bool vec = rows.aligned;
   dim3 grid(p.splits, R);
   // one launch: the rows' last slices merge (needs the zeroed counters of a prepared workspace)
   const bool fused = prepared && slices == nullptr && p.splits > 1 && p.splits * K <= FUSED_CAP;
@@ -790,7 +807,7 @@ static hs_status entropy_topk_impl(const float* logits, int64_t row_stride, cons
   HS_REQUIRE(temperature > 0.f, HS_ERR_SHAPE, "hs_draft_entropy_topk: temperature must be positive");
   if (R == 0) return HS_OK;
   HS_REQUIRE(logits && topk_idx && topk_logp && ent_topk, HS_ERR_NULL, "hs_draft_entropy_topk: NULL argument");
-  const size_t need = hs::row_topk_need(R, V, K, false);
+  const size_t need = hs::row_topk_need(R, V, K, hs::ScanRows{hs::scan_aligned(logits, nullptr, row_stride), false, false});
   HS_REQUIRE(workspace && workspace_bytes >= need && reinterpret_cast<uintptr_t>(workspace) % 256 == 0,
              HS_ERR_WORKSPACE, "hs_draft_entropy_topk: workspace needs %zu bytes, 256-byte aligned (got %zu)", need,
              workspace_bytes);

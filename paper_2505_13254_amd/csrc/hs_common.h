@@ -35,10 +35,19 @@ struct Carver {
 };
 
 // Row scan shared by hs_draft_entropy_topk and hs_verify_accept (defined in entropy_topk.hip).
+// What of a call, besides R, V and K, decides how its rows are cut.
+struct ScanRows {
+  bool aligned;     // scan_aligned
+  bool sparse;      // with `row_active`
+  bool pairs_only;  // with `slices`, pairs_only
+};
+// Every row begins at a multiple of 16 bytes: it is read four values at a time.  (logits2 may be NULL)
+inline bool scan_aligned(const float* logits, const float* logits2, int64_t row_stride) {
+  return reinterpret_cast<uintptr_t>(logits) % 16 == 0 && reinterpret_cast<uintptr_t>(logits2) % 16 == 0 && row_stride % 4 == 0;
+}
 // row_topk_workspace never falls as R grows (a workspace for R rows holds fewer); a call asks for row_topk_need.
-// sparse: with `row_active`.
 size_t row_topk_workspace(int R, int V, int K, bool sparse);
-size_t row_topk_need(int R, int V, int K, bool sparse);
+size_t row_topk_need(int R, int V, int K, const ScanRows& rows);
 // `slices` (may be NULL): when the rows had to be cut into slices, the merge launch is left to the
 // caller, who receives the per-slice results instead: entry (row * count + slice) * K + k of `key` is
 // the slice's k-th best pair as one number: of two keys the larger is the better pair, the lower half

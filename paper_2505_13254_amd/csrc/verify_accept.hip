@@ -1070,7 +1070,8 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
   }
   // (what this call's scan needs; the query gives what any call of up to NN rows can need)
   const bool ratio = mode == HS_ACCEPT_STOCHASTIC;
-  const size_t need = NN > 0 ? hs::accept_arrays_bytes(NN, V, ratio) + hs::row_topk_need(ratio ? 2 * NN : NN, V, 1, ratio) : 0;
+  const hs::ScanRows rows{hs::scan_aligned(target_logits, ratio ? draft_logits : nullptr, row_stride), ratio, !stochastic};
+  const size_t need = NN > 0 ? hs::accept_arrays_bytes(NN, V, ratio) + hs::row_topk_need(ratio ? 2 * NN : NN, V, 1, rows) : 0;
   HS_REQUIRE(need == 0 || (workspace && workspace_bytes >= need && reinterpret_cast<uintptr_t>(workspace) % 256 == 0),
              HS_ERR_WORKSPACE, "hs_verify_accept: workspace needs %zu bytes, 256-byte aligned (got %zu)", need,
              workspace_bytes);

@@ -289,7 +289,8 @@ def test_masked_logits_at_any_place(G, R, V, T):
 
 
 @pytest.mark.parametrize("R,V,K,slices", [(97, 128256, 10, 2), (51, 128256, 10, 4), (200, 50257, 10, 1), (40, 8000, 40, 1), (97, 8000, 10, 1),
-                                          (16, 12000, 3, 1), (10, 128256, 10, 16), (600, 8193, 10, 1), (260, 131072, 10, 2)])
+                                          (16, 12000, 3, 1), (10, 128256, 10, 16), (600, 8193, 10, 1), (260, 131072, 10, 2),
+                                          (260, 61443, 10, 3), (7, 137847, 10, 34), (14, 70001, 24, 18), (16, 70001, 24, 9), (342, 61443, 1, 1)])
 def test_a_workspace_for_the_slices_of_the_call(G, R, V, K, slices):
     """A call asks for the slices that its own rows are cut into (a statistics record of 16 bytes and K keys of
     8 each, behind the 65536 counters), not for what smaller calls could need, and is refused without them."""
@@ -338,3 +339,35 @@ def test_accept_workspaces_hold_every_smaller_call(G):
             if all(np.array_equal(n[k], near[1][k]) for n in near for k in near[1] if k in got):
                 _accept_equal(got, near[1])
         assert bool((guard[need:] == 77).all())
+
+
+@pytest.mark.parametrize("R,V,slices", [(2, 11379, 3), (16, 8191, 2), (9, 8192, 1), (257, 8193, 3), (341, 4099, 2), (342, 8193, 1), (260, 12288, 3),
+                                        (360, 98304, 2), (361, 98304, 1), (400, 98305, 2)])
+def test_argmax_slices_of_a_greedy_walk(G, R, V, slices):
+    """Greedy walks over rows cut into up to three slices, aligned or not: every row's largest value stands in two
+    places, in the first tile and in the last, and the first one counts.  The workspace holds the slices of the call
+    (records of 16 bytes, keys of 8, behind the 65536 counters and the walk's arrays), and no less will do."""
+    import paper_2505_13254_amd as hs
+    rs = np.random.RandomState(R + V)
+    x = torch.randn((R, V), generator=torch.Generator(device=G.DEV).manual_seed(R), device=G.DEV)
+    best = rs.randint(0, 4000, size=R)
+    rows = torch.arange(R, device=G.DEV)
+    x[rows, torch.from_numpy(V - 1 - rs.randint(0, 60, size=R)).to(G.DEV)] = 9.0
+    x[rows, torch.from_numpy(best).to(G.DEV)] = 9.0
+    # a chain through the first rows, the others hang off it with tokens that no row confirms
+    n = min(R, 9)
+    parent = np.asarray([-1] + [i - 1 if i < n else rs.randint(0, n) for i in range(1, R)], np.int32)
+    token = np.asarray([0] + [best[i - 1] if i < n else 4096 + i for i in range(1, R)], np.int32)
+    args = [x, None, G.dev(token, torch.int32), G.dev(parent, torch.int32), G.dev(np.asarray([0, R]), torch.int32), 0, 1.0, None, 12]
+    up = lambda n: -(-n // 256) * 256
+    query = hs.lib().hs_verify_accept_workspace_mode(1, R, V, 0)
+    guard = torch.full((query + 4096,), 77, dtype=torch.uint8, device=G.DEV)
+    own = 3 * up(8 * R) + 5 * up(8 * R) + up(2 * R) + 4 * 65536 + up(R * slices * 16) + up(R * slices * 8)
+    assert own <= query
+    got = hs.hs_verify_accept(*args, ws=guard[:own])
+    assert int(got["accept_len"][0]) == n - 1
+    assert got["accept_path"][0, :n - 1].tolist() == list(range(1, n))
+    assert int(got["bonus_token"][0]) == best[n - 1]
+    assert bool((guard[own:] == 77).all())
+    with pytest.raises(hs.HsError):
+        hs.hs_verify_accept(*args, ws=guard[:own - 256])
