@@ -147,7 +147,7 @@ def test_a_workspace_without_room_for_the_finer_last_round(G):
     """The same launch with no room for records runs uncut; a launch that is cut in any plan (one sequence
     of few heads) is refused."""
     import paper_2505_13254_amd as hs
-    from test_gpu_attention import _case, _random_parents
+    from test_gpu_attention import P, _case, _random_parents
     for D, hq, hkv, M, L, B in [(128, 8, 8, 9, 1500, 33), (64, 8, 8, 5, 1000, 66), (128, 8, 4, 40, 833, 70), (128, 8, 4, 9, 4000, 1)]:
         w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
         rs = np.random.RandomState(B)
@@ -160,11 +160,13 @@ def test_a_workspace_without_room_for_the_finer_last_round(G):
             with pytest.raises(hs.HsError):
                 hs.hs_tree_attention(*args, ws=small)
             continue
-        want, _ = G.run_attention(step)
         got, _ = hs.hs_tree_attention(*args, ws=small)
-        # both sum in float32 and round weights and results to bfloat16: at most a unit each, 2^-8 of the
-        # values that are averaged
-        assert np.abs(G.host(got) - want).max() <= 2.0 ** -7 * np.abs(G.host(args[2])).max()
+        # against the checker, within what the kernel's roundings imply element by element, and within 1e-2 of the
+        # largest output (what the other bfloat16 comparisons ask; a tile of keys left out moves an output by more)
+        want, _ = P.attention_out(step)
+        diff = np.abs(G.host(got).astype(np.float64) - want)
+        assert (diff / G.attention_error_bound(step, want)).max() <= 1.0
+        assert diff.max() <= 1e-2 * np.abs(want).max()
 
 
 @pytest.mark.parametrize("mode", [1, 2])
