@@ -10,8 +10,9 @@
 // (k_scan_finalize).
 //
 // Top-K selection never sorts the data.  Each wave keeps its K best pairs as a sorted list in
-// registers, entry l in lane l.  Per tile only the elements that are not worse than the list's K-th
-// entry are looked at (one ballot per register); each of them is broadcast and inserted: the lanes
+// registers, entry l in lane l, a pair being one 64-bit key.  Per tile only the lanes that hold a value
+// not worse than the list's K-th entry are looked at: they put their values into LDS, which are taken up 64 at
+// a time, one to a lane; those that beat the K-th entry are broadcast and inserted one by one: the lanes
 // whose entry it beats take their left neighbour's entry (or the new one), a shift by one lane done
 // with a DPP move.  Before a list is full the threshold comes from the first tile: the K-th largest
 // of the workgroup's wave maxima (of its 16-lane row maxima when it has fewer waves than K, of a
@@ -504,7 +505,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
     if (FIRST) {
       // Groups that hold no value of the row have no maximum: counting them, the K-th largest of the
       // maxima would be -inf and every value of a short row would be inserted one by one (17 rows of
-      // 1024 logits: 26.8 us; with the groups counted and four-wave workgroups see plan_scan).
+      // 1024 logits: 26.8 us that way; of 1000 without the empty groups 12.1, in workgroups of four waves 7.9).
       const int n_here = min(V - tbase, SCAN_TILE);  // the tile's values; 4 neighbouring ones to a thread
       const int waves_here = min((n_here + 255) >> 8, SCAN_WAVES), groups_here = min((n_here + 63) >> 6, SCAN_GROUPS);
       if (K <= groups_here) {
@@ -533,9 +534,10 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
 
     // ---- insert the elements that reach the threshold.  A lane whose maximum does puts its 16 values into
     // LDS; 64 of them at a time, one to a lane, are then compared with the list's worst entry, and what
-    // beats it is inserted.  (One copy of the insertion for the whole tile, not one for each register: short
-    // scans wait for their instructions more than for anything else, 10 rows in 16 slices 13.9 us to 12.9.)  (The floor is a pair: of equal values only lower indices beat it, or rows of
-    // equal logits would send every element through the insertion.)
+    // beats it is inserted.  That entry is a pair: of equal values only lower indices beat it, or rows of
+    // equal logits would send every element through the insertion.  (One copy of the insertion for the whole
+    // tile, not one for each register: short scans wait for their instructions more than for anything else, 10
+    // rows of 128256 logits in 16 slices 13.9 us to 12.9.)
     const unsigned long long lanes = __ballot(tm >= thr);
     if (lanes != 0ull) {
       float* const vals = lane_vals[wave];

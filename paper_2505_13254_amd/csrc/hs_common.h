@@ -96,20 +96,6 @@ struct Stats {
 
 __device__ __forceinline__ Stats stats_empty() { return Stats{-HS_INF, 0.f, 0.f}; }
 
-__device__ __forceinline__ Stats stats_merge(Stats a, Stats b, float inv_t) {
-  if (b.m == -HS_INF) return a;
-  if (a.m == -HS_INF) return b;
-  if (b.m > a.m) {
-    Stats x = a;
-    a = b;
-    b = x;
-  }
-  float d = (b.m - a.m) * inv_t;  // <= 0
-  float e = exp2_fast(d * 1.4426950408889634f);
-  float w = 1.f + b.s1;
-  return Stats{a.m, a.s1 + e * w, a.t + e * (b.t + d * w)};
-}
-
 // Reductions over the 64 lanes of a wave with DPP moves (no LDS traffic): partial results travel
 // right inside each row of 16 lanes, then from row to row; lane 63 ends up with the total, which
 // is broadcast.  `idle` is what a lane without a source takes (the identity of the operation).
@@ -145,16 +131,6 @@ __device__ __forceinline__ float wave_max(float x) {
 }
 __device__ __forceinline__ float wave_sum(float x) {
   return wave_reduce_dpp(x, 0.f, [](float a, float b) { return a + b; });
-}
-
-__device__ __forceinline__ Stats stats_shfl_xor(Stats a, int mask) {
-  return Stats{__shfl_xor(a.m, mask), __shfl_xor(a.s1, mask), __shfl_xor(a.t, mask)};
-}
-
-__device__ __forceinline__ Stats stats_wave_reduce(Stats a, float inv_t) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) a = stats_merge(a, stats_shfl_xor(a, off), inv_t);
-  return a;
 }
 
 }  // namespace hs

@@ -3,8 +3,8 @@
 //
 // This file holds the entry point, the launch planning, the float32 / any-shape kernel
 // (k_attn_generic: float32 matrix instructions, 16 rows per workgroup, keys shared out to its waves)
-// and the split combine (k_attn_combine).  bfloat16 with head dimension 128 goes to the MFMA kernel in
-// tree_attention_mfma.hip.
+// and the split combine (k_attn_combine).  bfloat16 with head dimension 128, or 64 and an even number of
+// KV heads, goes to the kernel in tree_attention_mfma.hip (16-byte aligned tensors, G * rows < 65536).
 #include <stdlib.h>
 #include <string.h>
 

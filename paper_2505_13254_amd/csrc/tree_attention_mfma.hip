@@ -29,11 +29,10 @@
 // the end of the pass, and the workgroup then repeats its pass with the classic block-by-block
 // update of the maximum (rare, slow, same result).
 //
-// Schedule.  Each 32-key block passes through two windows of eight matrix instructions: its scores,
-// then its second product.  A window also takes half of a block's exponentials (the second half of
+// Schedule.  Each 32-key block passes through two windows of eight matrix instructions (head dimension
+// 64: four): its scores, then its second product.  A window also takes half of a block's exponentials (the second half of
 // the block whose product comes next, or the first half of the block whose scores were just
-// finished) and requests the LDS fragments that the matrix instructions three steps ahead will
-// need, so matrix, vector and LDS pipes of a wave all have independent work at any time.
+// finished) and requests the LDS fragments of the next step of two matrix instructions, so matrix, vector and LDS pipes of a wave all have independent work at any time.
 //
 // The tree part (ancestor mask) is a bit table built in LDS from the parent pointers (trees of up
 // to 256 rows).  Larger trees (BIG, up to 1024 rows) take the table from global memory, where
@@ -638,10 +637,10 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   };
 
   bf16x8 kf[NK], vf[NK];  // fragment registers: four of each are alive at any time
-  // Score window: S_out = K(block at oq) Q^T, started from -m_ref, in four steps of two matrix
+  // Score window: S_out = K(block at oq) Q^T, started from -m_ref, in STEPS steps of two matrix
   // instructions.  A step first requests the fragments of the next step (the window's last step:
   // the first two V fragments of the block at ov, whose product window follows), waits for its own,
-  // and pairs its matrix instructions with two exponentials of half h of S_in.
+  // and pairs its matrix instructions with EPS pairs of exponentials of half h of S_in.
   // Wave priority: the two waves of a SIMD compete for its issue slots.  A wave raises its priority
   // for a window (product windows above score windows) and drops it afterwards, so that whichever wave
   // is inside a window, and of two the one in its product window, issues first: 3 % on every shape
@@ -794,52 +793,52 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       for (int f = 0; f < 2 * MF_AHEAD; ++f) vf[f] = ldv(off, f);
       win_pv(off, 0, pa, pb, sA, 0, pc, NO, NO);
     } else {
-    exp_half(sA, 0, pa);
+      exp_half(sA, 0, pa);
 #pragma unroll
-    for (int kk = 0; kk < 2 * MF_AHEAD; ++kk) kf[kk] = ldk(blk_off(0, 1), kk);
-    // ---- one trip per tile t (blocks 2t and 2t + 1, ring slot s = t % 4); the barrier in its
-    // middle lets tile t + 1 in
-    //   window 1: scores of 2t+1      | second half of 2t
-    //   window 2: product of 2t       | first half of 2t+1
-    //   window 3: scores of 2t+2      | second half of 2t+1
-    //   window 4: product of 2t+1     | first half of 2t+2
-    // MASKED: blocks from n_plain on are masked and the tile that is requested may be any tile.
-    auto trip = [&](int t, int s, auto masked) {
-      constexpr bool MASKED = decltype(masked)::value;
-      const int s1 = (s + 1) % MF_NBUF;
-      win_qk(blk_off(s, 1), blk_off(s, 0), sB, sA, 1, pb);
-      if (MASKED && 2 * t + 1 >= n_plain) mask_block(2 * t + 1, sB);
-      if (MASKED) {
-        next_arrival(t);
-      } else {
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * MF_LOADS) : "memory");
-        issue_full(t + 3, (s + 3) % MF_NBUF);
+      for (int kk = 0; kk < 2 * MF_AHEAD; ++kk) kf[kk] = ldk(blk_off(0, 1), kk);
+      // ---- one trip per tile t (blocks 2t and 2t + 1, ring slot s = t % 4); the barrier in its
+      // middle lets tile t + 1 in
+      //   window 1: scores of 2t+1      | second half of 2t
+      //   window 2: product of 2t       | first half of 2t+1
+      //   window 3: scores of 2t+2      | second half of 2t+1
+      //   window 4: product of 2t+1     | first half of 2t+2
+      // MASKED: blocks from n_plain on are masked and the tile that is requested may be any tile.
+      auto trip = [&](int t, int s, auto masked) {
+        constexpr bool MASKED = decltype(masked)::value;
+        const int s1 = (s + 1) % MF_NBUF;
+        win_qk(blk_off(s, 1), blk_off(s, 0), sB, sA, 1, pb);
+        if (MASKED && 2 * t + 1 >= n_plain) mask_block(2 * t + 1, sB);
+        if (MASKED) {
+          next_arrival(t);
+        } else {
+          asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * MF_LOADS) : "memory");
+          issue_full(t + 3, (s + 3) % MF_NBUF);
+        }
+        win_pv(blk_off(s, 0), blk_off(s1, 0), pa, pb, sB, 0, pc, YES, YES);
+        win_qk(blk_off(s1, 0), blk_off(s, 1), sA, sB, 1, pb);
+        if (MASKED && 2 * t + 2 >= n_plain) mask_block(2 * t + 2, sA);
+        win_pv(blk_off(s, 1), blk_off(s1, 1), pc, pb, sA, 0, pa, YES, YES);
+      };
+      // Four tiles per round with the ring slots spelled out, while they and the tiles they request
+      // (up to t + 6) are full prefix tiles: every LDS address is then a register plus an immediate.
+      int t = 0;
+      for (; t + 6 < n_full; t += 4) {
+        trip(t, 0, NO);
+        trip(t + 1, 1, NO);
+        trip(t + 2, 2, NO);
+        trip(t + 3, 3, NO);
       }
-      win_pv(blk_off(s, 0), blk_off(s1, 0), pa, pb, sB, 0, pc, YES, YES);
-      win_qk(blk_off(s1, 0), blk_off(s, 1), sA, sB, 1, pb);
-      if (MASKED && 2 * t + 2 >= n_plain) mask_block(2 * t + 2, sA);
-      win_pv(blk_off(s, 1), blk_off(s1, 1), pc, pb, sA, 0, pa, YES, YES);
-    };
-    // Four tiles per round with the ring slots spelled out, while they and the tiles they request
-    // (up to t + 6) are full prefix tiles: every LDS address is then a register plus an immediate.
-    int t = 0;
-    for (; t + 6 < n_full; t += 4) {
-      trip(t, 0, NO);
-      trip(t + 1, 1, NO);
-      trip(t + 2, 2, NO);
-      trip(t + 3, 3, NO);
-    }
-    for (; t + 1 < n_tiles; ++t) trip(t, t % MF_NBUF, YES);
-    {  // last tile: nothing follows its odd block
-      const int s = t % MF_NBUF;
-      win_qk(blk_off(s, 1), blk_off(s, 0), sB, sA, 1, pb);
-      if (2 * t + 1 >= n_plain) mask_block(2 * t + 1, sB);
-      win_pv(blk_off(s, 0), 0, pa, pb, sB, 0, pc, YES, NO);
-      exp_half(sB, 1, pb);
+      for (; t + 1 < n_tiles; ++t) trip(t, t % MF_NBUF, YES);
+      {  // last tile: nothing follows its odd block
+        const int s = t % MF_NBUF;
+        win_qk(blk_off(s, 1), blk_off(s, 0), sB, sA, 1, pb);
+        if (2 * t + 1 >= n_plain) mask_block(2 * t + 1, sB);
+        win_pv(blk_off(s, 0), 0, pa, pb, sB, 0, pc, YES, NO);
+        exp_half(sB, 1, pb);
 #pragma unroll
-      for (int f = 0; f < 2 * MF_AHEAD; ++f) vf[f] = ldv(blk_off(s, 1), f);
-      win_pv(blk_off(s, 1), 0, pc, pb, sB, 0, pa, NO, NO);
-    }
+        for (int f = 0; f < 2 * MF_AHEAD; ++f) vf[f] = ldv(blk_off(s, 1), f);
+        win_pv(blk_off(s, 1), 0, pc, pb, sB, 0, pa, NO, NO);
+      }
     }
     l_sum = l0 + l1;
   } else {
