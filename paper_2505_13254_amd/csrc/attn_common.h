@@ -107,10 +107,34 @@ struct AttnArgs {
   int n_tbl;       // > 0: work-list launch (1-D grid over the items of tbl[0 .. n_tbl)); 0: grid.y = sequence
   int n_items;
   int narrow;      // work-list launches: 1 = two workgroups to an item, one for each 128 of its up to 256 rows
+  int share;       // matrix-core kernel: equal row groups of five or six blocks share what is behind the fourth, 1 = of
+                   // sequences with several groups, 2 = of all
   int cmb_row0;    // first tree row that the merge of the splits looks at
   alignas(16) SeqEntry tbl[ATTN_TBL];  // (lanes fetch their entry with 16-byte loads)
 };
 static_assert(offsetof(AttnArgs, tbl) % 16 == 0, "16-byte loads of the table entries");
+
+// Row groups of the matrix-core kernel: a KV head's rows, in blocks of 32, are spread over as many workgroups of up to
+// eight blocks (a block to a wave) as they need.  Where that leaves room for groups of at most six blocks each, they get
+// equal shares; otherwise full groups and a rest.  Groups of equal size pass over their keys at one pace and find
+// them in L2, and five or six blocks need not take as long as eight (`share` in AttnArgs).  (40 layers of the 8B layout in
+// one call, 73 rows on 2048 tokens, ten blocks as 5 + 5: whole step 197 -> 180 us, as 8 + 2 before; of the 70B layout, 71
+// rows, 18 blocks as 6 + 6 + 6: 852 -> 778.  No gain from unequal ones: 13 blocks as 8 + 5 with the five shared 2 %
+// slower, 25 as 8 + 6 + 6 + 5 1 %.)
+__host__ __device__ __forceinline__ int row_groups(int n_blk) { return (n_blk + 7) >> 3; }
+__host__ __device__ __forceinline__ bool equal_row_groups(int n_blk) { return n_blk <= 6 * row_groups(n_blk); }
+// First block and number of blocks of group rg (<= 0 when there is no such group).
+__host__ __device__ __forceinline__ void row_group(int n_blk, int rg, int* first, int* count) {
+  const int n_rg = row_groups(n_blk);
+  if (n_rg > 3 || !equal_row_groups(n_blk)) {  // (four groups hold more than 24 blocks)
+    *first = 8 * rg;
+    *count = n_blk - 8 * rg < 8 ? n_blk - 8 * rg : 8;
+    return;
+  }
+  const int each = n_rg == 1 ? n_blk : n_rg == 2 ? n_blk >> 1 : 5, more = n_blk - each * n_rg;  // (three: 17 or 18 blocks)
+  *first = rg * each + (rg < more ? rg : more);
+  *count = rg >= n_rg ? 0 : each + (rg < more ? 1 : 0);
+}
 
 // Prefix length of sequence s (plain launches read it on the device).
 __device__ __forceinline__ int64_t prefix_len_of(const AttnArgs& a, int s) {

@@ -421,6 +421,14 @@ static inline float plan_own_cu_us(bool narrow, bool half, int waves, int tiles,
   if (!narrow && waves > 4) tile = std::max(tile, half ? 1.35f : 1.5f);
   return item + (float)tiles * tile;
 }
+// Waves share row blocks (AttnArgs::share) in launches of more than one round of the compute units.  Sequences of a
+// single row group gain 3 to 4 % in launches that follow one another, but a launch that follows other kernels, as in a
+// step, loses about 10 us in its first round and earns them back in the fifth or so: 46 rows on 2048 tokens, 8 KV heads,
+// whole steps of 40 / 100 / 140 / 200 layers 133 / 253 / 314 / 428 us, shared 145 / 267 / 321 / 421; of 129 rows on 4096 tokens,
+// 40 heads, 20 and 40 layers 370 and 703, shared 362 and 685.  With several groups there is no such loss: 73 rows, 20 and 40
+// layers 138 and 197, now 127 and 180.  Nor in ragged batches, whose workgroups drift apart (16 sequences, whole step 400 us,
+// 395 with the sharing of several groups alone, 381 with both).
+constexpr int PLAN_SHARE_ITEMS = 5 * PLAN_CUS;
 constexpr int PLAN_MIN_SPLIT_TOKENS = PLAN_MIN_SPLIT_TILES * 64;
 static inline float plan_tile_us(int waves) { return 1.25f + 0.04f * (float)waves; }
 
@@ -481,14 +489,16 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     const int64_t L = hlens != nullptr ? hlens[s] : hpo[s + 1] - hpo[s];
     if (M <= 0) continue;
     if (n == ATTN_TBL || L >= (int64_t)1 << 30) return false;
-    const int blocks = (a.G * M + 31) / 32;  // 32-row wave blocks
+    // 32-row wave blocks (D = 64: counted head by head)
+    const int blocks = a.half ? 2 * ((a.G / 2 * M + 31) / 32) : (a.G * M + 31) / 32;
     Seq q;
     q.s = s;
     q.M = M;
     q.tiles = (int)((L + 63) / 64);
-    q.rg = (blocks + 7) / 8;
-    q.waves0 = blocks < 8 ? blocks : 8;
-    q.waves_last = blocks - 8 * (q.rg - 1);
+    q.rg = row_groups(blocks);
+    int first;
+    row_group(blocks, 0, &first, &q.waves0);
+    row_group(blocks, q.rg - 1, &first, &q.waves_last);
     q.ttiles = (M + 63) / 64;
     seqs[n++] = q;
   }
@@ -663,6 +673,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   a.n_tbl = n;
   a.n_items = (int)first;
   a.narrow = best.narrow;
+  a.share = first <= PLAN_CUS ? 0 : !equal || first > PLAN_SHARE_ITEMS ? 2 : 1;
   a.sp_max = sp_max;
   return true;
 }
@@ -674,7 +685,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
 struct PlanMemo {
   std::vector<int64_t> key;  // everything the plan is a function of; empty: unused slot
   bool ok;
-  int n_tbl, n_items, narrow, sp_max, cmb_row0;
+  int n_tbl, n_items, narrow, share, sp_max, cmb_row0;
   SeqEntry tbl[ATTN_TBL];
 };
 constexpr int PLAN_MEMO_SLOTS = 4;
@@ -706,6 +717,7 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
         a.n_tbl = m.n_tbl;
         a.n_items = m.n_items;
         a.narrow = m.narrow;
+        a.share = m.share;
         a.sp_max = m.sp_max;
         a.cmb_row0 = m.cmb_row0;
         memcpy(a.tbl, m.tbl, sizeof(SeqEntry) * (size_t)m.n_tbl);
@@ -719,6 +731,7 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
     m.n_tbl = a.n_tbl;
     m.n_items = a.n_items;
     m.narrow = a.narrow;
+    m.share = a.share;
     m.sp_max = a.sp_max;
     m.cmb_row0 = a.cmb_row0;
     memcpy(m.tbl, a.tbl, sizeof(SeqEntry) * (size_t)a.n_tbl);
@@ -865,7 +878,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   a.block_table = block_table; a.max_blocks = max_blocks;
   a.B = B; a.Hq = Hq; a.Hkv = mfma ? kv_units : Hkv; a.G = mfma ? g_unit : Hq / Hkv; a.half = mfma && pairs ? 1 : 0; a.scale = scale;
   a.o = o; a.lse = lse; a.part = static_cast<float*>(workspace);
-  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.cmb_row0 = 0; a.anc_tiles = nullptr;
+  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.share = 0; a.cmb_row0 = 0; a.anc_tiles = nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // the workspace query bounds the splits of a sequence the same way
   const int64_t sp_bound = total_prefix / PLAN_MIN_SPLIT_TOKENS + 1;
@@ -875,6 +888,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   if (!(mfma && plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, false))) {
     a.n_tbl = 0;
     a.cmb_row0 = 0;
+    a.share = (int64_t)B * a.Hkv > PLAN_SHARE_ITEMS ? 2 : 1;  // (more than 96 sequences, or not for the matrix-core kernel)
     plan = plan_attention(host_node_offsets, host_prefix_offsets, host_prefix_lens, B, Hq, a.Hkv, mfma ? 0 : GEN_ROWS);
     while (plan.sp_max > sp_cap) {
       plan.split_len *= 2;

@@ -219,12 +219,12 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   float* const h_lse = a.lse;
   float* const h_part = a.part;
   const float h_scale = a.scale;
-  const int h_sp_max = a.sp_max, h_n_tbl = a.n_tbl, h_tree_shared = a.tree_shared, h_narrow = a.narrow;
+  const int h_sp_max = a.sp_max, h_n_tbl = a.n_tbl, h_tree_shared = a.tree_shared, h_narrow = a.narrow, h_share = a.share;
   const int G = a.G, Hkv = a.Hkv, Hq = a.Hq;
   asm volatile("" : "+v"(t0_lo), "+v"(t0_hi));  // (keeps the request here instead of inside the branch that uses it)
   asm volatile("" ::"s"(h_q), "s"(h_k_prefix), "s"(h_v_prefix), "s"(h_k_tree), "s"(h_v_tree), "s"(h_parent), "s"(h_o),
                "s"(h_lse), "s"(h_part), "s"(h_scale), "s"(h_sp_max), "s"(h_n_tbl), "s"(G), "s"(Hkv), "s"(Hq),
-               "s"(n_rg_max), "s"(h_tree_shared), "s"(h_narrow));
+               "s"(n_rg_max), "s"(h_tree_shared), "s"(h_narrow), "s"(h_share));
   int n0, M, g, rg, sp, n_sp, tiles_per_split;
   int64_t p0, L;
   if (h_n_tbl > 0) {
@@ -291,9 +291,13 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const int Rh = Gh * M;                  // rows of a KV head
   const int nbh = (Rh + 31) >> 5;
   const int n_blk = HALF ? 2 * nbh : nbh;
-  const int blk_max = (MF_ROWS / 32) >> h_narrow;  // (eight, narrow launches: four)
-  const int blk0 = rg * blk_max;
-  const int blk_n = n_blk - blk0 < blk_max ? n_blk - blk0 : blk_max;  // blocks of this group
+  int blk0, blk_n;  // first block of this group, and how many
+  if (h_narrow != 0) {
+    blk0 = rg * 4;
+    blk_n = n_blk - blk0 < 4 ? n_blk - blk0 : 4;
+  } else {
+    row_group(n_blk, rg, &blk0, &blk_n);
+  }
   if (blk_n <= 0) return;  // (narrow: an item of at most 128 rows needs one of its two workgroups)
   // Narrow launches have compute units to spare and are bound by each workgroup's own pace: the
   // four blocks' waves alone, one to a SIMD, would have nothing to hide their chains of dependent
@@ -304,9 +308,16 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // run ahead of the other row groups of their keys, out of reach of the L2 copies: 0.8 % slower.)
   const bool ksplit = h_narrow != 0;
   const int pair_shift = !ksplit ? 3 : blk_n <= 1 ? 0 : blk_n == 2 ? 1 : 2;
-  const int my_blk = blk0 + (wave & ((1 << pair_shift) - 1));
-  const int kpar = wave >> pair_shift;    // (without sharing: 0)
-  const bool wave_active = my_blk < blk0 + blk_n && kpar < 2;
+  // Groups of five or six blocks, all groups being so: the first four waves, one to a SIMD, take a block each, and
+  // the other four share what is left: two waves to a block, as above, or all four of them to one, each with
+  // every fourth 32 keys.  `ways` is the number of waves that share this wave's block, kpar its share.  (With a wave
+  // to a block one or two SIMDs have two waves' work and the others one's: 129 rows on 4096 tokens, 40 layers and
+  // heads, 703 -> 685 us the whole step; ten blocks in two groups (row_group) 185 -> 180.  When: see a.share.)
+  const bool shared_tail = (blk_n == 5 || blk_n == 6) && equal_row_groups(n_blk) && h_share > (n_blk <= 6 ? 1 : 0);
+  const int ways = ksplit ? 2 : !shared_tail || wave < 4 ? 1 : blk_n == 5 ? 4 : 2;
+  const int my_blk = blk0 + (shared_tail && wave >= 4 ? 4 + (blk_n == 6 ? wave & 1 : 0) : wave & ((1 << pair_shift) - 1));
+  const int kpar = shared_tail ? (wave < 4 ? 0 : blk_n == 6 ? (wave - 4) >> 1 : wave - 4) : wave >> pair_shift;  // (without sharing: 0)
+  const bool wave_active = my_blk < blk0 + blk_n && kpar < ways;
   const int hb = HALF && my_blk >= nbh ? 1 : 0;          // head of the pair
   const int row_base = (my_blk - hb * nbh) * 32;          // of the head's rows
 
@@ -454,14 +465,12 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     asm volatile("global_load_dword %0, %1, off" : "=v"(my_parent) : "v"(src) : "memory");
   }
   uintx4 qraw[NK];
-  int tree_row;
   bool row_real;
   const int head0 = g * G + hb * Gh;  // first query head of this wave's KV head
   {
     const int r = row_base + col;
     const int rc = r < Rh ? r : Rh - 1;
     const int i = div_G(rc), gi = rc - i * Gh;
-    tree_row = i;
     row_real = r < Rh;
     const char* qrow = static_cast<const char*>(h_q) + ((int64_t)(n0 + i) * Hq + head0 + gi) * Q_ROW_BYTES + half * 16;
 #pragma unroll
@@ -567,13 +576,22 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
 
   // ---- masks of a block's scores: tree keys off the row's root path, keys past the end of the
   // split.  Only the blocks from n_plain on need it (the partial prefix tail and the tree part).
+  // (the lane's tree row is found again where a tree tile is masked, which the empty statements keep the compiler
+  // from doing ahead of the loops: registers for it would be spilled, and read back behind a wait for the tiles)
+  auto tree_row = [&]() {
+    unsigned l = ~0u;
+    int g = Gh;
+    asm volatile("" : "+s"(l), "+s"(g));
+    const int r = row_base + (int)(__builtin_amdgcn_mbcnt_hi(l, __builtin_amdgcn_mbcnt_lo(l, 0)) & 31);
+    return (int)(((float)(r < Rh ? r : Rh - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)g));  // (as div_G)
+  };
   auto mask_block = [&](int blk, floatx16& S) {
     const int t = blk >> 1;
     if (t >= n_ptiles) {
       const int bbase = (t - n_ptiles) * MF_TILE + (blk & 1) * 32;
       unsigned word;
       if constexpr (BIG) word = bbase < M ? anc[(t % MF_NBUF) * MF_ANC_SLICE + (wave * 32 + col) * 2 + (blk & 1)] : 0u;
-      else word = bbase < M ? anc[tree_row * 8 + (bbase >> 5)] : 0u;
+      else word = bbase < M ? anc[tree_row() * 8 + (bbase >> 5)] : 0u;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int bit = 8 * (v >> 2) + 4 * half + (v & 3);
@@ -745,7 +763,29 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       for (int v = 0; v < 16; ++v) sA[v] -= mx;
       set_reference(mx);
     }
-    if (ksplit) {
+    if (ways == 4) {
+      // ---- four waves to a row block: this one takes 32-key block kpar of every two tiles, in one go: it
+      // is busy for a quarter of what its SIMD's other wave has to do, so nothing is gained by overlapping its
+      // steps.  All four start from the first block's maximum.
+      const int par = kpar & 1, odd_tile = kpar >> 1;
+      for (int t = 0; t < n_tiles; ++t) {
+        if (t + 1 < n_tiles) next_arrival(t);
+        if ((t & 1) != odd_tile) continue;
+        const int off = blk_off(t % MF_NBUF, par);
+        if (t > 0 || par != 0) {
+#pragma unroll
+          for (int kk = 0; kk < NK; ++kk)
+            sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ldk(off, kk), qf[kk], kk == 0 ? negm : sA, 0, 0, 0);
+          if (2 * t + par >= n_plain) mask_block(2 * t + par, sA);
+        }
+        exp_half(sA, 0, pa);
+        exp_half(sA, 1, pb);
+        const bf16x8 b0 = __builtin_bit_cast(bf16x8, pa), b1 = __builtin_bit_cast(bf16x8, pb);
+#pragma unroll
+        for (int f = 0; f < NK; ++f)
+          acc[f % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ldv(off, f), f < NT ? b0 : b1, acc[f % NT], 0, 0, 0);
+      }
+    } else if (ways == 2) {
       // ---- two waves to a row block: this one takes 32-key block `kpar` of every tile.  Both start from
       // the first block's maximum, so their sums need no rescaling when they meet.
       //   window 1: scores of tile t+1  | second half of tile t
@@ -938,6 +978,52 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     // (every wave has its sums before the staging below reuses the ring)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   }
+  if (shared_tail) {
+    // ---- the waves that share a row block leave their sums in the (now free) V ring, 16 bytes to a lane, and each
+    // adds up its part of the columns, wave by wave in rising order.
+    float* const den = reinterpret_cast<float*>(&anc[0]);  // [wave][denominators, reference maxima]
+    const bool sharing = wave >= 4;
+    if (sharing) {
+      float* const ex = reinterpret_cast<float*>(lds_v[wave - 4]);
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          float4 f = {acc[tt][4 * b], acc[tt][4 * b + 1], acc[tt][4 * b + 2], acc[tt][4 * b + 3]};
+          *reinterpret_cast<float4*>(ex + (tt * 4 + b) * 256 + lane * 4) = f;
+        }
+      den[wave * 128 + lane] = l_tot;
+      den[wave * 128 + 64 + lane] = m_ref;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (sharing) {
+      const int step = ways == 4 ? 1 : 2;              // from one of the sharing waves to the next
+      const int first = ways == 4 ? 0 : wave & 1;       // the first of them, counted from wave 4
+      const int keep = ways == 4 ? 1 : NT / 2;          // column blocks of this wave
+      const int tt0 = kpar * keep;
+      if (tt0 >= NT) return;  // (head dimension 64: two column blocks for four waves)
+      m_ref = den[(4 + first) * 128 + 64 + lane];  // (the exact path moves the first wave's only)
+      l_tot = 0.f;
+      for (int w = 0; w < ways; ++w) l_tot += den[(4 + first + w * step) * 128 + lane];
+#pragma unroll
+      for (int tt = 0; tt < NT / 2; ++tt) {
+        if (tt >= keep) break;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[tt][v] = 0.f;
+        for (int w = 0; w < ways; ++w) {
+          const float* from = reinterpret_cast<const float*>(lds_v[first + w * step]) + (tt0 + tt) * 1024;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const float4 f = *reinterpret_cast<const float4*>(from + b * 256 + lane * 4);
+            acc[tt][4 * b] += f.x;
+            acc[tt][4 * b + 1] += f.y;
+            acc[tt][4 * b + 2] += f.z;
+            acc[tt][4 * b + 3] += f.w;
+          }
+        }
+      }
+    }
+  }
   if (!wave_active) return;
 
   // `NB` column blocks (acc[0 .. NB)) of this wave's 32 rows, from column col0 of the head's row on
@@ -949,7 +1035,10 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       // block around in LDS (the tile ring is free: every wave has passed the last barrier),
       // so that a lane stores 16 contiguous bytes and a store instruction covers whole rows.
       constexpr int ST_ROW = 64 * NB + 16;  // padded row: the 8-byte writes of 16 rows spread over all banks
-      char* stage = wave < 4 ? lds_k[wave] : lds_v[wave - 4];
+      // (waves that share a block still read each other's sums in the V ring: they turn theirs around behind
+      // the first four waves' rows)
+      char* stage = shared_tail && wave >= 4 ? lds_k[wave - 4] + 32 * (64 * NT + 16) : wave < 4 ? lds_k[wave] : lds_v[wave - 4];
+      static_assert(32 * (64 * 4 + 16) + 32 * (64 * 2 + 16) <= MF_TILE_BYTES, "two waves' rows in a tile buffer");
       const float inv = 1.f / l_tot;
 #pragma unroll
       for (int tt = 0; tt < NB; ++tt)
@@ -1005,8 +1094,9 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       }
     }
   };
-  if (ksplit) write_out(std::integral_constant<int, NT / 2>{}, kpar * (16 * NT));
-  else write_out(std::integral_constant<int, NT>{}, 0);
+  if (ways == 1) write_out(std::integral_constant<int, NT>{}, 0);
+  else if (ways == 2 || NT == 2) write_out(std::integral_constant<int, NT / 2>{}, kpar * (16 * NT));
+  else write_out(std::integral_constant<int, 1>{}, kpar * 32);
 }
 
 // `ev_start` / `ev_stop` (may be NULL): HIP events attached to this dispatch; the runtime stamps them

@@ -63,6 +63,22 @@ def test_launches_that_leave_compute_units_to_spare(G, D, hq, hkv, M, L, variant
     _compare(G, _case(w, M, [_random_parents(rs, M, back=9)], [L], variant), "bf16", big_scores=variant != "unit")
 
 
+@pytest.mark.parametrize("variant", ["unit", "hot"])
+@pytest.mark.parametrize("D,hq,hkv,M,L,B", [
+    (128, 8, 8, 129, 300, 20), (128, 8, 8, 129, 31, 20), (128, 8, 8, 161, 65, 20), (128, 8, 8, 192, 640, 20),
+    (128, 32, 4, 65, 130, 17), (128, 16, 4, 150, 97, 18), (128, 8, 8, 129, 1500, 16), (128, 8, 8, 257, 100, 16),
+    (128, 8, 8, 129, 70, 100), (64, 16, 16, 65, 200, 20), (64, 16, 16, 129, 65, 18), (64, 32, 8, 37, 500, 40)])
+def test_row_blocks_shared_by_waves(G, D, hq, hkv, M, L, B, variant):
+    """Launches beyond 128 work items whose row groups hold five or six 32-row blocks: the blocks behind the fourth are
+    shared by four waves, or by two each, key block by key block.  One tile and many, an odd last tile, groups of
+    unequal size, one grid row to a sequence, trees beyond 256 rows, the exact second pass."""
+    from test_gpu_attention import _case, _compare, _random_parents
+    w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
+    rs = np.random.RandomState(M + L)
+    lens = [L] * B if B > 20 else [max(0, L - 16 * i) for i in range(B)]
+    _compare(G, _case(w, M, [_random_parents(rs, M, back=9) for _ in range(B)], lens, variant), "bf16", big_scores=variant != "unit")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("D,hq,hkv,M,L,offset", [
     (64, 3, 3, 1, 0, 0), (64, 3, 3, 16, 15, 0), (64, 6, 3, 17, 16, 1), (64, 3, 1, 33, 511, 0), (64, 3, 3, 5, 1040, 3),
