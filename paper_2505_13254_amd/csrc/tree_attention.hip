@@ -481,6 +481,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
                           int sp_cap, bool lean) {
   struct Seq {
     int s, M, tiles, rg, waves0, waves_last, ttiles;
+    float tile_us;  // of its largest group if that were full: what the entries are ordered by
   };
   Seq seqs[ATTN_TBL];
   int n = 0;
@@ -495,6 +496,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     q.s = s;
     q.M = M;
     q.tiles = (int)((L + 63) / 64);
+    q.tile_us = plan_tile_us(std::min(8, (a.G * M + 31) / 32));
     q.rg = row_groups(blocks);
     int first;
     row_group(blocks, 0, &first, &q.waves0);
@@ -537,7 +539,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       if (one_last < mn) mn = one_last;
       if (nsp > 1) rec_bytes += (double)q.M * a.Hq * nsp * ((a.half ? 64 : 128) + ATTN_REC_PAD) * 4 * 2;  // written, then read
       ord[i] = i;
-      seq_cost[i] = (float)per * plan_tile_us(q.waves0);
+      seq_cost[i] = (float)per * q.tile_us;
     }
     const float combine_us = rec_bytes > 0.0 ? 4.f + (float)(rec_bytes / 2.5e6) : 0.f;  // the combine launch, ~2.5 TB/s
     if (items <= PLAN_CUS && !lean) {  // every item has a compute unit of its own
@@ -645,7 +647,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       per_of[i] = (per_of[i] + best.cuts - 1) / best.cuts;
       nsp_of[i] = (q.tiles + per_of[i] - 1) / per_of[i];
     }
-    cost[i] = (float)per_of[i] * plan_tile_us(q.waves0);
+    cost[i] = (float)per_of[i] * q.tile_us;
     order[i] = i;
   }
   std::stable_sort(order, order + n, [&](int x, int y) { return cost[x] > cost[y]; });
