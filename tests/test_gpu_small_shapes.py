@@ -389,3 +389,40 @@ def test_argmax_slices_of_a_greedy_walk(G, R, V, slices):
     assert bool((guard[own:] == 77).all())
     with pytest.raises(hs.HsError):
         hs.hs_verify_accept(*args, ws=guard[:own - 256])
+
+
+@pytest.mark.parametrize("n,depth", [(17, 15), (17, 16), (18, 17), (512, 16), (513, 17), (1024, 16), (1025, 15), (4096, 16), (4097, 16), (8192, 16), (8193, 17)])
+def test_trees_around_the_limits_of_a_workgroup(G, n, depth):
+    """Trees as deep as a walk in registers and one level deeper, with as many rows as a workgroup has threads or LDS has
+    room for, and one more; many equal values.  One tree, and three in a batch."""
+    from oracle import adaptive_control, tree_prune
+    import paper_2505_13254_amd as hs
+    from test_gpu_entropy_prune_accept import _prune_equal
+    rs = np.random.RandomState(n + depth)
+    def tree(m):
+        d, par = [0], [-1]
+        for i in range(1, m):                                          # a chain first, then anywhere above the last level
+            p = i - 1 if i <= depth else int(rs.randint(0, i))
+            while d[p] >= depth:
+                p = par[p]
+            par.append(p)
+            d.append(d[p] + 1)
+        lc = np.round(-rs.exponential(0.4, size=m) * 4).astype(np.float32) / 4
+        lc[0] = 0
+        return np.asarray(par, np.int32), lc
+    for sizes in ([n], [n, 5, max(1, n // 3)]):
+        ts = [tree(m) for m in sizes]
+        off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        par, lc = np.concatenate([t[0] for t in ts]), np.concatenate([t[1] for t in ts])
+        B = len(sizes)
+        for budget in (0, max(1, n // 2)):
+            pin = dict(parent=par, logc=lc, node_offsets=off, d_max=np.full(B, depth - (budget > 0), np.int32),
+                       theta=np.full(B, -6.0, np.float32), max_nodes=np.full(B, budget, np.int32))
+            _prune_equal(G.run_prune(pin), tree_prune(par, lc, off, pin["d_max"], pin["theta"], pin["max_nodes"]))
+        ent = rs.uniform(0.0, 0.4, size=len(par)).astype(np.float32)
+        for mode in (0, 1):
+            want = adaptive_control(par, lc, ent, off, [1.0, 2.0, 3.0], [0.5, 0.8], 3, 6, 60, mode)
+            got = hs.hs_adaptive_control(G.dev(par), G.dev(lc), G.dev(ent), G.dev(off), None, [1.0, 2.0, 3.0], [0.5, 0.8], 3, 6, 60, mode)
+            for k in ("pstar", "bin", "d_prime", "n_prime"):
+                assert np.array_equal(G.host(got[k]), want[k]), (k, mode)
+            assert np.allclose(G.host(got["phi"]), want["phi"], rtol=1e-5, atol=1e-8)
