@@ -3,19 +3,19 @@
 // Section 4.2: entropy bins; Section 4.3: depth extension d' and node budget N').
 //
 // Nothing to stream: a few hundred nodes per sequence, one workgroup per sequence, no workspace.
-// The parent pointers are staged in LDS (trees of up to 8192 rows; larger ones are walked in global
-// memory).  Every node finds its depth by walking to the root; the nodes of the deepest level form their
-// value root-first (the float32 add per node of the reranking step, so the choice of P* is taken
-// on the same numbers as the pruning that follows); one 64-bit (value, row) key per node and a
-// workgroup maximum pick P*; one thread then sums the path's entropies root-first in float32 and
-// looks up the bin.
+// The tree is staged in LDS (up to 8192 rows; larger ones are walked in global memory).  A walk from each node
+// to the root gives its depth and value (the float32 add per node of the reranking step, so the choice of P* is taken on
+// the same numbers as the pruning that follows); one 64-bit (depth, value, row) key per node and a workgroup
+// maximum pick P*; the first wave then sums the path's entropies root-first in float32 and looks up the bin.
+// What bounds it is the chain of trips to memory and of barriers.  (Two walks from every node for
+// the depths, the deepest nodes' values and the path's entropies from global memory: 511 rows 7.4 us, now 4.3.)
 #include <limits.h>
 
-#include "hs_common.h"
+#include "tree_settle.h"
 
 namespace hs {
 
-constexpr int CTL_THREADS = 256;
+constexpr int CTL_THREADS = 512;
 constexpr int CTL_MAX_BINS = 64;
 constexpr int CTL_MAX_LOW = 8;
 constexpr int CTL_LDS_NODES = 8192;
@@ -51,9 +51,7 @@ __host__ __device__ inline void bin_policy(int b, int n_low, int alpha, int d_ba
 
 // (value, row) as one key: larger key = larger value, then lower row; never 0 for a real node.
 __device__ __forceinline__ unsigned long long control_key(float v, int i) {
-  unsigned u = __builtin_bit_cast(unsigned, v);
-  u ^= (u >> 31) ? 0xffffffffu : 0x80000000u;  // monotone map of float order onto unsigned order
-  return ((unsigned long long)u << 32) | (unsigned)(0x7fffffff - i);
+  return ((unsigned long long)order_bits(v) << 32) | (unsigned)(0x7fffffff - i);
 }
 
 // The ancestor of node i that is `up` levels above it.
@@ -63,57 +61,20 @@ __device__ __forceinline__ int ancestor(IP par, int i, int up) {
   return i;
 }
 
-// The decision for one sequence; `par` points to LDS or to global memory.
+// The workgroup's largest key, in every thread (red_k: 0 before a barrier).
+__device__ __forceinline__ unsigned long long best_key(unsigned long long best, unsigned long long* red_k) {
+  best = wave_max_u64(best);
+  if ((threadIdx.x & 63) == 0) atomicMax(red_k, best);
+  __syncthreads();
+  return *red_k;
+}
+
+// The decision, given P* = p at depth D (first wave): Eq. 1 along the path to P*, i.e. over the rows of its strict
+// ancestors, root first.  The lanes fetch 64 path entries at a time side by side (one round trip instead of one
+// per level); the float32 sum still takes them one by one in path order.
 template <typename IP>
-__device__ __forceinline__ void control_sequence(const ControlArgs& a, int s, int n, IP par,
-                                                 const float* __restrict__ lc, const float* __restrict__ ent,
-                                                 int* red_i, unsigned long long* red_k) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-  // deepest level
-  int my_max = 0;
-  for (int i = tid; i < n; i += CTL_THREADS) {
-    int d = 0;
-    for (int j = par[i]; j >= 0; j = par[j]) ++d;
-    my_max = max(my_max, d);
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) my_max = max(my_max, __shfl_xor(my_max, off));
-  if (lane == 0) red_i[wave] = my_max;
-  __syncthreads();
-  int D = red_i[0];
-  for (int w = 1; w < CTL_THREADS / 64; ++w) D = max(D, red_i[w]);
-
-  // best node of that level
-  unsigned long long best = 0ull;
-  for (int i = tid; i < n; i += CTL_THREADS) {
-    int d = 0;
-    for (int j = par[i]; j >= 0; j = par[j]) ++d;
-    if (d != D) continue;
-    float v;
-    if (a.mode == 0) {
-      v = 0.f;  // value of the root; then one float32 add per level, root first
-      for (int t = 1; t <= D; ++t) v = v + fminf(lc[ancestor(par, i, D - t)], 0.f);
-    } else {
-      v = i == 0 ? 0.f : fminf(lc[i], 0.f);
-    }
-    const unsigned long long k = control_key(v, i);
-    best = k > best ? k : best;
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const unsigned long long other = __shfl_xor(best, off);
-    best = other > best ? other : best;
-  }
-  if (lane == 0) red_k[wave] = best;
-  __syncthreads();
-  if (tid >= 64) return;  // the first wave finishes (no barrier from here on)
-  for (int w = 1; w < CTL_THREADS / 64; ++w) best = red_k[w] > best ? red_k[w] : best;
-  const int p = 0x7fffffff - (int)(unsigned)(best & 0xffffffffull);
-
-  // Eq. 1 along the path to P*: the rows of its strict ancestors, root first.  The lanes fetch 64
-  // path entries at a time side by side (one round trip instead of one per level); the float32 sum
-  // still takes them one by one in path order.
+__device__ __forceinline__ void decide(const ControlArgs& a, int s, int p, int D, IP par, const float* __restrict__ ent) {
+  const int lane = threadIdx.x;
   float acc = 0.f;
   for (int t0 = 0; t0 < D; t0 += 64) {
     const int t = t0 + lane;
@@ -121,9 +82,9 @@ __device__ __forceinline__ void control_sequence(const ControlArgs& a, int s, in
     const int m = D - t0 < 64 ? D - t0 : 64;
     for (int l = 0; l < m; ++l) acc = acc + __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, e), l));
   }
+  // (the boundaries are the lanes': one to each)
+  const int b = __popcll(__ballot(lane < a.n_edges && acc >= a.edges[lane < a.n_edges ? lane : 0]));
   if (lane != 0) return;
-  int b = 0;
-  for (int e = 0; e < a.n_edges; ++e) b += acc >= a.edges[e] ? 1 : 0;
   int dp, np_;
   bin_policy(b, a.n_low, a.alpha, a.d_base, a.n_default, a.gamma, &dp, &np_);
   a.phi[s] = acc;
@@ -133,10 +94,49 @@ __device__ __forceinline__ void control_sequence(const ControlArgs& a, int s, in
   a.n_prime[s] = np_;
 }
 
+// Trees that do not fit LDS.
+__device__ __forceinline__ void control_large(const ControlArgs& a, int s, int o, int n, unsigned long long* red_k) {
+  __shared__ int deepest;
+  const int tid = threadIdx.x;
+  const int* par = a.parent + o;
+  const float* lc = a.logc + o;
+  auto depth_of = [&](int i) {
+    int d = 0;
+    for (int j = par[i]; j >= 0; j = par[j]) ++d;
+    return d;
+  };
+  if (tid == 0) {
+    deepest = 0;
+    *red_k = 0ull;
+  }
+  __syncthreads();
+  int my_max = 0;
+  for (int i = tid; i < n; i += CTL_THREADS) my_max = max(my_max, depth_of(i));
+  my_max = (int)wave_max_u32((unsigned)my_max);
+  if ((tid & 63) == 0) atomicMax(&deepest, my_max);
+  __syncthreads();
+  const int D = deepest;
+  unsigned long long best = 0ull;
+  for (int i = tid; i < n; i += CTL_THREADS) {
+    if (depth_of(i) != D) continue;
+    float v = 0.f;
+    if (a.mode == 0)  // value of the root, then one float32 add per level, root first
+      for (int t = 1; t <= D; ++t) v = v + fminf(lc[ancestor(par, i, D - t)], 0.f);
+    else if (i != 0)
+      v = fminf(lc[i], 0.f);
+    const unsigned long long k = control_key(v, i);
+    best = k > best ? k : best;
+  }
+  best = best_key(best, red_k);
+  if (tid < 64) decide(a, s, 0x7fffffff - (int)(unsigned)(best & 0xffffffffull), D, par, a.ent + o);
+}
+
 __global__ __launch_bounds__(CTL_THREADS) void k_adaptive_control(ControlArgs a) {
-  __shared__ int red_i[CTL_THREADS / 64];
-  __shared__ unsigned long long red_k[CTL_THREADS / 64];
-  __shared__ int par_lds[CTL_LDS_NODES];
+  __shared__ unsigned long long red_k;
+  __shared__ int l_par[CTL_LDS_NODES];
+  __shared__ float l_logc[CTL_LDS_NODES];
+  __shared__ unsigned long long l_node[CTL_LDS_NODES];  // deep trees: the nodes' words; else the entropies
+  __shared__ int unsettled[3];
   const int s = blockIdx.x, tid = threadIdx.x;
   const int o = a.node_offsets[s];
   const int n = a.node_counts != nullptr ? a.node_counts[s] : a.node_offsets[s + 1] - o;
@@ -150,15 +150,45 @@ __global__ __launch_bounds__(CTL_THREADS) void k_adaptive_control(ControlArgs a)
     }
     return;
   }
-  const float* __restrict__ lc = a.logc + o;
-  const float* __restrict__ ent = a.ent + o;
-  if (n <= CTL_LDS_NODES) {
-    for (int i = tid; i < n; i += CTL_THREADS) par_lds[i] = a.parent[o + i];
-    __syncthreads();
-    control_sequence(a, s, n, (const int*)par_lds, lc, ent, red_i, red_k);
-  } else {
-    control_sequence(a, s, n, a.parent + o, lc, ent, red_i, red_k);
+  if (n > CTL_LDS_NODES) {
+    control_large(a, s, o, n, &red_k);
+    return;
   }
+  float* const l_ent = reinterpret_cast<float*>(l_node);
+  for (int i = tid; i < n; i += CTL_THREADS) {
+    l_par[i] = a.parent[o + i];
+    l_logc[i] = a.logc[o + i];
+    l_ent[i] = a.ent[o + i];
+  }
+  if (tid < 3) unsettled[tid] = 0;
+  if (tid == 0) red_k = 0ull;
+  __syncthreads();
+  // the best node of the deepest level: (depth, value, row) as one key
+  static_assert(CTL_LDS_NODES <= 1 << 13, "13 bits of depth, 32 of value, 13 of row");
+  auto key_of = [&](int i, unsigned long long w) {
+    const float v = a.mode == 0 ? node_sum(w) : i == 0 ? 0.f : fminf(l_logc[i], 0.f);
+    return ((unsigned long long)(unsigned)node_depth(w) << 45) | ((unsigned long long)order_bits(v) << 13) | (unsigned)(8191 - i);
+  };
+  auto any = [](bool, float, int) { return true; };
+  unsigned long long best = 0ull;
+  bool deep = false;
+  for (int i = tid; i < n; i += CTL_THREADS) {
+    const unsigned long long w = walk_node(l_par, l_logc, i, n, any);
+    deep = deep || w == 0ull;
+    best = max(best, key_of(i, w));
+  }
+  const float* ent = l_ent;
+  if (__syncthreads_or(deep ? 1 : 0)) {
+    ent = a.ent + o;
+    for (int i = tid; i < n; i += CTL_THREADS) l_node[i] = i == 0 ? node_word(0.f, 0, true) : 0ull;
+    __syncthreads();
+    settle_nodes<CTL_THREADS, CTL_LDS_NODES>(l_par, l_logc, l_node, unsettled, n, any);
+    best = 0ull;
+    for (int i = tid; i < n; i += CTL_THREADS)
+      if (l_node[i] != 0ull) best = max(best, key_of(i, l_node[i]));  // (0: not settled, a malformed tree)
+  }
+  best = best_key(best, &red_k);
+  if (tid < 64) decide(a, s, 8191 - (int)(best & 8191ull), (int)(best >> 45), (const int*)l_par, ent);
 }
 
 }  // namespace hs
