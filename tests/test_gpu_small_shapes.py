@@ -426,3 +426,22 @@ def test_trees_around_the_limits_of_a_workgroup(G, n, depth):
             for k in ("pstar", "bin", "d_prime", "n_prime"):
                 assert np.array_equal(G.host(got[k]), want[k]), (k, mode)
             assert np.allclose(G.host(got["phi"]), want["phi"], rtol=1e-5, atol=1e-8)
+
+
+@pytest.mark.parametrize("K,F", [(10, 10), (1, 7), (13, 10), (16, 40), (4, 1), (3, 300)])
+def test_expansion_of_equal_values(G, K, F):
+    """Rows of equal value go by their number, across the threads that share a comparison and the ends of their pieces."""
+    import paper_2505_13254_amd as hs
+    from oracle.tree_expand import new_state, tree_expand
+    rs = np.random.RandomState(K * F)
+    cap = 1 + 5 * K * F
+    state, ref = hs.new_tree_state(1, cap, F, G.DEV), new_state()
+    for lvl in range(4):
+        lp = np.round(-rs.exponential(0.5, size=(F, K)) * 2).astype(np.float32) / 2
+        idx, ent = rs.randint(0, 1000, size=(F, K)).astype(np.int32), rs.uniform(0, 2, size=F).astype(np.float32)
+        hs.hs_tree_expand(state, G.dev(idx), G.dev(lp), G.dev(ent), None, 1, cap, F, K, first=lvl == 0)
+        tree_expand(ref, idx, lp, ent, F, cap, None)
+        n, nf = int(G.host(state["n_nodes"])[0]), int(G.host(state["n_frontier"])[0])
+        assert n == len(ref["parent"]) and list(G.host(state["frontier"])[:nf]) == ref["frontier"], lvl
+        assert np.array_equal(G.host(state["parent"])[:n], ref["parent"])
+        assert np.array_equal(G.host(state["cumlogp"])[:n].view(np.uint32), np.asarray(ref["cum"], np.float32).view(np.uint32))
