@@ -24,7 +24,7 @@
 //               and a scan inside the one row that is hit.
 #include <limits.h>
 
-#include "hs_common.h"
+#include "tree_settle.h"
 
 namespace hs {
 
@@ -135,6 +135,190 @@ __global__ __launch_bounds__(GR_THREADS) void k_accept_greedy(int32_t* __restric
       node = staged ? l_par[node] : parent[o + node];
     }
   }
+}
+
+// The greedy walk on its own, for calls of many rows: one workgroup to a sequence reads the rows of the path it
+// takes and no others.  A level is one row streamed by one compute unit, which bounds it (128256 logits in 7.2 us, 71 GB/s;
+// 32000 in 2.8), so a path costs levels, where the scan of every row costs bytes: see greedy_by_path.
+//
+// Nodes of a level that are confirmed (their root path is what the target's argmax says) are listed; usually there is
+// one, several when siblings carry the same token.  Each gets its row's argmax, its children that carry it make up
+// the next list, and the lowest row of the last list that is not empty ends the path, as in k_accept_greedy.
+constexpr int GP_THREADS = 1024;
+constexpr int GP_WAVES = GP_THREADS / 64;
+constexpr int GP_LDS_ROWS = 4096;   // tree rows in LDS; of larger trees the lists and the argmax are in the workspace
+constexpr int GP_AHEAD = 16;        // 16-byte loads that a lane has in flight
+template <bool VEC>
+__global__ __launch_bounds__(GP_THREADS) void k_greedy_path(const float* __restrict__ target, int64_t row_stride, int V, int NN,
+                                                            const int32_t* __restrict__ token,
+                                                            const int32_t* __restrict__ parent,
+                                                            const int32_t* __restrict__ node_offsets, int max_depth,
+                                                            int32_t* __restrict__ ws_arg, int32_t* __restrict__ ws_list,
+                                                            int32_t* __restrict__ accept_len,
+                                                            int32_t* __restrict__ accept_path,
+                                                            int32_t* __restrict__ bonus_token) {
+  __shared__ int l_par[GP_LDS_ROWS], l_tok[GP_LDS_ROWS], l_arg[GP_LDS_ROWS];
+  __shared__ int l_list[2][GP_LDS_ROWS];
+  __shared__ int n_list[2];
+  __shared__ unsigned long long wave_key[2][GP_WAVES];
+  const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int o = node_offsets[s];
+  const int n = node_offsets[s + 1] - o;
+  int32_t* path = accept_path + (int64_t)s * max_depth;
+  for (int d = tid; d < max_depth; d += GP_THREADS) path[d] = -1;
+  if (n <= 0) {
+    if (tid == 0) {
+      accept_len[s] = 0;
+      bonus_token[s] = -1;
+    }
+    return;
+  }
+  const bool staged = n <= GP_LDS_ROWS;
+  if (staged)
+    for (int i = tid; i < n; i += GP_THREADS) {
+      l_par[i] = parent[o + i];
+      l_tok[i] = token[o + i];
+    }
+  auto par_of = [&](int i) { return staged ? l_par[i] : parent[o + i]; };
+  auto tok_of = [&](int i) { return staged ? l_tok[i] : token[o + i]; };
+  auto put = [&](int which, int at, int node) {
+    if (staged) l_list[which][at] = node;
+    else ws_list[(int64_t)which * NN + o + at] = node;
+  };
+  auto get = [&](int which, int at) { return staged ? l_list[which][at] : ws_list[(int64_t)which * NN + o + at]; };
+  if (tid == 0) {
+    n_list[0] = 1;
+    put(0, 0, 0);
+  }
+  __syncthreads();
+
+  // The row's largest value with the lowest index, in every thread.  Chunk k is the row's elements 4096 k .. 4096 k + 4095,
+  // four to a thread; a wave keeps its largest value so far and, per lane, the last four values that were above it: an
+  // equal value of a later chunk has a higher index.
+  constexpr int CHUNK = 4 * GP_THREADS;
+  int turn = 0;
+  auto row_argmax = [&](int node) {
+    const float* __restrict__ x = target + (int64_t)(o + node) * row_stride;
+    float thr = -HS_INF;
+    float4 best = make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
+    int best_chunk = 0;
+    auto take = [&](const float4 f, int k) {
+      const float m = fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w));
+      if (__ballot(m > thr) != 0ull) {
+        if (m > thr) {
+          best = f;
+          best_chunk = k;
+        }
+        thr = wave_max(fmaxf(m, thr));
+      }
+    };
+    // whole chunks by loads without conditions, the rest of the row by one that is requested first and looked at last
+    const int n_full = V / CHUNK;
+    float4 tail = make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
+    {
+      const int i0 = n_full * CHUNK + tid * 4;
+      if (VEC && i0 + 3 < V) {
+        tail = *reinterpret_cast<const float4*>(x + i0);
+      } else {
+        if (i0 < V) tail.x = x[i0];
+        if (i0 + 1 < V) tail.y = x[i0 + 1];
+        if (i0 + 2 < V) tail.z = x[i0 + 2];
+        if (i0 + 3 < V) tail.w = x[i0 + 3];
+      }
+    }
+    const float* __restrict__ src = x + tid * 4;
+    auto load = [&](int k) {
+      const float* __restrict__ at = src + (int64_t)k * CHUNK;
+      return VEC ? *reinterpret_cast<const float4*>(at) : make_float4(at[0], at[1], at[2], at[3]);
+    };
+    float4 f[GP_AHEAD];
+    int k = 0;
+    if (n_full >= GP_AHEAD) {
+#pragma unroll
+      for (int u = 0; u < GP_AHEAD; ++u) f[u] = load(u);
+      for (; k + 2 * GP_AHEAD <= n_full; k += GP_AHEAD)
+#pragma unroll
+        for (int u = 0; u < GP_AHEAD; ++u) {
+          take(f[u], k + u);
+          f[u] = load(k + u + GP_AHEAD);
+        }
+#pragma unroll
+      for (int u = 0; u < GP_AHEAD; ++u) {
+        take(f[u], k + u);
+        if (k + u + GP_AHEAD < n_full) f[u] = load(k + u + GP_AHEAD);
+      }
+      k += GP_AHEAD;
+    } else {
+#pragma unroll
+      for (int u = 0; u < GP_AHEAD; ++u)
+        if (u < n_full) f[u] = load(u);
+    }
+#pragma unroll
+    for (int u = 0; u < GP_AHEAD; ++u)
+      if (k + u < n_full) take(f[u], k + u);
+    take(tail, n_full);
+    // the lane's best pair: of its four values the first that is the wave's largest
+    const float m = fmaxf(fmaxf(best.x, best.y), fmaxf(best.z, best.w));
+    const int e = best.x == m ? 0 : best.y == m ? 1 : best.z == m ? 2 : 3;
+    const unsigned at = (unsigned)(best_chunk * CHUNK + tid * 4 + e);
+    unsigned long long key = ((unsigned long long)order_bits(m + 0.f) << 32) | (0xffffffffu - at);
+    key = wave_max_u64(key);
+    unsigned long long* const keys = wave_key[turn & 1];  // (the other one may still be read)
+    ++turn;
+    if (lane == 0) keys[wave] = key;
+    __syncthreads();
+    key = wave_max_u64(lane < GP_WAVES ? keys[lane] : 0ull);
+    return (int)(0xffffffffu - (unsigned)key);
+  };
+
+  int depth = 0, cur = 0;
+  for (;;) {
+    const int count = n_list[cur];
+    if (tid == 0) n_list[cur ^ 1] = 0;
+    __syncthreads();
+    for (int c = 0; c < count; ++c) {
+      const int node = get(cur, c);
+      const int arg = row_argmax(node);
+      if (tid == 0) {
+        if (staged) l_arg[node] = arg;
+        else ws_arg[o + node] = arg;
+      }
+      if (depth < max_depth)
+        for (int i = 1 + tid; i < n; i += GP_THREADS)
+          if (par_of(i) == node && tok_of(i) == arg) put(cur ^ 1, atomicAdd(&n_list[cur ^ 1], 1), i);
+    }
+    __syncthreads();
+    if (n_list[cur ^ 1] == 0) break;
+    cur ^= 1;
+    ++depth;
+  }
+  // ---- the lowest row of the last list ends the path
+  if (wave == 0) {
+    unsigned best = 0u;
+    for (int c = lane; c < n_list[cur]; c += 64) best = max(best, 0x7fffffffu - (unsigned)get(cur, c));
+    int node = (int)(0x7fffffffu - wave_max_u32(best));
+    if (lane == 0) {
+      accept_len[s] = depth;
+      bonus_token[s] = staged ? l_arg[node] : ws_arg[o + node];
+      for (int k = depth - 1; k >= 0; --k) {
+        path[k] = node;
+        node = par_of(node);
+      }
+    }
+  }
+}
+
+// Which of the two a greedy call takes: the scan of every row, or the rows of the paths alone, one after the other.  The
+// longest path there can be decides, so that no tree is slower than by the scan.  Sequences of 61 rows, paths of 1, 5 and 11
+// rows of a longest 11, whole calls of 12 to 13 us at least: 16 of 128256 tokens 91 us by the scan, 12.7, 41 and 86 by
+// the paths; 64 of them 339 and 13, 43, 140; 64 of 32000 tokens 92 and 12.5, 21, 41; 200 of 8000 75 and 12.5, 14, 29.
+// (16 sequences of 8 to 128 nodes on 128256 tokens, the whole step: 382 us, 303.)
+static bool greedy_by_path(int B, int NN, int V, int max_depth, bool aligned) {
+  const double row_bytes = 4.0 * V;
+  const double scan_us = 6.0 + (double)NN * row_bytes / 6.0e6;
+  const double row_us = fmax(2.0 + row_bytes / (aligned ? 1.0e5 : 2.0e4), (double)B * row_bytes / 2.2e6);
+  return 6.0 + row_us * ((double)max_depth + 1.0) < scan_us;
 }
 
 // ----------------------------------------------------------------------------------- stochastic
@@ -1104,6 +1288,16 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     void* scan_ws = c.take<char>(0);
     const float T = stochastic ? temperature : 1.0f;
     hs_status r;
+    if (!stochastic && hs::greedy_by_path(B, NN, V, max_depth, rows.aligned)) {
+      int32_t* list = reinterpret_cast<int32_t*>(t_lz);  // (2 NN words that the scan would fill)
+      if (rows.aligned)
+        hipLaunchKernelGGL(hs::k_greedy_path<true>, dim3(B), dim3(hs::GP_THREADS), 0, st, target_logits, row_stride, V, NN, token,
+                           parent, node_offsets, max_depth, t_arg, list, accept_len, accept_path, bonus_token);
+      else
+        hipLaunchKernelGGL(hs::k_greedy_path<false>, dim3(B), dim3(hs::GP_THREADS), 0, st, target_logits, row_stride, V, NN, token,
+                           parent, node_offsets, max_depth, t_arg, list, accept_len, accept_path, bonus_token);
+      return hs::launch_status("accept (greedy path)");
+    }
     if (mode == HS_ACCEPT_STOCHASTIC) {
       // one scan over [target rows ; draft rows]; draft rows are read where a row has children, and
       // nowhere else

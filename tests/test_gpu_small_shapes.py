@@ -445,3 +445,64 @@ def test_expansion_of_equal_values(G, K, F):
         assert n == len(ref["parent"]) and list(G.host(state["frontier"])[:nf]) == ref["frontier"], lvl
         assert np.array_equal(G.host(state["parent"])[:n], ref["parent"])
         assert np.array_equal(G.host(state["cumlogp"])[:n].view(np.uint32), np.asarray(ref["cum"], np.float32).view(np.uint32))
+
+
+@pytest.mark.parametrize("sizes,V,pad,depth", [
+    ([9000, 9000], 700, 0, 2), ([9000, 9000], 701, 0, 2), ([3, 5000, 0, 4097, 1], 1025, 3, 2), ([60] * 90, 4096, 0, 3),
+    ([60] * 90, 4099, 0, 3), ([33] * 30, 65536, 0, 4), ([33] * 20, 65540, 0, 2), ([33] * 40, 65539, 0, 1), ([17] * 40, 131071, 1, 3),
+    ([2000, 2000], 4100, 0, 3), ([6000] * 10, 130, 2, 1)])
+def test_greedy_walk_by_paths(G, sizes, V, pad, depth):
+    """Greedy calls of so many rows that only the paths' rows are read: rows of less than one piece of a workgroup, of whole
+    ones and of one more value, aligned or not, trees beyond LDS, empty sequences; equal largest values, masked rows, siblings
+    that carry the same token (the deepest confirmed row counts, then the lowest), paths cut off at the depth limit.  Rows
+    off the paths are NaN where the outcome may not depend on them."""
+    import paper_2505_13254_amd as hs
+    rs = np.random.RandomState(V + len(sizes))
+    NN = sum(sizes)
+    x = torch.full((NN, V + pad), float("nan"), device=G.DEV)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    parent, token, want = [], [], []
+    for s, n in enumerate(sizes):
+        if n == 0:
+            want.append((0, [], -1))
+            continue
+        par = [-1] + [int(rs.randint(max(0, i - 8), i)) if i < 40 else int(rs.randint(0, i)) for i in range(1, n)]
+        tok = rs.randint(0, V, size=n)
+        arg = {}
+        def row(i):
+            if i not in arg:
+                r = np.round(rs.randn(V).astype(np.float32) * 4) / 4
+                if rs.rand() < 0.3:
+                    r[rs.randint(0, V):] = -np.inf
+                if rs.rand() < 0.1:
+                    r[:] = -np.inf
+                x[int(off[s]) + i, :V] = torch.from_numpy(r).to(G.DEV)
+                arg[i] = int(np.argmax(r))
+            return arg[i]
+        level, d = [0], 0
+        while True:
+            for i in level:
+                a = row(i)
+                kids = [c for c in range(1, n) if par[c] == i]
+                for c in kids:
+                    if tok[c] == a:
+                        tok[c] = (a + 1) % V
+                for c in kids[:: max(1, len(kids) - 1)][:2] if rs.rand() < 0.8 else []:  # (up to two siblings of one token)
+                    tok[c] = a
+            nxt = [c for c in range(1, n) if par[c] in level and tok[c] == arg[par[c]]] if d < depth else []
+            if not nxt:
+                break
+            level, d = nxt, d + 1
+        path, i = [], min(level)
+        while i > 0:
+            path.append(i)
+            i = par[i]
+        want.append((d, path[::-1], arg[min(level)]))
+        parent += par
+        token += list(tok)
+    out = hs.hs_verify_accept(x[:, :V], None, G.dev(np.asarray(token, np.int32)), G.dev(np.asarray(parent, np.int32)), G.dev(off), 0, 1.0, None, depth)
+    out = {k: G.host(v) for k, v in out.items()}
+    for s, (d, path, bonus) in enumerate(want):
+        assert int(out["accept_len"][s]) == d and int(out["bonus_token"][s]) == bonus, s
+        assert list(out["accept_path"][s]) == path + [-1] * (depth - d), s
+    assert max(w[0] for w in want) >= 1
