@@ -140,6 +140,38 @@ __device__ __forceinline__ int wave_rank(float v, int i, int n) {
   return r;
 }
 
+// The K-th largest (K <= 16) of 16 values of which every row of 16 lanes holds a copy, in every lane.  The lanes of a row
+// rotate (DPP), so there is no chain through scalar registers as in wave_rank.
+template <int N>
+__device__ __forceinline__ int row_rotated(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, 0x120 + N, 0xf, 0xf, false);  // row_ror:N
+}
+template <int N = 1>
+__device__ __forceinline__ void rank16(float v, int& above, int& not_below) {
+  if constexpr (N < 16) {
+    const float o = __builtin_bit_cast(float, row_rotated<N>(__builtin_bit_cast(int, v)));
+    above += o > v ? 1 : 0;
+    not_below += o >= v ? 1 : 0;
+    rank16<N + 1>(v, above, not_below);
+  }
+}
+__device__ __forceinline__ float kth_of_16(float v, int K) {
+  int above = 0, not_below = 1;
+  rank16(v, above, not_below);
+  const unsigned long long who = __ballot(above < K && not_below >= K);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), __ffsll((long long)who) - 1));
+}
+// How many of the 16 keys of a lane's row (a copy in every row) are larger than the lane's.
+template <int N = 1>
+__device__ __forceinline__ int keys_above16(unsigned long long k) {
+  if constexpr (N < 16) {
+    const unsigned long long o = ((unsigned long long)(unsigned)row_rotated<N>((int)(k >> 32)) << 32) | (unsigned)row_rotated<N>((int)k);
+    return (o > k ? 1 : 0) + keys_above16<N + 1>(k);
+  } else {
+    return 0;
+  }
+}
+
 // Inserts the wave-uniform key x into the sorted list held one entry per lane (largest first).
 __device__ __forceinline__ void list_insert(unsigned long long x, unsigned long long& list) {
   // the left neighbour's entry (lane 0: one that nothing beats)
@@ -184,7 +216,7 @@ __device__ __forceinline__ Stats stats_wave_sum(Stats a, float inv_t) {
 // Scratch of the merges (shared memory).
 template <int CAP>
 struct MergeScratch {
-  unsigned long long key[CAP];         // candidates (pair_key; 0: none)
+  __attribute__((aligned(16))) unsigned long long key[CAP];  // candidates (pair_key; 0: none)
   unsigned long long best[HS_MAX_TOPK];  // the K best of them, in order (0: fewer than K)
   int cnt;
   Stats total;
@@ -192,12 +224,18 @@ struct MergeScratch {
 
 // A key that at least K entries of S <= 64 sorted lists reach, so that nothing below it is among the K best:
 // with r = ceil(K / S), the ceil(K / r)-th largest of the lists' r-th entries (1, which every entry
-// reaches, when fewer lists are that long).  `rth`: list s's r-th entry in lane s < S, 0 in the other lanes.
+// reaches, when fewer lists are that long).  `rth`: list s's r-th entry in lane s < S, 0 in the other lanes; up to 16 lists:
+// list s's in lane s of every row of 16 lanes (list_lane).
 __device__ __forceinline__ int threshold_depth(int S, int K) { return (K + S - 1) / S; }
+__device__ __forceinline__ int list_lane(int S, int lane) { return S <= 16 ? lane & 15 : lane; }
 __device__ __forceinline__ unsigned long long lists_threshold(unsigned long long rth, int S, int K) {
   const int r = threshold_depth(S, K), m = (K + r - 1) / r;
   int rank = 0;
-  for (int l = 0; l < S; ++l) rank += lane_key(rth, l) > rth ? 1 : 0;
+  if (S <= 16) {
+    rank = keys_above16(rth);
+  } else {
+    for (int l = 0; l < S; ++l) rank += lane_key(rth, l) > rth ? 1 : 0;
+  }
   const unsigned long long who = __ballot(rank == m - 1 && rth != 0ull);
   return who != 0ull ? lane_key(rth, __ffsll((long long)who) - 1) : 1ull;
 }
@@ -232,6 +270,45 @@ __device__ __forceinline__ void rank_candidates(MergeScratch<CAP>& sm, int n, in
   __syncthreads();
 }
 
+// The same for n <= 64 candidates by one wave alone, a candidate to a lane: the opponents come as broadcast reads of LDS,
+// eight requested together.  Leaves the K best in sm.best (zero on entry) for the same wave; no barrier.
+template <int CAP>
+__device__ __forceinline__ void rank_few(MergeScratch<CAP>& sm, int n, int K, int lane) {
+  static_assert(CAP >= 72, "64 candidates and what fills the last eight");
+  if (lane < 8) sm.key[n + lane] = 0ull;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const unsigned long long mine = lane < n ? sm.key[lane] : 0ull;
+  int rank = 0;
+  for (int o = 0; o < n; o += 8) {
+    ulonglong2 k[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) k[q] = reinterpret_cast<const ulonglong2*>(sm.key)[(o >> 1) + q];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rank += (k[q].x > mine ? 1 : 0) + (k[q].y > mine ? 1 : 0);
+  }
+  if (mine != 0ull && rank < K) sm.best[rank] = mine;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// The place of a wave's entry in the order of all lists of a workgroup of four waves, K <= 16 entries each, unused ones (0)
+// last: its place in its own list, and what the other lists hold above it.  sm.key: wave w's list from 16 w on,
+// filled up with zeros.
+template <int PAIRS, int CAP>
+__device__ __forceinline__ int place_of_four(const MergeScratch<CAP>& sm, unsigned long long mine, int wave, int lane) {
+  int place = lane;
+#pragma unroll
+  for (int d = 1; d < 4; ++d) {
+    const int w = (wave + d) & 3;
+    const unsigned long long low = w < wave ? 1ull : 0ull;  // (equal, i.e. unused, entries: the lower wave's first)
+    ulonglong2 k[PAIRS];
+#pragma unroll
+    for (int q = 0; q < PAIRS; ++q) k[q] = reinterpret_cast<const ulonglong2*>(sm.key)[w * 8 + q];
+#pragma unroll
+    for (int q = 0; q < PAIRS; ++q) place += (k[q].x + low > mine ? 1 : 0) + (k[q].y + low > mine ? 1 : 0);
+  }
+  return place;
+}
+
 // Loads and stores that are coherent across the chip's XCDs (each has an L2 of its own): relaxed
 // atomics of device scope, which go past a stale or private cache line.  What workgroups of one
 // launch use to hand their slices' results to each other: a fence that reaches the other XCDs
@@ -244,17 +321,19 @@ __device__ __forceinline__ void st_dev(unsigned long long* p, unsigned long long
 // Merges S <= 64 slices of a row: statistics st[s] (m, s1, t) and sorted K-lists pk[s * K + k] of keys.
 // COHERENT: the slices were written by other workgroups of the same launch (ld_dev).
 // Leaves the row's statistics in sm.total and its K best pairs, in order, in sm.best.
-// Called by all `nthreads` threads of the workgroup (tid 0..nthreads-1) after a barrier; ends with a barrier.
+// sm.cnt and sm.best are zero and the workgroup has met a barrier since.  Called by all `nthreads` threads; the results
+// are the first wave's (every wave's after a barrier).
 // Everything the merge reads from memory is requested at once (one trip, which is most of its
-// time when the slices come from other workgroups): the lists by all threads, the statistics by the
-// last wave.  Then the lists' heads (fewer lists than K: their r-th entries) give a threshold, which every wave
-// finds for itself; only a few entries pass it, and those are ranked by counting.  (With a threshold for at least
-// K lists only, one row of 128256 logits in 32 slices took 957 us for K = 64.)
+// time when the slices come from other workgroups): the lists by all threads, their heads (fewer lists than K: their
+// r-th entries) by every wave once more, the statistics by the last wave.  The heads give a threshold; only a few
+// entries pass it, and those are ranked by counting, by the first wave if it can hold them.  (With a threshold for at
+// least K lists only, one row of 128256 logits in 32 slices took 957 us for K = 64.  With the heads passed on
+// through LDS and all waves ranking, three barriers instead of one, and a slice's own merge likewise: 10 rows of 128256 logits
+// in 16 slices 13.0 us a launch, now 11.7; the ratio rule's 61 rows and 20 parents 17.8 and 16.8.)
 template <bool COHERENT, int CAP>
 __device__ __forceinline__ void merge_slices(const float4* st, const unsigned long long* pk, int S, int K, float inv_t,
                                              MergeScratch<CAP>& sm, int tid, int nthreads) {
   const int lane = tid & 63;
-  __shared__ unsigned long long rth[MAX_SPLITS];
   constexpr int PER = 4;  // entries a thread keeps in registers (a trip covers PER x nthreads of the S x K)
   const int n_all = S * K;
   unsigned long long ek[PER];
@@ -263,6 +342,11 @@ __device__ __forceinline__ void merge_slices(const float4* st, const unsigned lo
     const int e = tid + q * nthreads;
     ek[q] = 0ull;
     if (e < n_all) ek[q] = COHERENT ? ld_dev(pk + e) : pk[e];
+  }
+  unsigned long long rth = 0ull;
+  if (list_lane(S, lane) < S) {
+    const unsigned long long* e = pk + (int64_t)list_lane(S, lane) * K + threshold_depth(S, K) - 1;
+    rth = COHERENT ? ld_dev(e) : *e;
   }
   Stats a = stats_empty();
   const bool stats_wave = tid >= nthreads - 64;
@@ -275,28 +359,32 @@ __device__ __forceinline__ void merge_slices(const float4* st, const unsigned lo
       a = Stats{f.x, f.y, f.z};
     }
   }
-  // (by loads of their own: the S x K entries may be more than the threads hold in registers)
-  if (tid < S) {
-    const unsigned long long* e = pk + (int64_t)tid * K + threshold_depth(S, K) - 1;
-    rth[tid] = COHERENT ? ld_dev(e) : *e;
-  }
-  if (tid == 0) sm.cnt = 0;
-  if (tid < HS_MAX_TOPK) sm.best[tid] = 0ull;
-  __syncthreads();
-  const unsigned long long thr = lists_threshold(lane < S ? rth[lane] : 0ull, S, K);
+  const unsigned long long thr = lists_threshold(rth, S, K);
+  // (order of arrival does not matter; at most S * K <= CAP entries)
   auto admit = [&](unsigned long long k) {
-    if (k >= thr) sm.key[atomicAdd(&sm.cnt, 1)] = k;  // (order of arrival does not matter; at most S * K <= CAP entries)
+    const unsigned long long who = __ballot(k >= thr);
+    if (who == 0ull) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&sm.cnt, __popcll(who));
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (k >= thr) sm.key[base + lanes_below(who)] = k;
   };
 #pragma unroll
   for (int q = 0; q < PER; ++q) admit(ek[q]);
-  for (int e = tid + PER * nthreads; e < n_all; e += nthreads)  // (more entries than PER x nthreads: the rest)
-    admit(COHERENT ? ld_dev(pk + e) : pk[e]);
+  for (int e0 = PER * nthreads; e0 < n_all; e0 += nthreads) {  // (more entries than PER x nthreads: the rest)
+    const int e = e0 + tid;
+    admit(e < n_all ? (COHERENT ? ld_dev(pk + e) : pk[e]) : 0ull);
+  }
   if (stats_wave) {
     a = stats_wave_sum(a, inv_t);
     if (lane == 0) sm.total = a;
   }
   __syncthreads();
-  rank_candidates(sm, sm.cnt, K, tid, nthreads);
+  if (sm.cnt <= 64) {
+    if (tid < 64) rank_few(sm, sm.cnt, K, lane);
+  } else {
+    rank_candidates(sm, sm.cnt, K, tid, nthreads);
+  }
 }
 
 // Writes a row's results from its merged statistics and Top-K list (first wave of the workgroup).
@@ -391,6 +479,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
   float ref = -HS_INF, s1 = 0.f, t2 = 0.f;
   bool masked = false;  // a masked logit has been met: the wave's sums are clamped from there on
   if (tid < HS_MAX_TOPK) sm.best[tid] = 0ull;  // (a slice with fewer than K elements leaves the rest unused)
+  if (tid == 0) sm.cnt = 0;
 
   auto load_tile = [&](int tile, float (&v)[SCAN_VPT]) {
     const int tbase = (split * tiles_per_wg + tile) * SCAN_TILE;
@@ -521,10 +610,14 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
         }
         // an exchange through LDS only: the barrier must not wait for the next tiles' loads
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        const float mine = lane < n_groups ? group_maxima[lane] : -HS_INF;
-        const int r = wave_rank(mine, lane, n_groups);
-        const unsigned long long who = __ballot(r == K - 1 && lane < n_groups);
-        thr = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), __ffsll((long long)who) - 1));
+        if (n_groups == 16) {
+          thr = kth_of_16(group_maxima[lane & 15], K);
+        } else {
+          const float mine = lane < n_groups ? group_maxima[lane] : -HS_INF;
+          const int r = wave_rank(mine, lane, n_groups);
+          const unsigned long long who = __ballot(r == K - 1 && lane < n_groups);
+          thr = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), __ffsll((long long)who) - 1));
+        }
       } else {
         const int r = wave_rank(tm, lane, 64);
         const unsigned long long who = __ballot(r == K - 1);
@@ -615,73 +708,107 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
     const float ws = wave_sum(s1), wt = wave_sum(t2);
     if (lane == 0) wave_st[wave] = make_float4(ref, ws, wt * 0.6931471805599453f, 0.f);
   }
-  // Lists that fit one wave of opponents are ranked whole.  Of longer ones only the entries that reach a threshold
-  // join, a wave's in one piece (ranked whole, or with the threshold but from the lists' places, K = 40: 40 rows of
-  // 16384 logits 49 and 21 us, 15 now; 200 rows 51 and 23, 17 now).
-  __shared__ unsigned long long rth[SCAN_WAVES];
-  const bool whole = SCAN_WAVES * K <= 64;
-  if (whole) {
-    if (lane < K) sm.key[wave * K + lane] = best;
-  } else {
-    if (lane == threshold_depth(SCAN_WAVES, K) - 1) rth[wave] = best;
-    if (tid == 0) sm.cnt = 0;
-  }
-  __syncthreads();
-  if (!whole) {
-    const unsigned long long list_thr = lists_threshold(lane < SCAN_WAVES ? rth[lane] : 0ull, SCAN_WAVES, K);
-    const bool joins = lane < K && best >= list_thr;  // (a list's first entries)
-    const int n_joins = __popcll(__ballot(joins));
-    int base = 0;
-    if (lane == 0) base = atomicAdd(&sm.cnt, n_joins);
-    base = __builtin_amdgcn_readfirstlane(base);
-    if (joins) sm.key[base + lane] = best;
-  }
-  if (STATS && tid < 64) {
+  static_assert(STATS || !FUSED, "rows are finished by the caller of a scan without statistics");
+  // What becomes of the slice's k-th best pair: kept for write_row when the row is one slice, else handed on.
+  const int64_t slot = (int64_t)row * S + split;
+  auto put = [&](int k, unsigned long long key) {
+    if (S == 1) {
+      if (STATS) sm.best[k] = key;
+      else if (key != 0ull) topk_idx[row * K + k] = (int)(0xffffffffu - (unsigned)key);
+      else topk_idx[row * K + k] = INT_MAX;
+    } else if (FUSED) {
+      st_dev(part_key + slot * K + k, key);  // (a store that the other XCDs see)
+    } else {
+      part_key[slot * K + k] = key;
+    }
+  };
+  // The workgroup's statistics, by its first wave (after the barrier that publishes wave_st).
+  auto put_stats = [&]() {
     Stats a = stats_empty();
     if (lane < SCAN_WAVES) {
       const float4 f = wave_st[lane];
       a = Stats{f.x, f.y, f.z};
     }
     a = stats_wave_sum(a, inv_t);
-    if (lane == 0) sm.total = a;
-  }
-  if (!whole) __syncthreads();
-  rank_candidates(sm, whole ? SCAN_WAVES * K : sm.cnt, K, tid, SCAN_THREADS);  // (its barrier also publishes sm.total)
-  static_assert(STATS || !FUSED, "rows are finished by the caller of a scan without statistics");
-  if (S == 1) {
-    if (STATS) write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
-    else if (tid < K) {
-      float ov;
-      int oi;
-      pair_of(sm.best[tid], ov, oi);
-      topk_idx[row * K + tid] = oi;
+    if (S == 1) {
+      if (lane == 0) sm.total = a;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    } else if (FUSED) {
+      if (lane < 3) st_dev(reinterpret_cast<float*>(part_stats + slot) + lane, lane == 0 ? a.m : lane == 1 ? a.s1 : a.t);
+    } else {
+      if (lane == 0) part_stats[slot] = make_float4(a.m, a.s1, a.t, 0.f);
+    }
+  };
+  // Lists that fit one wave of opponents: every wave finds the places of its own entries and hands them on itself (see
+  // merge_slices).  Of longer ones only the entries that reach a
+  // threshold join, a wave's in one piece (ranked whole, or with the threshold but from the lists' places, K = 40: 40 rows of
+  // 16384 logits 49 and 21 us, 15 now; 200 rows 51 and 23, 17 now).
+  __shared__ unsigned long long rth[SCAN_WAVES];
+  const bool whole = SCAN_WAVES * K <= 64;
+  if (SCAN_WAVES == 4 && whole) {
+    if (lane < 16) sm.key[wave * 16 + lane] = lane < K ? best : 0ull;
+    __syncthreads();
+    const int place = K <= 4 ? place_of_four<2>(sm, best, wave, lane) : K <= 10 ? place_of_four<5>(sm, best, wave, lane) : place_of_four<8>(sm, best, wave, lane);
+    if (lane < K && place < K) put(place, best);
+    if (STATS && wave == 0) put_stats();
+    if (S == 1) {
+      if (!STATS) return;
+      __syncthreads();
+      write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
+      return;
     }
   } else {
-    const int64_t slot = (int64_t)row * S + split;
-    if (!FUSED) {
-      if (tid < K) part_key[slot * K + tid] = sm.best[tid];
-      if (STATS && tid == 0) part_stats[slot] = make_float4(sm.total.m, sm.total.s1, sm.total.t, 0.f);
-    } else {
-      __shared__ int is_last;
-      // The slice's results go out by the first wave alone, with stores that the other XCDs see; once
-      // they are acknowledged (vmcnt) the ticket is drawn.  The workgroup that draws the last one
-      // finds every slice of the row written.
-      if (tid < 64) {
-        if (tid < K) st_dev(part_key + slot * K + tid, sm.best[tid]);
-        if (tid < 3) st_dev(reinterpret_cast<float*>(part_stats + slot) + tid, tid == 0 ? sm.total.m : tid == 1 ? sm.total.s1 : sm.total.t);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (tid == 0) {
-          const unsigned drawn = __hip_atomic_fetch_add(&tickets[row], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          is_last = drawn == (unsigned)(S - 1) ? 1 : 0;
-          // (nobody else touches this row's counter any more: back to zero for the next launch)
-          if (is_last) __hip_atomic_store(&tickets[row], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-      }
+    if (whole) {
+      if (lane < K) sm.key[wave * K + lane] = best;
+    } else if (lane == threshold_depth(SCAN_WAVES, K) - 1) {
+      rth[wave] = best;
+    }
+    __syncthreads();
+    if (!whole) {
+      const int l = list_lane(SCAN_WAVES, lane);
+      const unsigned long long list_thr = lists_threshold(l < SCAN_WAVES ? rth[l] : 0ull, SCAN_WAVES, K);
+      const bool joins = lane < K && best >= list_thr;  // (a list's first entries)
+      const int n_joins = __popcll(__ballot(joins));
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&sm.cnt, n_joins);
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (joins) sm.key[base + lane] = best;
       __syncthreads();
-      if (is_last) {
-        merge_slices<true>(part_stats + (int64_t)row * S, part_key + (int64_t)row * S * K, S, K, inv_t, sm, tid, SCAN_THREADS);
-        write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
+    }
+    const int n = whole ? SCAN_WAVES * K : sm.cnt;
+    if (n <= 64) {  // (by the first wave alone: the others only wait to be told whether to merge)
+      if (tid < 64) rank_few(sm, n, K, lane);
+    } else {
+      rank_candidates(sm, n, K, tid, SCAN_THREADS);
+    }
+    if (tid < 64) {
+      if (STATS) put_stats();
+      if (!(S == 1 && STATS) && lane < K) put(lane, sm.best[lane]);
+      if (S == 1) {
+        if (STATS) write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
+      } else if (FUSED) {  // (for the merge of the slices)
+        sm.best[lane] = 0ull;
+        if (lane == 0) sm.cnt = 0;
       }
+    }
+    if (S == 1) return;
+  }
+  if (FUSED) {
+    __shared__ int is_last;
+    // Once the slice's results are acknowledged (each wave waits for its own stores) the ticket is drawn.  The workgroup
+    // that draws the last one finds every slice of the row written.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+      const unsigned drawn = __hip_atomic_fetch_add(&tickets[row], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      is_last = drawn == (unsigned)(S - 1) ? 1 : 0;
+      // (nobody else touches this row's counter any more: back to zero for the next launch)
+      if (is_last) __hip_atomic_store(&tickets[row], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (is_last) {
+      merge_slices<true>(part_stats + (int64_t)row * S, part_key + (int64_t)row * S * K, S, K, inv_t, sm, tid, SCAN_THREADS);
+      write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
     }
   }
 }
@@ -706,6 +833,9 @@ __global__ __launch_bounds__(FIN_THREADS) void k_scan_finalize(const float4* __r
   const int64_t row = blockIdx.x;
   if (row_active != nullptr && row_active[row] == 0) return;
   if (row_index != nullptr && row_index[row] < 0) return;
+  if (tid < HS_MAX_TOPK) sm.best[tid] = 0ull;
+  if (tid == 0) sm.cnt = 0;
+  __syncthreads();
   merge_slices<false>(part_stats + row * S, part_key + row * S * K, S, K, inv_t, sm, tid, FIN_THREADS);
   write_row(sm, row, K, inv_t, topk_idx, topk_logp, ent_topk, ent_full, lse, tid);
 }
