@@ -15,7 +15,7 @@
 //               one child gets it from one cooperative pass over its two vocabulary rows; a node with
 //               several has the tokens with p > q sorted by p / q into buckets with their sums (one
 //               kernel on the whole chip), after which every normaliser of its chain is two
-//               suffix sums plus, from the second rejection on, the tokens of three buckets.  One
+//               suffix sums plus, from the second rejection on, the tokens of one bucket.  One
 //               workgroup per node with children runs that node's chain of rejections ahead of
 //               the walk, all nodes in parallel (k_accept_chain), and leaves each child's pair of
 //               current probabilities; the walk itself (k_accept_walk, one workgroup per sequence) then
@@ -371,13 +371,17 @@ __device__ __forceinline__ double wave_sum_dpp(double x) {
   return t;
 }
 
+// Inclusive prefix sums over the lanes of a wave: DPP moves inside the rows of 16 lanes, then the totals of the rows before.
 __device__ __forceinline__ double wave_incl_scan(double v, int lane) {
+  v = row16_sum(v);  // (each step adds what lies 1, 2, 4, 8 lanes to the left: every lane ends up with its prefix)
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  double before = 0.0;
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    double o = __shfl_up(v, off);
-    if (lane >= off) v += o;
+  for (int l = 15; l < 63; l += 16) {
+    const double t = __hiloint2double(__builtin_amdgcn_readlane(hi, l), __builtin_amdgcn_readlane(lo, l));
+    before += lane > l ? t : 0.0;
   }
-  return v;
+  return v + before;
 }
 
 // Sum of max(p(v) - beta q(v), 0) over the vocabulary, all threads of the workgroup; the result is
@@ -425,7 +429,7 @@ __device__ __forceinline__ double token_weight(const RowView& p, const RowView& 
 // Children of local row `cur` of a sequence of n rows, ascending, into kids_sorted; returns their
 // number (at most AC_MAX_KIDS: of a node with more children the AC_MAX_KIDS lowest rows are taken,
 // whatever order the threads arrive in).  Called by all threads; ends with a barrier.
-__device__ __forceinline__ int gather_children(const int32_t* __restrict__ parent, int o, int n, int cur, bool any,
+__device__ __forceinline__ int gather_children(const int* parent, int o, int n, int cur, bool any,
                                                int* kids, int* kids_sorted, int* n_kids) {
   const int tid = threadIdx.x;
   if (tid == 0) *n_kids = 0;
@@ -468,12 +472,12 @@ __device__ __forceinline__ int gather_children(const int32_t* __restrict__ paren
 // vocabulary slice by their ratio into BK_N buckets (a counting sort inside a workgroup, the slice
 // read twice) and keeps, per bucket, the sums of p and of q.  F(1) is the sum of all of them, F(beta)
 //     sum over the buckets well above beta of (P_b - beta Q_b)      two suffix sums, read once
-//   + sum over the tokens of the three buckets around beta of max(p - beta q, 0)
+//   + sum over the tokens of beta's bucket (and of the next one where beta is near its edge) of max(p - beta q, 0)
 // which is what k_accept_chain evaluates per rejection: a few thousand pairs instead of two
 // vocabulary rows.  (Sorted across slices, with a scan and a second pass over the rows in launches of
 // their own: 23.6 us for a 61-row tree; now 16.3.)  A token's bucket is floor(BK_PER_OCTAVE * log2(p / q)), taken from the two
 // exponent arguments (p = exp2(a_p)): the rounding of that difference is many orders below a
-// bucket's width, and one bucket to either side of beta's own is still treated token by token, so
+// bucket's width, and where beta lies near the edge of a bucket the next one is treated token by token as well, so
 // no token is ever taken for live or dead by its bucket alone when it is not.  All sums are 64-bit
 // integers in units of 2^-62 (LDS and per-slice partial sums), so neither the order in which the
 // lanes' atomic additions arrive nor the order of the tokens inside a bucket changes a result.
@@ -504,29 +508,51 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
   __shared__ unsigned long long ps[BK_N], qs[BK_N];
   __shared__ unsigned wave_total[BK_N / 64];
   const int slice = blockIdx.x, g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nk = n_tried[g];
+  // (one trip for what the row's statistics say, one for the slice and the two maxima)
+  const int nk = n_tried[g], p_arg = t_arg[g], q_arg = d_arg[g];
+  const float p_lz = t_lz[g], q_lz = d_lz[g];
   if (nk < 2) return;
   cnt[tid] = 0u;
   ps[tid] = 0ull;
   qs[tid] = 0ull;
   const float* p_row = target + (int64_t)g * row_stride;
   const float* q_row = draft + (int64_t)g * row_stride;
-  const RowView p(p_row, p_row[t_arg[g]], t_lz[g], inv_t);
-  const RowView q(q_row, q_row[d_arg[g]], d_lz[g], inv_t);
   const int n4 = V >> 2;
   const int per = (n4 + BK_SLICES - 1) / BK_SLICES;
   const int i0 = min(n4, slice * per), i1 = min(n4, i0 + per);
   const int tail = slice == BK_SLICES - 1 ? V & 3 : 0;  // the last V % 4 tokens are the last slice's
   const float4* __restrict__ px = reinterpret_cast<const float4*>(p_row);
   const float4* __restrict__ qx = reinterpret_cast<const float4*>(q_row);
+  // A thread's tokens stay in its registers for both passes where they fit, requested all at once.  (Read twice, two at a
+  // time: 61 rows of 128256 tokens 15.7 us, now 12.1; 97 rows 28.7 and 19.8.)
+  constexpr int KEEP = 8;
+  const bool kept = i1 - i0 <= KEEP * BK_THREADS;
+  float4 fp[KEEP], fq[KEEP];
+  if (kept) {
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u) {
+      const int i = i0 + tid + u * BK_THREADS;
+      const bool mine = i < i1;  // (p = q = 0 elsewhere: not live)
+      fp[u] = mine ? px[i] : make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
+      fq[u] = mine ? qx[i] : make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
+    }
+  }
+  const RowView p(p_row, p_row[p_arg], p_lz, inv_t);
+  const RowView q(q_row, q_row[q_arg], q_lz, inv_t);
   auto each_token = [&](auto token) {
+    auto four = [&](const float4 a, const float4 b) {
+      token(a.x, b.x);
+      token(a.y, b.y);
+      token(a.z, b.z);
+      token(a.w, b.w);
+    };
+    if (kept) {
+#pragma unroll
+      for (int u = 0; u < KEEP; ++u)
+        if (i0 + tid + u * BK_THREADS < i1) four(fp[u], fq[u]);
+    } else {
 #pragma unroll 2
-    for (int i = i0 + tid; i < i1; i += BK_THREADS) {
-      const float4 fp = px[i], fq = qx[i];
-      token(fp.x, fq.x);
-      token(fp.y, fq.y);
-      token(fp.z, fq.z);
-      token(fp.w, fq.w);
+      for (int i = i0 + tid; i < i1; i += BK_THREADS) four(px[i], qx[i]);
     }
     if (tid < tail) token(p_row[(n4 << 2) + tid], q_row[(n4 << 2) + tid]);
   };
@@ -556,7 +582,7 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
   cnt[tid] = first;
   __syncthreads();
   float2* __restrict__ pairs = ws.pairs + (int64_t)g * V;
-  each_token([&](float xp, float xq) {  // (the slice again, from the caches)
+  each_token([&](float xp, float xq) {
     const float ap = p.arg(xp), aq = q.arg(xq);
     const float pv = exp2_fast(ap), qv = exp2_fast(aq);
     if (pv > qv) pairs[atomicAdd(&cnt[bucket_of(ap, aq)], 1u)] = make_float2(pv, qv);
@@ -590,31 +616,54 @@ struct BucketTables {
   unsigned start[BK_SLICES][BK_N + 1];
   unsigned long long sp[BK_N + 1], sq[BK_N + 1];  // sums of p and of q over the buckets >= b
 };
-// (all AC_THREADS threads; no barrier at the end)
-__device__ __forceinline__ void load_bucket_tables(const BucketWs& ws, int g, BucketTables& t) {
-  constexpr int PARTS = AC_THREADS / BK_N, PER = BK_SLICES / PARTS;
-  static_assert(PARTS * BK_N == AC_THREADS && PER * PARTS == BK_SLICES, "a thread per bucket and group of slices");
-  __shared__ unsigned long long part_p[PARTS][BK_N], part_q[PARTS][BK_N], wave_p[BK_N / 64], wave_q[BK_N / 64];
-  const int tid = threadIdx.x, lane = tid & 63;
+// What a thread requests of them, ahead of everything that the tree says ...
+constexpr int BT_PARTS = AC_THREADS / BK_N, BT_PER = BK_SLICES / BT_PARTS;
+static_assert(BT_PARTS * BK_N == AC_THREADS && BT_PER * BT_PARTS == BK_SLICES, "a thread per bucket and group of slices");
+constexpr int BT_STARTS = (BK_SLICES * (BK_N + 1) + AC_THREADS - 1) / AC_THREADS;
+struct BucketLoads {
+  unsigned long long p[BT_PER], q[BT_PER];
+  unsigned start[BT_STARTS];
+};
+__device__ __forceinline__ void request_bucket_tables(const BucketWs& ws, int g, BucketLoads& l) {
+  const int tid = threadIdx.x, b = tid % BK_N, part = tid / BK_N;
   const int64_t first = (int64_t)g * BK_SLICES;
+#pragma unroll
+  for (int k = 0; k < BT_PER; ++k) {
+    l.p[k] = ws.psum[(first + part * BT_PER + k) * BK_N + b];
+    l.q[k] = ws.qsum[(first + part * BT_PER + k) * BK_N + b];
+  }
+#pragma unroll
+  for (int k = 0; k < BT_STARTS; ++k) {
+    const int e = tid + k * AC_THREADS;
+    l.start[k] = ws.start[first * (BK_N + 1) + (e < BK_SLICES * (BK_N + 1) ? e : 0)];
+  }
+}
+// ... and what becomes of it (all AC_THREADS threads; no barrier at the end).
+__device__ __forceinline__ void make_bucket_tables(const BucketLoads& l, BucketTables& t) {
+  __shared__ unsigned long long part_p[BT_PARTS][BK_N], part_q[BT_PARTS][BK_N], wave_p[BK_N / 64], wave_q[BK_N / 64];
+  const int tid = threadIdx.x, lane = tid & 63;
   {
     const int b = tid % BK_N, part = tid / BK_N;
     unsigned long long tp = 0ull, tq = 0ull;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      tp += ws.psum[(first + part * PER + k) * BK_N + b];
-      tq += ws.qsum[(first + part * PER + k) * BK_N + b];
+    for (int k = 0; k < BT_PER; ++k) {
+      tp += l.p[k];
+      tq += l.q[k];
     }
     part_p[part][b] = tp;
     part_q[part][b] = tq;
   }
-  for (int e = tid; e < BK_SLICES * (BK_N + 1); e += AC_THREADS) (&t.start[0][0])[e] = ws.start[first * (BK_N + 1) + e];
+#pragma unroll
+  for (int k = 0; k < BT_STARTS; ++k) {
+    const int e = tid + k * AC_THREADS;
+    if (e < BK_SLICES * (BK_N + 1)) (&t.start[0][0])[e] = l.start[k];
+  }
   __syncthreads();
   unsigned long long ip = 0ull, iq = 0ull;
   const int b = BK_N - 1 - tid;  // (from the top: prefix sums over the threads are suffix sums over the buckets)
   if (tid < BK_N) {
 #pragma unroll
-    for (int k = 0; k < PARTS; ++k) {
+    for (int k = 0; k < BT_PARTS; ++k) {
       ip += part_p[k][b];
       iq += part_q[k][b];
     }
@@ -644,12 +693,17 @@ struct BucketStep {
   unsigned long long part[AC_WAVES];   // their terms, summed per wave
 };
 
-// beta's own bucket with one bucket to either side: [b_lo, b_hi).  NaN and infinity end up at valid
-// indices as well; float32 is enough to pick the bucket, as it is for the tokens' buckets.
+// beta's own bucket, with the next one on the side where beta lies within a hundredth of a bucket of the edge: [b_lo,
+// b_hi).  NaN and infinity end up at valid indices as well; float32 is enough to pick the bucket, as it is for the tokens'
+// buckets: the difference of two exponent arguments below 2^7, times 32, is off by 1e-3 of a bucket at most, and so
+// is beta's place, so tokens beyond are live, or not, as a bucket.  (One bucket to either side always: three times the
+// pairs, 2.3 us a step instead of 2.0.)
 __device__ __forceinline__ void near_buckets(double beta, int& b_lo, int& b_hi) {
-  const int own = (int)fminf(fmaxf(__log2f((float)beta) * BK_PER_OCTAVE, 0.f), (float)(BK_N - 1));
-  b_lo = own > 0 ? own - 1 : 0;
-  b_hi = own + 2 < BK_N ? own + 2 : BK_N;
+  const float place = fminf(fmaxf(__log2f((float)beta) * BK_PER_OCTAVE, 0.f), (float)(BK_N - 1));
+  const int own = (int)place;
+  const float inside = place - (float)own;
+  b_lo = own > 0 && !(inside > 0.01f) ? own - 1 : own;
+  b_hi = own + 1 < BK_N && !(inside < 0.99f) ? own + 2 : own + 1;
 }
 
 // The terms max(p - beta q, 0) of the pairs in buckets [b_lo, b_hi), a slice to a wave, summed per wave
@@ -832,17 +886,24 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
     if (out.bonus_rows != nullptr) bonus_row_sums(p, p, false, 0.0, V, 0, n_rows, out.bonus_rows + (int64_t)g * n_rows);
     return;
   }
-  gather_children(parent, o, n, cur, true, kids, kids_sorted, &n_kids);
   const float* q_row = draft + (int64_t)g * row_stride;
   const RowView q(q_row, q_row[q_arg], q_lz, inv_t);
-  // every child's token and its two probabilities, fetched side by side: the chain below is serial,
-  // and a round trip to memory per step would dominate it
   const bool sorted = bk.pairs != nullptr && nk >= 2;  // there is a sorted residual
-  if (sorted) load_bucket_tables(bk, g, tables);
+  // Everything is requested side by side: the tables, the children and their tokens, then the tokens' logits; the chain
+  // below is serial, and a round trip to memory per step would dominate it.
+  BucketLoads loads;
+  if (sorted) request_bucket_tables(bk, g, loads);
+  gather_children(parent, o, n, cur, true, kids, kids_sorted, &n_kids);
+  float xp = 0.f, xq = 0.f;
   if (tid < nk) {
     const int x = token[o + kids_sorted[tid]];
-    kid_p[tid] = p.prob(x);
-    kid_q[tid] = q.prob(x);
+    xp = p_row[x];
+    xq = q_row[x];
+  }
+  if (sorted) make_bucket_tables(loads, tables);
+  if (tid < nk) {
+    kid_p[tid] = p.of(xp);
+    kid_q[tid] = q.of(xq);
   }
   __syncthreads();
   const float2* __restrict__ pairs = sorted ? bk.pairs + (int64_t)g * V : nullptr;
@@ -853,7 +914,7 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
     // A step is a chain of its own, a division, two barriers and a trip to memory, so whatever is not
     // part of it is left for later or for other lanes: lane j keeps what child j's probabilities are
     // made of, the rejected tokens' corrections are a lane each, sums travel by DPP moves.  (61 rows, chains of
-    // ten: 2.2 us a step, most of it the trip to memory, and 0.6 for the first; 2.6 and a trip before.)
+    // ten: 2.0 us a step, most of it the trip to memory, and 0.6 for the first; 2.6 and a trip before.)
     const bool lead = tid < 64;
     const int lane = tid & 63;
     double my_px = 0.0, my_qx = 0.0, my_Z = 1.0, my_rem = 1.0;
@@ -1003,19 +1064,24 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
   // Under the ratio rule every child's test is known before the walk (k_accept_chain left its two
   // probabilities): all nodes test themselves at once and the first accepted child of each node is found,
   // so the walk itself is a chase through LDS, and only the node where it stops is looked at below.
-  // (Level by level, each a few trips to memory, 12.6 us for a 61-row tree and 22 for 97 rows; now 9.4 and 11.8.)
+  // (Level by level, each a few trips to memory, 12.6 us for a 61-row tree and 22 for 97 rows; 9.4 and 11.8 with the children gathered from memory again, now 7.5 and 9.5.)
+  __shared__ int l_par[GR_LDS_ROWS];
+  bool chased = false;  // `cur` is where the walk ends, l_par holds the tree
+  constexpr int PRE = AC_MAX_ROWS / AC_THREADS;
+  double pre[PRE];      // then: its row sums, requested before its children are looked at
+  const int n_rows = (V + 63) / 64;
   if (ratio_mode && n <= GR_LDS_ROWS) {
     __shared__ int first_acc[GR_LDS_ROWS], stop[2];
     for (int i = tid; i < n; i += AC_THREADS) first_acc[i] = INT_MAX;
     __syncthreads();
     bool many = false;
     for (int i = tid; i < n; i += AC_THREADS) {
-      many = many || chain.n_tried[o + i] >= AC_MAX_KIDS;  // (there may be children that no test is tried on)
-      if (i > 0) {
-        // (below the last level that is tried the probabilities are undefined; the chase does not go there)
-        const double pc = chain.child_p[o + i], qc = chain.child_q[o + i];
-        if (pc >= qc || (double)uniforms[o + i] * qc < pc) atomicMin(&first_acc[parent[o + i]], i);
-      }
+      const int tried = chain.n_tried[o + i], up = parent[o + i];
+      // (below the last level that is tried the probabilities are undefined; the chase does not go there)
+      const double pc = chain.child_p[o + i], qc = chain.child_q[o + i], u = (double)uniforms[o + i];
+      many = many || tried >= AC_MAX_KIDS;  // (there may be children that no test is tried on)
+      l_par[i] = up;
+      if (i > 0 && (pc >= qc || u * qc < pc)) atomicMin(&first_acc[up], i);
     }
     if (!__syncthreads_or(many ? 1 : 0)) {
       if (tid == 0) {
@@ -1026,10 +1092,18 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
       __syncthreads();
       cur = stop[0];
       len = stop[1];
+      chased = true;
+      if (chain.bonus_rows != nullptr) {
+        const double* __restrict__ sums = chain.bonus_rows + (int64_t)(o + cur) * n_rows;
+#pragma unroll
+        for (int k = 0; k < PRE; ++k)
+          if (k * AC_THREADS < n_rows) pre[k] = sums[min(tid + k * AC_THREADS, n_rows - 1)];
+      }
     }
   }
   for (;;) {
-    const int nk = gather_children(parent, o, n, cur, len < max_depth, kids, kids_sorted, &n_kids);
+    const int nk = chased ? gather_children(l_par, 0, n, cur, len < max_depth, kids, kids_sorted, &n_kids)
+                          : gather_children(parent, o, n, cur, len < max_depth, kids, kids_sorted, &n_kids);
 
     const float* p_row = target + (int64_t)(o + cur) * row_stride;
     const RowView p(p_row, p_row[t_arg[o + cur]], t_lz[o + cur], inv_t);
@@ -1094,10 +1168,13 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
     const bool sub_q = use_q && n_rej > 0;
     const double total = ratio_mode ? Z : rem;
     const double goal = (double)uniforms[NN + s] * total;
-    const int n_rows = (V + 63) / 64;
-    if (chain.bonus_rows != nullptr) {  // summed ahead of the walk, for every row (k_bonus_rows)
-      const double* __restrict__ pre = chain.bonus_rows + (int64_t)(o + cur) * n_rows;
-      for (int r = tid; r < n_rows; r += AC_THREADS) rowsum[r] = pre[r];
+    if (chased && chain.bonus_rows != nullptr) {
+#pragma unroll
+      for (int k = 0; k < PRE; ++k)
+        if (tid + k * AC_THREADS < n_rows) rowsum[tid + k * AC_THREADS] = pre[k];
+    } else if (chain.bonus_rows != nullptr) {  // summed ahead of the walk, for every row (k_bonus_rows)
+      const double* __restrict__ sums = chain.bonus_rows + (int64_t)(o + cur) * n_rows;
+      for (int r = tid; r < n_rows; r += AC_THREADS) rowsum[r] = sums[r];
     } else {
       bonus_row_sums(p, q, sub_q, beta, V, 0, n_rows, rowsum);
     }
@@ -1113,7 +1190,7 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
     for (int c = wave; c < n_chunks; c += AC_WAVES) {
       const int r = c * 64 + lane;
       const double val = r < n_rows ? rowsum[r] : 0.0;
-      const double tot = wave_sum(val);
+      const double tot = wave_sum_dpp(val);
       const unsigned long long pos = __ballot(r < n_rows && val > 0.0);
       if (lane == 0) {
         chunk_tot[c] = tot;
