@@ -12,5 +12,6 @@ _BINDING = ("hs_draft_entropy_topk", "hs_workspace_prepare", "hs_tree_prune", "h
 def __getattr__(name):
     if name in _BINDING:
         from . import binding
-        return getattr(binding, name)
+        globals()[name] = value = getattr(binding, name)  # (found here from now on)
+        return value
     raise AttributeError(name)

@@ -1,4 +1,4 @@
-"""ctypes binding of libheterospec.so: argument marshalling only.
+"""Binding of libheterospec.so: argument marshalling only.
 
 Every function has the name and the arguments of the C entry point it calls (see
 include/heterospec.h); tensors are torch tensors on the GPU, used purely as device memory.
@@ -7,6 +7,7 @@ There is no CPU path: if the library is not built, importing this module's funct
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Dict, Optional
 
@@ -14,6 +15,7 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libheterospec.so")
+MARSHAL_PATH = os.path.join(_PKG, "_marshal.so")
 
 HS_F32, HS_BF16 = 0, 1
 HS_ERR_WORKSPACE = 4
@@ -99,19 +101,30 @@ def _check(status: int, where: str):
         raise HsError(status, where, lib().hs_last_error().decode())
 
 
-# The short calls are bound by what happens here: addresses go to ctypes as plain integers (the declared
-# argument types convert them), the current stream's handle is asked for without building a Stream object,
-# and host arrays that already have the right type are passed as they are (one attention call 17.6 us of host
-# time with objects and copies, 13 us now).
+class _Calls:
+    """The library's calls as functions of tensors and numbers (csrc/marshal.cpp): one native function checks the
+    tensors, takes their addresses and makes the call, which returns its status.  The short calls are bound by
+    what happens on the host (four calls of a tiny step: 31.9 us checked and converted in Python, now 19.6)."""
+    _module = None
+
+    def __getattr__(self, name):
+        address = ctypes.cast(getattr(lib(), name), _vp).value
+        if _Calls._module is None:
+            if not os.path.exists(MARSHAL_PATH):
+                raise RuntimeError("_marshal.so is not built: run `python -m paper_2505_13254_amd.build` first")
+            spec = importlib.util.spec_from_file_location(__package__ + "._marshal", MARSHAL_PATH)
+            _Calls._module = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(_Calls._module)
+        fn = _Calls._module.function(name, address)
+        setattr(self, name, fn)
+        return fn
+
+
+_calls = _Calls()
+
+
 def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
-
-
-def _host(t: torch.Tensor, dtype) -> torch.Tensor:
-    """`t` as a contiguous CPU tensor of type dtype."""
-    if t.dtype is dtype and t.device.type == "cpu" and t.is_contiguous():
-        return t
-    return t.to(dtype=dtype, device="cpu").contiguous()
 
 
 def _dev(t: torch.Tensor, dtype, name: str) -> torch.Tensor:
@@ -154,31 +167,30 @@ def hs_draft_entropy_topk(logits: torch.Tensor, K: int, temperature: float = 1.0
     N, V = logits.shape
     R = N
     if row_index is not None:
-        _dev(row_index, torch.int32, "row_index")
         R = row_index.numel()
-    dev = logits.device
     if out is None:
+        dev = logits.device
         out = dict(topk_idx=torch.empty((R, K), dtype=torch.int32, device=dev),
                    topk_logp=torch.empty((R, K), dtype=torch.float32, device=dev),
                    ent_topk=torch.empty(R, dtype=torch.float32, device=dev))
         if want_full:
             out["ent_full"] = torch.empty(R, dtype=torch.float32, device=dev)
             out["lse"] = torch.empty(R, dtype=torch.float32, device=dev)
-    need = lib().hs_draft_entropy_topk_workspace(R, V, K)
     if ws is None and not fused:
-        ws = workspace(need, dev)
+        ws = workspace(lib().hs_draft_entropy_topk_workspace(R, V, K), logits.device)
     stride = logits.stride(0) if N > 1 else max(V, logits.stride(0))
-    tail = (_ptr(out["topk_idx"]), _ptr(out["topk_logp"]), _ptr(out["ent_topk"]), _ptr(out.get("ent_full")),
-            _ptr(out.get("lse")), _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream))
+    tail = (R, V, K, temperature, out["topk_idx"], out["topk_logp"], out["ent_topk"], out.get("ent_full"), out.get("lse"), ws,
+            stream)
     if fused:
-        st = HS_ERR_WORKSPACE if ws is None else lib().hs_draft_entropy_topk_fused(
-            _ptr(logits), stride, _ptr(row_index), R, V, K, float(temperature), *tail)
-        if st == HS_ERR_WORKSPACE and (ws is None or ws.numel() < need):
-            raise ValueError("the fused call needs a prepared workspace of at least %d bytes" % need)
+        st = HS_ERR_WORKSPACE if ws is None else _calls.hs_draft_entropy_topk_fused(logits, stride, row_index, *tail)
+        if st == HS_ERR_WORKSPACE:
+            need = lib().hs_draft_entropy_topk_workspace(R, V, K)
+            if ws is None or ws.numel() < need:
+                raise ValueError("the fused call needs a prepared workspace of at least %d bytes" % need)
     elif row_index is None:
-        st = lib().hs_draft_entropy_topk(_ptr(logits), stride, R, V, K, float(temperature), *tail)
+        st = _calls.hs_draft_entropy_topk(logits, stride, *tail)
     else:
-        st = lib().hs_draft_entropy_topk_rows(_ptr(logits), stride, _ptr(row_index), R, V, K, float(temperature), *tail)
+        st = _calls.hs_draft_entropy_topk_rows(logits, stride, row_index, *tail)
     _check(st, "hs_draft_entropy_topk")
     return out
 
@@ -191,14 +203,9 @@ def hs_tree_prune(parent: torch.Tensor, logc: torch.Tensor, node_offsets: torch.
     d_max int32 [B], theta float32 [B], max_nodes int32 [B].  Returns depth, cumlogp, keep, out_offsets,
     out_src, out_parent (the last two sized NN; the first out_offsets[B] entries are valid).
     With node_counts int32 [B] the call is hs_tree_prune_counted (trees stored with spare capacity)."""
-    if node_counts is not None:
-        _dev(node_counts, torch.int32, "node_counts")
-    _dev(parent, torch.int32, "parent"); _dev(logc, torch.float32, "logc")
-    _dev(node_offsets, torch.int32, "node_offsets"); _dev(d_max, torch.int32, "d_max")
-    _dev(theta, torch.float32, "theta"); _dev(max_nodes, torch.int32, "max_nodes")
     NN, B = parent.numel(), node_offsets.numel() - 1
-    dev = parent.device
     if out is None:
+        dev = parent.device
         out = dict(depth=torch.empty(NN, dtype=torch.int32, device=dev),
                    cumlogp=torch.empty(NN, dtype=torch.float32, device=dev),
                    keep=torch.empty(NN, dtype=torch.uint8, device=dev),
@@ -206,14 +213,13 @@ def hs_tree_prune(parent: torch.Tensor, logc: torch.Tensor, node_offsets: torch.
                    out_src=torch.empty(max(NN, 1), dtype=torch.int32, device=dev),
                    out_parent=torch.empty(max(NN, 1), dtype=torch.int32, device=dev))
     if ws is None:
-        ws = workspace(lib().hs_tree_prune_workspace(B, NN), dev)
-    tail = (_ptr(d_max), _ptr(theta), _ptr(max_nodes), _ptr(out["depth"]), _ptr(out["cumlogp"]), _ptr(out["keep"]),
-            _ptr(out["out_offsets"]), _ptr(out["out_src"]), _ptr(out["out_parent"]),
-            _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream))
+        ws = workspace(lib().hs_tree_prune_workspace(B, NN), parent.device)
+    tail = (B, NN, d_max, theta, max_nodes, out["depth"], out["cumlogp"], out["keep"], out["out_offsets"], out["out_src"],
+            out["out_parent"], ws, stream)
     if node_counts is None:
-        st = lib().hs_tree_prune(_ptr(parent), _ptr(logc), _ptr(node_offsets), B, NN, *tail)
+        st = _calls.hs_tree_prune(parent, logc, node_offsets, *tail)
     else:
-        st = lib().hs_tree_prune_counted(_ptr(parent), _ptr(logc), _ptr(node_offsets), _ptr(node_counts), B, NN, *tail)
+        st = _calls.hs_tree_prune_counted(parent, logc, node_offsets, node_counts, *tail)
     _check(st, "hs_tree_prune")
     return out
 
@@ -251,23 +257,13 @@ def hs_tree_expand(state: Dict[str, torch.Tensor], topk_idx, topk_logp, ent_topk
                    K: int, first: bool, *, stream=None) -> Dict[str, torch.Tensor]:
     """state: the tensors of new_tree_state(); topk_idx int32 [B*F, K], topk_logp float32 [B*F, K], ent_topk
     float32 [B*F] (hs_draft_entropy_topk's results for the frontier slots); d_limit int32 [B] or None."""
-    _dev(topk_idx, torch.int32, "topk_idx"); _dev(topk_logp, torch.float32, "topk_logp")
-    _dev(ent_topk, torch.float32, "ent_topk")
     if topk_idx.numel() < B * F * K or ent_topk.numel() < B * F:
         raise ValueError("Top-K results must cover B * F frontier slots")
-    if d_limit is not None:
-        _dev(d_limit, torch.int32, "d_limit")
-    for k in ("parent", "token", "depth", "n_nodes", "level", "frontier", "n_frontier", "frontier_rows"):
-        _dev(state[k], torch.int32, k)
-    for k in ("logc", "cumlogp", "ent"):
-        _dev(state[k], torch.float32, k)
     if state["parent"].numel() < B * cap or state["frontier"].numel() < B * F:
         raise ValueError("state arrays are smaller than B * cap / B * F")
-    st = lib().hs_tree_expand(_ptr(state["parent"]), _ptr(state["token"]), _ptr(state["logc"]), _ptr(state["cumlogp"]),
-                              _ptr(state["depth"]), _ptr(state["ent"]), _ptr(state["n_nodes"]), _ptr(state["level"]),
-                              _ptr(state["frontier"]), _ptr(state["n_frontier"]), _ptr(state["frontier_rows"]),
-                              _ptr(topk_idx), _ptr(topk_logp), _ptr(ent_topk), _ptr(d_limit), B, cap, F, K,
-                              1 if first else 0, _stream(stream))
+    st = _calls.hs_tree_expand(state["parent"], state["token"], state["logc"], state["cumlogp"], state["depth"], state["ent"],
+                               state["n_nodes"], state["level"], state["frontier"], state["n_frontier"], state["frontier_rows"],
+                               topk_idx, topk_logp, ent_topk, d_limit, B, cap, F, K, 1 if first else 0, stream)
     _check(st, "hs_tree_expand")
     return state
 
@@ -278,22 +274,15 @@ def hs_adaptive_control(parent, logc, ent, node_offsets, node_counts, bin_edges,
     """parent int32 [NN], logc / ent float32 [NN], node_offsets int32 [B+1], node_counts int32 [B] or None (GPU);
     bin_edges (ascending, n_bins - 1 values) and gamma are host sequences of floats.
     Returns phi float32 [B] and pstar, bin, d_prime, n_prime int32 [B]."""
-    _dev(parent, torch.int32, "parent"); _dev(logc, torch.float32, "logc"); _dev(ent, torch.float32, "ent")
-    _dev(node_offsets, torch.int32, "node_offsets")
-    if node_counts is not None:
-        _dev(node_counts, torch.int32, "node_counts")
     B, NN = node_offsets.numel() - 1, parent.numel()
-    dev = parent.device
-    edges = (_f32 * max(1, len(bin_edges)))(*[float(x) for x in bin_edges])
-    gam = (_f32 * max(1, len(gamma)))(*[float(x) for x in gamma])
     if out is None:
+        dev = parent.device
         out = dict(phi=torch.empty(B, dtype=torch.float32, device=dev))
         for k in ("pstar", "bin", "d_prime", "n_prime"):
             out[k] = torch.empty(B, dtype=torch.int32, device=dev)
-    st = lib().hs_adaptive_control(_ptr(parent), _ptr(logc), _ptr(ent), _ptr(node_offsets), _ptr(node_counts), B, NN,
-                                   _c.cast(edges, _vp), len(bin_edges) + 1, _c.cast(gam, _vp), len(gamma), int(alpha),
-                                   int(d_base), int(n_default), int(mode), _ptr(out["phi"]), _ptr(out["pstar"]),
-                                   _ptr(out["bin"]), _ptr(out["d_prime"]), _ptr(out["n_prime"]), _stream(stream))
+    st = _calls.hs_adaptive_control(parent, logc, ent, node_offsets, node_counts, B, NN, bin_edges, len(bin_edges) + 1, gamma,
+                                    len(gamma), int(alpha), int(d_base), int(n_default), int(mode), out["phi"], out["pstar"],
+                                    out["bin"], out["d_prime"], out["n_prime"], stream)
     _check(st, "hs_adaptive_control")
     return out
 
@@ -329,37 +318,27 @@ def hs_tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, parent, node_offset
     hs_tree_attention_lens: prefix_offsets then delimit cache regions with spare capacity.
     shared_tree: the call is hs_tree_attention_shared_tree: parent int32 [M] is one tree that all B entries
     (of M rows each) use."""
-    dt = _dtype_code(q)
-    for name, t in (("q", q), ("k_prefix", k_prefix), ("v_prefix", v_prefix), ("k_tree", k_tree), ("v_tree", v_tree)):
-        _dev(t, q.dtype, name)
-    _dev(parent, torch.int32, "parent"); _dev(node_offsets, torch.int32, "node_offsets")
-    _dev(prefix_offsets, torch.int64, "prefix_offsets")
-    hno = _host(host_node_offsets, torch.int32)
-    hpo = _host(host_prefix_offsets, torch.int64)
     NN, Hq, D = q.shape
     Hkv = k_tree.shape[1]
-    B = hno.numel() - 1
-    dev = q.device
+    B = host_node_offsets.numel() - 1
     if out is None:
         out = torch.empty_like(q)
     if want_lse and lse is None:
-        lse = torch.empty((NN, Hq), dtype=torch.float32, device=dev)
+        lse = torch.empty((NN, Hq), dtype=torch.float32, device=q.device)
     if ws is None:
-        ws = workspace(lib().hs_tree_attention_workspace(B, NN, int(hpo[-1]), Hq, Hkv, D, dt), dev)
-    head = (_ptr(q), _ptr(k_prefix), _ptr(v_prefix), _ptr(k_tree), _ptr(v_tree), _ptr(parent),
-            _ptr(node_offsets), _ptr(prefix_offsets), hno.data_ptr(), hpo.data_ptr())
-    tail = (B, Hq, Hkv, D, dt, float(scale), _ptr(out), _ptr(lse), _ptr(ws), 0 if ws is None else ws.numel(),
-            _stream(stream))
+        ws = workspace(lib().hs_tree_attention_workspace(B, NN, int(host_prefix_offsets[-1]), Hq, Hkv, D, _dtype_code(q)), q.device)
     if shared_tree:
         if prefix_lens is not None:
             raise ValueError("shared_tree and prefix_lens cannot be combined")
-        st = lib().hs_tree_attention_shared_tree(*head, *tail)
+        st = _calls.hs_tree_attention_shared_tree(q, k_prefix, v_prefix, k_tree, v_tree, parent, node_offsets, prefix_offsets,
+                                                  host_node_offsets, host_prefix_offsets, B, Hq, Hkv, D, scale, out, lse, ws, stream)
     elif prefix_lens is None:
-        st = lib().hs_tree_attention(*head, *tail)
+        st = _calls.hs_tree_attention(q, k_prefix, v_prefix, k_tree, v_tree, parent, node_offsets, prefix_offsets,
+                                      host_node_offsets, host_prefix_offsets, B, Hq, Hkv, D, scale, out, lse, ws, stream)
     else:
-        _dev(prefix_lens, torch.int64, "prefix_lens")
-        hl = _host(host_prefix_lens, torch.int64)
-        st = lib().hs_tree_attention_lens(*head, _ptr(prefix_lens), hl.data_ptr(), *tail)
+        st = _calls.hs_tree_attention_lens(q, k_prefix, v_prefix, k_tree, v_tree, parent, node_offsets, prefix_offsets,
+                                           host_node_offsets, host_prefix_offsets, prefix_lens, host_prefix_lens, B, Hq, Hkv, D,
+                                           scale, out, lse, ws, stream)
     _check(st, "hs_tree_attention")
     return out, lse
 
@@ -371,30 +350,20 @@ def hs_tree_attention_paged(q, k_pages, v_pages, k_tree, v_tree, parent, node_of
     """q [NN,Hq,D]; k_pages, v_pages [n_pages, page_tokens, Hkv, D]; k_tree, v_tree [NN,Hkv,D]; parent int32 [NN],
     node_offsets int32 [B+1], block_table int32 [B, max_blocks], prefix_lens int64 [B] on the GPU;
     host_node_offsets and host_prefix_lens the same on the CPU.  Returns (o, lse or None)."""
-    dt = _dtype_code(q)
-    for name, t in (("q", q), ("k_pages", k_pages), ("v_pages", v_pages), ("k_tree", k_tree), ("v_tree", v_tree)):
-        _dev(t, q.dtype, name)
-    _dev(parent, torch.int32, "parent"); _dev(node_offsets, torch.int32, "node_offsets")
-    _dev(block_table, torch.int32, "block_table"); _dev(prefix_lens, torch.int64, "prefix_lens")
-    hno = _host(host_node_offsets, torch.int32)
-    hl = _host(host_prefix_lens, torch.int64)
     NN, Hq, D = q.shape
     Hkv = k_tree.shape[1]
-    B = hno.numel() - 1
+    B = host_node_offsets.numel() - 1
     if block_table.dim() != 2 or block_table.shape[0] != B or k_pages.dim() != 4:
         raise ValueError("block_table must be [B, max_blocks] and the pools [n_pages, page_tokens, Hkv, D]")
-    dev = q.device
     if out is None:
         out = torch.empty_like(q)
     if want_lse and lse is None:
-        lse = torch.empty((NN, Hq), dtype=torch.float32, device=dev)
+        lse = torch.empty((NN, Hq), dtype=torch.float32, device=q.device)
     if ws is None:
-        ws = workspace(lib().hs_tree_attention_workspace(B, NN, int(hl.sum()), Hq, Hkv, D, dt), dev)
-    st = lib().hs_tree_attention_paged(_ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(k_tree), _ptr(v_tree), _ptr(parent),
-                                       _ptr(node_offsets), hno.data_ptr(), _ptr(block_table), block_table.shape[1],
-                                       k_pages.shape[1], _ptr(prefix_lens), hl.data_ptr(), B, Hq, Hkv, D, dt,
-                                       float(scale), _ptr(out), _ptr(lse), _ptr(ws), 0 if ws is None else ws.numel(),
-                                       _stream(stream))
+        ws = workspace(lib().hs_tree_attention_workspace(B, NN, int(host_prefix_lens.sum()), Hq, Hkv, D, _dtype_code(q)), q.device)
+    st = _calls.hs_tree_attention_paged(q, k_pages, v_pages, k_tree, v_tree, parent, node_offsets, host_node_offsets, block_table,
+                                        block_table.shape[1], k_pages.shape[1], prefix_lens, host_prefix_lens, B, Hq, Hkv, D,
+                                        scale, out, lse, ws, stream)
     _check(st, "hs_tree_attention_paged")
     return out, lse
 
@@ -403,17 +372,10 @@ def hs_kv_commit_paged(k_tree, v_tree, node_offsets, accept_path, accept_len, k_
                        *, stream=None):
     """As hs_kv_commit, into pools k_pages, v_pages [n_pages, page_tokens, Hkv, D] through block_table int32
     [B, max_blocks]; cache_lens int64 [B] is updated in place."""
-    dt = _dtype_code(k_tree)
-    for name, t in (("k_tree", k_tree), ("v_tree", v_tree), ("k_pages", k_pages), ("v_pages", v_pages)):
-        _dev(t, k_tree.dtype, name)
-    _dev(node_offsets, torch.int32, "node_offsets"); _dev(accept_path, torch.int32, "accept_path")
-    _dev(accept_len, torch.int32, "accept_len"); _dev(block_table, torch.int32, "block_table")
-    _dev(cache_lens, torch.int64, "cache_lens")
-    B = node_offsets.numel() - 1
     Hkv, D = k_tree.shape[1], k_tree.shape[2]
-    st = lib().hs_kv_commit_paged(_ptr(k_tree), _ptr(v_tree), _ptr(node_offsets), _ptr(accept_path), _ptr(accept_len),
-                                  accept_path.shape[1], _ptr(k_pages), _ptr(v_pages), _ptr(block_table),
-                                  block_table.shape[1], k_pages.shape[1], _ptr(cache_lens), B, Hkv, D, dt, _stream(stream))
+    st = _calls.hs_kv_commit_paged(k_tree, v_tree, node_offsets, accept_path, accept_len, accept_path.shape[1], k_pages, v_pages,
+                                   block_table, block_table.shape[1], k_pages.shape[1], cache_lens, node_offsets.numel() - 1,
+                                   Hkv, D, stream)
     _check(st, "hs_kv_commit_paged")
     return cache_lens
 
@@ -423,19 +385,12 @@ def hs_kv_commit(k_tree, v_tree, node_offsets, accept_path, accept_len, k_cache,
     """k_tree, v_tree [NN,Hkv,D] and k_cache, v_cache [capacity,Hkv,D] of one element type; node_offsets int32
     [B+1], accept_path int32 [B,max_depth], accept_len int32 [B], cache_offsets int64 [B+1], cache_lens int64
     [B] (updated in place); all on the GPU."""
-    dt = _dtype_code(k_tree)
-    for name, t in (("k_tree", k_tree), ("v_tree", v_tree), ("k_cache", k_cache), ("v_cache", v_cache)):
-        _dev(t, k_tree.dtype, name)
-    _dev(node_offsets, torch.int32, "node_offsets"); _dev(accept_path, torch.int32, "accept_path")
-    _dev(accept_len, torch.int32, "accept_len"); _dev(cache_offsets, torch.int64, "cache_offsets")
-    _dev(cache_lens, torch.int64, "cache_lens")
     B = node_offsets.numel() - 1
     if accept_path.dim() != 2 or accept_path.shape[0] != B or accept_len.numel() != B or cache_lens.numel() != B:
         raise ValueError("accept_path must be [B, max_depth]; accept_len and cache_lens [B]")
     Hkv, D = k_tree.shape[1], k_tree.shape[2]
-    st = lib().hs_kv_commit(_ptr(k_tree), _ptr(v_tree), _ptr(node_offsets), _ptr(accept_path), _ptr(accept_len),
-                            accept_path.shape[1], _ptr(k_cache), _ptr(v_cache), _ptr(cache_offsets), _ptr(cache_lens),
-                            B, Hkv, D, dt, _stream(stream))
+    st = _calls.hs_kv_commit(k_tree, v_tree, node_offsets, accept_path, accept_len, accept_path.shape[1], k_cache, v_cache,
+                             cache_offsets, cache_lens, B, Hkv, D, stream)
     _check(st, "hs_kv_commit")
     return cache_lens
 
@@ -454,26 +409,21 @@ def hs_verify_accept(target_logits, draft_logits, token, parent, node_offsets, m
     row_stride = rows(target_logits, "target_logits")
     NN, V = target_logits.shape
     B = node_offsets.numel() - 1
-    dev = target_logits.device
     if draft_logits is not None:
         if draft_logits.shape != target_logits.shape or rows(draft_logits, "draft_logits") != row_stride:
             raise ValueError("draft_logits must have the shape and row stride of target_logits")
-    if uniforms is not None:
-        _dev(uniforms, torch.float32, "uniforms")
-        if uniforms.numel() != NN + B:
-            raise ValueError("uniforms must hold NN + B values")
-    _dev(token, torch.int32, "token"); _dev(parent, torch.int32, "parent")
-    _dev(node_offsets, torch.int32, "node_offsets")
+    if uniforms is not None and uniforms.numel() != NN + B:
+        raise ValueError("uniforms must hold NN + B values")
     if out is None:
+        dev = target_logits.device
         out = dict(accept_len=torch.empty(B, dtype=torch.int32, device=dev),
                    accept_path=torch.empty((B, max_depth), dtype=torch.int32, device=dev),
                    bonus_token=torch.empty(B, dtype=torch.int32, device=dev))
     if ws is None:
-        ws = workspace(lib().hs_verify_accept_workspace_mode(B, NN, V, int(mode)), dev)
-    st = lib().hs_verify_accept(_ptr(target_logits), _ptr(draft_logits), row_stride, _ptr(token), _ptr(parent),
-                                _ptr(node_offsets), B, NN, V, int(mode), float(temperature), _ptr(uniforms),
-                                int(max_depth), _ptr(out["accept_len"]), _ptr(out["accept_path"]),
-                                _ptr(out["bonus_token"]), _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream))
+        ws = workspace(lib().hs_verify_accept_workspace_mode(B, NN, V, int(mode)), target_logits.device)
+    st = _calls.hs_verify_accept(target_logits, draft_logits, row_stride, token, parent, node_offsets, B, NN, V, int(mode),
+                                 temperature, uniforms, int(max_depth), out["accept_len"], out["accept_path"],
+                                 out["bonus_token"], ws, stream)
     _check(st, "hs_verify_accept")
     return out
 
