@@ -272,34 +272,43 @@ __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
   }
 }
 
-// Merges the splits of one (node, head) row: weights exp(m_sp - max m), splits taken in rising
-// order.  One wave per row, lane l owns D / 64 adjacent output elements
-constexpr int CMB_ROWS = 4;  // rows (waves) per workgroup
+// Merges the splits of a (node, head) row: weights exp(m_sp - max m), splits taken in rising order, eight at a time.
+// D / 4 lanes to a row, four output elements each.  A workgroup has rows of one node, whose split count is a scalar,
+// and of every CMB_UNITS-th KV head: workgroup x of a launch runs on XCD x % 8, so with a multiple of eight KV heads it
+// merges records that its own XCD has written (all heads of a node spread over the XCDs: 4.2 us a launch became 6.3).
+// The launch is a chain of trips to memory: the arguments, the table (a single entry's count is an argument), then
+// everything of eight splits at once.
+constexpr int CMB_UNITS = 8;
+constexpr int CMB_THREADS = 256;  // at most
 template <typename T, int D>
-__global__ __launch_bounds__(64 * CMB_ROWS) void k_attn_combine(AttnArgs a, int64_t n_rows) {
+__global__ __launch_bounds__(CMB_THREADS) void k_attn_combine(AttnArgs a) {
+  constexpr int LPR = D / 4;  // lanes of a row
+  constexpr int REC = D + ATTN_REC_PAD;
+  constexpr int AT_ONCE = 8;
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)a.cmb_row0 * a.Hq + (int64_t)blockIdx.x * CMB_ROWS + (threadIdx.x >> 6);  // node_global * Hq + h
-  if (row >= n_rows) return;
-  const int node = (int)(row / a.Hq);
-  int n_sp;
-  if (a.n_tbl > 0) {
+  // (all in one batch, as in the matrix-core kernel)
+  const int n_tbl = a.n_tbl, n_sp0 = a.tbl[0].n_sp, row0 = a.cmb_row0, Hkv = a.Hkv, G = a.G, Hq = a.Hq, sp_max = a.sp_max;
+  const float* const part = a.part;
+  void* const out = a.o;
+  float* const lse = a.lse;
+  asm volatile("" ::"s"(n_tbl), "s"(n_sp0), "s"(row0), "s"(Hkv), "s"(G), "s"(Hq), "s"(sp_max), "s"(part), "s"(out), "s"(lse), "s"(a.half));
+  const int units = Hkv < CMB_UNITS ? Hkv : CMB_UNITS;
+  const int node = row0 + (int)blockIdx.x / units, unit = (int)blockIdx.x % units;
+  int n_sp = n_sp0;
+  if (n_tbl > 1) {
     // the table entry whose row range holds this node
     n_sp = 1;
-    for (int base = 0; base < a.n_tbl; base += 64) {
+    for (int base = 0; base < n_tbl; base += 64) {
       const int idx = base + lane;
-      bool mine = false;
-      int cnt = 0;
-      if (idx < a.n_tbl) {
-        mine = node >= a.tbl[idx].n0 && node < a.tbl[idx].n0 + a.tbl[idx].M;
-        cnt = a.tbl[idx].n_sp;
-      }
-      const unsigned long long hit = __ballot(mine);
+      const int at = idx < n_tbl ? idx : n_tbl - 1;
+      const int n0 = a.tbl[at].n0, M = a.tbl[at].M, cnt = a.tbl[at].n_sp;
+      const unsigned long long hit = __ballot((node >= n0) & (node < n0 + M));
       if (hit != 0ull) {
         n_sp = __builtin_amdgcn_readlane(cnt, __builtin_ctzll(hit));
         break;
       }
     }
-  } else {
+  } else if (n_tbl == 0) {
     // sequence of this node: last s with node_offsets[s] <= node
     int lo = 0, hi = a.B;
     while (hi - lo > 1) {
@@ -309,39 +318,46 @@ __global__ __launch_bounds__(64 * CMB_ROWS) void k_attn_combine(AttnArgs a, int6
     n_sp = splits_of(prefix_len_of(a, lo), a.split_len);
   }
   if (n_sp == 1) return;  // written directly by the attention kernel
-  constexpr int REC = D + ATTN_REC_PAD;
-  const float* rec = a.part + row * a.sp_max * REC;
-  // lane sp holds split sp's reference maximum and denominator (at most 64 splits): one trip to memory
-  // for all of them, then the splits' rows four at a time
-  float mv = -HS_INF, lv = 0.f;
-  if (lane < n_sp) {
-    mv = rec[lane * REC + D];
-    lv = rec[lane * REC + D + 1];
-  }
-  const float m = wave_max(mv);
-  const float w = lane < n_sp ? __expf(mv - m) : 0.f;
-  const float l = wave_sum(lv * w);
-  constexpr int DPL = D / 64;
-  float o[DPL];
+  const int d = (int)threadIdx.x % LPR * 4;
+  const int rows = (Hkv - unit + CMB_UNITS - 1) / CMB_UNITS * G;  // of this workgroup
+  for (int j = (int)threadIdx.x / LPR; j < rows; j += (int)blockDim.x / LPR) {
+    const int64_t row = (int64_t)node * Hq + (unit + j / G * CMB_UNITS) * G + j % G;
+    const float* rec = part + row * sp_max * REC;
+    float m = -HS_INF, l = 0.f;
+    float4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int sp0 = 0; sp0 < n_sp; sp0 += AT_ONCE, rec += AT_ONCE * REC) {
+      float2 ml[AT_ONCE];  // reference maximum and denominator, the same for all lanes of the row
+      float4 v[AT_ONCE];
 #pragma unroll
-  for (int dd = 0; dd < DPL; ++dd) o[dd] = 0.f;
-  for (int sp0 = 0; sp0 < n_sp; sp0 += 4) {
-    float v[4][DPL];
+      for (int u = 0; u < AT_ONCE; ++u) {
+        ml[u] = make_float2(-HS_INF, 0.f);
+        v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (sp0 + u < n_sp) {
+          ml[u] = *reinterpret_cast<const float2*>(rec + u * REC + D);
+          v[u] = *reinterpret_cast<const float4*>(rec + u * REC + d);
+        }
+      }
+      float top = m;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < AT_ONCE; ++u) top = fmaxf(top, ml[u].x);
+      const float f = __expf(m - top);  // (0 at the first eight)
+      m = top;
+      l *= f;
+      o = make_float4(o.x * f, o.y * f, o.z * f, o.w * f);
 #pragma unroll
-      for (int dd = 0; dd < DPL; ++dd) v[u][dd] = sp0 + u < n_sp ? rec[(sp0 + u) * REC + lane * DPL + dd] : 0.f;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float wu = __shfl(w, (sp0 + u) & 63);  // (0 beyond the last split)
-#pragma unroll
-      for (int dd = 0; dd < DPL; ++dd) o[dd] = fmaf(v[u][dd], wu, o[dd]);
+      for (int u = 0; u < AT_ONCE; ++u) {
+        const float w = __expf(ml[u].x - m);  // (0 beyond the last split)
+        l = fmaf(ml[u].y, w, l);
+        o.x = fmaf(v[u].x, w, o.x);
+        o.y = fmaf(v[u].y, w, o.y);
+        o.z = fmaf(v[u].z, w, o.z);
+        o.w = fmaf(v[u].w, w, o.w);
+      }
     }
+    const float inv = 1.f / l;
+    store4<T>(static_cast<T*>(out) + row * D + d, make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv));
+    if (lse && d == 0) lse[row] = m + __logf(l);
   }
-  const float inv = 1.f / l;
-#pragma unroll
-  for (int dd = 0; dd < DPL; ++dd) store_elem<T>(static_cast<T*>(a.o) + row * D + lane * DPL + dd, o[dd] * inv);
-  if (a.lse && lane == 0) a.lse[row] = m + __logf(l);
 }
 
 constexpr int PLAN_CUS = 256;
@@ -962,13 +978,13 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
     last_kernel = 2;
   }
   if (a.sp_max > 1) {
-    const int64_t n_rows = (int64_t)NN * Hq;
-    const int64_t merged = n_rows - (int64_t)a.cmb_row0 * Hq;
-    dim3 grid((unsigned)((merged + CMB_ROWS - 1) / CMB_ROWS)), block(64 * CMB_ROWS);
-    if (dt == HS_F32 && D == 64) hipLaunchKernelGGL((k_attn_combine<float, 64>), grid, block, 0, st, a, n_rows);
-    else if (dt == HS_F32) hipLaunchKernelGGL((k_attn_combine<float, 128>), grid, block, 0, st, a, n_rows);
-    else if (D == 64) hipLaunchKernelGGL((k_attn_combine<bf16_t, 64>), grid, block, 0, st, a, n_rows);
-    else hipLaunchKernelGGL((k_attn_combine<bf16_t, 128>), grid, block, 0, st, a, n_rows);
+    const int units = std::min(a.Hkv, CMB_UNITS);
+    const int rows = (a.Hkv + CMB_UNITS - 1) / CMB_UNITS * a.G;  // of a workgroup
+    dim3 grid((unsigned)(NN - a.cmb_row0) * units), block((unsigned)std::min((rows * (D / 4) + 63) / 64 * 64, CMB_THREADS));
+    if (dt == HS_F32 && D == 64) hipLaunchKernelGGL((k_attn_combine<float, 64>), grid, block, 0, st, a);
+    else if (dt == HS_F32) hipLaunchKernelGGL((k_attn_combine<float, 128>), grid, block, 0, st, a);
+    else if (D == 64) hipLaunchKernelGGL((k_attn_combine<bf16_t, 64>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((k_attn_combine<bf16_t, 128>), grid, block, 0, st, a);
     return launch_status("tree attention combine");
   }
   return HS_OK;
