@@ -42,8 +42,8 @@ constexpr int MAX_TREE_ROWS = 1024;
 // The contraction order is free, so K, Q and V go from global memory into operand registers 16 bytes at
 // a time and nothing is staged in LDS; output column block b holds columns i * D / 16 + b.
 // (One row group of four rows per wave on the vector ALUs, K and V staged through LDS, five LDS reads to
-// four multiply-adds: three sequences of 100 to 1500 tokens, 8 heads of 64, 17 to 40 rows: 84 us a call; now 23.
-// One of 16384 tokens, 32 heads of 128 on 8, 61 rows: 2048 us a call; now 218.)
+// four multiply-adds: three sequences of 100 to 1500 tokens, 8 heads of 64, 17 to 40 rows: 84 us a call, 23 then and 17 now;
+// one of 16384 tokens, 32 heads of 128 on 8, 61 rows: 2048 us a call, now 210.)
 template <typename T, int D>
 __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
   constexpr int NQ = D / 16;            // 16-byte (float32) pieces of a lane's part of a K, Q or V row group
@@ -119,12 +119,20 @@ __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
     }
   };
 
+  // The parent pointers are requested first, and nothing behind them depends on a condition, so that the wait for them
+  // counts the younger loads: the root paths are found while the first keys are on their way.
+  constexpr int PAR_PER = MAX_TREE_ROWS / GEN_THREADS;
+  int my_par[PAR_PER];
+  const int32_t* parent = a.parent + (a.tree_shared ? 0 : n0);
+#pragma unroll
+  for (int k = 0; k < PAR_PER; ++k) my_par[k] = parent[min(tid + k * GEN_THREADS, M - 1)];
+  asm volatile("" ::: "memory");  // (keeps the requests in this order)
+
   Frag cur[GPI], nxt[GPI];
   const int stride = GEN_WAVES * GPI;
   int grp = wave * GPI;
 #pragma unroll
-  for (int u = 0; u < GPI; ++u)
-    if (grp + u < n_groups) load_group(grp + u, cur[u]);
+  for (int u = 0; u < GPI; ++u) load_group(min(grp + u, n_groups - 1), cur[u]);
 
   float4 qf[NQ];
 #pragma unroll
@@ -132,18 +140,19 @@ __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
 
   // ---- the rows' root paths as bit sets over the tree rows
   if (last_split) {
-    const int32_t* parent = a.parent + (a.tree_shared ? 0 : n0);
-    for (int i = tid; i < M; i += GEN_THREADS) par[i] = parent[i];
+#pragma unroll
+    for (int k = 0; k < PAR_PER; ++k)
+      if (tid + k * GEN_THREADS < M) par[tid + k * GEN_THREADS] = my_par[k];
     for (int e = tid; e < GEN_ROWS * (ANC_WORDS + 1); e += GEN_THREADS) (&anc[0][0])[e] = 0u;
-    __syncthreads();
-    if (tid < GEN_ROWS) {  // (lane tid of the first wave: its own row)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (through LDS only: the keys stay on their way)
+    if (tid < GEN_ROWS) {  // (lane tid of the first wave: its own row; nobody waits for the ORs)
       for (int j = node; j >= 0;) {
-        anc[tid][j >> 5] |= 1u << (j & 31);
+        atomicOr(&anc[tid][j >> 5], 1u << (j & 31));
         const int up = par[j];
         j = up < j ? up : -1;  // (a malformed tree cannot keep the walk from ending)
       }
     }
-    __syncthreads();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   }
 
   floatx4 acc[DPL];
@@ -368,10 +377,52 @@ struct AttnPlan {
   bool ok;
 };
 
+// Splits of the float32 kernel: a workgroup's time is its chain of trips over its split's keys, 5 us and 0.014 (D = 64) or
+// 0.028 us a key; beyond one workgroup to a compute unit they slow each other down, first by half, then in proportion
+// (workgroups of the grid that have nothing to do get in the way as well: three in five of the grid's count at least); the merge
+// launch takes 4 us.  Measured, whole calls, 8 KV heads, split into: D = 64, 3 sequences of 962 to 1319 tokens, 33 to
+// 40 rows: 256 tokens (360 workgroups) 18.8 us, 384 (264) 20.3, 512 (192) 17.1, 1024 (120) 24.1; one of 2000, 20 rows: 256
+// 13.4, 512 15.9, 1024 22.9, unsplit 33.2; 4 of 283 to 437: 256 13.3, unsplit 12.7; 8 of 866 to 1819: 512 (704) 39.4,
+// unsplit (216) 32.0.  D = 128, one of 432, 55 rows: 128 13.5, 256 16.3, unsplit 19.1; one of 595: 128 14.2, 256 15.5,
+// 512 22.6; one of 213: 128 14.1, unsplit 14.4.
+static int64_t plan_float_split(const int32_t* hno, const int64_t* hpo, const int64_t* hlens, int B, int G, int Hkv, int D,
+                                int n_rb_max, int rows_per_wg, int64_t max_L) {
+  const float key_us = D == 64 ? 0.014f : 0.028f;
+  const int64_t least = D == 64 ? 256 : 128;  // a trip's keys
+  int64_t best = 0, last = 0;
+  float best_us = 0.f;
+  for (int64_t cut = 1; cut <= 64; ++cut) {
+    const int64_t len = std::max(least, ((max_L + cut - 1) / cut + 127) / 128 * 128);
+    if (len == last) continue;
+    last = len;
+    int64_t wgs = 0, keys = 0;
+    for (int s = 0; s < B; ++s) {
+      const int M = hno[s + 1] - hno[s];
+      if (M <= 0) continue;
+      const int64_t L = hlens != nullptr ? hlens[s] : hpo[s + 1] - hpo[s];
+      const int n = splits_of(L, (int)len);
+      wgs += (int64_t)Hkv * ((G * M + rows_per_wg - 1) / rows_per_wg) * n;
+      keys = std::max(keys, std::max(n > 1 ? len : 0, L - (n - 1) * len + M));
+    }
+    const int sp_max = splits_of(max_L, (int)len);
+    const float grid = (float)Hkv * n_rb_max * sp_max * B;
+    const float w = std::max((float)wgs, 0.6f * grid) / PLAN_CUS;
+    const float us = (5.f + key_us * keys) * (w <= 1.f ? 1.f : std::max(w, 1.f + 0.5f * w)) + (sp_max > 1 ? 4.f : 0.f);
+    if (best == 0 || us < best_us) {
+      best = len;
+      best_us = us;
+    }
+    if (len == least || w > 4.f) break;
+  }
+  return best;
+}
+
 // Chooses the split length from the host copies of the offsets: enough workgroups to fill the
 // chip, but splits long enough that partial records stay small next to the K/V they summarise.
-static AttnPlan plan_attention(const int32_t* hno, const int64_t* hpo, const int64_t* hlens, int B, int Hq, int Hkv,
-                               int rows_per_wg) {
+// rows_per_wg: of the float32 kernel, 0 for the matrix-core kernel.  lean: the plan for a workspace that does not hold the
+// usual one's records.
+static AttnPlan plan_attention(const int32_t* hno, const int64_t* hpo, const int64_t* hlens, int B, int Hq, int Hkv, int D,
+                               int rows_per_wg, bool lean) {
   AttnPlan p{};
   int max_M = 0;
   int64_t max_L = 0, sum_L = 0;
@@ -391,14 +442,15 @@ static AttnPlan plan_attention(const int32_t* hno, const int64_t* hpo, const int
   if (p.n_rb_max < 1) p.n_rb_max = 1;
   // workgroups without splitting: one per (sequence, head, row block); split until the target is met
   const int64_t base_wgs = (int64_t)B * Hkv * p.n_rb_max;
-  // (a workgroup per compute unit: float32, four sequences of 200 to 2000 tokens, 8 heads of 128 on 2, up to 64
-  // rows, 128 workgroups unsplit: 42.7 us with splits for 512 workgroups, 32.4 us with splits for 256)
   int64_t want = base_wgs > 0 ? (PLAN_CUS + base_wgs - 1) / base_wgs : 1;  // splits per average sequence
   if (want < 1) want = 1;
   const int64_t mean_L = B > 0 ? sum_L / B : 0;
   int64_t len = (mean_L + want - 1) / want;
   len = (len + 255) / 256 * 256;   // multiple of 256 tokens
   if (len < 512) len = 512;        // never split finer than 512 tokens
+  // (many rounds of workgroups, of which the estimate knows nothing, are left to the rule above)
+  if (rows_per_wg > 0 && !lean && base_wgs <= 4 * PLAN_CUS && max_L < (int64_t)1 << 30)
+    len = plan_float_split(hno, hpo, hlens, B, G, Hkv, D, p.n_rb_max, rows_per_wg, max_L);
   p.split_len = (int)len;
   p.sp_max = splits_of(max_L, p.split_len);
   p.ok = true;
@@ -903,11 +955,8 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   const int sp_cap = (int)(sp_bound < 2 ? 2 : sp_bound > 64 ? 64 : sp_bound);
 
   AttnPlan plan{};
-  if (!(mfma && plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, false))) {
-    a.n_tbl = 0;
-    a.cmb_row0 = 0;
-    a.share = (int64_t)B * a.Hkv > PLAN_SHARE_ITEMS ? 2 : 1;  // (more than 96 sequences, or not for the matrix-core kernel)
-    plan = plan_attention(host_node_offsets, host_prefix_offsets, host_prefix_lens, B, Hq, a.Hkv, mfma ? 0 : GEN_ROWS);
+  auto plan_plain = [&](bool lean) {
+    plan = plan_attention(host_node_offsets, host_prefix_offsets, host_prefix_lens, B, Hq, a.Hkv, D, mfma ? 0 : GEN_ROWS, lean);
     while (plan.sp_max > sp_cap) {
       plan.split_len *= 2;
       plan.sp_max = splits_of(plan.max_L, plan.split_len);
@@ -917,14 +966,21 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
       plan.sp_max = splits_of(plan.max_L, plan.split_len);
     }
     a.split_len = plan.split_len; a.sp_max = plan.sp_max; a.n_rb_max = plan.n_rb_max;
+  };
+  if (!(mfma && plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, false))) {
+    a.n_tbl = 0;
+    a.cmb_row0 = 0;
+    a.share = (int64_t)B * a.Hkv > PLAN_SHARE_ITEMS ? 2 : 1;  // (more than 96 sequences, or not for the matrix-core kernel)
+    plan_plain(false);
   } else {
     a.split_len = 0; a.n_rb_max = 1;
   }
   const size_t table_bytes = mfma ? align_up(attn_mfma_table_bytes(max_M, NN), 256) : 0;
   size_t need = part_bytes(NN, Hq, D, a.sp_max) + table_bytes;
   // a workspace that is too small for this plan may still hold the one with fewer cuts
-  if (a.n_tbl > 0 && !plan_only && a.sp_max > 1 && (workspace == nullptr || workspace_bytes < need)) {
-    plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, true);
+  if (!plan_only && a.sp_max > 1 && (workspace == nullptr || workspace_bytes < need)) {
+    if (a.n_tbl > 0) plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, true);
+    else plan_plain(true);
     need = part_bytes(NN, Hq, D, a.sp_max) + table_bytes;
   }
   if (table_bytes != 0 && workspace != nullptr)

@@ -117,6 +117,35 @@ def test_attention_of_any_shape_and_address(G, dtype, D, hq, hkv, M, L, offset):
     assert np.abs(lse.cpu().numpy() - want_lse).max() <= 2e-5
 
 
+@pytest.mark.parametrize("D,hq,hkv,Ms,Ls", [
+    (128, 8, 8, [55], [257]), (128, 8, 8, [17, 3, 31], [385, 0, 1000]), (128, 8, 2, [40], [1025]), (128, 3, 3, [1], [1153]),
+    (64, 8, 8, [33, 16], [513, 1300]), (64, 8, 2, [5, 1], [2000, 127]), (64, 6, 3, [20], [4100])])
+def test_float32_prefixes_in_splits(G, D, hq, hkv, Ms, Ls):
+    """The float32 kernel's splits: of 128 tokens and more, last ones of a single key, beside sequences that are not split,
+    up to 16 and more of them (the merge takes eight at a time).  A workspace without room for their records gets the
+    coarser cut."""
+    import paper_2505_13254_amd as hs
+    from test_gpu_attention import _case, _random_parents
+    w = W.small(W.WORKLOADS[1], Hq=hq, Hkv=hkv, D=D)
+    rs = np.random.RandomState(sum(Ls))
+    step = _case(w, sum(Ms), [_random_parents(rs, m, back=9) for m in Ms], Ls, "unit")
+    want_o, want_lse = P.attention_out(step)
+    no, po = torch.from_numpy(step["node_offsets"]), torch.from_numpy(step["prefix_offsets"])
+    totals, _ = hs.hs_tree_attention_plan(no, po, hq, hkv, D, hs.HS_F32)
+    assert totals[0] == 2 and totals[2] > 1
+    for ws in (None, hs.workspace(int(totals[4]) - 256, "cuda:0")):
+        try:
+            o, lse = hs.hs_tree_attention(*(G.dev(step[n]) for n in ("q", "k_prefix", "v_prefix", "k_tree", "v_tree")),
+                                          G.dev(step["parent"]), G.dev(step["node_offsets"]), G.dev(step["prefix_offsets"]), no, po,
+                                          step["scale"], want_lse=True, ws=ws)
+        except hs.HsError:
+            assert ws is not None and max(Ls) > 512  # (the coarser cut has records as well)
+            continue
+        # float32 arithmetic: sums of up to 4120 terms, each rounded at 2^-24 of values of order 1
+        assert np.abs(G.host(o) - want_o).max() <= 2e-6 + 1e-5 * np.abs(want_o).max()
+        assert np.abs(G.host(lse) - want_lse).max() <= 2e-5
+
+
 @pytest.mark.parametrize("sizes,spare", [([1], 2), ([5, 3], 3), ([1030], 0), ([1100, 4], 5)])
 def test_ratio_rule_on_large_trees_and_spare_rows(G, sizes, spare):
     """Sampling with the draft's ratio rule: trees beyond the 1024 rows that are staged in LDS, and rows
