@@ -106,7 +106,7 @@ struct AttnArgs {
   const unsigned* anc_tiles;  // ancestor table of large trees (matrix-core kernel), in the workspace; else NULL
   int n_tbl;       // > 0: work-list launch (1-D grid over the items of tbl[0 .. n_tbl)); 0: grid.y = sequence
   int n_items;
-  int narrow;      // work-list launches: 1 = two workgroups to an item, one for each 128 of its up to 256 rows
+  int narrow;      // work-list launches: 1 = two workgroups to an item, one for each 128 of its up to 256 rows; 2 = four
   int share;       // matrix-core kernel: equal row groups of five or six blocks share what is behind the fourth, 1 = of
                    // sequences with several groups, 2 = of all
   int cmb_row0;    // first tree row that the merge of the splits looks at

@@ -472,7 +472,12 @@ constexpr int PLAN_MIN_SPLIT_TILES = 2;
 // in which two waves share a row block and take every other 32 keys ("narrow"): 0.65 us a tile instead of 1.05 on
 // an otherwise idle chip for items of more than 128 rows (33 and 126 tiles a workgroup, 244 rows: 43.9 and 140 us
 // -> 31.2 and 91 us).
-constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2;
+// At most a quarter as many can be given four, of up to 64 rows each: four waves to a row block, half the sums to
+// exchange and half the records to write for each of them.  Whole calls, one layer, 8 KV heads, best cut with two and with four: 61 rows on 500 /
+// 1000 / 2048 / 4096 tokens 14.6 / 16.0 / 18.3 / 20.3 us and 13.9 / 15.1 / 16.7 / 19.5, D = 64 on 2048 13.3 and 12.9; 40
+// heads, 129 rows on 400 tokens 18.3 and 16.4.  None gained by items of at most 128 rows (20 on 2048 14.9 and 15.3), nor by long
+// prefixes, which want more splits than that leaves room for (9000 tokens 27.1 and 29.5).
+constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2, PLAN_QUARTER_ITEMS = PLAN_CUS / 4;
 // Launches that give every item a compute unit of its own, either way: the longest item decides.  A tile costs
 // the more the more K/V streams are read at a time, and above 128 rows, where two waves share a SIMD, the matrix
 // instructions' time at least; up to 128 rows two waves to a row block gain nothing, and cost more to start and
@@ -483,8 +488,9 @@ constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2;
 // of fuller launches that they are compared with are high as well.  (Every launch of up to 128 items narrow, with
 // flat costs a tile: 2.0 %; 3 entries of 2344 tokens, 66 rows, 40 heads 49.0 us, now and without narrow launches 39.4;
 // one of 8945 tokens, 130 rows 68 and 55; without narrow launches 9.9 % on average.)
-static inline float plan_own_cu_us(bool narrow, bool half, int waves, int tiles, float streams) {
-  const float item = waves > 4 ? 12.f : narrow && waves > 2 ? 8.4f : 6.5f;
+// (narrow: 0 to 2, as in AttnArgs)
+static inline float plan_own_cu_us(int narrow, bool half, int waves, int tiles, float streams) {
+  const float item = waves > 4 ? (narrow == 2 ? 10.4f : 12.f) : narrow && waves > 2 ? 8.4f : 6.5f;
   float tile = narrow ? 0.88f + 0.0029f * streams : 1.07f + 0.0018f * streams;
   if (!narrow && waves > 4) tile = std::max(tile, half ? 1.35f : 1.5f);
   return item + (float)tiles * tile;
@@ -504,7 +510,7 @@ struct ListPlan {
   float est_us;
   int target;
   int tail, cuts;  // the last `tail` entries have each of their splits cut into `cuts` once more (0, 1: none)
-  int narrow;      // two workgroups to an item
+  int narrow;      // 1: two workgroups to an item, 2: four
 };
 
 // Equal entries whose items do not fill whole rounds of the compute units: the entries that spill into the
@@ -621,13 +627,13 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
         streamed += (double)a.Hkv * nsp * (per + q.ttiles);
       }
       const float streams = (float)(streamed / longest);  // read at a time while the longest item runs
-      for (int narrow = 0; narrow <= (items <= PLAN_NARROW_ITEMS ? 1 : 0); ++narrow) {
+      for (int narrow = 0; narrow <= (items <= PLAN_QUARTER_ITEMS ? 2 : items <= PLAN_NARROW_ITEMS ? 1 : 0); ++narrow) {
         float est = 0.f;
         for (int i = 0; i < n; ++i) {
           const Seq& q = seqs[i];
           int nsp, per;
           plan_cut(q.tiles, target, sp_cap, a.block_table != nullptr, &nsp, &per);
-          est = std::max(est, plan_own_cu_us(narrow != 0, a.half != 0, q.waves0, per + q.ttiles, streams));
+          est = std::max(est, plan_own_cu_us(narrow, a.half != 0, q.waves0, per + q.ttiles, streams));
         }
         est += combine_us;
         if (best.target == 0 || est < best.est_us) best = ListPlan{est, target, 0, 1, narrow};

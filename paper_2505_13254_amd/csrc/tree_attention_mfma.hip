@@ -232,7 +232,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     // Work-list launch: the table of sequences sits in the kernel arguments; lane l fetches entry
     // l (and l + 64), a ballot finds the entry whose item range holds this workgroup, and its
     // fields are read from that lane: one memory round trip, no dependent offset loads.
-    const int x = blockIdx.x, item = x >> h_narrow;  // (narrow launches: two workgroups to an item of the table)
+    const int x = blockIdx.x, item = x >> h_narrow;  // (narrow launches: two or four workgroups to an item of the table)
     unsigned f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int base = 0; base < h_n_tbl; base += 64) {
       const int idx = base + lane;
@@ -287,19 +287,20 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // Rows.  The rows of a (pair of) KV head(s) are numbered head by head in blocks of 32, tree row by tree
   // row inside a head: block b belongs to head b / nbh of the pair and holds its rows 32 (b % nbh) ...
   // (HALF: a wave's rows all read the same head of the pair, so it multiplies that head's half of the
-  // 256-byte K and V rows only).  A row group is up to eight blocks, in narrow launches up to four.
+  // 256-byte K and V rows only).  A row group is up to eight blocks, in narrow launches up to four or two.
   const int Gh = HALF ? G >> 1 : G;      // query heads per KV head
   const int Rh = Gh * M;                  // rows of a KV head
   const int nbh = (Rh + 31) >> 5;
   const int n_blk = HALF ? 2 * nbh : nbh;
   int blk0, blk_n;  // first block of this group, and how many
   if (h_narrow != 0) {
-    blk0 = rg * 4;
-    blk_n = n_blk - blk0 < 4 ? n_blk - blk0 : 4;
+    const int most = 8 >> h_narrow;
+    blk0 = rg * most;
+    blk_n = n_blk - blk0 < most ? n_blk - blk0 : most;
   } else {
     row_group(n_blk, rg, &blk0, &blk_n);
   }
-  if (blk_n <= 0) return;  // (narrow: an item of at most 128 rows needs one of its two workgroups)
+  if (blk_n <= 0) return;  // (narrow: an item of few rows needs some of its two or four workgroups)
   // Narrow launches have compute units to spare and are bound by each workgroup's own pace: the
   // four blocks' waves alone, one to a SIMD, would have nothing to hide their chains of dependent
   // steps behind.  There two waves share a row block, one takes the even 32-key blocks of the
@@ -309,13 +310,16 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // run ahead of the other row groups of their keys, out of reach of the L2 copies: 0.8 % slower.)
   const bool ksplit = h_narrow != 0;
   const int pair_shift = !ksplit ? 3 : blk_n <= 1 ? 0 : blk_n == 2 ? 1 : 2;
+  // With four workgroups to an item there are at most two blocks for the eight waves: four waves share one, each with
+  // every fourth 32 keys (`quarter`).  (61 rows on 2048 tokens, 8 KV heads, 32 layers one by one: 589 -> 535 us.)
+  const bool quarter = h_narrow == 2;
   // Groups of five or six blocks, all groups being so: the first four waves, one to a SIMD, take a block each, and
   // the other four share what is left: two waves to a block, as above, or all four of them to one, each with
   // every fourth 32 keys.  `ways` is the number of waves that share this wave's block, kpar its share.  (With a wave
   // to a block one or two SIMDs have two waves' work and the others one's: 129 rows on 4096 tokens, 40 layers and
   // heads, 703 -> 685 us the whole step; ten blocks in two groups (row_group) 185 -> 180.  When: see a.share.)
   const bool shared_tail = (blk_n == 5 || blk_n == 6) && equal_row_groups(n_blk) && h_share > (n_blk <= 6 ? 1 : 0);
-  const int ways = ksplit ? 2 : !shared_tail || wave < 4 ? 1 : blk_n == 5 ? 4 : 2;
+  const int ways = quarter ? 4 : ksplit ? 2 : !shared_tail || wave < 4 ? 1 : blk_n == 5 ? 4 : 2;
   const int my_blk = blk0 + (shared_tail && wave >= 4 ? 4 + (blk_n == 6 ? wave & 1 : 0) : wave & ((1 << pair_shift) - 1));
   const int kpar = shared_tail ? (wave < 4 ? 0 : blk_n == 6 ? (wave - 4) >> 1 : wave - 4) : wave >> pair_shift;  // (without sharing: 0)
   const bool wave_active = my_blk < blk0 + blk_n && kpar < ways;
@@ -944,7 +948,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     l_tot = l_sum + __shfl_xor(l_sum, 32);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   }
-  if (ksplit) {
+  if (ksplit && !quarter) {
     // ---- the two waves of a row block swap halves of their columns through the (now free) tile ring:
     // each ends up with the sums of NT / 2 column blocks, kept in acc[0 .. NT / 2), and the denominator.
     // A wave's 8 NT KB of floats lie 16 bytes to a lane, so both sides move whole 1 KB pieces.
@@ -986,13 +990,14 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     // (every wave has its sums before the staging below reuses the ring)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   }
-  if (shared_tail) {
-    // ---- the waves that share a row block leave their sums in the (now free) V ring, 16 bytes to a lane, and each
-    // adds up its part of the columns, wave by wave in rising order.
+  if (shared_tail || quarter) {
+    // ---- the waves that share a row block leave their sums in the (now free) V ring (quarter: the first four in
+    // the K ring), 16 bytes to a lane, and each adds up its part of the columns, wave by wave in rising order.
     float* const den = reinterpret_cast<float*>(&anc[0]);  // [wave][denominators, reference maxima]
-    const bool sharing = wave >= 4;
+    const bool sharing = quarter ? wave_active : wave >= 4;
+    auto left_by = [&](int w) { return reinterpret_cast<float*>(w < 4 ? lds_k[w] : lds_v[w - 4]); };
     if (sharing) {
-      float* const ex = reinterpret_cast<float*>(lds_v[wave - 4]);
+      float* const ex = left_by(wave);
 #pragma unroll
       for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
@@ -1005,21 +1010,25 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (sharing) {
-      const int step = ways == 4 ? 1 : 2;              // from one of the sharing waves to the next
-      const int first = ways == 4 ? 0 : wave & 1;       // the first of them, counted from wave 4
+      // the first of the sharing waves, and how far it is to the next one
+      const int step = quarter ? 1 << pair_shift : ways == 4 ? 1 : 2;
+      const int first = quarter ? wave & (step - 1) : ways == 4 ? 4 : 4 + (wave & 1);
       const int keep = ways == 4 ? 1 : NT / 2;          // column blocks of this wave
       const int tt0 = kpar * keep;
-      if (tt0 >= NT) return;  // (head dimension 64: two column blocks for four waves)
-      m_ref = den[(4 + first) * 128 + 64 + lane];  // (the exact path moves the first wave's only)
+      if (tt0 >= NT) {  // (head dimension 64: two column blocks for four waves)
+        if (quarter) asm volatile("s_barrier" ::: "memory");
+        return;
+      }
+      m_ref = den[first * 128 + 64 + lane];  // (the exact path moves the first wave's only)
       l_tot = 0.f;
-      for (int w = 0; w < ways; ++w) l_tot += den[(4 + first + w * step) * 128 + lane];
+      for (int w = 0; w < ways; ++w) l_tot += den[(first + w * step) * 128 + lane];
 #pragma unroll
       for (int tt = 0; tt < NT / 2; ++tt) {
         if (tt >= keep) break;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[tt][v] = 0.f;
         for (int w = 0; w < ways; ++w) {
-          const float* from = reinterpret_cast<const float*>(lds_v[first + w * step]) + (tt0 + tt) * 1024;
+          const float* from = left_by(first + w * step) + (tt0 + tt) * 1024;
 #pragma unroll
           for (int b = 0; b < 4; ++b) {
             const float4 f = *reinterpret_cast<const float4*>(from + b * 256 + lane * 4);
@@ -1031,6 +1040,8 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
         }
       }
     }
+    // (quarter: every wave has its sums before the staging below reuses the rings)
+    if (quarter) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   }
   if (!wave_active) return;
 

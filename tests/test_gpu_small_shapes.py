@@ -64,6 +64,20 @@ def test_launches_that_leave_compute_units_to_spare(G, D, hq, hkv, M, L, variant
 
 
 @pytest.mark.parametrize("variant", ["unit", "hot"])
+@pytest.mark.parametrize("D,hq,hkv,Ms,Ls", [
+    (128, 8, 2, [40], [0]), (128, 8, 2, [33], [31]), (128, 8, 2, [56], [64]), (128, 8, 2, [64], [449]), (128, 16, 2, [33], [2048]),
+    (128, 8, 2, [65], [130]), (128, 8, 8, [130, 5], [200, 90]), (64, 8, 2, [20], [33]), (64, 8, 2, [33], [300]), (64, 8, 4, [129], [1000])])
+def test_four_workgroups_to_an_item(G, D, hq, hkv, Ms, Ls, variant):
+    """Launches of at most 64 items of more than 128 rows: one or two row blocks to a workgroup, four waves to a block, each on
+    every fourth 32 keys.  Fewer keys than waves have turns, odd last blocks and groups, beside a sequence of few rows,
+    unsplit and in splits, the exact second pass."""
+    from test_gpu_attention import _case, _compare, _random_parents
+    w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
+    rs = np.random.RandomState(sum(Ms) + sum(Ls))
+    _compare(G, _case(w, sum(Ms), [_random_parents(rs, m, back=9) for m in Ms], Ls, variant), "bf16", big_scores=variant != "unit")
+
+
+@pytest.mark.parametrize("variant", ["unit", "hot"])
 @pytest.mark.parametrize("D,hq,hkv,M,L,B", [
     (128, 8, 8, 129, 300, 20), (128, 8, 8, 129, 31, 20), (128, 8, 8, 161, 65, 20), (128, 8, 8, 192, 640, 20),
     (128, 32, 4, 65, 130, 17), (128, 16, 4, 150, 97, 18), (128, 8, 8, 129, 1500, 16), (128, 8, 8, 257, 100, 16),
