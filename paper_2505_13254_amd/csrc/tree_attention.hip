@@ -615,10 +615,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
       ord[i] = i;
       seq_cost[i] = (float)per * q.tile_us;
     }
-    // The combine launch, and the records' way there and back.  (Whole calls, one layer.  D = 128, 40 heads, at 2.5 TB/s and at 5: 124
-    // rows on 894 tokens 23.6 and 18.9 us, 100 on 754 21.1 and 18.8, 92 on 1177 19.4 and 18.6; 64 heads on 8, 123 on 1147 21.8 and 21.6.
-    // D = 64: 6 sequences of 586 to 856 tokens 21.2 and 25.0, 5 of 99 to 2351 27.2 and 28.3.)
-    const float combine_us = rec_bytes > 0.0 ? 4.f + (float)(rec_bytes / (a.half ? 2.5e6 : 5.0e6)) : 0.f;
+    const float combine_us = rec_bytes > 0.0 ? 4.f + (float)(rec_bytes / 2.5e6) : 0.f;  // the combine launch, ~2.5 TB/s
     if (items <= PLAN_CUS && !lean) {  // every item has a compute unit of its own
       int longest = 0;     // tiles of an item
       double streamed = 0.0;  // tiles of all items, row groups of the same keys as one
