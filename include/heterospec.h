@@ -348,7 +348,9 @@ hs_status hs_tree_prune_counted(const int32_t* parent, const float* logc, const 
  * indices, ascending) and n_frontier [B] how many of them there are.
  *
  * One call grows every sequence by one level from the results of hs_draft_entropy_topk on the
- * draft distributions of its frontier rows: result row s * F + j belongs to frontier[s,j].
+ * draft distributions of its frontier rows: result row s * F + j belongs to frontier[s,j].  Rows of
+ * slots past n_frontier are not read: the arrays end with the last sequence's last frontier row, e.g.
+ * after [K] entries on a first call with B = 1.
  *   first != 0: the state is initialised first (root alone: parent -1, token -1, values 0; the
  *     frontier is the root, level 0), so the results are those of the roots' rows (j = 0).
  *   For each frontier row f (in order) and k < K: a new row with parent f, token topk_idx[.,k],

@@ -51,13 +51,6 @@ __global__ __launch_bounds__(EXP_THREADS) void k_tree_expand(ExpandArgs a) {
   // e / K for e < EXP_MAX_NEW: (e + 0.5) / K is at least 1 / (2 K) away from an integer, far more than its rounding
   auto frontier_slot = [&](int e) { return (int)(((float)e + 0.5f) * inv_K); };
   int n, lvl, nf;
-  // What does not depend on the frontier is requested with it.
-  float first_logp = 0.f;
-  int first_idx = 0;
-  if (tid < F * K) {
-    first_logp = a.topk_logp[(int64_t)s * F * K + tid];
-    first_idx = a.topk_idx[(int64_t)s * F * K + tid];
-  }
   if (a.first) {
     n = 1;
     lvl = 0;
@@ -100,15 +93,17 @@ __global__ __launch_bounds__(EXP_THREADS) void k_tree_expand(ExpandArgs a) {
   for (int e = tid; e < m; e += EXP_THREADS) {
     const int j = frontier_slot(e);
     const int f = fr_old[j];
+    // (of the results only the rows of frontier slots that exist are there to be read; they come with the parents' values)
     const int64_t src = (int64_t)s * F * K + e;
-    const float lc = e == tid ? first_logp : a.topk_logp[src];
+    const float lc = a.topk_logp[src];
+    const int tok = a.topk_idx[src];
     // the root's value is 0 by definition (on a first call its row may not be visible yet)
     const float up = (a.first || f == 0) ? 0.f : a.cumlogp[base + f];
     const float v = up + fminf(lc, 0.f);
     const int dep = (a.first || f == 0) ? 0 : a.depth[base + f];
     const int64_t row = base + n + e;
     a.parent[row] = f;
-    a.token[row] = e == tid ? first_idx : a.topk_idx[src];
+    a.token[row] = tok;
     a.logc[row] = lc;
     a.cumlogp[row] = v;
     a.depth[row] = dep + 1;

@@ -151,6 +151,36 @@ def test_prune_counted_matches_the_checker(G):
         assert np.array_equal(got["depth"][a:a + c], want["depth"][b:b + c])
 
 
+@pytest.mark.parametrize("B,K,F", [(1, 10, 10), (1, 64, 64), (3, 3, 12), (2, 7, 100)])
+def test_expand_reads_no_results_behind_the_last_frontier_row(G, B, K, F):
+    """The result arrays may end with the last sequence's last frontier row: [K] entries on a first call with one
+    sequence, fewer than B * F rows where its frontier is short.  (Called past the binding, which asks for B * F rows.)"""
+    import paper_2505_13254_amd as hs
+    rs = np.random.RandomState(K + F)
+    cap = 1 + K + K * F
+    state = hs.new_tree_state(B, cap, F, G.DEV)
+    ref = [new_state() for _ in range(B)]
+    nf = 1
+    for lvl in range(2):
+        idx, lp, ent = _random_results(rs, B * F, K)
+        rows = (B - 1) * F + nf
+        arrays = [G.dev(x[:rows]) for x in (idx, lp, ent)]
+        st = hs.lib().hs_tree_expand(*(state[k].data_ptr() for k in ("parent", "token", "logc", "cumlogp", "depth", "ent", "n_nodes",
+                                                                    "level", "frontier", "n_frontier", "frontier_rows")),
+                                     *(x.data_ptr() for x in arrays), None, B, cap, F, K, 1 if lvl == 0 else 0,
+                                     torch.cuda.current_stream().cuda_stream)
+        assert st == 0
+        got = _host_state(state, B, cap, F)
+        for s in range(B):
+            tree_expand(ref[s], idx[s * F:(s + 1) * F], lp[s * F:(s + 1) * F], ent[s * F:(s + 1) * F], F, cap, None)
+            n = len(ref[s]["parent"])
+            nf = len(ref[s]["frontier"])
+            assert int(got["n_nodes"][s]) == n and int(got["n_frontier"][s]) == nf
+            assert list(got["frontier"][s * F:s * F + nf]) == ref[s]["frontier"]
+            assert np.array_equal(got["token"][s * cap:s * cap + n], ref[s]["token"])
+    assert nf == min(F, K * min(F, K))
+
+
 def test_device_loop_grows_the_pipelines_tree(G):
     """Expansion driven entirely on the device (gather of the frontier's draft rows, quantification,
     growth) reproduces the candidate tree that the checker's pipeline builds on the host."""
