@@ -349,13 +349,15 @@ __global__ __launch_bounds__(CMB_THREADS) void k_attn_combine(AttnArgs a) {
       float top = m;
 #pragma unroll
       for (int u = 0; u < AT_ONCE; ++u) top = fmaxf(top, ml[u].x);
-      const float f = __expf(m - top);  // (0 at the first eight)
+      // (a split without a finite score, e.g. of keys masked by -inf, left -inf, 0 and zeros: no weight, first or not)
+      const float ref = top == -HS_INF ? 0.f : top;
+      const float f = __expf(m - ref);  // (0 at the first eight)
       m = top;
       l *= f;
       o = make_float4(o.x * f, o.y * f, o.z * f, o.w * f);
 #pragma unroll
       for (int u = 0; u < AT_ONCE; ++u) {
-        const float w = __expf(ml[u].x - m);  // (0 beyond the last split)
+        const float w = __expf(ml[u].x - ref);  // (0 beyond the last split)
         l = fmaf(ml[u].y, w, l);
         o.x = fmaf(v[u].x, w, o.x);
         o.y = fmaf(v[u].y, w, o.y);

@@ -160,6 +160,23 @@ def test_float32_prefixes_in_splits(G, D, hq, hkv, Ms, Ls):
         assert np.abs(G.host(lse) - want_lse).max() <= 2e-5
 
 
+@pytest.mark.parametrize("D,hq,hkv,M,L", [(128, 3, 3, 1, 1153), (64, 6, 3, 20, 4100)])
+@pytest.mark.parametrize("splits,more", [(1, 0), (8, 0), (8, 37), (9, 1)])
+def test_float32_splits_of_masked_keys(G, D, hq, hkv, M, L, splits, more):
+    """Keys whose scores are -inf (weight 0) fill whole splits of a float32 call, the first eight that the merge takes
+    together among them."""
+    import paper_2505_13254_amd as hs
+    from test_gpu_attention import _case, _compare, _random_parents
+    w = W.small(W.WORKLOADS[1], Hq=hq, Hkv=hkv, D=D)
+    rs = np.random.RandomState(D + splits)
+    step = _case(w, M, [_random_parents(rs, M, back=9)], [L], "unit")
+    totals, _ = hs.hs_tree_attention_plan(torch.from_numpy(step["node_offsets"]), torch.from_numpy(step["prefix_offsets"]), hq, hkv, D, hs.HS_F32)
+    assert totals[0] == 2 and totals[2] > splits and totals[2] > 8
+    step["q"][:, :, 0] = np.abs(step["q"][:, :, 0]) + 0.1
+    step["k_prefix"][:splits * int(totals[3]) + more, :, 0] = -np.inf
+    _compare(G, step, "f32")
+
+
 @pytest.mark.parametrize("sizes,spare", [([1], 2), ([5, 3], 3), ([1030], 0), ([1100, 4], 5)])
 def test_ratio_rule_on_large_trees_and_spare_rows(G, sizes, spare):
     """Sampling with the draft's ratio rule: trees beyond the 1024 rows that are staged in LDS, and rows
