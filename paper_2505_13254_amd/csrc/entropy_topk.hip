@@ -430,7 +430,8 @@ __device__ __forceinline__ void write_row(const MergeScratch<CAP>& sm, int64_t r
 // (`tickets`, zero before the launch), the one that draws S - 1 knows that all slices are written,
 // puts the counter back to zero for the next launch, merges the slices and writes the row.
 constexpr int FUSED_CAP = 1024;  // slices x K that the merging workgroup's scratch holds
-constexpr size_t TICKET_BYTES = 65536 * sizeof(unsigned);  // a counter for each of the at most 65535 rows of a call
+constexpr size_t TICKET_BYTES = 65536 * sizeof(unsigned);  // a counter for each of the at most ROW_SCAN_MAX rows of a call
+static_assert(ROW_SCAN_MAX * sizeof(unsigned) <= TICKET_BYTES, "every row has its counter");
 // STATS false: only the K best pairs are wanted (the greedy accept walk's argmax scan); the softmax
 // statistics, most of the arithmetic of a tile, are left out and part_stats is not written.
 template <bool VEC, int SCAN_THREADS, bool FUSED, int NBUF, bool STATS>
@@ -867,7 +868,7 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
                           void* workspace, hipStream_t stream, ScanSlices* slices, const uint8_t* row_active,
                           const int32_t* row_index, const float* logits2, int rows1, bool prepared) {
   // (rows are the grid's second dimension)
-  HS_REQUIRE(R <= 65535, HS_ERR_UNSUPPORTED, "row scan: %d rows in one call (at most 65535)", R);
+  HS_REQUIRE(R <= ROW_SCAN_MAX, HS_ERR_UNSUPPORTED, "row scan: %d rows in one call (at most %d)", R, ROW_SCAN_MAX);
   const ScanRows rows{scan_aligned(logits, logits2, row_stride), row_active != nullptr, slices != nullptr && slices->pairs_only};
   ScanPlan p = plan_scan(R, V, K, rows);
   Carver c(workspace);

@@ -63,6 +63,7 @@ struct ScanSlices {
   int count;
   bool pairs_only = false;  // in: the caller wants the slices' best pairs only, no softmax statistics
 };
+constexpr int ROW_SCAN_MAX = 65535;  // rows of a scan (they are a grid's second dimension)
 hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V, int K, float temperature,
                           int32_t* topk_idx, float* topk_logp, float* ent_topk, float* ent_full, float* lse,
                           void* workspace, hipStream_t stream, ScanSlices* slices = nullptr,

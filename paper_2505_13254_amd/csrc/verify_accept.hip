@@ -1338,6 +1338,10 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
   HS_REQUIRE(need == 0 || (workspace && workspace_bytes >= need && reinterpret_cast<uintptr_t>(workspace) % 256 == 0),
              HS_ERR_WORKSPACE, "hs_verify_accept: workspace needs %zu bytes, 256-byte aligned (got %zu)", need,
              workspace_bytes);
+  // (for every call, whichever way it takes, and before anything is launched)
+  const int64_t scanned = ratio ? 2 * (int64_t)NN : NN;
+  HS_REQUIRE(scanned <= hs::ROW_SCAN_MAX, HS_ERR_UNSUPPORTED, "hs_verify_accept: NN=%d, %lld rows to scan in one call (at most %d)",
+             NN, (long long)scanned, hs::ROW_SCAN_MAX);
   int32_t *t_arg = nullptr, *d_arg = nullptr;
   float *t_lz = nullptr, *d_lz = nullptr;
   hs::ScanSlices slices{nullptr, 1};

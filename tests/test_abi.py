@@ -130,6 +130,21 @@ def test_a_workspace_for_many_rows_holds_fewer(lib, V):
         assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("B,NN,V,depth", [(1, 65536, 8, 1), (1, 65536, 32000, 1), (1000, 65536, 128256, 4), (70000, 70000, 100, 2),
+                                          (1, 1 << 30, 600, 1)])
+def test_accept_calls_of_too_many_rows_are_refused_whatever_their_shape(lib, B, NN, V, depth):
+    """More than 65535 rows to scan (the ratio rule scans twice the rows): HS_ERR_UNSUPPORTED on the host, for shapes that the
+    greedy walk would take row by row along the paths as well."""
+    va = lib.hs_verify_accept
+    va.restype = ctypes.c_int
+    va.argtypes = [ctypes.c_void_p] * 2 + [ctypes.c_int64] + [ctypes.c_void_p] * 3 + [ctypes.c_int32] * 3 + \
+                  [ctypes.c_int, ctypes.c_float, ctypes.c_void_p, ctypes.c_int32] + [ctypes.c_void_p] * 4 + \
+                  [ctypes.c_size_t, ctypes.c_void_p]
+    d = ctypes.c_void_p(256)
+    for mode, rows in [(0, NN), (1, 32768), (1, NN), (2, NN)]:
+        assert va(d, d, V, d, d, d, B, rows, V, mode, 1.0, d, depth, d, d, d, d, 1 << 62, None) == 3, mode
+
+
 def test_adaptive_policy_on_the_host_matches_the_worked_table(lib):
     """hs_adaptive_policy (host arithmetic only) against the hand-worked Section 4.3 table of the figure example."""
     f = lib.hs_adaptive_policy
