@@ -1,4 +1,5 @@
-"""Builds libheterospec.so (HIP, gfx950) in-tree with hipcc.  `python -m paper_2505_13254_amd.build`."""
+"""Builds libheterospec.so (HIP, gfx950) in-tree with hipcc, and the binding's native module.  `python -m
+paper_2505_13254_amd.build`; the library alone, without torch: `python paper_2505_13254_amd/build.py --library`."""
 from __future__ import annotations
 
 import os
@@ -38,30 +39,29 @@ def marshal_command():
             os.path.join(CSRC, "marshal.cpp"), "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", MARSHAL]
 
 
-def build(verbose: bool = True) -> str:
-    """Compiles every source and links the shared library, and the binding's native module; always rebuilds."""
-    objdir = os.path.join(PKG, "_build")
-    os.makedirs(objdir, exist_ok=True)
-    objs = []
-    procs = []
-    cmd = marshal_command()
+def _start(cmd, verbose: bool):
     if verbose:
         print(" ".join(cmd), flush=True)
-    procs.append(("marshal.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    for src in SOURCES:
-        obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
-        cmd = [hipcc()] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-        objs.append(obj)
+    return subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
+
+def _finish(src: str, p, verbose: bool) -> None:
+    out, _ = p.communicate()
+    out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
+    if p.returncode != 0:
+        raise RuntimeError("compiling %s failed:\n%s" % (src, out))
+    if verbose and out.strip():
+        print(out)
+
+
+def build_library(verbose: bool = True) -> str:
+    """Compiles every source and links the shared library, with hipcc and nothing else; always rebuilds."""
+    objdir = os.path.join(PKG, "_build")
+    os.makedirs(objdir, exist_ok=True)
+    objs = [os.path.join(objdir, os.path.splitext(src)[0] + ".o") for src in SOURCES]
+    procs = [(src, _start([hipcc()] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj], verbose)) for src, obj in zip(SOURCES, objs)]
     for src, p in procs:
-        out, _ = p.communicate()
-        out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
-        if p.returncode != 0:
-            raise RuntimeError("compiling %s failed:\n%s" % (src, out))
-        if verbose and out.strip():
-            print(out)
+        _finish(src, p, verbose)
     cmd = [hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -69,7 +69,25 @@ def build(verbose: bool = True) -> str:
     return LIB
 
 
-if __name__ == "__main__":
-    build()
+def build(verbose: bool = True) -> str:
+    """The shared library, and the binding's native module beside it, which needs torch, Python's headers and a host
+    compiler: where that fails, the library is there all the same when the error is raised."""
+    marshal, failed = None, None
+    try:
+        marshal = _start(marshal_command(), verbose)
+    except Exception as e:
+        failed = e
+    build_library(verbose)
+    if marshal is None:
+        raise RuntimeError("the binding's native module was not compiled (the library was)") from failed
+    _finish("marshal.cpp", marshal, verbose)
+    return LIB
+
+
+if __name__ == "__main__":  # --library: libheterospec.so alone, for users of the C interface
+    if "--library" in sys.argv[1:]:
+        build_library()
+    else:
+        build()
     print("built", LIB)
     sys.exit(0)

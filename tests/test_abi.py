@@ -145,6 +145,28 @@ def test_accept_calls_of_too_many_rows_are_refused_whatever_their_shape(lib, B, 
         assert va(d, d, V, d, d, d, B, rows, V, mode, 1.0, d, depth, d, d, d, d, 1 << 62, None) == 3, mode
 
 
+@pytest.mark.parametrize("missing", ["torch", "compiler", "headers"])
+def test_the_library_is_linked_where_the_native_module_cannot_be(tmp_path, monkeypatch, missing):
+    """libheterospec.so needs hipcc and nothing else: what the binding's module needs may be absent (the compile and link
+    lines are stood in for, the order and what is raised are the build's own)."""
+    from paper_2505_13254_amd import build as B
+    tool = tmp_path / "hipcc"
+    tool.write_text('#!/bin/sh\nwhile [ "$1" != "-o" ]; do shift; done\necho built > "$2"\n')
+    tool.chmod(0o755)
+    for name, value in [("PKG", str(tmp_path)), ("LIB", str(tmp_path / "lib.so")), ("MARSHAL", str(tmp_path / "_m.so")), ("hipcc", lambda: str(tool))]:
+        monkeypatch.setattr(B, name, value)
+    def no_torch():
+        raise ImportError("No module named 'torch'")
+    monkeypatch.setattr(B, "marshal_command", {"torch": no_torch, "compiler": lambda: [str(tmp_path / "no-such-compiler")],
+                                               "headers": lambda: ["/bin/sh", "-c", "echo Python.h: No such file; exit 1"]}[missing])
+    with pytest.raises(RuntimeError, match="marshal|native module"):
+        B.build(verbose=False)
+    assert (tmp_path / "lib.so").read_text() == "built\n" and not (tmp_path / "_m.so").exists()
+    (tmp_path / "lib.so").unlink()
+    B.build_library(verbose=False)
+    assert (tmp_path / "lib.so").exists()
+
+
 def test_adaptive_policy_on_the_host_matches_the_worked_table(lib):
     """hs_adaptive_policy (host arithmetic only) against the hand-worked Section 4.3 table of the figure example."""
     f = lib.hs_adaptive_policy
