@@ -147,17 +147,16 @@ def test_float32_prefixes_in_splits(G, D, hq, hkv, Ms, Ls):
     no, po = torch.from_numpy(step["node_offsets"]), torch.from_numpy(step["prefix_offsets"])
     totals, _ = hs.hs_tree_attention_plan(no, po, hq, hkv, D, hs.HS_F32)
     assert totals[0] == 2 and totals[2] > 1
+    args = [G.dev(step[n]) for n in ("q", "k_prefix", "v_prefix", "k_tree", "v_tree", "parent", "node_offsets", "prefix_offsets")]
     for ws in (None, hs.workspace(int(totals[4]) - 256, "cuda:0")):
-        try:
-            o, lse = hs.hs_tree_attention(*(G.dev(step[n]) for n in ("q", "k_prefix", "v_prefix", "k_tree", "v_tree")),
-                                          G.dev(step["parent"]), G.dev(step["node_offsets"]), G.dev(step["prefix_offsets"]), no, po,
-                                          step["scale"], want_lse=True, ws=ws)
-        except hs.HsError:
-            assert ws is not None and max(Ls) > 512  # (the coarser cut has records as well)
-            continue
+        o, lse = hs.hs_tree_attention(*args, no, po, step["scale"], want_lse=True, ws=ws)
         # float32 arithmetic: sums of up to 4120 terms, each rounded at 2^-24 of values of order 1
         assert np.abs(G.host(o) - want_o).max() <= 2e-6 + 1e-5 * np.abs(want_o).max()
         assert np.abs(G.host(lse) - want_lse).max() <= 2e-5
+    if max(Ls) > 1500:  # (the coarser cut has records as well)
+        with pytest.raises(hs.HsError) as e:
+            hs.hs_tree_attention(*args, no, po, step["scale"], want_lse=True, ws=hs.workspace(256, "cuda:0"))
+        assert e.value.status == hs.binding.HS_ERR_WORKSPACE
 
 
 @pytest.mark.parametrize("D,hq,hkv,M,L", [(128, 3, 3, 1, 1153), (64, 6, 3, 20, 4100)])
