@@ -478,6 +478,17 @@ hs_status hs_time_next_attention(void* start_event, void* stop_event);
  * 0 = none (no such call yet, an empty batch, or the call failed before its launch). */
 int32_t hs_tree_attention_last_kernel(void);
 
+/* hs_tree_attention_last_form  (debugging aid, not a step of the method)
+ *
+ * How the calling thread's last such call that the matrix-core kernel took, or the last batch that
+ * hs_tree_attention_plan was asked about, deals the 32-row blocks of a KV head to workgroups and waves:
+ *   workgroups that a work item gets, 1, 2 or 4 (several: waves share row blocks, each with every second
+ *   or fourth 32 keys of the item), plus
+ *   16 or 32: in row groups of five or six blocks (equal groups only) four waves share what is behind the
+ *   fourth block; 16 = of sequences with several row groups, 32 = of all.
+ * 0: the any-shape kernel, or nothing planned. */
+int32_t hs_tree_attention_last_form(void);
+
 /* hs_tree_attention_plan  (diagnostic, host only: no GPU is touched, nothing is launched)
  *
  * How hs_tree_attention / _lens (host_prefix_lens given) / _paged (paged != 0: host_prefix_offsets is
@@ -485,8 +496,9 @@ int32_t hs_tree_attention_last_kernel(void);
  * work items (a KV head's row group and key split), assuming 16-byte aligned tensors.  The host arrays are checked as in the real call
  * (same status codes).
  *   totals [6] (host, written): [0] kernel as in hs_tree_attention_last_kernel (0: nothing to launch),
- *     [1] work items of the attention launch: a workgroup each, or, where a launch has at most 128
- *     items and gains by it, two, one for each half of an item's up to 256 rows, [2] largest number of key splits of a sequence,
+ *     [1] work items of the attention launch: a workgroup each, or, where a launch has at most 128 (64)
+ *     items and gains by it, two (four) for an item's up to 256 rows (hs_tree_attention_last_form tells),
+ *     [2] largest number of key splits of a sequence,
  *     [3] tokens per split when all sequences are cut alike (0: each sequence has its own cut, see
  *     per_seq), [4] workspace bytes the call needs, [5] 1 if a combine launch follows.
  *   per_seq [B][4] (host, written; may be NULL): key splits, 64-key tiles per split, row groups

@@ -61,6 +61,7 @@ _SIGNATURES = {
     "hs_tree_validate": (_c.c_int, [_vp, _vp, _vp, _i32, _i32, _vp, _vp]),
     "hs_time_next_attention": (_c.c_int, [_vp, _vp]),
     "hs_tree_attention_last_kernel": (_c.c_int32, []),
+    "hs_tree_attention_last_form": (_c.c_int32, []),
     "hs_tree_attention_plan": (_c.c_int, [_vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _c.c_int, _vp, _vp]),
     "hs_verify_accept_workspace": (_sz, [_i32, _i32, _i32]),
     "hs_verify_accept_workspace_mode": (_sz, [_i32, _i32, _i32, _c.c_int]),
@@ -461,6 +462,12 @@ def hs_tree_attention_plan(host_node_offsets, host_prefix_offsets, Hq, Hkv, D, d
 def hs_tree_attention_last_kernel() -> int:
     """1: this thread's last tree-attention call ran the bfloat16 matrix-core kernel, 2: the any-shape kernel, 0: it launched nothing."""
     return int(lib().hs_tree_attention_last_kernel())
+
+
+def hs_tree_attention_last_form() -> int:
+    """Workgroups to a work item (1, 2, 4) of this thread's last tree-attention call or plan query, plus 16 or 32 where row
+    groups share blocks among waves, as the header describes it; 0: not the matrix-core kernel."""
+    return int(lib().hs_tree_attention_last_form())
 
 
 def hs_tree_validate(parent, token, node_offsets, *, stream=None) -> torch.Tensor:

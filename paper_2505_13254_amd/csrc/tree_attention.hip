@@ -855,6 +855,11 @@ static thread_local int last_kernel = 0;
 
 extern "C" int32_t hs_tree_attention_last_kernel(void) { return last_kernel; }
 
+// How its row blocks went to workgroups and waves, or would have (hs_tree_attention_last_form).
+static thread_local int last_form = 0;
+
+extern "C" int32_t hs_tree_attention_last_form(void) { return last_form; }
+
 extern "C" hs_status hs_time_next_attention(void* start_event, void* stop_event) {
   clear_error();
   HS_REQUIRE((start_event == nullptr) == (stop_event == nullptr), HS_ERR_NULL,
@@ -888,6 +893,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
     for (int k = 0; k < 6; ++k) report->totals[k] = 0;
   const bool paged = block_table != nullptr;
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
+  last_form = 0;
   if (!plan_only) {
     ev_start = timing_start;  // one-shot, whatever this call comes to
     ev_stop = timing_stop;
@@ -991,6 +997,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
     else plan_plain(true);
     need = part_bytes(NN, Hq, D, a.sp_max) + table_bytes;
   }
+  last_form = mfma ? (1 << a.narrow) + 16 * a.share : 0;
   if (table_bytes != 0 && workspace != nullptr)
     a.anc_tiles = reinterpret_cast<const unsigned*>(static_cast<const char*>(workspace) + part_bytes(NN, Hq, D, a.sp_max));
   if (plan_only) {

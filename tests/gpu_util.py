@@ -73,6 +73,20 @@ def entropy_err(got, want):
     return float(np.max(np.abs(got - want) / (1e-5 * np.maximum(np.abs(want), 1e-3))))
 
 
+def row_groups(M, Hq, Hkv, D):
+    """32-row blocks of each row group of a sequence of M tree rows, and whether groups of five or six blocks may share
+    them among waves: (blocks per group, groups that share under HS form 16, under form 32)."""
+    Gh = Hq // Hkv
+    n = (Gh * M + 31) // 32 * (2 if D == 64 else 1)
+    rg = (n + 7) // 8
+    equal = n <= 6 * rg
+    if rg > 3 or not equal:
+        return [min(8, n - 8 * i) for i in range(rg)], [], []
+    blocks = [n // rg + (i < n % rg) for i in range(rg)]
+    several = [b for b in blocks if b in (5, 6) and n > 6]
+    return blocks, several, [b for b in blocks if b in (5, 6)]
+
+
 BF16_U = 2.0 ** -8      # unit roundoff of bfloat16 (8 significant bits, round to nearest)
 
 

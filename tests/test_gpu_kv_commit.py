@@ -313,3 +313,33 @@ def test_paged_attention_with_several_row_groups(G, D, sizes):
                                       G.dev(lens), torch.from_numpy(lens.copy()), 1.0 / float(np.sqrt(w.D)))
     assert np.abs(G.host(o).astype(np.float64) - want_o).max() <= 2e-2
     assert hs.hs_tree_attention_last_kernel() == 1
+
+
+@pytest.mark.parametrize("D,hq,hkv,M,L,B,form", [
+    (128, 32, 8, 61, 700, 1, 4), (128, 8, 2, 65, 130, 1, 4), (64, 8, 4, 129, 700, 1, 4),             # four workgroups to an item
+    (128, 8, 8, 129, 900, 16, 2),                                                                     # two
+    (128, 16, 16, 129, 97, 17, 33), (128, 16, 16, 161, 65, 17, 33), (128, 16, 16, 257, 100, 17, 33),  # shared row blocks: five, six,
+    (128, 16, 16, 129, 1500, 17, 33), (128, 32, 8, 73, 100, 33, 17), (64, 32, 32, 81, 65, 20, 33),    # beyond 256 rows, splits, several
+    (128, 16, 16, 129, 70, 100, 33)])                                                                 # groups, one grid row to a sequence
+def test_paged_attention_in_every_launch_form(G, D, hq, hkv, M, L, B, form):
+    """The forms in which waves share row blocks, over paged caches in shuffled page order: the checker's results, and the
+    bits of the same call on packed caches."""
+    import paper_2505_13254_amd as hs
+    from test_gpu_attention import _case
+    w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
+    rs = np.random.RandomState(M + L)
+    lens = np.asarray([L] * B if B > 20 else [max(0, L - 16 * i) for i in range(B)], np.int64)
+    step = _case(w, M, [_random_parents(rs, M) for _ in range(B)], lens, "unit")
+    max_blocks = int((lens.max() + 63) // 64)
+    pools = [_paginate(np.random.RandomState(5), step[k], step["prefix_offsets"], lens, max_blocks) for k in ("k_prefix", "v_prefix")]
+    no = step["node_offsets"]
+    o, _ = hs.hs_tree_attention_paged(G.dev_store(step["q"]), G.dev_store(pools[0][0]), G.dev_store(pools[1][0]), G.dev_store(step["k_tree"]),
+                                      G.dev_store(step["v_tree"]), G.dev(step["parent"]), G.dev(no), torch.from_numpy(no), G.dev(pools[0][1]),
+                                      G.dev(lens), torch.from_numpy(lens.copy()), float(step["scale"]))
+    assert hs.hs_tree_attention_last_form() == form
+    packed, _ = G.run_attention(step, want_lse=False)
+    assert hs.hs_tree_attention_last_form() == form
+    assert np.array_equal(G.host(o), packed)
+    want_o, _ = tree_attention(step["q"], step["k_prefix"], step["v_prefix"], step["k_tree"], step["v_tree"], step["parent"], no,
+                               step["prefix_offsets"], step["scale"])
+    assert np.abs(packed.astype(np.float64) - want_o).max() <= 2e-2

@@ -75,22 +75,36 @@ def test_four_workgroups_to_an_item(G, D, hq, hkv, Ms, Ls, variant):
     w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
     rs = np.random.RandomState(sum(Ms) + sum(Ls))
     _compare(G, _case(w, sum(Ms), [_random_parents(rs, m, back=9) for m in Ms], Ls, variant), "bf16", big_scores=variant != "unit")
+    import paper_2505_13254_amd as hs
+    assert hs.hs_tree_attention_last_form() == 4
 
 
 @pytest.mark.parametrize("variant", ["unit", "hot"])
-@pytest.mark.parametrize("D,hq,hkv,M,L,B", [
-    (128, 8, 8, 129, 300, 20), (128, 8, 8, 129, 31, 20), (128, 8, 8, 161, 65, 20), (128, 8, 8, 192, 640, 20),
-    (128, 32, 4, 65, 130, 17), (128, 16, 4, 150, 97, 18), (128, 8, 8, 129, 1500, 16), (128, 8, 8, 257, 100, 16),
-    (128, 8, 8, 129, 70, 100), (64, 16, 16, 65, 200, 20), (64, 16, 16, 129, 65, 18), (64, 32, 8, 37, 500, 40)])
-def test_row_blocks_shared_by_waves(G, D, hq, hkv, M, L, B, variant):
-    """Launches beyond 128 work items whose row groups hold five or six 32-row blocks: the blocks behind the fourth are
-    shared by four waves, or by two each, key block by key block.  One tile and many, an odd last tile, groups of
-    unequal size, one grid row to a sequence, trees beyond 256 rows, the exact second pass."""
+@pytest.mark.parametrize("D,hq,hkv,M,L,B,shared", [
+    # a block to a wave: at most 256 items, equal single groups up to 1280
+    (128, 8, 8, 129, 300, 20, []), (128, 8, 8, 161, 65, 20, []), (128, 32, 4, 65, 130, 17, []), (128, 16, 4, 150, 97, 18, []),
+    (128, 8, 8, 129, 1500, 16, []), (128, 8, 8, 257, 100, 16, []), (128, 8, 8, 129, 70, 100, []), (64, 16, 16, 65, 200, 20, []),
+    # ragged, more than 256 items: single groups, one tile and many, in splits, trees beyond 256 rows
+    (128, 16, 16, 129, 31, 20, [5]), (128, 16, 16, 129, 300, 17, [5]), (128, 16, 16, 192, 640, 17, [6]), (128, 16, 16, 161, 65, 17, [6]),
+    (128, 16, 16, 129, 1500, 17, [5]), (128, 16, 16, 257, 100, 17, [5]), (128, 16, 16, 340, 130, 17, [6, 5]), (128, 16, 16, 560, 70, 17, [6, 6, 6]),
+    (64, 32, 32, 65, 200, 20, [6]), (64, 32, 32, 81, 65, 20, [6]), (64, 16, 16, 129, 65, 18, [5, 5]),
+    # equal sequences: several groups, in splits too; single groups beyond 1280 items
+    (128, 32, 8, 73, 100, 33, [5, 5]), (128, 32, 8, 90, 1000, 33, [6, 6]), (64, 32, 8, 37, 500, 40, [5, 5]),
+    (128, 33, 33, 129, 70, 40, [5]), (128, 33, 33, 170, 64, 40, [6]),
+    # one grid row to a sequence
+    (128, 16, 16, 129, 70, 100, [5]), (128, 16, 16, 170, 70, 100, [6]), (128, 16, 8, 70, 65, 100, [])])
+def test_row_blocks_shared_by_waves(G, D, hq, hkv, M, L, B, shared, variant):
+    """Row groups of five or six 32-row blocks: in launches of many items the blocks behind the fourth are shared by four
+    waves, or by two each, key block by key block (`shared`: the groups that are).  One tile and many, an odd last tile,
+    groups of unequal size, splits, one grid row to a sequence, trees beyond 256 rows, the exact second pass."""
+    import paper_2505_13254_amd as hs
     from test_gpu_attention import _case, _compare, _random_parents
     w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
     rs = np.random.RandomState(M + L)
     lens = [L] * B if B > 20 else [max(0, L - 16 * i) for i in range(B)]
     _compare(G, _case(w, M, [_random_parents(rs, M, back=9) for _ in range(B)], lens, variant), "bf16", big_scores=variant != "unit")
+    _, several, every = G.row_groups(M, hq, hkv, D)
+    assert {0: [], 1: several, 2: every}[hs.hs_tree_attention_last_form() >> 4] == shared
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
