@@ -190,6 +190,79 @@ def test_float32_splits_of_masked_keys(G, D, hq, hkv, M, L, splits, more):
     _compare(G, step, "f32")
 
 
+@pytest.mark.parametrize("k,rem", [(1, 0.6), (8, 0.6), (20, 0.6), (32, 0.5), (64, 0.25), (96, 0.12)])
+def test_ratio_rule_around_the_edge_of_a_bucket(G, k, rem):
+    """Chains of rejections whose second residual max(p - beta q, 0) has beta at 2^(k/32) and to either side of it, where the
+    sort's buckets of the ratio p / q meet, and many tokens with such ratios: the third child's test is put 4e-4 to either
+    side of what 64 bits say.  (The kernel's terms carry a few 1e-6 of p each, so its quotient about 1e-4 at most; the tokens
+    around the edge, taken for dead or live as a whole bucket, move it by 1e-3 to 1e-2.)"""
+    from oracle import verify_accept
+    V, NA = 8192, 3000
+    steps = [-0.5, -0.02, -0.009, -0.003, 0.0, 0.003, 0.009, 0.02, 0.5]
+    rs = np.random.RandomState(k)
+    target, draft, u, want_hit, bonus_u = [], [], [], [], []
+    for e in steps:
+        beta = 2.0 ** ((k + e) / 32)
+        near = 2.0 ** ((k + rs.choice([-1.1, -0.9, -0.3, -0.012, -0.008, -0.002, 0.0, 0.002, 0.008, 0.012, 0.3, 0.9, 1.1], size=NA)) / 32)
+        pa = rs.uniform(0.5, 1.5, size=NA)
+        pa *= (0.1 if k == 1 else 0.4) / pa.sum()
+        qa = pa / near
+        z1 = (beta - 1.0) * rem                                     # so that 1 + Z / (1 - q(x1)) is beta
+        ph = (z1 - (np.maximum(pa - qa, 0)).sum()) / (1 - 1 / (4 * beta))
+        p3 = 1e-5                                                   # the third child's token; x1, x2: rejected for certain
+        z2 = np.maximum(pa - beta * qa, 0).sum() + ph * 0.75
+        eps = 0.5 * z2 / (beta * rem)
+        q3 = p3 / (beta * (1 + eps))
+        ph -= (p3 - q3) / (1 - 1 / (4 * beta))
+        n_h, n_l = 1000, V - NA - 1000 - 3
+        h_p = np.full(n_h, ph / n_h)
+        q1, q2, p2 = 1 - rem, 1e-5, 1e-7
+        low = 1 - q1 - q2 - q3 - qa.sum() - ph / (4 * beta)          # of q, on tokens that p falls short on, x1 among them
+        l_q = np.full(n_l, low / n_l)
+        l_p = l_q * (1 - min(0.5, 0.5 * z1 / low))
+        p1 = 1 - pa.sum() - ph - p2 - p3 - l_p.sum()
+        assert ph > 0 and low > 0 and 0 < p1 < 0.995 * q1
+        p = np.concatenate([[p1, p2, p3], pa, h_p, l_p])
+        q = np.concatenate([[q1, q2, q3], qa, h_p / (4 * beta), l_q])
+        order = rs.permutation(V)                                   # the tokens' places in the vocabulary
+        place = np.argsort(order)
+        t, d = np.log(p[order]).astype(np.float32), np.log(q[order]).astype(np.float32)
+        # 64-bit chain on the rounded logits
+        P64, Q64 = (np.exp(x.astype(np.float64)) for x in (t, d))
+        P64, Q64 = P64 / P64.sum(), Q64 / Q64.sum()
+        cp, cq = P64.copy(), Q64.copy()
+        for c in (0, 1):
+            r = np.maximum(cp - cq, 0)
+            cp = r / r.sum()
+            cq[place[c]] = 0
+            cq /= cq.sum()
+        got_beta = 1 + np.maximum(P64 - Q64, 0).sum() / (1 - Q64[place[0]])
+        assert abs(32 * np.log2(got_beta) - (k + e)) < 1e-3
+        ratio = cp[place[2]] / cq[place[2]]
+        assert 0.4 < ratio < 0.6
+        rest = np.maximum(cp - cq, 0)
+        rest /= rest.sum()
+        for sign, last in ((-1, P64), (1, rest)):                   # accepted: the child's own row decides the bonus
+            best = int(np.argmax(last))
+            target.append(np.repeat(t[None], 4, axis=0))
+            draft.append(np.repeat(d[None], 4, axis=0))
+            u.append([0.5, 0.999, 0.999, np.float32(ratio * (1 + sign * 4e-4))])
+            bonus_u.append(np.float32(last[:best].sum() + 0.5 * last[best]))
+            want_hit.append((sign, place[:3]))
+    B = len(u)
+    target, draft = np.concatenate(target), np.concatenate(draft)
+    token = np.concatenate([np.concatenate([[0], pl]) for _, pl in want_hit]).astype(np.int32)
+    parent = np.tile(np.asarray([-1, 0, 0, 0], np.int32), B)
+    off = (4 * np.arange(B + 1)).astype(np.int32)
+    uniforms = np.concatenate([np.asarray(u, np.float32).ravel(), np.asarray(bonus_u, np.float32)])
+    want = verify_accept(target, draft, token, parent, off, 1, 1.0, uniforms, 2)
+    assert list(want["accept_len"]) == [1 if sign < 0 else 0 for sign, _ in want_hit]
+    got = G.run_accept(dict(w=W.WORKLOADS[1], target_logits=target, draft_logits=draft, token=token, parent=parent, node_offsets=off),
+                       1, uniforms, 2, temperature=1.0)
+    for name in want:
+        assert np.array_equal(got[name], want[name]), name
+
+
 @pytest.mark.parametrize("sizes,spare", [([1], 2), ([5, 3], 3), ([1030], 0), ([1100, 4], 5)])
 def test_ratio_rule_on_large_trees_and_spare_rows(G, sizes, spare):
     """Sampling with the draft's ratio rule: trees beyond the 1024 rows that are staged in LDS, and rows
