@@ -123,6 +123,15 @@ static_assert(offsetof(AttnArgs, tbl) % 16 == 0, "16-byte loads of the table ent
 // slower, 25 as 8 + 6 + 6 + 5 1 %.)
 __host__ __device__ __forceinline__ int row_groups(int n_blk) { return (n_blk + 7) >> 3; }
 __host__ __device__ __forceinline__ bool equal_row_groups(int n_blk) { return n_blk <= 6 * row_groups(n_blk); }
+// 32-row blocks of M tree rows; head dimension 64: counted head by head of the pair.
+__host__ __device__ __forceinline__ int row_blocks(int G, int half, int M) {
+  return half ? 2 * ((G / 2 * M + 31) >> 5) : (G * M + 31) >> 5;
+}
+// Whether groups of such a sequence share blocks under AttnArgs::share (equal groups beyond four blocks hold five or six each,
+// or, of nine, five and four).
+__host__ __device__ __forceinline__ bool groups_share(int n_blk, int share) {
+  return share > (n_blk <= 6 ? 1 : 0) && n_blk > 4 && equal_row_groups(n_blk);
+}
 // First block and number of blocks of group rg (<= 0 when there is no such group).
 __host__ __device__ __forceinline__ void row_group(int n_blk, int rg, int* first, int* count) {
   const int n_rg = row_groups(n_blk);

@@ -566,8 +566,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     const int64_t L = hlens != nullptr ? hlens[s] : hpo[s + 1] - hpo[s];
     if (M <= 0) continue;
     if (n == ATTN_TBL || L >= (int64_t)1 << 30) return false;
-    // 32-row wave blocks (D = 64: counted head by head)
-    const int blocks = a.half ? 2 * ((a.G / 2 * M + 31) / 32) : (a.G * M + 31) / 32;
+    const int blocks = row_blocks(a.G, a.half, M);
     Seq q;
     q.s = s;
     q.M = M;
@@ -996,6 +995,12 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
     if (a.n_tbl > 0) plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, true);
     else plan_plain(true);
     need = part_bytes(NN, Hq, D, a.sp_max) + table_bytes;
+  }
+  if (a.share != 0) {  // (none shares: the launch takes the instantiation without that code)
+    bool any = false;
+    for (int s = 0; s < B && !any; ++s)
+      any = groups_share(row_blocks(a.G, a.half, host_node_offsets[s + 1] - host_node_offsets[s]), a.share);
+    if (!any) a.share = 0;
   }
   last_form = mfma ? (1 << a.narrow) + 16 * a.share : 0;
   if (table_bytes != 0 && workspace != nullptr)

@@ -184,7 +184,10 @@ __device__ __forceinline__ void wait_lds(int n) {  // n is a constant once the w
 // wave's rows all belong to one head of the pair, whose half of the 256-byte rows it multiplies; K and
 // V are read once, in whole rows.  (Query rows widened to 128 elements with zeros took twice the matrix
 // instructions: 32 query heads, trees of 21 to 97 rows on 700 to 6001 tokens, 26.2 us -> 20.3 us.)
-template <bool PAGED, bool ONCE, bool BIG, bool HALF>
+// SHARE: waves share row blocks behind the fourth, or four of them a block (a.share, a.narrow == 2).  The code for it is kept
+// out of the other launches: with it in all of them, 8 KB of 47, a launch of few short items lost 1 us (one row, 40 heads
+// on 1056 tokens, 9 layers 42.6 -> 43.3; 18 paged sequences of up to 1585 tokens 217.8 -> 218.8, now 216.5).
+template <bool PAGED, bool ONCE, bool BIG, bool HALF, bool SHARE>
 __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_max) {
   constexpr int Q_ROW_BYTES = HALF ? MF_ROW_BYTES / 2 : MF_ROW_BYTES;  // a row of Q and of O
   constexpr int NK = HALF ? 4 : 8;  // matrix instructions (and K fragments) of a 32-key score block
@@ -291,7 +294,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const int Gh = HALF ? G >> 1 : G;      // query heads per KV head
   const int Rh = Gh * M;                  // rows of a KV head
   const int nbh = (Rh + 31) >> 5;
-  const int n_blk = HALF ? 2 * nbh : nbh;
+  const int n_blk = HALF ? 2 * nbh : nbh;  // (row_blocks)
   int blk0, blk_n;  // first block of this group, and how many
   if (h_narrow != 0) {
     const int most = 8 >> h_narrow;
@@ -312,13 +315,13 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const int pair_shift = !ksplit ? 3 : blk_n <= 1 ? 0 : blk_n == 2 ? 1 : 2;
   // With four workgroups to an item there are at most two blocks for the eight waves: four waves share one, each with
   // every fourth 32 keys (`quarter`).  (61 rows on 2048 tokens, 8 KV heads, 32 layers one by one: 589 -> 535 us.)
-  const bool quarter = h_narrow == 2;
+  const bool quarter = SHARE && h_narrow == 2;
   // Groups of five or six blocks, all groups being so: the first four waves, one to a SIMD, take a block each, and
   // the other four share what is left: two waves to a block, as above, or all four of them to one, each with
   // every fourth 32 keys.  `ways` is the number of waves that share this wave's block, kpar its share.  (With a wave
   // to a block one or two SIMDs have two waves' work and the others one's: 129 rows on 4096 tokens, 40 layers and
   // heads, 703 -> 685 us the whole step; ten blocks in two groups (row_group) 185 -> 180.  When: see a.share.)
-  const bool shared_tail = (blk_n == 5 || blk_n == 6) && equal_row_groups(n_blk) && h_share > (n_blk <= 6 ? 1 : 0);
+  const bool shared_tail = SHARE && (blk_n == 5 || blk_n == 6) && groups_share(n_blk, h_share);
   const int ways = quarter ? 4 : ksplit ? 2 : !shared_tail || wave < 4 ? 1 : blk_n == 5 ? 4 : 2;
   const int my_blk = blk0 + (shared_tail && wave >= 4 ? 4 + (blk_n == 6 ? wave & 1 : 0) : wave & ((1 << pair_shift) - 1));
   const int kpar = shared_tail ? (wave < 4 ? 0 : blk_n == 6 ? (wave - 4) >> 1 : wave - 4) : wave >> pair_shift;  // (without sharing: 0)
@@ -1135,12 +1138,15 @@ hs_status attn_mfma_launch(const AttnArgs& a, int max_tree_rows, hipStream_t str
     hs_status r = launch_status("tree attention (ancestor table)");
     if (r != HS_OK) return r;
   }
-#define MF_LAUNCH(PAGED, ONCE, BIG)                                                                                        \
-  do {                                                                                                                     \
-    if (a.half)                                                                                                            \
-      hipExtLaunchKernelGGL((k_attn_mfma<PAGED, ONCE, BIG, true>), grid, block, 0, stream, ev_start, ev_stop, 0, a, n_rg_max);  \
-    else                                                                                                                   \
-      hipExtLaunchKernelGGL((k_attn_mfma<PAGED, ONCE, BIG, false>), grid, block, 0, stream, ev_start, ev_stop, 0, a, n_rg_max); \
+  const bool share = a.share != 0 || a.narrow == 2;
+#define MF_LAUNCH_AS(PAGED, ONCE, BIG, HALF, SHARE) \
+  hipExtLaunchKernelGGL((k_attn_mfma<PAGED, ONCE, BIG, HALF, SHARE>), grid, block, 0, stream, ev_start, ev_stop, 0, a, n_rg_max)
+#define MF_LAUNCH(PAGED, ONCE, BIG)                                 \
+  do {                                                              \
+    if (a.half && share) MF_LAUNCH_AS(PAGED, ONCE, BIG, true, true);   \
+    else if (a.half) MF_LAUNCH_AS(PAGED, ONCE, BIG, true, false);      \
+    else if (share) MF_LAUNCH_AS(PAGED, ONCE, BIG, false, true);       \
+    else MF_LAUNCH_AS(PAGED, ONCE, BIG, false, false);                 \
   } while (0)
   if (a.block_table != nullptr) {
     if (big) MF_LAUNCH(true, false, true);
@@ -1152,6 +1158,7 @@ hs_status attn_mfma_launch(const AttnArgs& a, int max_tree_rows, hipStream_t str
     else MF_LAUNCH(false, false, false);
   }
 #undef MF_LAUNCH
+#undef MF_LAUNCH_AS
   return launch_status("tree attention (mfma)");
 }
 

@@ -310,10 +310,14 @@ __global__ __launch_bounds__(GP_THREADS) void k_greedy_path(const float* __restr
 }
 
 // Which of the two a greedy call takes: the scan of every row, or the rows of the paths alone, one after the other.  The
-// longest path there can be decides, so that no tree is slower than by the scan.  Sequences of 61 rows, paths of 1, 5 and 11
-// rows of a longest 11, whole calls of 12 to 13 us at least: 16 of 128256 tokens 91 us by the scan, 12.7, 41 and 86 by
-// the paths; 64 of them 339 and 13, 43, 140; 64 of 32000 tokens 92 and 12.5, 21, 41; 200 of 8000 75 and 12.5, 14, 29.
-// (16 sequences of 8 to 128 nodes on 128256 tokens, the whole step: 382 us, 303.)
+// longest path that the call allows decides, so that a tree whose path is as long as that is no slower than by the scan; sibling
+// tokens differ, as everywhere (a level with several confirmed nodes is read row by row, right but slower).  Sequences of 61
+// rows, paths of 1, 5 and 11 rows of a longest 11, whole calls of 12 to 13 us at least: 16 of 128256 tokens 91 us by the scan,
+// 12.7, 41 and 86 by the paths; 64 of them 339 and 13, 43, 140; 64 of 32000 tokens 92 and 12.5, 21, 41; 200 of 8000 75 and
+// 12.5, 14, 29.  (16 sequences of 8 to 128 nodes on 128256 tokens, the whole step: 382 us, 303.)  Looking for children in
+// trees beyond LDS is priced on neither side: 3 us a level and 20000 rows here, but more in the walk that follows the scan
+// (one tree of 60000 rows on 600 tokens, depth limit 10, all children of the root or at random depths: 258 and 826 us by the
+// scan, 119 and 113 by the paths; of 9000 rows on 2000 tokens, limit 4, 45 and 111, 19 and 18).
 static bool greedy_by_path(int B, int NN, int V, int max_depth, bool aligned) {
   const double row_bytes = 4.0 * V;
   const double scan_us = 6.0 + (double)NN * row_bytes / 6.0e6;
@@ -469,13 +473,14 @@ __device__ __forceinline__ int gather_children(const int* parent, int o, int n, 
 // taken at an increasing sequence of beta >= 1 that is not known in advance, but for the first:
 // 1.  A token contributes p - beta q while its ratio p / q exceeds beta and nothing afterwards.  So, for
 // every node with at least two children, a kernel that runs on the whole chip sorts the tokens with p > q of each
-// vocabulary slice by their ratio into BK_N buckets (a counting sort inside a workgroup, the slice
-// read twice) and keeps, per bucket, the sums of p and of q.  F(1) is the sum of all of them, F(beta)
+// vocabulary slice by their ratio into BK_N buckets (a counting sort inside a workgroup: count, then place) and keeps,
+// per bucket, the sums of p and of q.  F(1) is the sum of all of them, F(beta)
 //     sum over the buckets well above beta of (P_b - beta Q_b)      two suffix sums, read once
 //   + sum over the tokens of beta's bucket (and of the next one where beta is near its edge) of max(p - beta q, 0)
-// which is what k_accept_chain evaluates per rejection: a few thousand pairs instead of two
+// which is what k_accept_chain evaluates per rejection: about a thousand pairs instead of two
 // vocabulary rows.  (Sorted across slices, with a scan and a second pass over the rows in launches of
-// their own: 23.6 us for a 61-row tree; now 16.3.)  A token's bucket is floor(BK_PER_OCTAVE * log2(p / q)), taken from the two
+// their own: 23.6 us for a 61-row tree; slice by slice, read twice, 15.7; kept in registers for the second pass, now, 12.1.)
+// A token's bucket is floor(BK_PER_OCTAVE * log2(p / q)), taken from the two
 // exponent arguments (p = exp2(a_p)): the rounding of that difference is many orders below a
 // bucket's width, and where beta lies near the edge of a bucket the next one is treated token by token as well, so
 // no token is ever taken for live or dead by its bucket alone when it is not.  All sums are 64-bit

@@ -193,11 +193,15 @@ def test_more_sequences_than_the_table_holds_take_a_plain_grid():
 @pytest.mark.parametrize("Ms,Ls,Hq,Hkv,D,form", [
     ([61], [2048], 32, 8, 128, 4), ([61], [2048], 32, 8, 64, 4), ([20], [2048], 32, 8, 128, 1),   # four workgroups: more than 128 rows
     ([129] * 16, [1500] * 16, 8, 8, 128, 2), ([61] * 17, [2048] * 17, 32, 8, 128, 1),             # two: at most 128 items
-    ([129] * 32, [300] * 32, 8, 8, 128, 1), ([129] * 33, [300] * 33, 8, 8, 128, 17),               # sharing beyond 256 items, of
-    ([73] * 33, [100] * 33, 32, 8, 128, 17), ([61] * 32, [2048] * 32, 32, 8, 128, 1),              # several groups alone
-    ([129] * 40, [70] * 40, 32, 32, 128, 17), ([129] * 41, [70] * 41, 32, 32, 128, 33),            # beyond 1280 of single ones too
+    ([73] * 16, [100] * 16, 32, 8, 128, 1), ([73] * 17, [100] * 17, 32, 8, 128, 17),               # sharing: beyond 256 items, of several
+    ([129] * 33, [300] * 33, 8, 8, 128, 1), ([61] * 33, [2048] * 33, 32, 8, 128, 1),               # groups alone
+    ([129] * 40, [70] * 40, 32, 32, 128, 1), ([129] * 41, [70] * 41, 32, 32, 128, 33),             # beyond 1280 of single ones too
+    ([128] * 41, [70] * 41, 32, 32, 128, 1), ([193] * 41, [70] * 41, 32, 32, 128, 1),              # four blocks, seven
     ([129] * 17, list(range(300, 44, -16)) + [40], 16, 16, 128, 33),                               # ragged
-    ([129] * 100, [70] * 100, 16, 16, 128, 33), ([129] * 100, [70] * 100, 8, 8, 128, 17)])         # plain grid
+    ([61] * 17, list(range(300, 44, -16)) + [40], 32, 16, 128, 1),                                 # four blocks
+    ([61] * 16 + [129], list(range(300, 44, -16)) + [40], 16, 16, 128, 33),                        # one sequence that shares
+    ([129] * 100, [70] * 100, 16, 16, 128, 33), ([129] * 100, [70] * 100, 8, 8, 128, 1),           # plain grid
+    ([70] * 100, [70] * 100, 16, 8, 128, 1), ([73] * 100, [70] * 100, 32, 8, 128, 17)])
 def test_how_row_blocks_go_to_workgroups_and_waves(Ms, Ls, Hq, Hkv, D, form):
     assert _plan(Ms, Ls, Hq, Hkv, D)[0][0] == 1
     assert hs.hs_tree_attention_last_form() == form
