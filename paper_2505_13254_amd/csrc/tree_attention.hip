@@ -387,8 +387,13 @@ struct AttnPlan {
 // 13.4, 512 15.9, 1024 22.9, unsplit 33.2; 4 of 283 to 437: 256 13.3, unsplit 12.7; 8 of 866 to 1819: 512 (704) 39.4,
 // unsplit (216) 32.0.  D = 128, one of 432, 55 rows: 128 13.5, 256 16.3, unsplit 19.1; one of 595: 128 14.2, 256 15.5,
 // 512 22.6; one of 213: 128 14.1, unsplit 14.4.
+// one_launch: by the rule without this estimate the call would be unsplit.  It stays so while its chain is no longer than what
+// a second launch costs the host: calls one behind the other take 14.6 us at least with one launch and 18 with two (D = 128, 8
+// KV heads, in splits of 128 and unsplit: one and two sequences of 300 tokens, 20 rows 17.9 and 15.5, 18.0 and 15.7; 4 of 110 to
+// 355, 10 to 21 rows 18.2 and 16.1; 4 of 350, 16 rows 18.2 and 17.1; with 40 rows on 2 KV heads 18.6 both).
+constexpr float PLAN_ONE_LAUNCH_US = 15.7f;
 static int64_t plan_float_split(const int32_t* hno, const int64_t* hpo, const int64_t* hlens, int B, int G, int Hkv, int D,
-                                int n_rb_max, int rows_per_wg, int64_t max_L) {
+                                int n_rb_max, int rows_per_wg, int64_t max_L, bool one_launch) {
   const float key_us = D == 64 ? 0.014f : 0.028f;
   const int64_t least = D == 64 ? 256 : 128;  // a trip's keys
   int64_t best = 0, last = 0;
@@ -414,7 +419,7 @@ static int64_t plan_float_split(const int32_t* hno, const int64_t* hpo, const in
       best = len;
       best_us = us;
     }
-    if (len == least || w > 4.f) break;
+    if (len == least || w > 4.f || (one_launch && sp_max == 1 && us <= PLAN_ONE_LAUNCH_US)) break;
   }
   return best;
 }
@@ -452,7 +457,7 @@ static AttnPlan plan_attention(const int32_t* hno, const int64_t* hpo, const int
   if (len < 512) len = 512;        // never split finer than 512 tokens
   // (many rounds of workgroups, of which the estimate knows nothing, are left to the rule above)
   if (rows_per_wg > 0 && !lean && base_wgs <= 4 * PLAN_CUS && max_L < (int64_t)1 << 30)
-    len = plan_float_split(hno, hpo, hlens, B, G, Hkv, D, p.n_rb_max, rows_per_wg, max_L);
+    len = plan_float_split(hno, hpo, hlens, B, G, Hkv, D, p.n_rb_max, rows_per_wg, max_L, splits_of(max_L, (int)len) == 1);
   p.split_len = (int)len;
   p.sp_max = splits_of(max_L, p.split_len);
   p.ok = true;

@@ -211,6 +211,15 @@ def test_how_row_blocks_go_to_workgroups_and_waves(Ms, Ls, Hq, Hkv, D, form):
     assert hs.hs_tree_attention_last_form() == 0
 
 
+@pytest.mark.parametrize("Ms,Ls,Hkv,D,splits", [
+    ([20], [300], 8, 128, 1), ([20, 20], [300, 300], 8, 128, 1), ([16] * 4, [350] * 4, 8, 128, 1), ([21, 10, 15, 15], [116, 321, 110, 355], 8, 128, 1),
+    ([40] * 4, [350] * 4, 2, 128, 3), ([55], [432], 8, 128, 4), ([20], [500], 8, 64, 1), ([20], [1000], 8, 64, 4), ([20], [2000], 8, 64, 8)])
+def test_float32_calls_that_one_launch_serves_as_well_are_not_split(Ms, Ls, Hkv, D, splits):
+    """The merge is a second launch, which a short call does not earn back on the host."""
+    totals, _ = _plan(Ms, Ls, 8, Hkv, D, dt=hs.HS_F32)
+    assert totals[0] == 2 and totals[2] == splits and totals[5] == (splits > 1)
+
+
 def test_which_kernel_a_shape_gets():
     assert _plan([61], [300], 8, 2)[0][0] == 1
     assert _plan([61], [300], 8, 2, dt=hs.HS_F32)[0][0] == 2

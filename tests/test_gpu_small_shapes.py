@@ -146,7 +146,7 @@ def test_attention_of_any_shape_and_address(G, dtype, D, hq, hkv, M, L, offset):
 
 
 @pytest.mark.parametrize("D,hq,hkv,Ms,Ls", [
-    (128, 8, 8, [55], [257]), (128, 8, 8, [17, 3, 31], [385, 0, 1000]), (128, 8, 2, [40], [1025]), (128, 3, 3, [1], [1153]),
+    (128, 8, 8, [55], [385]), (128, 8, 8, [17, 3, 31], [385, 0, 1000]), (128, 8, 2, [40], [1025]), (128, 3, 3, [1], [1153]),
     (64, 8, 8, [33, 16], [513, 1300]), (64, 8, 2, [5, 1], [2000, 127]), (64, 6, 3, [20], [4100])])
 def test_float32_prefixes_in_splits(G, D, hq, hkv, Ms, Ls):
     """The float32 kernel's splits: of 128 tokens and more, last ones of a single key, beside sequences that are not split,
