@@ -66,11 +66,12 @@ def test_launches_that_leave_compute_units_to_spare(G, D, hq, hkv, M, L, variant
 @pytest.mark.parametrize("variant", ["unit", "hot"])
 @pytest.mark.parametrize("D,hq,hkv,Ms,Ls", [
     (128, 8, 2, [40], [0]), (128, 8, 2, [33], [31]), (128, 8, 2, [56], [64]), (128, 8, 2, [64], [449]), (128, 16, 2, [33], [2048]),
-    (128, 8, 2, [65], [130]), (128, 8, 8, [130, 5], [200, 90]), (64, 8, 2, [20], [33]), (64, 8, 2, [33], [300]), (64, 8, 4, [129], [1000])])
+    (128, 8, 2, [65], [130]), (128, 8, 8, [130, 5], [200, 90]), (64, 8, 2, [20], [33]), (64, 8, 2, [33], [300]), (64, 8, 4, [129], [1000]),
+    (128, 8, 8, [260], [100]), (64, 8, 8, [260], [100]), (128, 8, 2, [300], [700])])
 def test_four_workgroups_to_an_item(G, D, hq, hkv, Ms, Ls, variant):
     """Launches of at most 64 items of more than 128 rows: one or two row blocks to a workgroup, four waves to a block, each on
     every fourth 32 keys.  Fewer keys than waves have turns, odd last blocks and groups, beside a sequence of few rows,
-    unsplit and in splits, the exact second pass."""
+    unsplit and in splits, trees beyond 256 rows, the exact second pass."""
     from test_gpu_attention import _case, _compare, _random_parents
     w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=D)
     rs = np.random.RandomState(sum(Ms) + sum(Ls))
@@ -87,7 +88,7 @@ def test_four_workgroups_to_an_item(G, D, hq, hkv, Ms, Ls, variant):
     # ragged, more than 256 items: single groups, one tile and many, in splits, trees beyond 256 rows
     (128, 16, 16, 129, 31, 20, [5]), (128, 16, 16, 129, 300, 17, [5]), (128, 16, 16, 192, 640, 17, [6]), (128, 16, 16, 161, 65, 17, [6]),
     (128, 16, 16, 129, 1500, 17, [5]), (128, 16, 16, 257, 100, 17, [5]), (128, 16, 16, 340, 130, 17, [6, 5]), (128, 16, 16, 560, 70, 17, [6, 6, 6]),
-    (64, 32, 32, 65, 200, 20, [6]), (64, 32, 32, 81, 65, 20, [6]), (64, 16, 16, 129, 65, 18, [5, 5]),
+    (64, 32, 32, 65, 200, 20, [6]), (64, 32, 32, 81, 65, 20, [6]), (64, 16, 16, 129, 65, 18, [5, 5]), (64, 32, 32, 257, 65, 20, [6, 6, 6]),
     # equal sequences: several groups, in splits too; single groups beyond 1280 items
     (128, 32, 8, 73, 100, 33, [5, 5]), (128, 32, 8, 90, 1000, 33, [6, 6]), (64, 32, 8, 37, 500, 40, [5, 5]),
     (128, 33, 33, 129, 70, 40, [5]), (128, 33, 33, 170, 64, 40, [6]),
