@@ -3,7 +3,7 @@
 // Section 4.2: entropy bins; Section 4.3: depth extension d' and node budget N').
 //
 // Nothing to stream: a few hundred nodes per sequence, one workgroup per sequence, no workspace.
-// The tree is staged in LDS (up to 8192 rows; larger ones are walked in global memory).  A walk from each node
+// The tree is staged in LDS (up to 8192 rows; of larger ones the parents alone, or nothing).  A walk from each node
 // to the root gives its depth and value (the float32 add per node of the reranking step, so the choice of P* is taken on
 // the same numbers as the pruning that follows); one 64-bit (depth, value, row) key per node and a workgroup
 // maximum pick P*; the first wave then sums the path's entropies root-first in float32 and looks up the bin.
@@ -18,7 +18,12 @@ namespace hs {
 constexpr int CTL_THREADS = 512;
 constexpr int CTL_MAX_BINS = 64;
 constexpr int CTL_MAX_LOW = 8;
-constexpr int CTL_LDS_NODES = 8192;
+// Rows whose tree lies in LDS, at 16 bytes a row.  A compute unit holds one workgroup of the larger kernel, so calls of
+// more sequences than there are compute units take the smaller one, of which it holds four; trees that outgrow that have their
+// parents in the same 32 KB.  (1024 sequences of 61 / 511 / 1500 rows 10.6 / 12.4 / 19.2 us by the larger one, 4.4 / 5.8 / 10.1 by the
+// smaller; with the parents in LDS alone, whatever the size, 7.8 / 7.8 / 13.1, and one sequence 8.3 / 7.9 / 12.0, now 3.7 / 3.8 / 5.6.)
+constexpr int CTL_LDS_NODES = 8192, CTL_LDS_NODES_MANY = 2048;
+constexpr int CTL_CUS = 256;
 
 struct ControlArgs {
   const int32_t* parent;
@@ -94,11 +99,11 @@ __device__ __forceinline__ void decide(const ControlArgs& a, int s, int p, int D
   a.n_prime[s] = np_;
 }
 
-// Trees that do not fit LDS.
-__device__ __forceinline__ void control_large(const ControlArgs& a, int s, int o, int n, unsigned long long* red_k) {
+// Trees that do not fit LDS; `par` may.
+template <typename IP>
+__device__ __forceinline__ void control_large(const ControlArgs& a, int s, int o, int n, IP par, unsigned long long* red_k) {
   __shared__ int deepest;
   const int tid = threadIdx.x;
-  const int* par = a.parent + o;
   const float* lc = a.logc + o;
   auto depth_of = [&](int i) {
     int d = 0;
@@ -131,11 +136,13 @@ __device__ __forceinline__ void control_large(const ControlArgs& a, int s, int o
   if (tid < 64) decide(a, s, 0x7fffffff - (int)(unsigned)(best & 0xffffffffull), D, par, a.ent + o);
 }
 
+template <int NODES>
 __global__ __launch_bounds__(CTL_THREADS) void k_adaptive_control(ControlArgs a) {
   __shared__ unsigned long long red_k;
-  __shared__ int l_par[CTL_LDS_NODES];
-  __shared__ float l_logc[CTL_LDS_NODES];
-  __shared__ unsigned long long l_node[CTL_LDS_NODES];  // deep trees: the nodes' words; else the entropies
+  __shared__ unsigned long long pool[2 * NODES];
+  int* const l_par = reinterpret_cast<int*>(pool);
+  float* const l_logc = reinterpret_cast<float*>(l_par + NODES);
+  unsigned long long* const l_node = pool + NODES;  // deep trees: the nodes' words; else the entropies
   __shared__ int unsettled[3];
   const int s = blockIdx.x, tid = threadIdx.x;
   const int o = a.node_offsets[s];
@@ -150,8 +157,13 @@ __global__ __launch_bounds__(CTL_THREADS) void k_adaptive_control(ControlArgs a)
     }
     return;
   }
-  if (n > CTL_LDS_NODES) {
-    control_large(a, s, o, n, &red_k);
+  if (n > NODES) {
+    if (n <= 4 * NODES) {
+      for (int i = tid; i < n; i += CTL_THREADS) l_par[i] = a.parent[o + i];
+      control_large(a, s, o, n, (const int*)l_par, &red_k);  // (its first barrier comes before it looks at them)
+    } else {
+      control_large(a, s, o, n, a.parent + o, &red_k);
+    }
     return;
   }
   float* const l_ent = reinterpret_cast<float*>(l_node);
@@ -164,7 +176,7 @@ __global__ __launch_bounds__(CTL_THREADS) void k_adaptive_control(ControlArgs a)
   if (tid == 0) red_k = 0ull;
   __syncthreads();
   // the best node of the deepest level: (depth, value, row) as one key
-  static_assert(CTL_LDS_NODES <= 1 << 13, "13 bits of depth, 32 of value, 13 of row");
+  static_assert(NODES <= 1 << 13, "13 bits of depth, 32 of value, 13 of row");
   auto key_of = [&](int i, unsigned long long w) {
     const float v = a.mode == 0 ? node_sum(w) : i == 0 ? 0.f : fminf(l_logc[i], 0.f);
     return ((unsigned long long)(unsigned)node_depth(w) << 45) | ((unsigned long long)order_bits(v) << 13) | (unsigned)(8191 - i);
@@ -182,7 +194,7 @@ __global__ __launch_bounds__(CTL_THREADS) void k_adaptive_control(ControlArgs a)
     ent = a.ent + o;
     for (int i = tid; i < n; i += CTL_THREADS) l_node[i] = i == 0 ? node_word(0.f, 0, true) : 0ull;
     __syncthreads();
-    settle_nodes<CTL_THREADS, CTL_LDS_NODES>(l_par, l_logc, l_node, unsettled, n, any);
+    settle_nodes<CTL_THREADS, NODES>(l_par, l_logc, l_node, unsettled, n, any);
     best = 0ull;
     for (int i = tid; i < n; i += CTL_THREADS)
       if (l_node[i] != 0ull) best = max(best, key_of(i, l_node[i]));  // (0: not settled, a malformed tree)
@@ -226,7 +238,11 @@ extern "C" hs_status hs_adaptive_control(const int32_t* parent, const float* log
   for (int e = 0; e < CTL_MAX_BINS - 1; ++e) a.edges[e] = e < n_bins - 1 ? host_bin_edges[e] : 0.f;
   for (int e = 0; e < CTL_MAX_LOW; ++e) a.gamma[e] = e < n_low ? host_gamma[e] : 0.f;
   a.phi = phi; a.pstar = pstar; a.bin = bin; a.d_prime = d_prime; a.n_prime = n_prime;
-  hipLaunchKernelGGL(k_adaptive_control, dim3((unsigned)B), dim3(CTL_THREADS), 0, static_cast<hipStream_t>(stream), a);
+  const dim3 grid((unsigned)B), block(CTL_THREADS);
+  if (B > CTL_CUS && NN <= (int64_t)CTL_LDS_NODES_MANY * B)
+    hipLaunchKernelGGL(k_adaptive_control<CTL_LDS_NODES_MANY>, grid, block, 0, static_cast<hipStream_t>(stream), a);
+  else
+    hipLaunchKernelGGL(k_adaptive_control<CTL_LDS_NODES>, grid, block, 0, static_cast<hipStream_t>(stream), a);
   return launch_status("adaptive control");
 }
 

@@ -151,6 +151,36 @@ def test_prune_counted_matches_the_checker(G):
         assert np.array_equal(got["depth"][a:a + c], want["depth"][b:b + c])
 
 
+@pytest.mark.parametrize("big,depth", [(2048, 12), (2049, 12), (8192, 17), (8193, 12), (2048, 30), (9000, 40)])
+@pytest.mark.parametrize("B", [256, 257, 300])
+def test_adaptive_control_on_more_sequences_than_compute_units(G, B, big, depth):
+    """The kernel for many sequences: trees as large as its LDS holds and larger, shallow and deep, among small and empty ones."""
+    import paper_2505_13254_amd as hs
+    rs = np.random.RandomState(B + big + depth)
+    sizes = [int(x) for x in rs.randint(0, 40, size=B)]
+    sizes[3], sizes[B - 1] = big, 1
+    par, lc = [], []
+    for n in sizes:
+        p, d = [-1] if n else [], [0]
+        for i in range(1, n):
+            j = i - 1 if i <= depth else int(rs.randint(0, i))
+            while d[j] >= depth:
+                j = p[j]
+            p.append(j)
+            d.append(d[j] + 1)
+        par += p
+        lc += list(np.round(-rs.exponential(0.4, size=n) * 4) / 4)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    par, lc = np.asarray(par, np.int32), np.asarray(lc, np.float32)
+    ent = rs.uniform(0.0, 0.4, size=len(par)).astype(np.float32)
+    for mode in (0, 1):
+        want = adaptive_control(par, lc, ent, off, EDGES8, GAMMA, 3, 6, 60, mode)
+        got = hs.hs_adaptive_control(G.dev(par), G.dev(lc), G.dev(ent), G.dev(off), None, EDGES8, GAMMA, 3, 6, 60, mode)
+        for k in ("pstar", "bin", "d_prime", "n_prime"):
+            assert np.array_equal(G.host(got[k]), want[k]), (k, mode)
+        assert np.allclose(G.host(got["phi"]), want["phi"], rtol=1e-5, atol=1e-8)
+
+
 @pytest.mark.parametrize("B,K,F", [(1, 10, 10), (1, 64, 64), (3, 3, 12), (2, 7, 100)])
 def test_expand_reads_no_results_behind_the_last_frontier_row(G, B, K, F):
     """The result arrays may end with the last sequence's last frontier row: [K] entries on a first call with one
