@@ -24,6 +24,11 @@ size_t attn_mfma_table_bytes(int max_tree_rows, int64_t NN);
 constexpr int GEN_THREADS = 512;
 constexpr int GEN_WAVES = GEN_THREADS / 64;
 constexpr int GEN_ROWS = 16;  // rows per workgroup
+constexpr int gen_groups(int D) { return D == 64 ? 2 : 1; }  // key groups of a wave's trip
+// Whether a split of so many keys and a tree of max_M rows are one trip of the workgroup's waves at most.
+static inline bool generic_short(int64_t keys, int max_M, int D) {
+  return (keys + 15) / 16 + (max_M + 15) / 16 <= GEN_WAVES * gen_groups(D);
+}
 constexpr int GEN_TILE = 64;  // tokens of a page
 constexpr int MAX_TREE_ROWS = 1024;
 
@@ -44,10 +49,14 @@ constexpr int MAX_TREE_ROWS = 1024;
 // (One row group of four rows per wave on the vector ALUs, K and V staged through LDS, five LDS reads to
 // four multiply-adds: three sequences of 100 to 1500 tokens, 8 heads of 64, 17 to 40 rows: 84 us a call, 23 then and 17 now;
 // one of 16384 tokens, 32 heads of 128 on 8, 61 rows: 2048 us a call, now 210.)
-template <typename T, int D>
+// SHORT: no workgroup of the launch has more keys than one trip takes (generic_short), so that waves may have none.  These then
+// request none; in longer launches the branch would cost the loop its register allocation.  (77 sequences of one row, 8 heads of
+// 64, without a prefix: 11.0 us before the keys were requested ahead of the root paths, 13.4 with it, 11.2 now; 16 heads, 22
+// tokens 21.0, 24.2, 20.5; 4 sequences of 250 tokens, 20 rows, 8 heads of 128: 15.2, 14.6, and 15.1 to 15.7 with the branch.)
+template <typename T, int D, bool SHORT>
 __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
   constexpr int NQ = D / 16;            // 16-byte (float32) pieces of a lane's part of a K, Q or V row group
-  constexpr int GPI = D == 64 ? 2 : 1;  // key groups of a wave's trip
+  constexpr int GPI = gen_groups(D);
   constexpr int DPL = D / 16;           // output columns of a lane's row (and column blocks)
   constexpr int ANC_WORDS = MAX_TREE_ROWS / 32;
   __shared__ int par[MAX_TREE_ROWS];
@@ -128,18 +137,9 @@ __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
   for (int k = 0; k < PAR_PER; ++k) my_par[k] = parent[min(tid + k * GEN_THREADS, M - 1)];
   asm volatile("" ::: "memory");  // (keeps the requests in this order)
 
-  Frag cur[GPI], nxt[GPI];
-  const int stride = GEN_WAVES * GPI;
-  int grp = wave * GPI;
-#pragma unroll
-  for (int u = 0; u < GPI; ++u) load_group(min(grp + u, n_groups - 1), cur[u]);
-
-  float4 qf[NQ];
-#pragma unroll
-  for (int c = 0; c < NQ; ++c) qf[c] = load4<T>(q + qrow * D + 16 * c + 4 * h);
-
   // ---- the rows' root paths as bit sets over the tree rows
-  if (last_split) {
+  auto root_paths = [&]() {
+    if (!last_split) return;
 #pragma unroll
     for (int k = 0; k < PAR_PER; ++k)
       if (tid + k * GEN_THREADS < M) par[tid + k * GEN_THREADS] = my_par[k];
@@ -153,6 +153,20 @@ __global__ __launch_bounds__(GEN_THREADS) void k_attn_generic(AttnArgs a) {
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  };
+
+  Frag cur[GPI], nxt[GPI];
+  float4 qf[NQ];
+  const int stride = GEN_WAVES * GPI;
+  int grp = wave * GPI;
+  if (!SHORT || grp < n_groups) {
+#pragma unroll
+    for (int u = 0; u < GPI; ++u) load_group(min(grp + u, n_groups - 1), cur[u]);
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) qf[c] = load4<T>(q + qrow * D + 16 * c + 4 * h);
+    root_paths();
+  } else {  // (a wave without keys requests none; it meets the same barriers)
+    root_paths();
   }
 
   floatx4 acc[DPL];
@@ -1001,7 +1015,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
     else plan_plain(true);
     need = part_bytes(NN, Hq, D, a.sp_max) + table_bytes;
   }
-  if (a.share != 0) {  // (none shares: the launch takes the instantiation without that code)
+  if (mfma && a.share != 0) {  // (none shares: the launch takes the instantiation without that code)
     bool any = false;
     for (int s = 0; s < B && !any; ++s)
       any = groups_share(row_blocks(a.G, a.half, host_node_offsets[s + 1] - host_node_offsets[s]), a.share);
@@ -1050,10 +1064,17 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
     last_kernel = 1;
   } else {
     dim3 grid((unsigned)(Hkv * plan.n_rb_max * plan.sp_max), (unsigned)B);
-    if (dt == HS_F32 && D == 64) hipLaunchKernelGGL((k_attn_generic<float, 64>), grid, dim3(GEN_THREADS), 0, st, a);
-    else if (dt == HS_F32) hipLaunchKernelGGL((k_attn_generic<float, 128>), grid, dim3(GEN_THREADS), 0, st, a);
-    else if (D == 64) hipLaunchKernelGGL((k_attn_generic<bf16_t, 64>), grid, dim3(GEN_THREADS), 0, st, a);
-    else hipLaunchKernelGGL((k_attn_generic<bf16_t, 128>), grid, dim3(GEN_THREADS), 0, st, a);
+    const bool few = generic_short(std::min(plan.max_L, (int64_t)plan.split_len), max_M, D);
+#define GEN_LAUNCH(T, D)                                                                                             \
+  do {                                                                                                               \
+    if (few) hipLaunchKernelGGL((k_attn_generic<T, D, true>), grid, dim3(GEN_THREADS), 0, st, a);                     \
+    else hipLaunchKernelGGL((k_attn_generic<T, D, false>), grid, dim3(GEN_THREADS), 0, st, a);                        \
+  } while (0)
+    if (dt == HS_F32 && D == 64) GEN_LAUNCH(float, 64);
+    else if (dt == HS_F32) GEN_LAUNCH(float, 128);
+    else if (D == 64) GEN_LAUNCH(bf16_t, 64);
+    else GEN_LAUNCH(bf16_t, 128);
+#undef GEN_LAUNCH
     hs_status r = launch_status("tree attention");
     if (r != HS_OK) return r;
     last_kernel = 2;

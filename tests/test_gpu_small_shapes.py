@@ -111,11 +111,12 @@ def test_row_blocks_shared_by_waves(G, D, hq, hkv, M, L, B, shared, variant):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("D,hq,hkv,M,L,offset", [
     (64, 3, 3, 1, 0, 0), (64, 3, 3, 16, 15, 0), (64, 6, 3, 17, 16, 1), (64, 3, 1, 33, 511, 0), (64, 3, 3, 5, 1040, 3),
-    (128, 3, 3, 1, 1, 0), (128, 6, 3, 16, 17, 0), (128, 3, 1, 47, 513, 1), (128, 3, 3, 1024, 40, 0)])
+    (128, 3, 3, 1, 1, 0), (128, 6, 3, 16, 17, 0), (128, 3, 1, 47, 513, 1), (128, 3, 3, 1024, 40, 0),
+    (64, 3, 1, 33, 208, 0), (64, 3, 1, 33, 209, 0), (64, 3, 3, 256, 0, 0), (128, 3, 1, 16, 112, 0), (128, 3, 3, 17, 112, 0)])
 def test_attention_of_any_shape_and_address(G, dtype, D, hq, hkv, M, L, offset):
     """The kernel for float32 and for what the bfloat16 matrix kernel refuses (an odd number of KV heads of
-    64, arrays off a 16-byte boundary): groups of 16 keys that end short, fewer groups than waves, split
-    prefixes, the largest tree, arrays that start `offset` elements off."""
+    64, arrays off a 16-byte boundary): groups of 16 keys that end short, fewer groups than waves, as many as one trip takes and
+    one more, split prefixes, the largest tree, arrays that start `offset` elements off."""
     import paper_2505_13254_amd as hs
     from oracle import pipeline
     from test_gpu_attention import _case, _random_parents
