@@ -497,8 +497,10 @@ constexpr int PLAN_MIN_SPLIT_TILES = 2;
 // exchange and half the records to write for each of them.  Whole calls, one layer, 8 KV heads, best cut with two and with four: 61 rows on 500 /
 // 1000 / 2048 / 4096 tokens 14.6 / 16.0 / 18.3 / 20.3 us and 13.9 / 15.1 / 16.7 / 19.5, D = 64 on 2048 13.3 and 12.9; 40
 // heads, 129 rows on 400 tokens 18.3 and 16.4.  None gained by items of at most 128 rows (20 on 2048 14.9 and 15.3), nor by long
-// prefixes, which want more splits than that leaves room for (9000 tokens 27.1 and 29.5).
-constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2, PLAN_QUARTER_ITEMS = PLAN_CUS / 4;
+// prefixes, which want more splits than that leaves room for (9000 tokens 27.1 and 29.5).  Nor, with D = 128, by trees
+// beyond 256 rows, whose table comes tile by tile: 16 heads, 300 rows on 500 / 2000 tokens 21.5 / 35.9 us with two, 23.8 / 45.3 with four;
+// 1024 on 2000 51.8 and 59.8; D = 64, 300 on 1000 20.4 and 21.5, but 1024 on 200 28.0 and 26.6.
+constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2, PLAN_QUARTER_ITEMS = PLAN_CUS / 4, PLAN_QUARTER_ROWS = 256;
 // Launches that give every item a compute unit of its own, either way: the longest item decides.  A tile costs
 // the more the more K/V streams are read at a time, and above 128 rows, where two waves share a SIMD, the matrix
 // instructions' time at least; up to 128 rows two waves to a row block gain nothing, and cost more to start and
@@ -579,7 +581,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     float tile_us;  // of its largest group if that were full: what the entries are ordered by
   };
   Seq seqs[ATTN_TBL];
-  int n = 0;
+  int n = 0, max_rows = 0;
   for (int s = 0; s < B; ++s) {
     const int M = hno[s + 1] - hno[s];
     const int64_t L = hlens != nullptr ? hlens[s] : hpo[s + 1] - hpo[s];
@@ -589,6 +591,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
     Seq q;
     q.s = s;
     q.M = M;
+    max_rows = std::max(max_rows, M);
     q.tiles = (int)((L + 63) / 64);
     q.tile_us = plan_tile_us(std::min(8, (a.G * M + 31) / 32));
     q.rg = row_groups(blocks);
@@ -647,7 +650,8 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
         streamed += (double)a.Hkv * nsp * (per + q.ttiles);
       }
       const float streams = (float)(streamed / longest);  // read at a time while the longest item runs
-      for (int narrow = 0; narrow <= (items <= PLAN_QUARTER_ITEMS ? 2 : items <= PLAN_NARROW_ITEMS ? 1 : 0); ++narrow) {
+      const bool quarter = items <= PLAN_QUARTER_ITEMS && (a.half != 0 || max_rows <= PLAN_QUARTER_ROWS);
+      for (int narrow = 0; narrow <= (quarter ? 2 : items <= PLAN_NARROW_ITEMS ? 1 : 0); ++narrow) {
         float est = 0.f;
         for (int i = 0; i < n; ++i) {
           const Seq& q = seqs[i];

@@ -191,7 +191,8 @@ def test_more_sequences_than_the_table_holds_take_a_plain_grid():
 
 
 @pytest.mark.parametrize("Ms,Ls,Hq,Hkv,D,form", [
-    ([61], [2048], 32, 8, 128, 4), ([61], [2048], 32, 8, 64, 4), ([20], [2048], 32, 8, 128, 1),   # four workgroups: more than 128 rows
+    ([61], [2048], 32, 8, 128, 4), ([61], [2048], 32, 8, 64, 4), ([20], [2048], 32, 8, 128, 1),   # four workgroups: more than 128 rows,
+    ([256], [500], 16, 16, 128, 4), ([257], [500], 16, 16, 128, 2), ([257], [500], 16, 16, 64, 4),  # and, with D = 128, no tree beyond 256
     ([129] * 16, [1500] * 16, 8, 8, 128, 2), ([61] * 17, [2048] * 17, 32, 8, 128, 1),             # two: at most 128 items
     ([73] * 16, [100] * 16, 32, 8, 128, 1), ([73] * 17, [100] * 17, 32, 8, 128, 17),               # sharing: beyond 256 items, of several
     ([129] * 33, [300] * 33, 8, 8, 128, 1), ([61] * 33, [2048] * 33, 32, 8, 128, 1),               # groups alone

@@ -317,7 +317,7 @@ def test_paged_attention_with_several_row_groups(G, D, sizes):
 
 @pytest.mark.parametrize("D,hq,hkv,M,L,B,form", [
     (128, 32, 8, 61, 700, 1, 4), (128, 8, 2, 65, 130, 1, 4), (64, 8, 4, 129, 700, 1, 4),             # four workgroups to an item,
-    (128, 8, 2, 300, 700, 1, 4), (64, 8, 4, 300, 700, 1, 4), (64, 32, 32, 257, 65, 20, 33),           # also beyond 256 rows
+    (128, 8, 2, 300, 700, 1, 2), (64, 8, 4, 300, 700, 1, 4), (64, 32, 32, 257, 65, 20, 33),           # also beyond 256 rows
     (128, 8, 8, 129, 900, 16, 2),                                                                     # two
     (128, 16, 16, 129, 97, 17, 33), (128, 16, 16, 161, 65, 17, 33), (128, 16, 16, 257, 100, 17, 33),  # shared row blocks: five, six,
     (128, 16, 16, 129, 1500, 17, 33), (128, 32, 8, 73, 100, 33, 17), (64, 32, 32, 81, 65, 20, 33),    # beyond 256 rows, splits, several

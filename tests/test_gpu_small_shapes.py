@@ -67,7 +67,7 @@ def test_launches_that_leave_compute_units_to_spare(G, D, hq, hkv, M, L, variant
 @pytest.mark.parametrize("D,hq,hkv,Ms,Ls", [
     (128, 8, 2, [40], [0]), (128, 8, 2, [33], [31]), (128, 8, 2, [56], [64]), (128, 8, 2, [64], [449]), (128, 16, 2, [33], [2048]),
     (128, 8, 2, [65], [130]), (128, 8, 8, [130, 5], [200, 90]), (64, 8, 2, [20], [33]), (64, 8, 2, [33], [300]), (64, 8, 4, [129], [1000]),
-    (128, 8, 8, [260], [100]), (64, 8, 8, [260], [100]), (128, 8, 2, [300], [700])])
+    (64, 8, 8, [260], [100]), (64, 8, 4, [1024], [200])])
 def test_four_workgroups_to_an_item(G, D, hq, hkv, Ms, Ls, variant):
     """Launches of at most 64 items of more than 128 rows: one or two row blocks to a workgroup, four waves to a block, each on
     every fourth 32 keys.  Fewer keys than waves have turns, odd last blocks and groups, beside a sequence of few rows,
