@@ -108,7 +108,7 @@ struct AttnArgs {
   int n_items;
   int narrow;      // work-list launches: 1 = two workgroups to an item, one for each 128 of its up to 256 rows; 2 = four
   int share;       // matrix-core kernel: equal row groups of five or six blocks share what is behind the fourth, 1 = of
-                   // sequences with several groups, 2 = of all
+                   // sequences with several groups, 2 = of all; 0 also where no group of the launch would
   int cmb_row0;    // first tree row that the merge of the splits looks at
   alignas(16) SeqEntry tbl[ATTN_TBL];  // (lanes fetch their entry with 16-byte loads)
 };

@@ -185,8 +185,8 @@ __device__ __forceinline__ void wait_lds(int n) {  // n is a constant once the w
 // V are read once, in whole rows.  (Query rows widened to 128 elements with zeros took twice the matrix
 // instructions: 32 query heads, trees of 21 to 97 rows on 700 to 6001 tokens, 26.2 us -> 20.3 us.)
 // SHARE: waves share row blocks behind the fourth, or four of them a block (a.share, a.narrow == 2).  The code for it is kept
-// out of the other launches: with it in all of them, 8 KB of 47, a launch of few short items lost 1 us (one row, 40 heads
-// on 1056 tokens, 9 layers 42.6 -> 43.3; 18 paged sequences of up to 1585 tokens 217.8 -> 218.8, now 216.5).
+// out of the other launches: with it in all of them, 8 KB of 47, launches of short items lost up to 1 us (one row, 40 heads on 1056
+// tokens, 9 / 20 layers 42.4 / 85.7 us before there was sharing, 43.3 / 86.2 with its code in every launch, 42.1 / 85.0 now).
 template <bool PAGED, bool ONCE, bool BIG, bool HALF, bool SHARE>
 __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_max) {
   constexpr int Q_ROW_BYTES = HALF ? MF_ROW_BYTES / 2 : MF_ROW_BYTES;  // a row of Q and of O
