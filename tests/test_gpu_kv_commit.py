@@ -323,7 +323,7 @@ def test_paged_attention_with_several_row_groups(G, D, sizes):
     (128, 16, 16, 129, 1500, 17, 33), (128, 32, 8, 73, 100, 33, 17), (64, 32, 32, 81, 65, 20, 33),    # beyond 256 rows, splits, several
     (128, 16, 16, 129, 70, 100, 33)])                                                                 # groups, one grid row to a sequence
 def test_paged_attention_in_every_launch_form(G, D, hq, hkv, M, L, B, form):
-    """The forms in which waves share row blocks, over paged caches in shuffled page order: the checker's results, and the
+    """The forms in which waves share row blocks, over paged caches in shuffled page order: the oracle's results, and the
     bits of the same call on packed caches."""
     import paper_2505_13254_amd as hs
     from test_gpu_attention import _case
