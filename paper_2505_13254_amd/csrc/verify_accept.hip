@@ -11,18 +11,19 @@
 //               led there.  The residual itself is never materialised: after j rejections it is
 //               max(p(v) - beta_j q(v), 0) for every token not yet rejected (beta_j a scalar that
 //               accumulates Z_i / (1 - sum of rejected q)), and frozen at its value of the time
-//               for a rejected token; only its normaliser is needed per rejection.  A node with
-//               one child gets it from one cooperative pass over its two vocabulary rows; a node with
-//               several has the tokens with p > q sorted by p / q into buckets with their sums (one
-//               kernel on the whole chip), after which every normaliser of its chain is two
+//               for a rejected token; only its normaliser is needed per rejection.  Whether a child is accepted
+//               when its turn comes is thus known without the walk: a node's chain of rejections ends with its first
+//               accepted child, for most nodes the first one, for which two probabilities are compared and nothing is
+//               summed.  Of a node whose first child is rejected the tokens with p > q are sorted by p / q into buckets
+//               with their sums (one kernel on the whole chip), after which every normaliser of its chain is two
 //               suffix sums plus, from the second rejection on, the tokens of one bucket.  One
-//               workgroup per node with children runs that node's chain of rejections ahead of
-//               the walk, all nodes in parallel (k_accept_chain), and leaves each child's pair of
-//               current probabilities; the walk itself (k_accept_walk, one workgroup per sequence) then
-//               only compares uniforms with them, and draws the bonus token at the node where it
-//               stops: an inverse-CDF search done as row sums of 64 tokens, a scan of the row sums,
-//               and a scan inside the one row that is hit.
+//               workgroup per node with children runs that node's chain, all nodes in parallel (k_accept_chain), and
+//               leaves the accepted child; the walk is a chase through them, made by every workgroup of the kernel that
+//               sums the row where it ends (k_bonus_rows); k_accept_walk draws the bonus token there: an inverse-CDF search
+//               done as row sums of 64 tokens, a scan of the row sums, and a scan inside the one row that is hit.
 #include <limits.h>
+
+#include <algorithm>
 
 #include "tree_settle.h"
 
@@ -34,7 +35,7 @@ constexpr int AC_THREADS = 1024;
 constexpr int AC_WAVES = AC_THREADS / 64;
 constexpr int AC_MAX_KIDS = 256;    // children tried per node
 constexpr int AC_MAX_ROWS = 8192;   // 64-token rows of the CDF search held in LDS (V <= 524288)
-constexpr int BR_SLICES = 16;     // workgroups per tree row that sum the bonus distribution's rows ahead of the walk
+constexpr int BR_SLICES = 64, BR_WGS = 1024;  // workgroups per sequence, and in all, that sum the row a bonus token is drawn from
 constexpr int BR_THREADS = 512;
 constexpr int BK_NODES = 4096;      // calls with up to this many tree rows get the sorted residual (below)
 constexpr int BK_SLICES = 16;       // vocabulary slices per row, each sorted by itself
@@ -468,6 +469,23 @@ __device__ __forceinline__ int gather_children(const int* parent, int o, int n, 
   return nk;
 }
 
+// What the tree says about each row (k_tree_rows), and what the walk needs from a node's chain of rejections.
+struct ChainOut {
+  int32_t* n_tried;      // [NN] number of children the node's chain tries (0: the node's residual is p itself)
+  int32_t* first;        // [NN] the first of them; at a sequence's first row, behind the chains: where its walk ends
+  int32_t* kid_tok;      // [NN] its token; at a sequence's first row, behind the chains: the length of its path
+  float* kid_u;          // [NN] its uniform
+  int32_t* accepted;     // [NN] the child that the chain ends with (a local row), -1: none is accepted
+  double* child_frozen;  // [NN] where none is: the child's weight in the residual after its own rejection
+  double* node_beta;     // [NN] and beta and normaliser after all of the node's children were rejected
+  double* node_Z;
+  double* bonus_rows;    // [NN][ceil(V / 64)] row sums of the distribution that the bonus token is drawn from, of the
+                         // row where a sequence's walk ends (NULL: the walk makes them itself)
+};
+
+// The test of a child under the ratio rule: current target and draft probability of its token.
+__device__ __forceinline__ bool ratio_accepts(double pc, double qc, float u) { return pc >= qc || (double)u * qc < pc; }
+
 // ------------------------------------------------------------------ the sorted residual
 // Along a node's chain of rejections only beta changes: F(beta) = sum_v max(p(v) - beta q(v), 0),
 // taken at an increasing sequence of beta >= 1 that is not known in advance, but for the first:
@@ -486,9 +504,7 @@ __device__ __forceinline__ int gather_children(const int* parent, int o, int n, 
 // no token is ever taken for live or dead by its bucket alone when it is not.  All sums are 64-bit
 // integers in units of 2^-62 (LDS and per-slice partial sums), so neither the order in which the
 // lanes' atomic additions arrive nor the order of the tokens inside a bucket changes a result.
-// (Two children: below that the node's own workgroup of k_accept_chain makes its one sum in a pass over both rows,
-// while others run their chains or sum their rows.  With such nodes sorted as well, trees without a branch waited for
-// the sort: 2 rows of 262144 tokens 68 us, now 58; 9 rows of 128256 52 and 46; random trees of 40 rows 0.99.)
+// (A chain of one rejection needs the sums alone: no pairs are written for it.)
 struct BucketWs {
   uint32_t* start;            // [NN][BK_SLICES][BK_N + 1] first position in `pairs` of a slice's buckets (ascending ratio)
   unsigned long long* psum;   // [NN][BK_SLICES][BK_N] sum of p over a slice's bucket
@@ -501,11 +517,10 @@ __device__ __forceinline__ int bucket_of(float ap, float aq) {
 }
 __device__ __forceinline__ unsigned long long to_fixed(float x) { return (unsigned long long)(x * FIX_SCALE); }
 
-// grid (BK_SLICES, NN): sorts slice blockIdx.x of row blockIdx.y.  n_tried[g]: children that row g's
-// chain tries.
+// grid (BK_SLICES, NN): sorts slice blockIdx.x of row blockIdx.y, if the row has children and the first is rejected.
 __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restrict__ target, const float* __restrict__ draft,
                                                             int64_t row_stride, int V, float inv_t,
-                                                            const int32_t* __restrict__ n_tried, const int32_t* __restrict__ t_arg,
+                                                            ChainOut chain, const int32_t* __restrict__ t_arg,
                                                             const float* __restrict__ t_lz, const int32_t* __restrict__ d_arg,
                                                             const float* __restrict__ d_lz, BucketWs ws) {
   static_assert(BK_THREADS == BK_N, "a thread per bucket");
@@ -514,9 +529,9 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
   __shared__ unsigned wave_total[BK_N / 64];
   const int slice = blockIdx.x, g = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // (one trip for what the row's statistics say, one for the slice and the two maxima)
-  const int nk = n_tried[g], p_arg = t_arg[g], q_arg = d_arg[g];
-  const float p_lz = t_lz[g], q_lz = d_lz[g];
-  if (nk < 2) return;
+  const int nk = chain.n_tried[g], p_arg = t_arg[g], q_arg = d_arg[g], x0 = chain.kid_tok[g];
+  const float p_lz = t_lz[g], q_lz = d_lz[g], u0 = chain.kid_u[g];
+  if (nk < 1) return;
   cnt[tid] = 0u;
   ps[tid] = 0ull;
   qs[tid] = 0ull;
@@ -544,6 +559,7 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
   }
   const RowView p(p_row, p_row[p_arg], p_lz, inv_t);
   const RowView q(q_row, q_row[q_arg], q_lz, inv_t);
+  if (ratio_accepts((double)p.prob(x0), (double)q.prob(x0), u0)) return;  // (the chain ends with its first child)
   auto each_token = [&](auto token) {
     auto four = [&](const float4 a, const float4 b) {
       token(a.x, b.x);
@@ -576,6 +592,7 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
   const int64_t slot = (int64_t)g * BK_SLICES + slice;
   ws.psum[slot * BK_N + tid] = ps[tid];
   ws.qsum[slot * BK_N + tid] = qs[tid];
+  if (nk == 1) return;  // (nothing comes behind the first rejection, which needs the sums alone)
   const unsigned mine = cnt[tid];
   const unsigned incl = (unsigned)wave_prefix_sum((int)mine);
   if (lane == 63) wave_total[wave] = incl;
@@ -693,6 +710,7 @@ __device__ __forceinline__ void make_bucket_tables(const BucketLoads& l, BucketT
 
 // What the first wave hands to the others for one rejection, and what they hand back.
 struct BucketStep {
+  int stop;                            // the chain has ended: a child was accepted
   double beta;
   int b_lo, b_hi;                      // buckets whose tokens are taken one by one
   unsigned long long part[AC_WAVES];   // their terms, summed per wave
@@ -741,13 +759,18 @@ __device__ __forceinline__ void near_terms(const float2* __restrict__ pairs, con
 //             (wanted[row] = 1) and the draft rows of the rows that are somebody's parent
 //             (wanted[NN + row]; nobody reads the draft row of a row without children)
 //   n_tried   children that the row's chain tries: none below the last level that may be accepted
+//   first     the first of them (a local row), kid_tok and kid_u its token and uniform: what later kernels need
+//             to tell whether there is a chain at all
 //   tickets   the scan's counters of these rows, cleared (its slices are merged by its own launch)
 // (Every later kernel used to walk from its row to the root for the depth, a chain of global reads.)
 __global__ __launch_bounds__(GR_THREADS) void k_tree_rows(const int32_t* __restrict__ parent,
-                                                          const int32_t* __restrict__ node_offsets, int NN, int max_depth,
-                                                          uint8_t* __restrict__ wanted, int32_t* __restrict__ n_tried,
+                                                          const int32_t* __restrict__ node_offsets,
+                                                          const int32_t* __restrict__ token, const float* __restrict__ uniforms,
+                                                          int NN, int max_depth, uint8_t* __restrict__ wanted, ChainOut chain,
                                                           unsigned* __restrict__ tickets) {
-  __shared__ int l_par[GR_LDS_ROWS], l_kids[GR_LDS_ROWS];
+  __shared__ int l_par[GR_LDS_ROWS], l_kids[GR_LDS_ROWS], l_first[GR_LDS_ROWS], l_tok[GR_LDS_ROWS];
+  __shared__ float l_u[GR_LDS_ROWS];
+  int32_t* const n_tried = chain.n_tried;
   const int s = blockIdx.x, tid = threadIdx.x;
   const int o = node_offsets[s];
   const int n = node_offsets[s + 1] - o;
@@ -766,15 +789,24 @@ __global__ __launch_bounds__(GR_THREADS) void k_tree_rows(const int32_t* __restr
     tickets[NN + o + i] = 0u;
     if (staged) {
       l_par[i] = parent[o + i];
+      l_tok[i] = token[o + i];
+      l_u[i] = uniforms[o + i];
       l_kids[i] = 0;
+      l_first[i] = INT_MAX;
     } else {
       n_tried[o + i] = 0;
+      chain.first[o + i] = INT_MAX;
     }
   }
   __syncthreads();
   for (int i = 1 + tid; i < n; i += GR_THREADS) {
-    if (staged) atomicAdd(&l_kids[l_par[i]], 1);
-    else atomicAdd(&n_tried[o + parent[o + i]], 1);
+    if (staged) {
+      atomicAdd(&l_kids[l_par[i]], 1);
+      atomicMin(&l_first[l_par[i]], i);
+    } else {
+      atomicAdd(&n_tried[o + parent[o + i]], 1);
+      atomicMin(&chain.first[o + parent[o + i]], i);
+    }
   }
   __syncthreads();
   for (int i = tid; i < n; i += GR_THREADS) {
@@ -784,22 +816,16 @@ __global__ __launch_bounds__(GR_THREADS) void k_tree_rows(const int32_t* __restr
     else
       for (int j = parent[o + i]; j >= 0; j = parent[o + j]) ++depth;
     const int kids = staged ? l_kids[i] : __hip_atomic_load(&n_tried[o + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (kids > 0) {
+      const int c = staged ? l_first[i] : __hip_atomic_load(&chain.first[o + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (staged) chain.first[o + i] = c;
+      chain.kid_tok[o + i] = staged ? l_tok[c] : token[o + c];
+      chain.kid_u[o + i] = staged ? l_u[c] : uniforms[o + c];
+    }
     wanted[NN + o + i] = kids > 0 ? 1 : 0;
     n_tried[o + i] = depth < max_depth ? min(kids, AC_MAX_KIDS) : 0;
   }
 }
-
-// What the stochastic walk needs from a node's chain of rejections.
-struct ChainOut {
-  double* child_p;       // [NN] current target probability of the child's token when its turn comes
-  double* child_q;       // [NN] current draft probability of it
-  double* child_frozen;  // [NN] its weight in the residual after its own rejection
-  double* node_beta;     // [NN] beta and normaliser after all of the node's children were rejected
-  double* node_Z;
-  int32_t* n_tried;      // [NN] number of children the node's chain tries (0: the node's residual is p itself)
-  double* bonus_rows;    // [NN][ceil(V / 64)] row sums of the residual a bonus token would be drawn from
-                         // if the walk stopped at the node (NULL: the walk sums the rows of its stop node)
-};
 
 // Sums of the bonus distribution's weights over rows of 64 tokens, rows [r_begin, r_end) of a node,
 // by all waves of the workgroup: dst[r] for each of them.  A lane takes four tokens, 16 lanes a row, a
@@ -852,22 +878,29 @@ __device__ __forceinline__ void bonus_row_sums(const RowView& p, const RowView& 
   }
 }
 
-// One workgroup per tree row that has children (others leave at once): the chain of rejections at
-// that node under the ratio rule, every child rejected in turn.
+// One workgroup per tree row that has children (others leave at once): the chain of rejections at that node under the
+// ratio rule.  Whether a child is accepted when its turn comes depends on the node, its uniform and the rejections before it, so the
+// chain ends with the first accepted child, usually the first child, before anything but its two probabilities has
+// been looked at.  (With every child rejected in turn, whatever the uniforms, and the rows of p summed here for every row
+// without children: 21.8 us for 61 rows of 128256 tokens, now 10.2; with all chains run to their ends the same as before.)
 __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
     const float* __restrict__ target, const float* __restrict__ draft, int64_t row_stride,
     const int32_t* __restrict__ token, const int32_t* __restrict__ parent, const int32_t* __restrict__ node_offsets,
-    int B, int V, float inv_t, const int32_t* __restrict__ t_arg, const float* __restrict__ t_lz,
+    int B, int V, float inv_t, const float* __restrict__ uniforms, const int32_t* __restrict__ t_arg, const float* __restrict__ t_lz,
     const int32_t* __restrict__ d_arg, const float* __restrict__ d_lz, ChainOut out, BucketWs bk) {
   __shared__ int kids[AC_MAX_KIDS];
   __shared__ int kids_sorted[AC_MAX_KIDS];
   __shared__ int n_kids;
   __shared__ double rej_w[AC_MAX_KIDS];
-  __shared__ float kid_p[AC_MAX_KIDS], kid_q[AC_MAX_KIDS];  // p(x), q(x) of each child's token
+  __shared__ float kid_p[AC_MAX_KIDS], kid_q[AC_MAX_KIDS], kid_u[AC_MAX_KIDS];  // p(x), q(x) of each child's token, its uniform
   __shared__ double red[AC_WAVES];
   __shared__ BucketTables tables;
   __shared__ BucketStep step;
   const int g = blockIdx.x, tid = threadIdx.x;
+  // (row statistics first: these loads do not depend on the tree)
+  const float p_lz = t_lz[g], q_lz = d_lz[g], u0 = out.kid_u[g];
+  const int p_arg = t_arg[g], q_arg = d_arg[g], x0 = out.kid_tok[g], first = out.first[g];
+  const int nk = out.n_tried[g];
   int lo = 0, hi = B;  // sequence of this row: last s with node_offsets[s] <= g
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
@@ -876,24 +909,20 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
   const int o = node_offsets[lo];
   const int n = node_offsets[lo + 1] - o;
   const int cur = g - o;
-  if (cur >= n) return;  // (an empty sequence before this row's: cannot happen, offsets are monotone)
-  // (row statistics first: these loads do not depend on the tree)
-  const float p_lz = t_lz[g], q_lz = d_lz[g];
-  const int p_arg = t_arg[g], q_arg = d_arg[g];
-  const int nk = out.n_tried[g];
-  const float* p_row = target + (int64_t)g * row_stride;
-  const RowView p(p_row, p_row[p_arg], p_lz, inv_t);
+  if (cur >= n) return;  // (a row behind the last sequence)
   if (nk == 0) {
-    // no chain to run: this workgroup sums the rows of p, the distribution a bonus token is drawn from
-    // if the walk stops here (done before the longest chain of the launch: with these rows left to
-    // k_bonus_rows that kernel took 10.3 us instead of 5.7 and this one no less)
-    const int n_rows = (V + 63) / 64;
-    if (out.bonus_rows != nullptr) bonus_row_sums(p, p, false, 0.0, V, 0, n_rows, out.bonus_rows + (int64_t)g * n_rows);
+    if (tid == 0) out.accepted[g] = -1;
     return;
   }
+  const float* p_row = target + (int64_t)g * row_stride;
   const float* q_row = draft + (int64_t)g * row_stride;
+  const RowView p(p_row, p_row[p_arg], p_lz, inv_t);
   const RowView q(q_row, q_row[q_arg], q_lz, inv_t);
-  const bool sorted = bk.pairs != nullptr && nk >= 2;  // there is a sorted residual
+  if (ratio_accepts((double)p.prob(x0), (double)q.prob(x0), u0)) {
+    if (tid == 0) out.accepted[g] = first;
+    return;
+  }
+  const bool sorted = bk.pairs != nullptr;  // there is a sorted residual
   // Everything is requested side by side: the tables, the children and their tokens, then the tokens' logits; the chain
   // below is serial, and a round trip to memory per step would dominate it.
   BucketLoads loads;
@@ -901,7 +930,9 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
   gather_children(parent, o, n, cur, true, kids, kids_sorted, &n_kids);
   float xp = 0.f, xq = 0.f;
   if (tid < nk) {
-    const int x = token[o + kids_sorted[tid]];
+    const int c = o + kids_sorted[tid];
+    const int x = token[c];
+    kid_u[tid] = uniforms[c];
     xp = p_row[x];
     xq = q_row[x];
   }
@@ -913,51 +944,44 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
   __syncthreads();
   const float2* __restrict__ pairs = sorted ? bk.pairs + (int64_t)g * V : nullptr;
   double beta = 0.0, Z = 1.0, sumq = 0.0;
+  int acc = -1;  // the accepted child's place among the children
   if (sorted) {
     // The first wave keeps the chain's scalars; the others only help with the tokens around beta.
     // (Sixteen waves that all repeat the scalar part take issue slots from one another: 4 us a step.)
-    // A step is a chain of its own, a division, two barriers and a trip to memory, so whatever is not
-    // part of it is left for later or for other lanes: lane j keeps what child j's probabilities are
-    // made of, the rejected tokens' corrections are a lane each, sums travel by DPP moves.  (61 rows, chains of
-    // ten: 2.0 us a step, most of it the trip to memory, and 0.6 for the first; 2.6 and a trip before.)
+    // A step is a chain of its own, two divisions, two barriers and a trip to memory, so whatever is not
+    // part of it is left for later or for other lanes: the rejected tokens' corrections are a lane each, sums travel by DPP
+    // moves.  (61 rows, chains of ten: 2.0 us a step, most of it the trip to memory, and 0.6 for the first; 2.6 and a
+    // trip before.)
     const bool lead = tid < 64;
     const int lane = tid & 63;
-    double my_px = 0.0, my_qx = 0.0, my_Z = 1.0, my_rem = 1.0;
     for (int j = 0; j < nk; ++j) {
       int b_hi = 0;
-      if (lead) {
+      if (lead && acc < 0) {
         const double px = (double)kid_p[j], qx = (double)kid_q[j];
         const double rem = 1.0 - sumq;
-        if (lane == (j & 63)) {
-          my_px = fmax(px - beta * qx, 0.0);  // current p(x), times Z
-          my_qx = qx;                         // current q(x), times rem
-          my_Z = Z;
-          my_rem = rem;
-        }
-        beta += Z / rem;
-        sumq += qx;
-        rej_w[j] = fmax(px - beta * qx, 0.0);  // (every lane of the wave stores the same value; LDS keeps a wave's order)
-        if ((j & 63) == 63 || j == nk - 1) {
-          const int i = (j & ~63) + lane;
-          if (i <= j) {
-            const int c = kids_sorted[i];
-            out.child_p[o + c] = my_px / my_Z;
-            out.child_q[o + c] = my_qx / my_rem;
-            out.child_frozen[o + c] = rej_w[i];
-          }
-        }
-        if (j > 0) {
-          int b_lo;
-          near_buckets(beta, b_lo, b_hi);
-          if (tid == 0) {
-            step.beta = beta;
-            step.b_lo = b_lo;
-            step.b_hi = b_hi;
+        // (current p(x) and q(x); the first child was rejected above)
+        if (j > 0 && ratio_accepts(fmax(px - beta * qx, 0.0) / Z, qx / rem, kid_u[j])) {
+          acc = j;
+        } else {
+          // rejected: p <- norm(max(p - q, 0)), q(x) <- 0, q <- norm(q)
+          beta += Z / rem;
+          sumq += qx;
+          rej_w[j] = fmax(px - beta * qx, 0.0);  // (every lane of the wave stores the same value; LDS keeps a wave's order)
+          if (j > 0) {
+            int b_lo;
+            near_buckets(beta, b_lo, b_hi);
+            if (tid == 0) {
+              step.beta = beta;
+              step.b_lo = b_lo;
+              step.b_hi = b_hi;
+            }
           }
         }
       }
       if (j > 0) {  // (beta = 1 at the first rejection: every sorted token is live)
+        if (tid == 0) step.stop = acc >= 0 ? 1 : 0;
         __syncthreads();
+        if (step.stop != 0) break;
         near_terms(pairs, tables, step);
         __syncthreads();
       }
@@ -975,59 +999,94 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
         Z = F + wave_sum_dpp(fix);
       }
     }
+    if (!lead) return;
   } else {
     for (int j = 0; j < nk; ++j) {
-      const int c = kids_sorted[j];
       const double px = (double)kid_p[j];
       const double qx = (double)kid_q[j];
-      const double pc = fmax(px - beta * qx, 0.0) / Z;  // current p(x)
-      const double qc = qx / (1.0 - sumq);              // current q(x)
-      // rejected: p <- norm(max(p - q, 0)), q(x) <- 0, q <- norm(q)
+      if (j > 0 && ratio_accepts(fmax(px - beta * qx, 0.0) / Z, qx / (1.0 - sumq), kid_u[j])) {
+        acc = j;
+        break;
+      }
       beta += Z / (1.0 - sumq);
       sumq += qx;
-      const double frozen = fmax(px - beta * qx, 0.0);
-      if (tid == 0) {
-        out.child_p[o + c] = pc;
-        out.child_q[o + c] = qc;
-        out.child_frozen[o + c] = frozen;
-        rej_w[j] = frozen;
-      }
+      if (tid == 0) rej_w[j] = fmax(px - beta * qx, 0.0);
       double F = residual_mass(p, q, beta, V, red);  // (its barriers also publish rej_w)
       // a rejected token's weight is frozen: its live term, as the pass formed it, leaves the sum
       const float bf = (float)beta;
       for (int i = 0; i <= j; ++i) F += rej_w[i] - (double)fmaxf(fmaf(-bf, kid_q[i], kid_p[i]), 0.f);
       Z = F;
     }
+    if (tid >= 64) return;
   }
+  // (the first wave, for which its own stores to LDS are in order; rej_w is tid 0's or the wave's own)
+  if (acc < 0)
+    for (int i = tid; i < nk; i += 64) out.child_frozen[o + kids_sorted[i]] = rej_w[i];
   if (tid == 0) {
-    out.node_beta[o + cur] = beta;
-    out.node_Z[o + cur] = Z;
+    out.accepted[g] = acc >= 0 ? kids_sorted[acc] : -1;
+    out.node_beta[g] = beta;
+    out.node_Z[g] = Z;
   }
 }
 
-// grid (BR_SLICES, NN), after the chains: the row sums the walk would need if it stopped at row
-// blockIdx.y, for every row with children at once (the walk visits a few rows one after the other and
-// knows its stop row last; summing that row's vocabulary on its single compute unit took 15 us).  The
-// residual at a row is fixed before the walk: max(p - beta q, 0) with the chain's final beta where all
-// children were rejected (summed here), p itself where no child is tried (summed by the row's own
-// workgroup of k_accept_chain, which has nothing else to do); the rejected tokens' frozen weights are
-// the walk's corrections, as before.
+// Where a sequence's walk ends under the ratio rule: from its root from one accepted child to the next.  Called by all
+// threads; `next` has room for the path's rows when they are wanted (NULL: not).
+__device__ __forceinline__ int chase(const int32_t* __restrict__ accepted, int o, int n, int max_depth, int* l_acc, int* len, int32_t* path) {
+  const bool staged = n <= GR_LDS_ROWS;
+  if (staged)
+    for (int i = threadIdx.x; i < n; i += blockDim.x) l_acc[i] = accepted[o + i];
+  __syncthreads();
+  int cur = 0, l = 0;
+  for (int c; l < max_depth && (c = staged ? l_acc[cur] : accepted[o + cur]) >= 0; ++l) {
+    if (path != nullptr && threadIdx.x == 0) path[l] = c;
+    cur = c;
+  }
+  if (path != nullptr)
+    for (int d = l + threadIdx.x; d < max_depth; d += blockDim.x) path[d] = -1;
+  *len = l;
+  return cur;
+}
+
+// grid (B, slices), after the chains: every workgroup finds where its sequence's walk ends and sums its slice of that
+// row, so that the draw of the bonus token need not sum a row of the vocabulary on its one compute unit (15 us).  The
+// distribution is max(p - beta q, 0) with the chain's final beta where all children were rejected, p itself where none is
+// tried; the rejected tokens' frozen weights are the draw's corrections.  The first slice's workgroup writes the path and
+// leaves for k_accept_walk where it ends.
 __global__ __launch_bounds__(BR_THREADS) void k_bonus_rows(const float* __restrict__ target,
                                                            const float* __restrict__ draft, int64_t row_stride, int V,
-                                                           float inv_t, const int32_t* __restrict__ t_arg,
+                                                           float inv_t, const int32_t* __restrict__ node_offsets, int max_depth,
+                                                           const int32_t* __restrict__ t_arg,
                                                            const float* __restrict__ t_lz,
                                                            const int32_t* __restrict__ d_arg,
-                                                           const float* __restrict__ d_lz, ChainOut chain) {
-  const int slice = blockIdx.x, g = blockIdx.y;
+                                                           const float* __restrict__ d_lz, ChainOut chain,
+                                                           int32_t* __restrict__ accept_path) {
+  __shared__ int l_acc[GR_LDS_ROWS];
+  const int s = blockIdx.x, slice = blockIdx.y;
+  const int o = node_offsets[s];
+  const int n = node_offsets[s + 1] - o;
+  if (n <= 0) return;
+  int len;
+  const int cur = chase(chain.accepted, o, n, max_depth, l_acc, &len, slice == 0 ? accept_path + (int64_t)s * max_depth : nullptr);
+  if (slice == 0 && threadIdx.x == 0) {
+    chain.first[o] = cur;
+    chain.kid_tok[o] = len;
+  }
   const int n_rows = (V + 63) / 64;
-  const int per = (n_rows + BR_SLICES - 1) / BR_SLICES;
+  const int per = (n_rows + (int)gridDim.y - 1) / (int)gridDim.y;
   const int r_begin = slice * per, r_end = min(n_rows, r_begin + per);
-  if (r_begin >= r_end || chain.n_tried[g] == 0) return;  // (a row without children: summed by its chain workgroup)
+  if (r_begin >= r_end) return;
+  const int g = o + cur;
+  const bool sub_q = chain.n_tried[g] > 0;
   const float* p_row = target + (int64_t)g * row_stride;
-  const float* q_row = draft + (int64_t)g * row_stride;
   const RowView p(p_row, p_row[t_arg[g]], t_lz[g], inv_t);
-  const RowView q(q_row, q_row[d_arg[g]], d_lz[g], inv_t);
-  bonus_row_sums(p, q, true, chain.node_beta[g], V, r_begin, r_end, chain.bonus_rows + (int64_t)g * n_rows);
+  RowView q = p;
+  double beta = 0.0;
+  if (sub_q) {
+    const float* q_row = draft + (int64_t)g * row_stride;
+    q = RowView(q_row, q_row[d_arg[g]], d_lz[g], inv_t);
+    beta = chain.node_beta[g];
+  }
+  bonus_row_sums(p, q, sub_q, beta, V, r_begin, r_end, chain.bonus_rows + (int64_t)g * n_rows);
 }
 
 __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
@@ -1046,7 +1105,7 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
   __shared__ int rej_tok[AC_MAX_KIDS];
   __shared__ double rej_w[AC_MAX_KIDS];  // frozen weight of each rejected token
   __shared__ float kid_u[AC_MAX_KIDS];    // the child's uniform
-  __shared__ double kid_a[AC_MAX_KIDS], kid_b[AC_MAX_KIDS];  // its current p(x) (and q(x) under the ratio rule)
+  __shared__ double kid_p[AC_MAX_KIDS];   // its p(x)
   __shared__ double rej_fix[AC_MAX_KIDS];  // bonus draw: what a rejected token's frozen weight changes in its row sum
   __shared__ double rowsum[AC_MAX_ROWS];
   __shared__ double chunk_tot[AC_MAX_ROWS / 64];  // sums of 64 rows
@@ -1056,7 +1115,9 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
   const int o = node_offsets[s];
   const int n = node_offsets[s + 1] - o;
   int32_t* path = accept_path + (int64_t)s * max_depth;
-  for (int d = tid; d < max_depth; d += AC_THREADS) path[d] = -1;
+  const bool ratio_mode = mode == HS_ACCEPT_STOCHASTIC;
+  if (n <= 0 || !ratio_mode)
+    for (int d = tid; d < max_depth; d += AC_THREADS) path[d] = -1;
   if (n <= 0) {
     if (tid == 0) {
       accept_len[s] = 0;
@@ -1064,51 +1125,28 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
     }
     return;
   }
-  const bool ratio_mode = mode == HS_ACCEPT_STOCHASTIC;
+  // Under the ratio rule the chains have left every node's accepted child, so the walk is a chase through them, made ahead of
+  // this kernel, and the node where it ends is looked at here, its row sums requested before its children are.
+  // (Level by level, each a few trips to memory, 12.6 us for a 61-row tree and 22 for 97 rows.)
   int cur = 0, len = 0;
-  // Under the ratio rule every child's test is known before the walk (k_accept_chain left its two
-  // probabilities): all nodes test themselves at once and the first accepted child of each node is found,
-  // so the walk itself is a chase through LDS, and only the node where it stops is looked at below.
-  // (Level by level, each a few trips to memory, 12.6 us for a 61-row tree and 22 for 97 rows; 9.4 and 11.8 with the children gathered from memory again, now 7.5 and 9.5.)
-  __shared__ int l_par[GR_LDS_ROWS];
-  bool chased = false;  // `cur` is where the walk ends, l_par holds the tree
   constexpr int PRE = AC_MAX_ROWS / AC_THREADS;
-  double pre[PRE];      // then: its row sums, requested before its children are looked at
+  double pre[PRE];
   const int n_rows = (V + 63) / 64;
-  if (ratio_mode && n <= GR_LDS_ROWS) {
-    __shared__ int first_acc[GR_LDS_ROWS], stop[2];
-    for (int i = tid; i < n; i += AC_THREADS) first_acc[i] = INT_MAX;
-    __syncthreads();
-    bool many = false;
-    for (int i = tid; i < n; i += AC_THREADS) {
-      const int tried = chain.n_tried[o + i], up = parent[o + i];
-      // (below the last level that is tried the probabilities are undefined; the chase does not go there)
-      const double pc = chain.child_p[o + i], qc = chain.child_q[o + i], u = (double)uniforms[o + i];
-      many = many || tried >= AC_MAX_KIDS;  // (there may be children that no test is tried on)
-      l_par[i] = up;
-      if (i > 0 && (pc >= qc || u * qc < pc)) atomicMin(&first_acc[up], i);
-    }
-    if (!__syncthreads_or(many ? 1 : 0)) {
-      if (tid == 0) {
-        for (int c; len < max_depth && (c = first_acc[cur]) != INT_MAX; cur = c) path[len++] = c;
-        stop[0] = cur;
-        stop[1] = len;
-      }
-      __syncthreads();
-      cur = stop[0];
-      len = stop[1];
-      chased = true;
-      if (chain.bonus_rows != nullptr) {
-        const double* __restrict__ sums = chain.bonus_rows + (int64_t)(o + cur) * n_rows;
+  if (ratio_mode) {
+    if (chain.bonus_rows != nullptr) {
+      cur = chain.first[o];
+      len = chain.kid_tok[o];
+      const double* __restrict__ sums = chain.bonus_rows + (int64_t)(o + cur) * n_rows;
 #pragma unroll
-        for (int k = 0; k < PRE; ++k)
-          if (k * AC_THREADS < n_rows) pre[k] = sums[min(tid + k * AC_THREADS, n_rows - 1)];
-      }
+      for (int k = 0; k < PRE; ++k)
+        if (k * AC_THREADS < n_rows) pre[k] = sums[min(tid + k * AC_THREADS, n_rows - 1)];
+    } else {
+      __shared__ int l_acc[GR_LDS_ROWS];
+      cur = chase(chain.accepted, o, n, max_depth, l_acc, &len, path);
     }
   }
   for (;;) {
-    const int nk = chased ? gather_children(l_par, 0, n, cur, len < max_depth, kids, kids_sorted, &n_kids)
-                          : gather_children(parent, o, n, cur, len < max_depth, kids, kids_sorted, &n_kids);
+    const int nk = gather_children(parent, o, n, cur, len < max_depth, kids, kids_sorted, &n_kids);
 
     const float* p_row = target + (int64_t)(o + cur) * row_stride;
     const RowView p(p_row, p_row[t_arg[o + cur]], t_lz[o + cur], inv_t);
@@ -1126,41 +1164,33 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
       const int c = kids_sorted[tid];
       const int x = token[o + c];
       rej_tok[tid] = x;
-      kid_u[tid] = uniforms[o + c];
-      if (ratio_mode) {  // the node's chain of rejections was run ahead of the walk (k_accept_chain)
-        kid_a[tid] = chain.child_p[o + c];
-        kid_b[tid] = chain.child_q[o + c];
+      if (ratio_mode) {  // (all of them were rejected: k_accept_chain)
         rej_w[tid] = chain.child_frozen[o + c];
       } else {
-        kid_a[tid] = (double)p.prob(x);
+        kid_u[tid] = uniforms[o + c];
+        kid_p[tid] = (double)p.prob(x);
         rej_w[tid] = 0.0;
       }
     }
     __syncthreads();
-    // ---- try the children in order (every thread runs the same scalar logic)
+    // ---- point-mass rule: try the children in order (every thread runs the same scalar logic)
     double beta = 0.0, Z = 1.0, rem = 1.0;
     int n_rej = 0, accepted = -1;
-    for (int j = 0; j < nk; ++j) {
-      const double u = (double)kid_u[j];
-      if (!ratio_mode) {
-        const double px = kid_a[j];
-        if (u * rem < px) {  // u < p(x) / rem
-          accepted = kids_sorted[j];
+    if (ratio_mode) {
+      n_rej = nk;
+      if (nk > 0) {
+        beta = chain.node_beta[o + cur];
+        Z = chain.node_Z[o + cur];
+      }
+    } else {
+      for (; n_rej < nk; ++n_rej) {
+        const double px = kid_p[n_rej];
+        if ((double)kid_u[n_rej] * rem < px) {  // u < p(x) / rem
+          accepted = kids_sorted[n_rej];
           break;
         }
         rem -= px;
-      } else {
-        const double pc = kid_a[j], qc = kid_b[j];
-        if (pc >= qc || u * qc < pc) {
-          accepted = kids_sorted[j];
-          break;
-        }
       }
-      ++n_rej;
-    }
-    if (ratio_mode && accepted < 0 && n_rej > 0) {
-      beta = chain.node_beta[o + cur];
-      Z = chain.node_Z[o + cur];
     }
     if (accepted >= 0) {
       if (tid == 0) path[len] = accepted;
@@ -1173,13 +1203,10 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
     const bool sub_q = use_q && n_rej > 0;
     const double total = ratio_mode ? Z : rem;
     const double goal = (double)uniforms[NN + s] * total;
-    if (chased && chain.bonus_rows != nullptr) {
+    if (chain.bonus_rows != nullptr) {  // summed ahead of the walk (k_bonus_rows)
 #pragma unroll
       for (int k = 0; k < PRE; ++k)
         if (tid + k * AC_THREADS < n_rows) rowsum[tid + k * AC_THREADS] = pre[k];
-    } else if (chain.bonus_rows != nullptr) {  // summed ahead of the walk, for every row (k_bonus_rows)
-      const double* __restrict__ sums = chain.bonus_rows + (int64_t)(o + cur) * n_rows;
-      for (int r = tid; r < n_rows; r += AC_THREADS) rowsum[r] = sums[r];
     } else {
       bonus_row_sums(p, q, sub_q, beta, V, 0, n_rows, rowsum);
     }
@@ -1351,7 +1378,7 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
   float *t_lz = nullptr, *d_lz = nullptr;
   hs::ScanSlices slices{nullptr, 1};
   slices.pairs_only = true;  // (the greedy walk needs the rows' argmax and nothing else)
-  hs::ChainOut chain{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  hs::ChainOut chain{};
   hs::BucketWs bk{};  // (all NULL: no sorted residual)
   if (NN > 0) {
     hs::Carver c(workspace);
@@ -1360,8 +1387,10 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     float* t_ent = c.take<float>(2 * (size_t)NN);
     d_arg = t_arg + NN;  // (the draft rows' results follow the target rows')
     d_lz = t_lz + NN;
-    chain.child_p = c.take<double>(NN);
-    chain.child_q = c.take<double>(NN);
+    chain.first = c.take<int32_t>(2 * (size_t)NN);
+    chain.kid_tok = chain.first + NN;
+    chain.kid_u = c.take<float>(2 * (size_t)NN);
+    chain.accepted = reinterpret_cast<int32_t*>(chain.kid_u + NN);
     chain.child_frozen = c.take<double>(NN);
     chain.node_beta = c.take<double>(NN);
     chain.node_Z = c.take<double>(NN);
@@ -1387,8 +1416,8 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     if (mode == HS_ACCEPT_STOCHASTIC) {
       // one scan over [target rows ; draft rows]; draft rows are read where a row has children, and
       // nowhere else
-      hipLaunchKernelGGL(hs::k_tree_rows, dim3(B), dim3(hs::GR_THREADS), 0, st, parent, node_offsets, NN, max_depth, wanted,
-                         chain.n_tried, static_cast<unsigned*>(scan_ws));
+      hipLaunchKernelGGL(hs::k_tree_rows, dim3(B), dim3(hs::GR_THREADS), 0, st, parent, node_offsets, token, uniforms, NN,
+                         max_depth, wanted, chain, static_cast<unsigned*>(scan_ws));
       r = hs::launch_status("accept (tree rows)");
       if (r != HS_OK) return r;
       // (the rows' counters are clear: the scan merges its slices itself)
@@ -1413,20 +1442,21 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
                         reinterpret_cast<uintptr_t>(draft_logits) % 16 == 0;
     if (sorted) {
       hipLaunchKernelGGL(hs::k_bucket_sort, dim3(hs::BK_SLICES, NN), dim3(hs::BK_THREADS), 0, st, target_logits, draft_logits,
-                         row_stride, V, 1.0f / temperature, chain.n_tried, t_arg, t_lz, d_arg, d_lz, bk);
+                         row_stride, V, 1.0f / temperature, chain, t_arg, t_lz, d_arg, d_lz, bk);
       hs_status r = hs::launch_status("accept (sorted residual)");
       if (r != HS_OK) return r;
     } else {
       bk.pairs = nullptr;
     }
     hipLaunchKernelGGL(hs::k_accept_chain, dim3(NN), dim3(hs::AC_THREADS), 0, st, target_logits, draft_logits,
-                       row_stride, token, parent, node_offsets, B, V, 1.0f / temperature, t_arg, t_lz, d_arg, d_lz,
-                       chain, bk);
+                       row_stride, token, parent, node_offsets, B, V, 1.0f / temperature, uniforms, t_arg, t_lz, d_arg,
+                       d_lz, chain, bk);
     hs_status r = hs::launch_status("accept (rejection chains)");
     if (r != HS_OK) return r;
     if (chain.bonus_rows != nullptr) {
-      hipLaunchKernelGGL(hs::k_bonus_rows, dim3(hs::BR_SLICES, NN), dim3(hs::BR_THREADS), 0, st, target_logits,
-                         draft_logits, row_stride, V, 1.0f / temperature, t_arg, t_lz, d_arg, d_lz, chain);
+      const unsigned slices = (unsigned)std::max(1, std::min(hs::BR_SLICES, hs::BR_WGS / B));
+      hipLaunchKernelGGL(hs::k_bonus_rows, dim3(B, slices), dim3(hs::BR_THREADS), 0, st, target_logits, draft_logits,
+                         row_stride, V, 1.0f / temperature, node_offsets, max_depth, t_arg, t_lz, d_arg, d_lz, chain, accept_path);
       r = hs::launch_status("accept (bonus rows)");
       if (r != HS_OK) return r;
     }

@@ -333,6 +333,50 @@ def test_a_workspace_without_room_for_the_finer_last_round(G):
         assert diff.max() <= 1e-2 * np.abs(want).max()
 
 
+@pytest.mark.parametrize("V", [4096, 8195])
+@pytest.mark.parametrize("n_kids,k", [(1, 0), (1, None), (2, 1), (5, 0), (5, 4), (66, 63), (66, 64), (66, None)])
+def test_chains_end_with_their_first_accepted_child(G, V, n_kids, k):
+    """The root's k-th child is accepted (None: no child is), and below it a chain of one child, accepted and then
+    rejected: one child with the sums alone, chains that end at any place, by the sorted residual (V = 4096) and by passes
+    over both rows.  An empty sequence lies between two copies of the tree, the second without room for a second level."""
+    import paper_2505_13254_amd as hs
+    from oracle import verify_accept
+    rs = np.random.RandomState(100 * n_kids + (k or 0))
+    at = 1 + (k if k is not None else 0)                   # the child that has the rest of the tree below it
+    parent = np.asarray([-1] + [0] * n_kids + [at, n_kids + 1], np.int32)
+    n = len(parent)
+    draft = (rs.normal(size=(n, V)) * 1.5).astype(np.float32)
+    target = (0.8 * draft + rs.normal(size=draft.shape)).astype(np.float32)
+    token = np.zeros(n, np.int32)
+    token[1:n_kids + 1] = np.argsort(-draft[0], kind="stable")[:n_kids]
+    token[n_kids + 1], token[n_kids + 2] = draft[at].argmax(), draft[n_kids + 1].argmax()
+    u = np.full(n, 0.9999, np.float32)
+    # (a rejected token stands well below its draft probability, an accepted one above it whatever was rejected before)
+    target[0, token[1:n_kids + 1]] = draft[0, token[1:n_kids + 1]] - 3.0
+    target[n_kids + 1, token[n_kids + 2]] = draft[n_kids + 1, token[n_kids + 2]] - 3.0
+    target[at, token[n_kids + 1]] += 9.0
+    if k is not None:
+        target[0, token[at]] += 12.0
+        u[at] = 0.0
+    two = [np.concatenate([x, x]) for x in (target, draft, token, parent)]
+    offs = np.asarray([0, n, n, 2 * n], np.int32)
+    for depth in (3, 1):
+        for draw in np.linspace(0.3, 0.7, 50):  # (a draw at the edge of a token's interval may fall to either side)
+            uu = np.concatenate([u, u, [draw, 0.5, draw + 0.1]]).astype(np.float32)
+            want = verify_accept(two[0], two[1], two[2], two[3], offs, 1, 1.0, uu, depth)
+            near = [verify_accept(two[0], two[1], two[2], two[3], offs, 1, 1.0, np.concatenate([uu[:-3], uu[-3:] + e]), depth)
+                    for e in (-1e-5, 1e-5)]
+            if all(np.array_equal(w["bonus_token"], want["bonus_token"]) for w in near):
+                break
+        else:
+            raise AssertionError("every draw lies at an edge")
+        assert want["accept_len"][0] == (0 if k is None else min(depth, 2))
+        out = hs.hs_verify_accept(G.dev(two[0]), G.dev(two[1]), G.dev(two[2], torch.int32), G.dev(two[3], torch.int32),
+                                  G.dev(offs, torch.int32), 1, 1.0, G.dev(uu, torch.float32), depth)
+        for key in want:
+            assert np.array_equal(G.host(out[key]), want[key]), (key, depth)
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("n_kids", [1, 63, 65, 250])
 def test_bonus_draws_after_many_rejections(G, mode, n_kids):
