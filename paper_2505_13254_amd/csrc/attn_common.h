@@ -30,9 +30,7 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {  // round to nearest, t
 }
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-// Four neighbouring elements as float32, at any element's address (the type's alignment is an
-// element's; global memory takes wide accesses at any address).
-typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+// Four neighbouring elements as float32, at any element's address (the type's alignment is an element's).
 typedef unsigned short bf16x4_any __attribute__((ext_vector_type(4), aligned(2)));
 template <typename T>
 __device__ __forceinline__ float4 load4(const T* p);

@@ -66,7 +66,9 @@ struct ScanPlan {
 // `rows.sparse`: a good part of the rows will be left out (row_active), so that large scans have room for workgroups of
 // four waves in more slices (61 rows and their 20 parents of 128256 logits, K = 1, the ratio rule's whole call: 67.8 us,
 // 69.7 by the rule for full scans).
-// Rows that are not 16-byte aligned are read a value at a time, which only more workgroups make up for; slices whose
+// Rows that are not 16-byte aligned were read a value at a time when these rules were made, which only more workgroups made up
+// for; read 16 bytes at a time like the others they lose nothing by the finer slices (301 of 132058: 43.9 us, by the rule for aligned
+// rows 52.2; 330 of 50257 23.4 both, 7 of 137847 11.8 and 12.2).  Slices whose
 // merge is the caller's (rows.pairs_only) cost no launch.  So the argmax scan takes 257 rows and more in three slices,
 // or two, as long as 1024 workgroups allow (277 rows of 50257: 1 slice 31.2, 2 28.7, 3 26.0; 305 of 187620, aligned: 57.1,
 // 50.5, 48.9; aligned rows from about 360 on gain nothing, 421 to 520 of 32000 or 50256 would lose 3 %), three-tile
@@ -434,7 +436,7 @@ constexpr size_t TICKET_BYTES = 65536 * sizeof(unsigned);  // a counter for each
 static_assert(ROW_SCAN_MAX * sizeof(unsigned) <= TICKET_BYTES, "every row has its counter");
 // STATS false: only the K best pairs are wanted (the greedy accept walk's argmax scan); the softmax
 // statistics, most of the arithmetic of a tile, are left out and part_stats is not written.
-template <bool VEC, int SCAN_THREADS, bool FUSED, int NBUF, bool STATS>
+template <int SCAN_THREADS, bool FUSED, int NBUF, bool STATS>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restrict__ logits, int64_t row_stride,
                                                             int V, int K, float inv_t, int tiles_per_wg,
                                                             float4* __restrict__ part_stats,
@@ -487,8 +489,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int i0 = tbase + (j * SCAN_THREADS + tid) * 4;
-      if (VEC && i0 + 3 < V) {
-        float4 f = *reinterpret_cast<const float4*>(x + i0);
+      if (i0 + 3 < V) {
+        const float4 f = load_float4(x + i0);
         v[j * 4 + 0] = f.x;
         v[j * 4 + 1] = f.y;
         v[j * 4 + 2] = f.z;
@@ -499,13 +501,13 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
       }
     }
   };
-  // a tile that lies inside the row as a whole (aligned rows): four loads, no conditions, so the
+  // a tile that lies inside the row as a whole: four loads, no conditions, so the
   // compiler can count them when it waits for an older tile
   auto load_full_tile = [&](int tile, float (&v)[SCAN_VPT]) {
     const float* __restrict__ src = x + (int64_t)(split * tiles_per_wg + tile) * SCAN_TILE + tid * 4;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float4 f = *reinterpret_cast<const float4*>(src + j * SCAN_THREADS * 4);
+      const float4 f = load_float4(src + j * SCAN_THREADS * 4);
       v[j * 4 + 0] = f.x;
       v[j * 4 + 1] = f.y;
       v[j * 4 + 2] = f.z;
@@ -515,7 +517,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
   // tiles this workgroup really has (uniform)
   int n_my = (V - split * tiles_per_wg * SCAN_TILE + SCAN_TILE - 1) / SCAN_TILE;
   n_my = n_my < 0 ? 0 : (n_my > tiles_per_wg ? tiles_per_wg : n_my);
-  int n_full = VEC ? (V - split * tiles_per_wg * SCAN_TILE) / SCAN_TILE : 0;  // leading whole tiles
+  int n_full = (V - split * tiles_per_wg * SCAN_TILE) / SCAN_TILE;  // leading whole tiles
   n_full = n_full < 0 ? 0 : (n_full > n_my ? n_my : n_full);
 
   // One tile: statistics of this thread's 16 values, threshold, insertion of the few values that
@@ -879,35 +881,22 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
   float4* part_stats = c.take<float4>(n);
   unsigned long long* part_key = c.take<unsigned long long>(n * K);
   const float inv_t = 1.0f / temperature;
-  const bool vec = rows.aligned;
   dim3 grid(p.splits, R);
   // one launch: the rows' last slices merge (needs the zeroed counters of a prepared workspace)
   const bool fused = prepared && slices == nullptr && p.splits > 1 && p.splits * K <= FUSED_CAP;
-#define HS_SCAN_LAUNCH(VEC, T, F, ST)                                                                                     \
-  hipLaunchKernelGGL((k_scan_rows<VEC, T, F, 3, ST>), grid, dim3(T), 0, stream, logits, row_stride, V, K, inv_t, p.tiles_per_wg, \
+#define HS_SCAN_LAUNCH(T, F, ST)                                                                                          \
+  hipLaunchKernelGGL((k_scan_rows<T, F, 3, ST>), grid, dim3(T), 0, stream, logits, row_stride, V, K, inv_t, p.tiles_per_wg, \
                      part_stats, part_key, topk_idx, topk_logp, ent_topk, ent_full, lse, row_active, row_index, logits2, rows1, tickets)
   if (slices != nullptr && slices->pairs_only) {
-    if (p.threads == SCAN_BIG) {
-      if (vec) HS_SCAN_LAUNCH(true, SCAN_BIG, false, false);
-      else HS_SCAN_LAUNCH(false, SCAN_BIG, false, false);
-    } else {
-      if (vec) HS_SCAN_LAUNCH(true, SCAN_SMALL, false, false);
-      else HS_SCAN_LAUNCH(false, SCAN_SMALL, false, false);
-    }
+    if (p.threads == SCAN_BIG) HS_SCAN_LAUNCH(SCAN_BIG, false, false);
+    else HS_SCAN_LAUNCH(SCAN_SMALL, false, false);
   } else if (fused) {
-    if (p.threads == SCAN_BIG) {
-      if (vec) HS_SCAN_LAUNCH(true, SCAN_BIG, true, true);
-      else HS_SCAN_LAUNCH(false, SCAN_BIG, true, true);
-    } else {
-      if (vec) HS_SCAN_LAUNCH(true, SCAN_SMALL, true, true);
-      else HS_SCAN_LAUNCH(false, SCAN_SMALL, true, true);
-    }
+    if (p.threads == SCAN_BIG) HS_SCAN_LAUNCH(SCAN_BIG, true, true);
+    else HS_SCAN_LAUNCH(SCAN_SMALL, true, true);
   } else if (p.threads == SCAN_BIG) {
-    if (vec) HS_SCAN_LAUNCH(true, SCAN_BIG, false, true);
-    else HS_SCAN_LAUNCH(false, SCAN_BIG, false, true);
+    HS_SCAN_LAUNCH(SCAN_BIG, false, true);
   } else {
-    if (vec) HS_SCAN_LAUNCH(true, SCAN_SMALL, false, true);
-    else HS_SCAN_LAUNCH(false, SCAN_SMALL, false, true);
+    HS_SCAN_LAUNCH(SCAN_SMALL, false, true);
   }
 #undef HS_SCAN_LAUNCH
   hs_status st = launch_status("row scan");

@@ -149,7 +149,6 @@ constexpr int GP_THREADS = 1024;
 constexpr int GP_WAVES = GP_THREADS / 64;
 constexpr int GP_LDS_ROWS = 4096;   // tree rows in LDS; of larger trees the lists and the argmax are in the workspace
 constexpr int GP_AHEAD = 16;        // 16-byte loads that a lane has in flight
-template <bool VEC>
 __global__ __launch_bounds__(GP_THREADS) void k_greedy_path(const float* __restrict__ target, int64_t row_stride, int V, int NN,
                                                             const int32_t* __restrict__ token,
                                                             const int32_t* __restrict__ parent,
@@ -219,8 +218,8 @@ __global__ __launch_bounds__(GP_THREADS) void k_greedy_path(const float* __restr
     float4 tail = make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
     {
       const int i0 = n_full * CHUNK + tid * 4;
-      if (VEC && i0 + 3 < V) {
-        tail = *reinterpret_cast<const float4*>(x + i0);
+      if (i0 + 3 < V) {
+        tail = load_float4(x + i0);
       } else {
         if (i0 < V) tail.x = x[i0];
         if (i0 + 1 < V) tail.y = x[i0 + 1];
@@ -229,10 +228,7 @@ __global__ __launch_bounds__(GP_THREADS) void k_greedy_path(const float* __restr
       }
     }
     const float* __restrict__ src = x + tid * 4;
-    auto load = [&](int k) {
-      const float* __restrict__ at = src + (int64_t)k * CHUNK;
-      return VEC ? *reinterpret_cast<const float4*>(at) : make_float4(at[0], at[1], at[2], at[3]);
-    };
+    auto load = [&](int k) { return load_float4(src + (int64_t)k * CHUNK); };
     float4 f[GP_AHEAD];
     int k = 0;
     if (n_full >= GP_AHEAD) {
@@ -319,10 +315,10 @@ __global__ __launch_bounds__(GP_THREADS) void k_greedy_path(const float* __restr
 // trees beyond LDS is priced on neither side: 3 us a level and 20000 rows here, but more in the walk that follows the scan
 // (one tree of 60000 rows on 600 tokens, depth limit 10, all children of the root or at random depths: 258 and 826 us by the
 // scan, 119 and 113 by the paths; of 9000 rows on 2000 tokens, limit 4, 45 and 111, 19 and 18).
-static bool greedy_by_path(int B, int NN, int V, int max_depth, bool aligned) {
+static bool greedy_by_path(int B, int NN, int V, int max_depth) {
   const double row_bytes = 4.0 * V;
   const double scan_us = 6.0 + (double)NN * row_bytes / 6.0e6;
-  const double row_us = fmax(2.0 + row_bytes / (aligned ? 1.0e5 : 2.0e4), (double)B * row_bytes / 2.2e6);
+  const double row_us = fmax(2.0 + row_bytes / 1.0e5, (double)B * row_bytes / 2.2e6);
   return 6.0 + row_us * ((double)max_depth + 1.0) < scan_us;
 }
 
@@ -341,9 +337,8 @@ struct RowView {
   __device__ __forceinline__ float of(float logit) const { return exp2_fast(arg(logit)); }
   __device__ __forceinline__ float prob(int v) const { return of(x[v]); }
   __device__ __forceinline__ float4 of4(const float4 f) const { return make_float4(of(f.x), of(f.y), of(f.z), of(f.w)); }
-  // tokens 4 i .. 4 i + 3 with one 16-byte load (the row must be 16-byte aligned)
-  __device__ __forceinline__ float4 prob4(int i) const { return of4(reinterpret_cast<const float4*>(x)[i]); }
-  __device__ __forceinline__ bool aligned16() const { return reinterpret_cast<uintptr_t>(x) % 16 == 0; }
+  // tokens 4 i .. 4 i + 3 with one 16-byte load
+  __device__ __forceinline__ float4 prob4(int i) const { return of4(load_float4(x + 4 * i)); }
 };
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -396,22 +391,18 @@ __device__ __forceinline__ double residual_mass(const RowView& p, const RowView&
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float bf = (float)beta;
   float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-  int v = tid;  // first token of the scalar part
-  if (p.aligned16() && q.aligned16()) {
-    // 16-byte loads, four of each row in flight per thread: a single compute unit streams the two
-    // rows, so what is in flight bounds the pass
-    const int n4 = V >> 2;
+  // 16-byte loads, four of each row in flight per thread: a single compute unit streams the two
+  // rows, so what is in flight bounds the pass
+  const int n4 = V >> 2;
 #pragma unroll 4
-    for (int i = tid; i < n4; i += AC_THREADS) {
-      const float4 pp = p.prob4(i), qq = q.prob4(i);
-      a0 += fmaxf(fmaf(-bf, qq.x, pp.x), 0.f);
-      a1 += fmaxf(fmaf(-bf, qq.y, pp.y), 0.f);
-      a2 += fmaxf(fmaf(-bf, qq.z, pp.z), 0.f);
-      a3 += fmaxf(fmaf(-bf, qq.w, pp.w), 0.f);
-    }
-    v = (n4 << 2) + tid;
+  for (int i = tid; i < n4; i += AC_THREADS) {
+    const float4 pp = p.prob4(i), qq = q.prob4(i);
+    a0 += fmaxf(fmaf(-bf, qq.x, pp.x), 0.f);
+    a1 += fmaxf(fmaf(-bf, qq.y, pp.y), 0.f);
+    a2 += fmaxf(fmaf(-bf, qq.z, pp.z), 0.f);
+    a3 += fmaxf(fmaf(-bf, qq.w, pp.w), 0.f);
   }
-  for (; v < V; v += AC_THREADS) a0 += fmaxf(fmaf(-bf, q.prob(v), p.prob(v)), 0.f);
+  for (int v = (n4 << 2) + tid; v < V; v += AC_THREADS) a0 += fmaxf(fmaf(-bf, q.prob(v), p.prob(v)), 0.f);
   double acc = wave_sum(((double)a0 + (double)a1) + ((double)a2 + (double)a3));
   __syncthreads();  // red is free
   if (lane == 0) red[wave] = acc;
@@ -541,8 +532,8 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
   const int per = (n4 + BK_SLICES - 1) / BK_SLICES;
   const int i0 = min(n4, slice * per), i1 = min(n4, i0 + per);
   const int tail = slice == BK_SLICES - 1 ? V & 3 : 0;  // the last V % 4 tokens are the last slice's
-  const float4* __restrict__ px = reinterpret_cast<const float4*>(p_row);
-  const float4* __restrict__ qx = reinterpret_cast<const float4*>(q_row);
+  auto px = [&](int i) { return load_float4(p_row + 4 * i); };
+  auto qx = [&](int i) { return load_float4(q_row + 4 * i); };
   // A thread's tokens stay in its registers for both passes where they fit, requested all at once.  (Read twice, two at a
   // time: 61 rows of 128256 tokens 15.7 us, now 12.1; 97 rows 28.7 and 19.8.)
   constexpr int KEEP = 8;
@@ -553,8 +544,8 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
     for (int u = 0; u < KEEP; ++u) {
       const int i = i0 + tid + u * BK_THREADS;
       const bool mine = i < i1;  // (p = q = 0 elsewhere: not live)
-      fp[u] = mine ? px[i] : make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
-      fq[u] = mine ? qx[i] : make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
+      fp[u] = mine ? px(i) : make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
+      fq[u] = mine ? qx(i) : make_float4(-HS_INF, -HS_INF, -HS_INF, -HS_INF);
     }
   }
   const RowView p(p_row, p_row[p_arg], p_lz, inv_t);
@@ -573,7 +564,7 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
         if (i0 + tid + u * BK_THREADS < i1) four(fp[u], fq[u]);
     } else {
 #pragma unroll 2
-      for (int i = i0 + tid; i < i1; i += BK_THREADS) four(px[i], qx[i]);
+      for (int i = i0 + tid; i < i1; i += BK_THREADS) four(px(i), qx(i));
     }
     if (tid < tail) token(p_row[(n4 << 2) + tid], q_row[(n4 << 2) + tid]);
   };
@@ -831,26 +822,24 @@ __global__ __launch_bounds__(GR_THREADS) void k_tree_rows(const int32_t* __restr
 // by all waves of the workgroup: dst[r] for each of them.  A lane takes four tokens, 16 lanes a row, a
 // wave four rows per trip; the loads of four trips are requested together (lanes past the last row
 // re-read it), and a row's 16 partial sums meet in its last lane by DPP moves.  Rows that are not
-// whole, or rows of arrays that are not 16-byte aligned, are summed a token per lane.  A row's sum
+// whole are summed a token per lane.  A row's sum
 // does not depend on who computes it: the walk and k_bonus_rows give the same bits.
 __device__ __forceinline__ void bonus_row_sums(const RowView& p, const RowView& q, bool sub_q, double beta, int V,
                                                int r_begin, int r_end, double* __restrict__ dst) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
   int first_row = r_begin;  // rows below it were summed with 16-byte loads
-  if (p.aligned16() && (!sub_q || q.aligned16()) && V >= 64) {
+  if (V >= 64) {
     constexpr int TRIPS = 4;
     const int full_end = min(V >> 6, r_end);
     const int sub = lane >> 4, l16 = lane & 15;
     const float bf = (float)beta;
-    const float4* __restrict__ px = reinterpret_cast<const float4*>(p.x);
-    const float4* __restrict__ qx = reinterpret_cast<const float4*>(q.x);
     for (int r0 = r_begin + wave * 4; r0 < full_end; r0 += n_waves * 4 * TRIPS) {
       float4 fp[TRIPS], fq[TRIPS];
 #pragma unroll
       for (int u = 0; u < TRIPS; ++u) {
         const int r = min(r0 + u * n_waves * 4 + sub, full_end - 1);
-        fp[u] = px[r * 16 + l16];
-        fq[u] = sub_q ? qx[r * 16 + l16] : fp[u];
+        fp[u] = load_float4(p.x + r * 64 + l16 * 4);
+        fq[u] = sub_q ? load_float4(q.x + r * 64 + l16 * 4) : fp[u];
       }
 #pragma unroll
       for (int u = 0; u < TRIPS; ++u) {
@@ -1403,14 +1392,10 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     void* scan_ws = c.take<char>(0);
     const float T = stochastic ? temperature : 1.0f;
     hs_status r;
-    if (!stochastic && hs::greedy_by_path(B, NN, V, max_depth, rows.aligned)) {
+    if (!stochastic && hs::greedy_by_path(B, NN, V, max_depth)) {
       int32_t* list = reinterpret_cast<int32_t*>(t_lz);  // (2 NN words that the scan would fill)
-      if (rows.aligned)
-        hipLaunchKernelGGL(hs::k_greedy_path<true>, dim3(B), dim3(hs::GP_THREADS), 0, st, target_logits, row_stride, V, NN, token,
-                           parent, node_offsets, max_depth, t_arg, list, accept_len, accept_path, bonus_token);
-      else
-        hipLaunchKernelGGL(hs::k_greedy_path<false>, dim3(B), dim3(hs::GP_THREADS), 0, st, target_logits, row_stride, V, NN, token,
-                           parent, node_offsets, max_depth, t_arg, list, accept_len, accept_path, bonus_token);
+      hipLaunchKernelGGL(hs::k_greedy_path, dim3(B), dim3(hs::GP_THREADS), 0, st, target_logits, row_stride, V, NN, token, parent,
+                         node_offsets, max_depth, t_arg, list, accept_len, accept_path, bonus_token);
       return hs::launch_status("accept (greedy path)");
     }
     if (mode == HS_ACCEPT_STOCHASTIC) {
@@ -1436,10 +1421,8 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     return hs::launch_status("accept (greedy)");
   }
   if (mode == HS_ACCEPT_STOCHASTIC && NN > 0) {
-    // the sorted residual pays from a few thousand tokens on and needs 16-byte aligned rows
-    const bool sorted = bk.pairs != nullptr && V >= 4096 && row_stride % 4 == 0 &&
-                        reinterpret_cast<uintptr_t>(target_logits) % 16 == 0 &&
-                        reinterpret_cast<uintptr_t>(draft_logits) % 16 == 0;
+    // the sorted residual pays from a few thousand tokens on
+    const bool sorted = bk.pairs != nullptr && V >= 4096;  // (its rows need no alignment: load_float4)
     if (sorted) {
       hipLaunchKernelGGL(hs::k_bucket_sort, dim3(hs::BK_SLICES, NN), dim3(hs::BK_THREADS), 0, st, target_logits, draft_logits,
                          row_stride, V, 1.0f / temperature, chain, t_arg, t_lz, d_arg, d_lz, bk);
