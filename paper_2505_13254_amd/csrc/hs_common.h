@@ -95,6 +95,12 @@ __device__ __forceinline__ float4 load_float4(const float* p) {
   return make_float4(f[0], f[1], f[2], f[3]);
 }
 
+// The same for data that nobody reads again.
+__device__ __forceinline__ float4 stream_float4(const float* p) {
+  const float4_any f = __builtin_nontemporal_load(reinterpret_cast<const float4_any*>(p));
+  return make_float4(f[0], f[1], f[2], f[3]);
+}
+
 // Running softmax statistics of a set of raw logits x, with y = x * inv_t:
 //   m  = max x (raw units, so comparisons stay exact);
 //   s1 = sum exp(y - y_max) over all elements but ONE instance of the max;

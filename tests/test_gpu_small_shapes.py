@@ -333,11 +333,11 @@ def test_a_workspace_without_room_for_the_finer_last_round(G):
         assert diff.max() <= 1e-2 * np.abs(want).max()
 
 
-@pytest.mark.parametrize("V", [4096, 8195])
+@pytest.mark.parametrize("V", [2050, 4096, 8195])
 @pytest.mark.parametrize("n_kids,k", [(1, 0), (1, None), (2, 1), (5, 0), (5, 4), (66, 63), (66, 64), (66, None)])
 def test_chains_end_with_their_first_accepted_child(G, V, n_kids, k):
     """The root's k-th child is accepted (None: no child is), and below it a chain of one child, accepted and then
-    rejected: one child with the sums alone, chains that end at any place, by the sorted residual (V = 4096) and by passes
+    rejected: one child with the sums alone, chains that end at any place, by the sorted residual and (V = 2050) by passes
     over both rows.  An empty sequence lies between two copies of the tree, the second without room for a second level."""
     import paper_2505_13254_amd as hs
     from oracle import verify_accept
