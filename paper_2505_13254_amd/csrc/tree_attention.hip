@@ -519,13 +519,15 @@ static inline float plan_own_cu_us(int narrow, bool half, int waves, int tiles, 
   return item + (float)tiles * tile;
 }
 // Waves share row blocks (AttnArgs::share) in launches of more than one round of the compute units.  Sequences of a
-// single row group gain 3 to 4 % in launches that follow one another, but a launch that follows other kernels, as in a
-// step, loses about 10 us in its first round and earns them back in the fifth or so: 46 rows on 2048 tokens, 8 KV heads,
-// whole steps of 40 / 100 / 140 / 200 layers 133 / 253 / 314 / 428 us, shared 145 / 267 / 321 / 421; of 129 rows on 4096 tokens,
-// 40 heads, 20 and 40 layers 370 and 703, shared 362 and 685.  With several groups there is no such loss: 73 rows, 20 and 40
-// layers 138 and 197, now 127 and 180.  Nor in ragged batches, whose workgroups drift apart (16 sequences, whole step 400 us,
+// single row group gain 3 to 5 % in launches that follow one another, but a launch that follows other kernels, as in a
+// step, loses some in its first round: short items earn that back in the fifth round or so, long ones in the second.  Whole
+// steps, a block to a wave and shared: 129 rows, 40 heads, 10 / 20 / 30 layers on 4096 tokens 224 / 376 / 539 us and 214 / 364 / 513, 20 layers on
+// 2000 tokens 241 and 231, on 1000 161 and 163; 46 rows, 8 KV heads, 80 layers on 2048 205 and 200, on 1000 137 and 141, 40 layers (320
+// items) on 2048 132 and 140.  With several groups there is no such loss: 73 rows, 20 and 40
+// layers 138 and 197, shared 127 and 180.  Nor in ragged batches, whose workgroups drift apart (16 sequences, whole step 400 us,
 // 395 with the sharing of several groups alone, 381 with both).
 constexpr int PLAN_SHARE_ITEMS = 5 * PLAN_CUS;
+constexpr int PLAN_SHARE_LONG_ITEMS = 3 * PLAN_CUS / 2, PLAN_SHARE_LONG = 24;  // (from so many tiles to an item)
 constexpr int PLAN_MIN_SPLIT_TOKENS = PLAN_MIN_SPLIT_TILES * 64;
 static inline float plan_tile_us(int waves) { return 1.25f + 0.04f * (float)waves; }
 
@@ -773,7 +775,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   a.n_tbl = n;
   a.n_items = (int)first;
   a.narrow = best.narrow;
-  a.share = first <= PLAN_CUS ? 0 : !equal || first > PLAN_SHARE_ITEMS ? 2 : 1;
+  a.share = first <= PLAN_CUS ? 0 : !equal || first > (per_of[0] >= PLAN_SHARE_LONG ? PLAN_SHARE_LONG_ITEMS : PLAN_SHARE_ITEMS) ? 2 : 1;
   a.sp_max = sp_max;
   return true;
 }

@@ -317,12 +317,13 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // every fourth 32 keys (`quarter`).  (61 rows on 2048 tokens, 8 KV heads, 32 layers one by one: 589 -> 535 us.)
   const bool quarter = SHARE && h_narrow == 2;
   // Groups of five or six blocks, all groups being so: the first four waves, one to a SIMD, take a block each, and
-  // the other four share what is left: two waves to a block, as above, or all four of them to one, each with
-  // every fourth 32 keys.  `ways` is the number of waves that share this wave's block, kpar its share.  (With a wave
-  // to a block one or two SIMDs have two waves' work and the others one's: 129 rows on 4096 tokens, 40 layers and
-  // heads, 703 -> 685 us the whole step; ten blocks in two groups (row_group) 185 -> 180.  When: see a.share.)
+  // of the other four two share each block that is left, as above.  `ways` is the number of waves that share this wave's block,
+  // kpar its share.  (With a wave to a block one or two SIMDs have two waves' work and the others one's: 129 rows on 4096 tokens, 40
+  // layers and heads, 703 -> 675 us the whole step; ten blocks in two groups (row_group) 185 -> 180.  A fifth block shared by all four
+  // of the others, each with every fourth 32 keys, kept two of the SIMDs busy for as long in every tile, the other two in the next, and in one go
+  // without overlap: 1.51 us a tile, where six blocks took 1.31 and five do now.  When: see a.share.)
   const bool shared_tail = SHARE && (blk_n == 5 || blk_n == 6) && groups_share(n_blk, h_share);
-  const int ways = quarter ? 4 : ksplit ? 2 : !shared_tail || wave < 4 ? 1 : blk_n == 5 ? 4 : 2;
+  const int ways = quarter ? 4 : ksplit || (shared_tail && wave >= 4) ? 2 : 1;
   const int my_blk = blk0 + (shared_tail && wave >= 4 ? 4 + (blk_n == 6 ? wave & 1 : 0) : wave & ((1 << pair_shift) - 1));
   const int kpar = shared_tail ? (wave < 4 ? 0 : blk_n == 6 ? (wave - 4) >> 1 : wave - 4) : wave >> pair_shift;  // (without sharing: 0)
   const bool wave_active = my_blk < blk0 + blk_n && kpar < ways;
@@ -997,7 +998,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     // ---- the waves that share a row block leave their sums in the (now free) V ring (quarter: the first four in
     // the K ring), 16 bytes to a lane, and each adds up its part of the columns, wave by wave in rising order.
     float* const den = reinterpret_cast<float*>(&anc[0]);  // [wave][denominators, reference maxima]
-    const bool sharing = quarter ? wave_active : wave >= 4;
+    const bool sharing = quarter ? wave_active : wave >= 4 && wave_active;
     auto left_by = [&](int w) { return reinterpret_cast<float*>(w < 4 ? lds_k[w] : lds_v[w - 4]); };
     if (sharing) {
       float* const ex = left_by(wave);
@@ -1014,8 +1015,8 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (sharing) {
       // the first of the sharing waves, and how far it is to the next one
-      const int step = quarter ? 1 << pair_shift : ways == 4 ? 1 : 2;
-      const int first = quarter ? wave & (step - 1) : ways == 4 ? 4 : 4 + (wave & 1);
+      const int step = quarter ? 1 << pair_shift : blk_n - 4;
+      const int first = quarter ? wave & (step - 1) : my_blk - blk0;
       const int keep = ways == 4 ? 1 : NT / 2;          // column blocks of this wave
       const int tt0 = kpar * keep;
       if (tt0 >= NT) {  // (head dimension 64: two column blocks for four waves)

@@ -212,6 +212,13 @@ def test_how_row_blocks_go_to_workgroups_and_waves(Ms, Ls, Hq, Hkv, D, form):
     assert hs.hs_tree_attention_last_form() == 0
 
 
+@pytest.mark.parametrize("B,L,form", [(24, 1600, 1), (25, 1600, 33), (25, 1473, 33), (25, 1472, 1), (80, 1472, 1), (81, 1472, 33)])
+def test_single_groups_share_earlier_where_items_are_long(B, L, form):
+    """Five blocks to a group, 16 heads: from 384 items of at least 24 tiles on, from 1280 of any length."""
+    assert _plan([129] * B, [L] * B, 16, 16)[0][0] == 1
+    assert hs.hs_tree_attention_last_form() == form
+
+
 @pytest.mark.parametrize("Ms,Ls,Hkv,D,splits", [
     ([20], [300], 8, 128, 1), ([20, 20], [300, 300], 8, 128, 1), ([16] * 4, [350] * 4, 8, 128, 1), ([21, 10, 15, 15], [116, 321, 110, 355], 8, 128, 1),
     ([40] * 4, [350] * 4, 2, 128, 3), ([55], [432], 8, 128, 4), ([20], [500], 8, 64, 1), ([20], [1000], 8, 64, 4), ([20], [2000], 8, 64, 8)])
