@@ -344,3 +344,9 @@ def test_paged_attention_in_every_launch_form(G, D, hq, hkv, M, L, B, form):
     want_o, _ = tree_attention(step["q"], step["k_prefix"], step["v_prefix"], step["k_tree"], step["v_tree"], step["parent"], no,
                                step["prefix_offsets"], step["scale"])
     assert np.abs(packed.astype(np.float64) - want_o).max() <= 2e-2
+
+
+@pytest.mark.parametrize("hq,hkv,M,L,B", [(32, 8, 65, 100, 33), (64, 4, 17, 1000, 66), (64, 8, 97, 129, 20)])
+def test_paged_attention_of_rows_that_ride_along(G, hq, hkv, M, L, B):
+    """The same for the rows behind full row groups that go with the last of these: one group, splits, three groups."""
+    test_paged_attention_in_every_launch_form(G, 128, hq, hkv, M, L, B if B > 20 else 21, 65)

@@ -108,6 +108,32 @@ def test_row_blocks_shared_by_waves(G, D, hq, hkv, M, L, B, shared, variant):
     assert {0: [], 1: several, 2: every}[hs.hs_tree_attention_last_form() >> 4] == shared
 
 
+@pytest.mark.parametrize("variant", ["unit", "hot", "last"])
+@pytest.mark.parametrize("hq,hkv,M,L,B,ride", [
+    (32, 8, 65, 100, 33, True), (32, 8, 68, 64, 40, True), (64, 8, 33, 0, 33, True), (8, 8, 65, 31, 40, False),  # one group: 4, 16, 8 rows; four blocks
+    (64, 4, 17, 1000, 66, True), (64, 4, 16, 200, 70, False),                                     # the last entries in splits; full groups alone
+    (64, 8, 65, 130, 32, True), (64, 8, 66, 65, 32, True), (64, 8, 67, 65, 32, False),            # two
+    (64, 8, 97, 129, 20, True), (64, 8, 98, 1, 32, True)])                                        # three
+def test_rows_that_ride_along_with_full_groups(G, hq, hkv, M, L, B, ride, variant):
+    """Up to 16 rows of a KV head behind its full row groups: one tile and many, a partial one, the tree's tiles alone, one node's
+    rows and two, splits; scores that leave the fixed reference, of any rows and ("last") of riding rows alone."""
+    import paper_2505_13254_amd as hs
+    from test_gpu_attention import _case, _compare, _random_parents
+    w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=128)
+    rs = np.random.RandomState(M + L)
+    step = _case(w, M, [_random_parents(rs, M, back=9) for _ in range(B)], [L] * B, "unit" if variant == "last" else variant)
+    if variant == "last":  # a late key of the prefix, or the tree's last one, along the last row's query of some head
+        as_float = lambda bits: (bits.astype(np.uint32) << 16).view(np.float32)
+        for s in range(B):
+            h, row = s % hq, (s + 1) * M - 1
+            q = as_float(step["q"][row, h])
+            key = q * np.float32((125.0 + s % 30) * np.sqrt(128.0) / np.dot(q, q))
+            keys, at = (step["k_prefix"], (s + 1) * L - 1 - s % min(L, 40)) if L > 0 and s % 3 else (step["k_tree"], row)
+            keys[at, h // (hq // hkv)] = torch.from_numpy(key).bfloat16().view(torch.int16).numpy().view(np.uint16)
+    _compare(G, step, "bf16", big_scores=variant != "unit")
+    assert (hs.hs_tree_attention_last_form() & 64 != 0) == ride
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("D,hq,hkv,M,L,offset", [
     (64, 3, 3, 1, 0, 0), (64, 3, 3, 16, 15, 0), (64, 6, 3, 17, 16, 1), (64, 3, 1, 33, 511, 0), (64, 3, 3, 5, 1040, 3),
