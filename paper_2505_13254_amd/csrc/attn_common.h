@@ -101,7 +101,6 @@ struct AttnArgs {
   void* o;
   float* lse;
   float* part;
-  const unsigned* anc_tiles;  // ancestor table of large trees (matrix-core kernel), in the workspace; else NULL
   int n_tbl;       // > 0: work-list launch (1-D grid over the items of tbl[0 .. n_tbl)); 0: grid.y = sequence
   int n_items;
   int narrow;      // work-list launches: 1 = two workgroups to an item, one for each 128 of its up to 256 rows; 2 = four

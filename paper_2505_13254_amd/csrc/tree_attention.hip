@@ -882,7 +882,7 @@ extern "C" size_t hs_tree_attention_workspace(int32_t B, int32_t NN, int64_t tot
   if (B <= 0 || NN <= 0 || Hq <= 0 || Hkv <= 0 || D <= 0 || total_prefix < 0) return 0;
   // upper bound over every plan the launch may choose: splits are at least PLAN_MIN_SPLIT_TOKENS long
   const int64_t sp_bound = total_prefix / PLAN_MIN_SPLIT_TOKENS + 1;
-  // (+ the ancestor table that trees of more than 256 rows keep there: such a tree needs NN > 256)
+  // (+ what trees of more than 256 rows ask for besides: such a tree needs NN > 256)
   return part_bytes(NN, Hq, D, (int)(sp_bound < 2 ? 2 : sp_bound > 64 ? 64 : sp_bound)) +
          align_up(attn_mfma_table_bytes(NN < MAX_TREE_ROWS ? NN : MAX_TREE_ROWS, NN), 256);
 }
@@ -1012,7 +1012,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   a.block_table = block_table; a.max_blocks = max_blocks;
   a.B = B; a.Hq = Hq; a.Hkv = mfma ? kv_units : Hkv; a.G = mfma ? g_unit : Hq / Hkv; a.half = mfma && pairs ? 1 : 0; a.scale = scale;
   a.o = o; a.lse = lse; a.part = static_cast<float*>(workspace);
-  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.share = 0; a.ride = 0; a.cmb_row0 = 0; a.anc_tiles = nullptr;
+  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.share = 0; a.ride = 0; a.cmb_row0 = 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // the workspace query bounds the splits of a sequence the same way
   const int64_t sp_bound = total_prefix / PLAN_MIN_SPLIT_TOKENS + 1;
@@ -1055,8 +1055,6 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
     if (!any) a.share = 0;
   }
   last_form = mfma ? (1 << a.narrow) + 16 * a.share + 64 * a.ride : 0;
-  if (table_bytes != 0 && workspace != nullptr)
-    a.anc_tiles = reinterpret_cast<const unsigned*>(static_cast<const char*>(workspace) + part_bytes(NN, Hq, D, a.sp_max));
   if (plan_only) {
     const int n_rg_max = mfma ? (a.G * max_M + 255) / 256 : plan.n_rb_max;
     report->totals[0] = mfma ? 1 : 2;

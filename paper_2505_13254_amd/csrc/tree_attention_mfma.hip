@@ -34,10 +34,9 @@
 // the block whose product comes next, or the first half of the block whose scores were just
 // finished) and requests the LDS fragments of the next step of two matrix instructions, so matrix, vector and LDS pipes of a wave all have independent work at any time.
 //
-// The tree part (ancestor mask) is a bit table built in LDS from the parent pointers (trees of up
-// to 256 rows).  Larger trees (BIG, up to 1024 rows) take the table from global memory, where
-// k_anc_tiles has laid it out per 64-key tile before the launch: the slice of a tree tile (two words
-// for each of the workgroup's 256 rows) travels into a ring in LDS together with the tile.
+// The tree part (ancestor mask) is a bit table built in LDS from the parent pointers: of all rows of a tree (up to
+// 256), or, in launches with larger trees (BIG, up to 1024 rows), of the tree rows that the workgroup's own blocks
+// hold, block by block.
 //
 // K/V tiles go from HBM straight into LDS (global_load_lds_dwordx4, 16 bytes per lane, no staging
 // registers) through a ring of four tile buffers: one tile is being multiplied, the next one has
@@ -69,8 +68,8 @@ constexpr int MF_TILE = 64;        // keys per LDS tile (two 32-key blocks)
 constexpr int MF_NBUF = 4;         // LDS ring: one tile in use, one landed, two on their way from HBM
 constexpr int MF_MAX_M = 256;      // tree rows per sequence whose ancestor bit table (M x 8 words) is built in LDS
 constexpr int MF_ANC_STRIDE = 9;   // words from one row of that table to the next (eight, and one so that the rows of a wave lie in different banks)
-constexpr int MF_BIG_M = 1024;     // tree rows per sequence with the table in global memory
-constexpr int MF_ANC_SLICE = 2 * MF_ROWS;  // words of a tree tile's mask slice: two per row of the workgroup
+constexpr int MF_BIG_M = 1024;     // tree rows per sequence at most
+constexpr int MF_BIG_WORDS = 7424; // words of a workgroup's table in launches with more than MF_MAX_M rows (AncBlocks)
 constexpr int MF_ROW_BYTES = 256;  // one K or V row of a head: 128 bf16
 constexpr int MF_TILE_BYTES = MF_TILE * MF_ROW_BYTES;
 constexpr int MF_BLOCK_BYTES = 32 * MF_ROW_BYTES;
@@ -85,46 +84,30 @@ bool attn_mfma_supported(int D, hs_dtype dt, int max_tree_rows, float scale) {
   return (D == 128 || D == 64) && dt == HS_BF16 && max_tree_rows <= MF_BIG_M && scale > 0.f;
 }
 
-// Bytes of the ancestor table that launches with more than MF_MAX_M rows in a tree keep in the
-// workspace: 16 tiles x two words for every tree row of the batch (0: no such table is needed).
+// Bytes that launches with more than MF_MAX_M rows in a tree ask for besides the partial records.  Nothing is kept in
+// them (an ancestor table was, before workgroups built their own); what a call asks for and which plan it takes at
+// which workspace size is as it was.
 size_t attn_mfma_table_bytes(int max_tree_rows, int64_t NN) {
   return max_tree_rows > MF_MAX_M ? (size_t)NN * (MF_BIG_M / MF_TILE) * 8 : 0;
 }
 
-// Ancestor table of large trees, one slice per 64-key tile: words (2 i, 2 i + 1) of tile tt hold bit
-// j - 64 tt for every tree row j of [64 tt, 64 tt + 64) on the root path of tree row i (itself
-// included).  The table of the sequence whose first row is n0 starts at word 32 n0; tile tt of a
-// tree of M rows lies 2 M tt words further.  grid: (row chunks of 256, sequences).
-__global__ __launch_bounds__(256) void k_anc_tiles(const int32_t* __restrict__ parent, const int32_t* __restrict__ node_offsets,
-                                                   unsigned* __restrict__ table) {
-  __shared__ int par[MF_BIG_M];
-  const int s = blockIdx.y;
-  const int n0 = node_offsets[s];
-  int M = node_offsets[s + 1] - n0;
-  if (M > MF_BIG_M) M = MF_BIG_M;  // (the host has refused larger trees)
-  if ((int)blockIdx.x * 256 >= M) return;
-  for (int i = threadIdx.x; i < M; i += 256) par[i] = parent[n0 + i];
-  __syncthreads();
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= M) return;
-  unsigned* out = table + (size_t)n0 * 32;
-  const int n_tt = (M + MF_TILE - 1) / MF_TILE;
-  // the path is walked once, from the row towards the root: row numbers fall, and so do the tiles
-  int j = i;
-  for (int tt = n_tt - 1; tt >= 0; --tt) {
-    const int lo = tt * MF_TILE;
-    unsigned w0 = 0, w1 = 0;
-    while (j >= lo) {
-      const int b = j - lo;
-      if (b < 32) w0 |= 1u << b;
-      else if (b < 64) w1 |= 1u << (b - 32);
-      const int up = par[j];
-      j = up < j ? up : -1;  // (a malformed tree cannot keep the walk from ending)
+// Where a workgroup of a launch with large trees keeps the ancestor bits of its rows: an area for each of its blocks
+// (b: 0 .. 7, by their order in the row group), in it a row of words for each tree row of the block, word q for the tree
+// rows 32 q ..  .  With one query head to a KV head a block is 32 tree rows and eight blocks reach 1024 rows of up to 32
+// words: there each block has the words of its own last row only, which is one word more from block to block.  Otherwise all
+// have the words of the tree's visible rows, an odd number, so that the rows lie in different banks.
+struct AncBlocks {
+  int stride, base;  // words from row to row; first word of block b
+  __host__ __device__ AncBlocks(int Gh, int tree_keys, int first_blk, int b) {
+    const int rows = Gh == 1 ? 32 : 31 / Gh + 2;
+    stride = ((tree_keys + 31) >> 5) | 1;
+    base = b * rows * stride;
+    if (8 * rows * stride > MF_BIG_WORDS) {  // (Gh == 1, beyond 928 rows)
+      stride = first_blk + b + 1;
+      base = 32 * (b * (first_blk + 1) + ((b * (b - 1)) >> 1));
     }
-    uint2 w = {w0, w1};
-    *reinterpret_cast<uint2*>(out + ((size_t)tt * M + i) * 2) = w;
   }
-}
+};
 
 // 16-byte chunk c (0..15) of row r lives at chunk position c ^ swz_key(r).  The key takes 16
 // different values over 16 consecutive rows (one K row per lane: conflict-free 16-byte reads) and
@@ -178,7 +161,10 @@ __device__ __forceinline__ void wait_lds(int n) {  // n is a constant once the w
 #define MF_PIN() __builtin_amdgcn_sched_barrier(0)
 
 // PAGED: the prefix K/V live in pages of MF_TILE tokens ([page, token, Hkv, D]); a tile is a page.
-// BIG: trees of more than MF_MAX_M rows may occur; the ancestor table comes from a.anc_tiles.
+// BIG: trees of more than MF_MAX_M rows may occur; a workgroup's ancestor table is of its own rows (AncBlocks).  (Until it was,
+// a launch ahead of this one laid a table out in the workspace and its slices travelled with the tree tiles: 300 rows on 300 tokens,
+// 32 heads on 8, 20.8 us a call and now 18.2; on 2048 tokens 32.3, 30.0; 1000 rows on 1000, 16 heads of one row each, 41.6, 37.7;
+// 12 ragged sequences of up to 300 rows, paged, 4 layers 634, 626.)
 // HALF: head dimension 64.  Two neighbouring KV heads of a token are 256 contiguous bytes, i.e. one
 // row of this kernel, and a.Hkv / a.G count such pairs and the 2 G query heads that read them.  A
 // wave's rows all belong to one head of the pair, whose half of the 256-byte rows it multiplies; K and
@@ -197,11 +183,12 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   constexpr int EPS = 4 / STEPS;    // pairs of exponentials a step takes along
   static_assert(!(BIG && ONCE), "more than 256 tree rows are several row groups");
   static_assert(!RIDE || (!BIG && !HALF && !SHARE), "riding rows: launches of one workgroup to an item, trees of up to 256 rows");
-  static_assert(MF_NBUF * MF_ANC_SLICE <= MF_MAX_M * MF_ANC_STRIDE, "the slice ring of large trees takes the place of the table");
   __shared__ __attribute__((aligned(16))) char lds_k[MF_NBUF][MF_TILE_BYTES];
   __shared__ __attribute__((aligned(16))) char lds_v[MF_NBUF][MF_TILE_BYTES];
-  __shared__ unsigned anc[MF_MAX_M * MF_ANC_STRIDE];
-  __shared__ int par_lds[MF_MAX_M];
+  __shared__ unsigned anc[BIG ? MF_BIG_WORDS : MF_MAX_M * MF_ANC_STRIDE];
+  __shared__ int par_small[BIG ? 1 : MF_MAX_M];
+  // (large trees: in the ring's last slot, which is requested after the barrier that follows the paths' walk)
+  int* const par_lds = BIG ? reinterpret_cast<int*>(lds_v[MF_NBUF - 1]) : par_small;
   __shared__ int exact_flag;
   __shared__ int page_lds[PAGED ? 256 : 1];
   constexpr int RIDE_P_ROW = 144;  // bytes from one riding row's weights of a tile to the next one's (64 bf16, and 16 so that rows lie in different banks)
@@ -228,7 +215,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const void* const h_v_tree = a.v_tree;
   const int32_t* const h_parent = a.parent;
   void* const h_o = a.o;
-  const unsigned* const h_anc = a.anc_tiles;
   float* const h_lse = a.lse;
   float* const h_part = a.part;
   const float h_scale = a.scale;
@@ -377,17 +363,9 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const unsigned dma_chunk = (unsigned)(((tid & 15) ^ swz_key(dma_row)) << 4);         // swz_key(row + 32) == swz_key(row)
   const unsigned lane_off0 = (unsigned)(dma_row * (int)tok_stride) + dma_chunk;        // inside a full tile: fixed
   const unsigned lane_off1 = lane_off0 + (unsigned)(32 * (int)tok_stride);
-  // Large trees: lane l of wave w fetches word l % 2 of the workgroup's row 32 w + l / 2 (rows past
-  // the end: of the last row) from a tile's slice of this sequence's table.
-  const unsigned lds_anc_addr = (unsigned)(uintptr_t)(lds_ptr)&anc[0];
-  const unsigned* anc_tbl = nullptr;
-  unsigned anc_lane_off = 0;
-  if constexpr (BIG) {
-    anc_tbl = h_anc + (size_t)(h_tree_shared ? 0 : n0) * 32;
-    int r = row_base + (lane >> 1);
-    r = r < Rh ? r : Rh - 1;
-    anc_lane_off = (unsigned)(((r / Gh) * 2 + (lane & 1)) * 4);
-  }
+  // Large trees: where the bits of this wave's block lie, and its first tree row.
+  const int blk_in_head = blk0 - (HALF && blk0 >= nbh ? nbh : 0);
+  const AncBlocks anc_at(Gh, tree_keys, blk_in_head, my_blk - blk0);
   // Paged caches: the pages of this split's tiles (at most 256) are staged in LDS; the requests
   // go out here, before the Q rows are asked for, so that waiting for them waits for nothing else.
   // A tile's page is then one LDS read.  (That read is older than every fragment read requested
@@ -425,19 +403,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     const int r1 = dma_row + 32 < rows ? dma_row + 32 : rows - 1;
     const unsigned ring = (unsigned)(t % MF_NBUF) * MF_TILE_BYTES + wave_lds;
     const int64_t off = tree ? base * tok_stride : prefix_tile(t);
-    if constexpr (BIG) {
-      // The tile's slice of the ancestor table goes first: one more load of this wave, older than the
-      // tile's four, so a wait that leaves the four youngest loads pending has seen it land.
-      if (tree) {
-        const unsigned* src = anc_tbl + (size_t)(t - n_ptiles) * (2 * (size_t)M);
-        const unsigned dst = lds_anc_addr + (unsigned)(t % MF_NBUF) * (MF_ANC_SLICE * 4) + (unsigned)(wave * 256);
-        unsigned saved;
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\tglobal_load_lds_dword %2, %3\n\ts_mov_b32 m0, %0"
-                     : "=&s"(saved)
-                     : "s"(dst), "v"(anc_lane_off), "s"(src)
-                     : "memory");
-      }
-    }
     lds_dma_tile<ONCE>(ks + off, vs + off, (unsigned)(r0 * (int)tok_stride) + dma_chunk,
                  (unsigned)(r1 * (int)tok_stride) + dma_chunk, lds_k_addr + ring, lds_v_addr + ring,
                  lds_k_addr + ring + MF_BLOCK_BYTES, lds_v_addr + ring + MF_BLOCK_BYTES);
@@ -487,10 +452,14 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     const char* src = static_cast<const char*>(h_q) + ((int64_t)(n0 + i) * Hq + g * G + gi) * MF_ROW_BYTES + (tid & 15) * 16;
     asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(ride_raw) : "v"(src) : "memory");
   }
-  int my_parent = 0;
-  if constexpr (!BIG) {
+  int my_parent = 0, far_parent = 0;  // (far: of tree row 512 + tid)
+  {
     const int32_t* src = h_parent + (h_tree_shared ? 0 : n0) + (tid < M ? tid : 0);  // (one tree for all entries, or each its own)
     asm volatile("global_load_dword %0, %1, off" : "=v"(my_parent) : "v"(src) : "memory");
+    if constexpr (BIG) {
+      const int32_t* far = h_parent + (h_tree_shared ? 0 : n0) + (tid + MF_THREADS < M ? tid + MF_THREADS : 0);
+      asm volatile("global_load_dword %0, %1, off" : "=v"(far_parent) : "v"(far) : "memory");
+    }
   }
   uintx4 qraw[NK];
   bool row_real;
@@ -507,8 +476,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   }
   issue(0);
   if (n_tiles > 1) issue(1);
-  // (large trees: a leading tree tile brings one load more; waiting for a multiple of four at most
-  // as large as the count waits for no less)
   const int first_tile_loads = 2 * MF_LOADS * (n_tiles < 2 ? n_tiles : 2);
   // ---- ancestor bit table: bit j of row i's words is set iff tree row j is on the root path of i.
   // The parent pointers are staged in LDS and the paths are walked there, a bit at a time straight into the row: a
@@ -519,10 +486,30 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
 #pragma unroll
     for (int q = 0; q < 8; ++q) anc[tid * MF_ANC_STRIDE + q] = 0u;
   }
-  if constexpr (!BIG) {
-    wait_vm(NK + first_tile_loads);  // the parent pointers are there (the Q loads and the tiles are younger)
-    asm volatile("" : "+v"(my_parent));
-    if constexpr (RIDE) asm volatile("" : "+v"(ride_raw));  // (older than the parent pointers)
+  wait_vm(NK + first_tile_loads);  // the parent pointers are there (the Q loads and the tiles are younger)
+  asm volatile("" : "+v"(my_parent), "+v"(far_parent));
+  if constexpr (RIDE) asm volatile("" : "+v"(ride_raw));  // (older than the parent pointers)
+  const int blk_node = div_G(row_base < Rh ? row_base : Rh - 1);  // first tree row of the block
+  if (BIG && last_split) {
+    // A lane walks one tree row's path.  (Two waves that share a block write the same bits: they are cleared before the
+    // barrier and only set behind it.)
+    unsigned* const area = &anc[anc_at.base];
+    const int last = row_base + 31 < Rh ? row_base + 31 : Rh - 1;
+    const int nodes = wave_active ? div_G(last) - blk_node + 1 : 0;
+    for (int i = lane; i < nodes * anc_at.stride; i += 64) area[i] = 0u;
+    par_lds[tid] = my_parent;
+    par_lds[tid + MF_THREADS] = far_parent;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (lane < nodes) {
+      unsigned* const row = area + lane * anc_at.stride;
+      const int i = blk_node + lane;
+      atomicOr(row + (i >> 5), 1u << (i & 31));
+      for (int j = i, up = par_lds[i]; up >= 0 && up < j;) {  // (a malformed tree cannot keep the walk from ending)
+        j = up;
+        up = par_lds[j];
+        atomicOr(row + (j >> 5), 1u << (j & 31));
+      }
+    }
   }
   if (!BIG && last_split) {
     if (tid < M) par_lds[tid] = my_parent;
@@ -637,7 +624,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     if (t >= n_ptiles) {
       const int bbase = (t - n_ptiles) * MF_TILE + (blk & 1) * 32;
       unsigned word;
-      if constexpr (BIG) word = bbase < M ? anc[(t % MF_NBUF) * MF_ANC_SLICE + (wave * 32 + col) * 2 + (blk & 1)] : 0u;
+      if constexpr (BIG) word = (bbase >> 5) < anc_at.stride ? anc[anc_at.base + (tree_row() - blk_node) * anc_at.stride + (bbase >> 5)] : 0u;
       else word = bbase < M ? anc[tree_row() * MF_ANC_STRIDE + (bbase >> 5)] : 0u;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -1341,13 +1328,6 @@ hs_status attn_mfma_launch(const AttnArgs& a, int max_tree_rows, hipStream_t str
   const bool once = n_rg_max == 1 && a.narrow == 0;  // every (sequence, head) is one row group: its keys have one reader
   const bool big = max_tree_rows > MF_MAX_M;
   const dim3 block(MF_THREADS);
-  if (big) {
-    if (a.anc_tiles == nullptr) return fail(HS_ERR_WORKSPACE, "tree attention: trees of %d rows need the ancestor table", max_tree_rows);
-    const dim3 tgrid((unsigned)((max_tree_rows + 255) / 256), (unsigned)(a.tree_shared ? 1 : a.B));
-    hipLaunchKernelGGL(k_anc_tiles, tgrid, dim3(256), 0, stream, a.parent, a.node_offsets, const_cast<unsigned*>(a.anc_tiles));
-    hs_status r = launch_status("tree attention (ancestor table)");
-    if (r != HS_OK) return r;
-  }
   const bool share = a.share != 0 || a.narrow == 2;
 #define MF_LAUNCH_AS(PAGED, ONCE, BIG, HALF, SHARE, RIDE) \
   hipExtLaunchKernelGGL((k_attn_mfma<PAGED, ONCE, BIG, HALF, SHARE, RIDE>), grid, block, 0, stream, ev_start, ev_stop, 0, a, n_rg_max)

@@ -213,9 +213,8 @@ def test_events_attached_to_the_attention_kernel(G):
 @pytest.mark.parametrize("hq,hkv", [(8, 2), (4, 4), (16, 2)])
 @pytest.mark.parametrize("M,L", [(256, 200), (257, 100), (1024, 70), (513, 0), (700, 1300)])
 def test_tree_row_limits(G, M, L, hq, hkv):
-    """Trees of up to 256 rows have their ancestor table built inside the attention kernel; larger ones
-    (up to the limit of 1024 rows) take it from a table laid out per key tile by a launch of its own.
-    Both run on the matrix cores.  G = 4, 1 and 8 query heads per KV head: up to 32 row groups; L = 0:
+    """Trees of up to 256 rows have their whole ancestor table in each workgroup, of larger ones (up to the
+    limit of 1024 rows) a workgroup has the rows of its own blocks.  Both run on the matrix cores.  G = 4, 1 and 8 query heads per KV head: up to 32 row groups; L = 0:
     the leading tiles are tree tiles."""
     import paper_2505_13254_amd as hs
     w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv)
@@ -235,6 +234,21 @@ def test_large_trees_of_extreme_shape(G, shape):
     w = W.small(W.WORKLOADS[2], Hq=8, Hkv=2)
     _compare(G, _case(w, 15, [par], [130], "peaky"), "bf16")
     assert hs.hs_tree_attention_last_kernel() == 1
+
+
+@pytest.mark.parametrize("heads", [4, 48])
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("M", [928, 929, 1023])
+def test_ancestor_tables_of_the_largest_trees(G, M, D, heads):
+    """One query head to a KV head: a block of 32 rows has 32 tree rows, and beyond 928 of them the blocks' tables no longer have
+    rows of one length.  Long chains set bits in every word; four heads leave two workgroups or four to a row
+    group, so that waves share blocks, 48 none."""
+    import paper_2505_13254_amd as hs
+    w = W.small(W.WORKLOADS[2], Hq=heads, Hkv=heads, D=D)
+    rs = np.random.RandomState(M)
+    _compare(G, _case(w, 17, [_random_parents(rs, M, back=3)], [70], "unit"), "bf16")
+    assert hs.hs_tree_attention_last_kernel() == 1
+    assert hs.lib().hs_tree_attention_last_form() & 7 == (1 if heads == 48 else 2 if D == 128 else 4)
 
 
 @pytest.mark.parametrize("seed", [3, 4])
