@@ -216,9 +216,8 @@ hs_status hs_tree_prune_static(const int32_t* parent, const float* logc, const i
  *   lse [NN,Hq] float: ln of the softmax denominator (of the scaled scores); may be NULL.
  * Requires Hq % Hkv == 0, D in {64, 128}, at most 1024 tree rows per sequence.
  * bfloat16 runs on the matrix cores (D = 64: with an even number of KV heads, which the kernel takes in
- * pairs); when a sequence has more than 256 tree rows, a
- * small launch ahead of the attention kernel writes the trees' ancestor table into the workspace
- * (128 bytes per tree row, included in the workspace query).
+ * pairs); calls with a sequence of more than 256 tree rows ask for 128 bytes of workspace per tree row
+ * besides (included in the workspace query).
  * Workspace: one partial record of D + 4 floats per (tree row, query head, key split); the query
  * returns the bound for min(64, total_prefix / 128 + 1) splits, more than any plan of that batch
  * uses (a batch whose keys are not cut needs none; hs_tree_attention_plan tells what a given batch needs).  The host keeps the last few plans per calling thread (a model's layers share theirs); the

@@ -164,7 +164,7 @@ def test_stochastic_accept_at_full_vocabulary(H, wid, mode):
 ])
 def test_large_trees_and_head_dimension_64_at_full_head_count(G, name, D, sizes, Ls, variant):
     """32 query heads on 8 KV heads as in the 8B workload, with what the matrix-core kernel takes beyond that
-    workload's own shape: trees past 256 rows (the ancestor table comes from its own launch) and head
+    workload's own shape: trees past 256 rows (a workgroup's ancestor table is of its own rows) and head
     dimension 64 (KV heads in pairs).  The launch covers all heads; two KV heads' query heads are compared
     with the checker, which gets those heads alone."""
     import paper_2505_13254_amd as hs

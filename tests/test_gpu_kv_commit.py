@@ -72,6 +72,38 @@ def test_commit_matches_the_checker(G, wid):
     assert int(want_l[4]) == caps[4] and int(want_l[3]) == 3
 
 
+@pytest.mark.parametrize("page_tokens", [0, 3, 64])
+@pytest.mark.parametrize("hkv,D,depth", [(1, 4, 1022), (1, 4, 1300), (8, 128, 3), (8, 128, 4), (40, 128, 2), (3, 20, 80)])
+def test_commits_around_the_size_of_a_workgroup(G, hkv, D, depth, page_tokens):
+    """Chains of which every row is accepted, in less, as many and more pieces of 16 bytes than a workgroup moves at a time,
+    rows of more pieces than that among them; behind them a sequence whose root alone is committed."""
+    import paper_2505_13254_amd as hs
+    from oracle.kv_commit import kv_commit_paged
+    rs = np.random.RandomState(depth)
+    M, used = depth + 1, 5
+    kt, vt = (rs.randn(M + 2, hkv, D).astype(np.float32) for _ in range(2))
+    no, alen, lens = np.asarray([0, M, M + 2], np.int32), np.asarray([depth, 0], np.int32), np.asarray([used, 2], np.int64)
+    path = np.full((2, depth), -1, np.int32)
+    path[0] = np.arange(1, M)
+    if page_tokens:
+        blocks = (used + M) // page_tokens + 1
+        table = rs.permutation(2 * blocks).astype(np.int32).reshape(2, blocks)
+        kc, vc = (rs.randn(2 * blocks, page_tokens, hkv, D).astype(np.float32) for _ in range(2))
+        want = kv_commit_paged(kt, vt, no, path, alen, kc, vc, table, lens)
+    else:
+        co = np.asarray([0, used + M, used + M + 4], np.int64)
+        kc, vc = (rs.randn(int(co[2]), hkv, D).astype(np.float32) for _ in range(2))
+        want = kv_commit(kt, vt, no, path, alen, kc, vc, co, lens)
+    dk, dv, dl = G.dev(kc), G.dev(vc), G.dev(lens)
+    args = [G.dev(kt), G.dev(vt), G.dev(no), G.dev(path), G.dev(alen), dk, dv]
+    if page_tokens:
+        hs.hs_kv_commit_paged(*args, G.dev(table), dl)
+    else:
+        hs.hs_kv_commit(*args, G.dev(co), dl)
+    for got, exp in zip((dk, dv, dl), want):
+        assert np.array_equal(_bits(got), exp)
+
+
 @pytest.mark.parametrize("wid,B", [(1, 3), (2, 4), (5, 100)])
 def test_decoding_loop_on_caches_with_spare_capacity(G, wid, B):
     """Three verify / commit rounds: attention over the used part of each cache region, a random
@@ -286,8 +318,7 @@ def test_paged_attention_with_several_row_groups(G, D, sizes):
     """Trees of more than 64 rows on the 8B shape (4 query heads per KV head: more than 256 rows per
     KV head, i.e. several row groups that read the same pages), next to small trees, over paged caches
     with a shuffled page order; one sequence long enough to be cut into key splits.  Also with head
-    dimension 64 (KV heads taken in pairs by the matrix-core kernel) and with trees past 256 rows (ancestor
-    table from its own launch)."""
+    dimension 64 (KV heads taken in pairs by the matrix-core kernel) and with trees past 256 rows."""
     import paper_2505_13254_amd as hs
     from oracle.kv_commit import gather_pages
     w = W.small(W.WORKLOADS[2], B=3, D=D)
