@@ -312,15 +312,6 @@ __device__ __forceinline__ int place_of_four(const MergeScratch<CAP>& sm, unsign
   return place;
 }
 
-// Loads and stores that are coherent across the chip's XCDs (each has an L2 of its own): relaxed
-// atomics of device scope, which go past a stale or private cache line.  What workgroups of one
-// launch use to hand their slices' results to each other: a fence that reaches the other XCDs
-// would write back and invalidate a whole L2, and cost the scan several times its own duration.
-__device__ __forceinline__ float ld_dev(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ unsigned long long ld_dev(const unsigned long long* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void st_dev(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void st_dev(unsigned long long* p, unsigned long long v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
 // Merges S <= 64 slices of a row: statistics st[s] (m, s1, t) and sorted K-lists pk[s * K + k] of keys.
 // COHERENT: the slices were written by other workgroups of the same launch (ld_dev).
 // Leaves the row's statistics in sm.total and its K best pairs, in order, in sm.best.

@@ -150,4 +150,13 @@ __device__ __forceinline__ float wave_sum(float x) {
   return wave_reduce_dpp(x, 0.f, [](float a, float b) { return a + b; });
 }
 
+// Loads and stores that are coherent across the chip's XCDs (each has an L2 of its own): relaxed
+// atomics of device scope, which go past a stale or private cache line.  What workgroups of one
+// launch use to hand their slices' results to each other: a fence that reaches the other XCDs
+// would write back and invalidate a whole L2, and cost the scan several times its own duration.
+__device__ __forceinline__ float ld_dev(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ unsigned long long ld_dev(const unsigned long long* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_dev(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_dev(unsigned long long* p, unsigned long long v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 }  // namespace hs

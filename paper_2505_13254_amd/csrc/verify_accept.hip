@@ -19,7 +19,7 @@
 //               suffix sums plus, from the second rejection on, the tokens of one bucket.  One
 //               workgroup per node with children runs that node's chain, all nodes in parallel (k_accept_chain), and
 //               leaves the accepted child; the walk is a chase through them, made by every workgroup of the kernel that
-//               sums the row where it ends (k_bonus_rows); k_accept_walk draws the bonus token there: an inverse-CDF search
+//               sums the row where it ends and draws the bonus token there (k_bonus_rows): an inverse-CDF search
 //               done as row sums of 64 tokens, a scan of the row sums, and a scan inside the one row that is hit.
 #include <limits.h>
 
@@ -37,6 +37,7 @@ constexpr int AC_MAX_KIDS = 256;    // children tried per node
 constexpr int AC_MAX_ROWS = 8192;   // 64-token rows of the CDF search held in LDS (V <= 524288)
 constexpr int BR_SLICES = 64, BR_WGS = 1024;  // workgroups per sequence, and in all, that sum the row a bonus token is drawn from
 constexpr int BR_THREADS = 512;
+constexpr int BR_FEW_ROWS = 2048;    // 64-token rows that most vocabularies have (V <= 131072)
 constexpr int BK_NODES = 4096;      // calls with up to this many tree rows get the sorted residual (below)
 constexpr int BK_SLICES = 16;       // vocabulary slices per row, each sorted by itself
 constexpr int BK_N = 256;           // buckets of the ratio p / q: BK_PER_OCTAVE per factor of two, from 1 upwards
@@ -425,13 +426,14 @@ __device__ __forceinline__ double token_weight(const RowView& p, const RowView& 
 // Children of local row `cur` of a sequence of n rows, ascending, into kids_sorted; returns their
 // number (at most AC_MAX_KIDS: of a node with more children the AC_MAX_KIDS lowest rows are taken,
 // whatever order the threads arrive in).  Called by all threads; ends with a barrier.
+template <int THREADS>
 __device__ __forceinline__ int gather_children(const int* parent, int o, int n, int cur, bool any,
                                                int* kids, int* kids_sorted, int* n_kids) {
   const int tid = threadIdx.x;
   if (tid == 0) *n_kids = 0;
   __syncthreads();
   if (any)
-    for (int i = 1 + tid; i < n; i += AC_THREADS)
+    for (int i = 1 + tid; i < n; i += THREADS)
       if (parent[o + i] == cur) {
         int pos = atomicAdd(n_kids, 1);
         if (pos < AC_MAX_KIDS) kids[pos] = i;
@@ -441,7 +443,7 @@ __device__ __forceinline__ int gather_children(const int* parent, int o, int n, 
     // more children than the lists hold (never with Top-k expansion): which of them the atomic
     // counter let in depends on arrival order, so the lists are made again by rank, each child
     // counting the children before it; the first AC_MAX_KIDS stay
-    for (int i = 1 + tid; i < n; i += AC_THREADS)
+    for (int i = 1 + tid; i < n; i += THREADS)
       if (parent[o + i] == cur) {
         int r = 0;
         for (int j = 1; j < i && r < AC_MAX_KIDS; ++j) r += parent[o + j] == cur ? 1 : 0;
@@ -463,15 +465,15 @@ __device__ __forceinline__ int gather_children(const int* parent, int o, int n, 
 // What the tree says about each row (k_tree_rows), and what the walk needs from a node's chain of rejections.
 struct ChainOut {
   int32_t* n_tried;      // [NN] number of children the node's chain tries (0: the node's residual is p itself)
-  int32_t* first;        // [NN] the first of them; at a sequence's first row, behind the chains: where its walk ends
-  int32_t* kid_tok;      // [NN] its token; at a sequence's first row, behind the chains: the length of its path
+  int32_t* first;        // [NN] the first of them
+  int32_t* kid_tok;      // [NN] its token
   float* kid_u;          // [NN] its uniform
   int32_t* accepted;     // [NN] the child that the chain ends with (a local row), -1: none is accepted
   double* child_frozen;  // [NN] where none is: the child's weight in the residual after its own rejection
   double* node_beta;     // [NN] and beta and normaliser after all of the node's children were rejected
   double* node_Z;
   double* bonus_rows;    // [NN][ceil(V / 64)] row sums of the distribution that the bonus token is drawn from, of the
-                         // row where a sequence's walk ends (NULL: the walk makes them itself)
+                         // row where a sequence's walk ends (NULL: k_accept_walk makes them itself)
 };
 
 // The test of a child under the ratio rule: current target and draft probability of its token.
@@ -823,10 +825,16 @@ __global__ __launch_bounds__(GR_THREADS) void k_tree_rows(const int32_t* __restr
 // wave four rows per trip; the loads of four trips are requested together (lanes past the last row
 // re-read it), and a row's 16 partial sums meet in its last lane by DPP moves.  Rows that are not
 // whole are summed a token per lane.  A row's sum
-// does not depend on who computes it: the walk and k_bonus_rows give the same bits.
+// does not depend on who computes it: the walk and k_bonus_rows give the same bits.  SHARED: another workgroup of the launch
+// reads them.
+template <bool SHARED>
 __device__ __forceinline__ void bonus_row_sums(const RowView& p, const RowView& q, bool sub_q, double beta, int V,
                                                int r_begin, int r_end, double* __restrict__ dst) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
+  auto put = [&](int r, double w) {
+    if (SHARED) st_dev(reinterpret_cast<unsigned long long*>(dst) + r, __builtin_bit_cast(unsigned long long, w));
+    else dst[r] = w;
+  };
   int first_row = r_begin;  // rows below it were summed with 16-byte loads
   if (V >= 64) {
     constexpr int TRIPS = 4;
@@ -854,7 +862,7 @@ __device__ __forceinline__ void bonus_row_sums(const RowView& p, const RowView& 
           w = ((double)pp.x + (double)pp.y) + ((double)pp.z + (double)pp.w);
         }
         w = row16_sum(w);
-        if (l16 == 15 && r < full_end) dst[r] = w;
+        if (l16 == 15 && r < full_end) put(r, w);
       }
     }
     first_row = max(full_end, r_begin);
@@ -863,7 +871,7 @@ __device__ __forceinline__ void bonus_row_sums(const RowView& p, const RowView& 
     const int v = r * 64 + lane;
     double w = v < V ? token_weight(p, q, sub_q, beta, v) : 0.0;
     w = wave_sum(w);
-    if (lane == 0) dst[r] = w;
+    if (lane == 0) put(r, w);
   }
 }
 
@@ -916,7 +924,7 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
   // below is serial, and a round trip to memory per step would dominate it.
   BucketLoads loads;
   if (sorted) request_bucket_tables(bk, g, loads);
-  gather_children(parent, o, n, cur, true, kids, kids_sorted, &n_kids);
+  gather_children<AC_THREADS>(parent, o, n, cur, true, kids, kids_sorted, &n_kids);
   float xp = 0.f, xq = 0.f;
   if (tid < nk) {
     const int c = o + kids_sorted[tid];
@@ -1036,32 +1044,142 @@ __device__ __forceinline__ int chase(const int32_t* __restrict__ accepted, int o
   return cur;
 }
 
+// Draws a sequence's bonus token: the first one at which the running sum of the weights passes `goal`.  rowsum: the weights'
+// sums over rows of 64 tokens, all tokens taken as live (LDS); rej_tok, rej_w: the n_rej rejected tokens and their frozen weights.  Called
+// by all threads, after a barrier.
+template <int THREADS>
+__device__ __forceinline__ void draw_bonus(const RowView& p, const RowView& q, bool sub_q, double beta, double goal, int V, int n_rej,
+                                           const int* rej_tok, const double* rej_w, double* rowsum, int s, int len,
+                                           int32_t* __restrict__ accept_len, int32_t* __restrict__ bonus_token) {
+  __shared__ double rej_fix[AC_MAX_KIDS];         // what a rejected token's frozen weight changes in its row sum
+  __shared__ double chunk_tot[AC_MAX_ROWS / 64];  // sums of 64 rows
+  __shared__ int chunk_last[AC_MAX_ROWS / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_rows = (V + 63) / 64;
+  // (every rejected token's correction by a thread of its own: one trip to memory for all of them)
+  if (tid < n_rej) rej_fix[tid] = rej_w[tid] - token_weight(p, q, sub_q, beta, rej_tok[tid]);
+  __syncthreads();
+  if (tid == 0)
+    for (int i = 0; i < n_rej; ++i) rowsum[rej_tok[i] >> 6] += rej_fix[i];
+  __syncthreads();
+  // two levels: the waves sum chunks of 64 rows side by side, one wave then looks for the
+  // chunk, the row inside it and the token inside the row
+  const int n_chunks = (n_rows + 63) >> 6;
+  for (int c = wave; c < n_chunks; c += THREADS / 64) {
+    const int r = c * 64 + lane;
+    const double val = r < n_rows ? rowsum[r] : 0.0;
+    const double tot = wave_sum_dpp(val);
+    const unsigned long long pos = __ballot(r < n_rows && val > 0.0);
+    if (lane == 0) {
+      chunk_tot[c] = tot;
+      chunk_last[c] = pos != 0ull ? c * 64 + 63 - __clzll((long long)pos) : -1;  // its last row with mass
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    double carry = 0.0, chunk_excl = 0.0;
+    int chunk = -1, last_pos = -1;
+    for (int cb = 0; cb < n_chunks && chunk < 0; cb += 64) {
+      const int c = cb + lane;
+      const double val = c < n_chunks ? chunk_tot[c] : 0.0;
+      const int lp = c < n_chunks ? chunk_last[c] : -1;
+      const double incl = wave_incl_scan(val, lane) + carry;
+      const unsigned long long hit = __ballot(c < n_chunks && incl > goal);
+      if (hit != 0ull) {
+        const int l = __ffsll((long long)hit) - 1;
+        chunk = cb + l;
+        chunk_excl = __shfl(incl - val, l);
+      } else {
+        const unsigned long long pos = __ballot(lp >= 0);
+        if (pos != 0ull) last_pos = __shfl(lp, 63 - __clzll((long long)pos));
+        carry = __shfl(incl, 63);
+      }
+    }
+    int row = -1;
+    double excl = 0.0;
+    if (chunk >= 0) {
+      const int r = chunk * 64 + lane;
+      const double val = r < n_rows ? rowsum[r] : 0.0;
+      const double incl = wave_incl_scan(val, lane) + chunk_excl;
+      const unsigned long long hit = __ballot(r < n_rows && incl > goal);
+      if (hit != 0ull) {
+        const int l = __ffsll((long long)hit) - 1;
+        row = chunk * 64 + l;
+        excl = __shfl(incl - val, l);
+      } else {
+        last_pos = chunk_last[chunk];  // (the two orders of summation differ by a rounding: the chunk's last row with mass)
+      }
+    }
+    double row_goal = goal - excl;
+    if (row < 0) {  // rounding left the goal at or above the total: take the last token with mass
+      row = last_pos < 0 ? 0 : last_pos;
+      row_goal = HS_INF;
+    }
+    const int v = row * 64 + lane;
+    double w = v < V ? token_weight(p, q, sub_q, beta, v) : 0.0;
+    for (int i = 0; i < n_rej; ++i)
+      if (rej_tok[i] == v) w = rej_w[i];
+    const double incl = wave_incl_scan(w, lane);
+    const unsigned long long hit = __ballot(incl > row_goal);
+    const unsigned long long pos = __ballot(w > 0.0);
+    int l;
+    if (hit != 0ull)
+      l = __ffsll((long long)hit) - 1;
+    else
+      l = pos != 0ull ? 63 - __clzll((long long)pos) : 0;
+    if (lane == 0) {
+      accept_len[s] = len;
+      int tok = row * 64 + l;
+      bonus_token[s] = tok < V ? tok : V - 1;
+    }
+  }
+}
+
 // grid (B, slices), after the chains: every workgroup finds where its sequence's walk ends and sums its slice of that
-// row, so that the draw of the bonus token need not sum a row of the vocabulary on its one compute unit (15 us).  The
+// row; one compute unit alone would take 15 us for a row of the vocabulary.  The
 // distribution is max(p - beta q, 0) with the chain's final beta where all children were rejected, p itself where none is
-// tried; the rejected tokens' frozen weights are the draw's corrections.  The first slice's workgroup writes the path and
-// leaves for k_accept_walk where it ends.
+// tried; the rejected tokens' frozen weights are the draw's corrections.  The first slice's workgroup writes the path, and the one that
+// draws the last ticket of its sequence (a counter of the scan's, zero before and cleared by each call's k_tree_rows) draws the bonus token.
+// ROWS: rows of 64 tokens that LDS has room for.  (The draw by a launch of its own: 4.9 and 6.1 us for 61 rows
+// of 128256 tokens, 9.1 in one now; the whole step 151.1 us, now 149.1, on 32000 tokens 133.7 and 131.0.)
+template <int ROWS>
 __global__ __launch_bounds__(BR_THREADS) void k_bonus_rows(const float* __restrict__ target,
-                                                           const float* __restrict__ draft, int64_t row_stride, int V,
-                                                           float inv_t, const int32_t* __restrict__ node_offsets, int max_depth,
-                                                           const int32_t* __restrict__ t_arg,
+                                                           const float* __restrict__ draft, int64_t row_stride,
+                                                           const int32_t* __restrict__ token,
+                                                           const int32_t* __restrict__ parent,
+                                                           const int32_t* __restrict__ node_offsets, int NN, int V,
+                                                           float inv_t, const float* __restrict__ uniforms, int max_depth,
+                                                           int slices, const int32_t* __restrict__ t_arg,
                                                            const float* __restrict__ t_lz,
                                                            const int32_t* __restrict__ d_arg,
                                                            const float* __restrict__ d_lz, ChainOut chain,
-                                                           int32_t* __restrict__ accept_path) {
+                                                           unsigned* __restrict__ tickets, int32_t* __restrict__ accept_len,
+                                                           int32_t* __restrict__ accept_path, int32_t* __restrict__ bonus_token) {
+  __shared__ double rowsum[ROWS];
   __shared__ int l_acc[GR_LDS_ROWS];
-  const int s = blockIdx.x, slice = blockIdx.y;
+  __shared__ int kids[AC_MAX_KIDS];
+  __shared__ int kids_sorted[AC_MAX_KIDS];
+  __shared__ int n_kids, is_last;
+  __shared__ int rej_tok[AC_MAX_KIDS];
+  __shared__ double rej_w[AC_MAX_KIDS];
+  const int s = blockIdx.x, slice = blockIdx.y, tid = threadIdx.x;
   const int o = node_offsets[s];
   const int n = node_offsets[s + 1] - o;
-  if (n <= 0) return;
-  int len;
-  const int cur = chase(chain.accepted, o, n, max_depth, l_acc, &len, slice == 0 ? accept_path + (int64_t)s * max_depth : nullptr);
-  if (slice == 0 && threadIdx.x == 0) {
-    chain.first[o] = cur;
-    chain.kid_tok[o] = len;
+  int32_t* const path = accept_path + (int64_t)s * max_depth;
+  if (n <= 0) {
+    if (slice == 0) {
+      for (int d = tid; d < max_depth; d += BR_THREADS) path[d] = -1;
+      if (tid == 0) {
+        accept_len[s] = 0;
+        bonus_token[s] = -1;
+      }
+    }
+    return;
   }
+  int len;
+  const int cur = chase(chain.accepted, o, n, max_depth, l_acc, &len, slice == 0 ? path : nullptr);
   const int n_rows = (V + 63) / 64;
-  const int per = (n_rows + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int per = (n_rows + slices - 1) / slices;
   const int r_begin = slice * per, r_end = min(n_rows, r_begin + per);
   if (r_begin >= r_end) return;
   const int g = o + cur;
@@ -1069,15 +1187,42 @@ __global__ __launch_bounds__(BR_THREADS) void k_bonus_rows(const float* __restri
   const float* p_row = target + (int64_t)g * row_stride;
   const RowView p(p_row, p_row[t_arg[g]], t_lz[g], inv_t);
   RowView q = p;
-  double beta = 0.0;
+  double beta = 0.0, Z = 1.0;
   if (sub_q) {
     const float* q_row = draft + (int64_t)g * row_stride;
     q = RowView(q_row, q_row[d_arg[g]], d_lz[g], inv_t);
     beta = chain.node_beta[g];
+    Z = chain.node_Z[g];
   }
-  bonus_row_sums(p, q, sub_q, beta, V, r_begin, r_end, chain.bonus_rows + (int64_t)g * n_rows);
+  double* const sums = chain.bonus_rows + (int64_t)g * n_rows;
+  bonus_row_sums<true>(p, q, sub_q, beta, V, r_begin, r_end, sums);
+  // (what the draw needs besides is looked up while the sums are on their way)
+  const double goal = (double)uniforms[NN + s] * Z;
+  const int n_rej = gather_children<BR_THREADS>(parent, o, n, cur, len < max_depth, kids, kids_sorted, &n_kids);
+  if (tid < n_rej) {
+    const int c = o + kids_sorted[tid];
+    rej_tok[tid] = token[c];
+    rej_w[tid] = chain.child_frozen[c];
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0)
+    is_last = __hip_atomic_fetch_add(&tickets[o], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)((n_rows + per - 1) / per - 1) ? 1 : 0;
+  __syncthreads();
+  if (!is_last) return;
+  constexpr int PER = 4;  // sums of a thread that are requested together
+  for (int r0 = tid; r0 < n_rows; r0 += PER * BR_THREADS) {
+    unsigned long long v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) v[k] = ld_dev(reinterpret_cast<const unsigned long long*>(sums) + min(r0 + k * BR_THREADS, n_rows - 1));
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (r0 + k * BR_THREADS < n_rows) rowsum[r0 + k * BR_THREADS] = __builtin_bit_cast(double, v[k]);
+  }
+  draw_bonus<BR_THREADS>(p, q, sub_q && n_rej > 0, beta, goal, V, n_rej, rej_tok, rej_w, rowsum, s, len, accept_len, bonus_token);
 }
 
+// The walk of the point-mass rule, and the end of the ratio rule's for trees beyond BK_NODES rows.
 __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
     const float* __restrict__ target, const float* __restrict__ draft, int64_t row_stride,
     const int32_t* __restrict__ token, const int32_t* __restrict__ parent, const int32_t* __restrict__ node_offsets,
@@ -1095,12 +1240,9 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
   __shared__ double rej_w[AC_MAX_KIDS];  // frozen weight of each rejected token
   __shared__ float kid_u[AC_MAX_KIDS];    // the child's uniform
   __shared__ double kid_p[AC_MAX_KIDS];   // its p(x)
-  __shared__ double rej_fix[AC_MAX_KIDS];  // bonus draw: what a rejected token's frozen weight changes in its row sum
   __shared__ double rowsum[AC_MAX_ROWS];
-  __shared__ double chunk_tot[AC_MAX_ROWS / 64];  // sums of 64 rows
-  __shared__ int chunk_last[AC_MAX_ROWS / 64];
 
-  const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int s = blockIdx.x, tid = threadIdx.x;
   const int o = node_offsets[s];
   const int n = node_offsets[s + 1] - o;
   int32_t* path = accept_path + (int64_t)s * max_depth;
@@ -1114,28 +1256,16 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
     }
     return;
   }
-  // Under the ratio rule the chains have left every node's accepted child, so the walk is a chase through them, made ahead of
-  // this kernel, and the node where it ends is looked at here, its row sums requested before its children are.
+  // Under the ratio rule the chains have left every node's accepted child: the walk is a chase through them.
   // (Level by level, each a few trips to memory, 12.6 us for a 61-row tree and 22 for 97 rows.)
   int cur = 0, len = 0;
-  constexpr int PRE = AC_MAX_ROWS / AC_THREADS;
-  double pre[PRE];
   const int n_rows = (V + 63) / 64;
   if (ratio_mode) {
-    if (chain.bonus_rows != nullptr) {
-      cur = chain.first[o];
-      len = chain.kid_tok[o];
-      const double* __restrict__ sums = chain.bonus_rows + (int64_t)(o + cur) * n_rows;
-#pragma unroll
-      for (int k = 0; k < PRE; ++k)
-        if (k * AC_THREADS < n_rows) pre[k] = sums[min(tid + k * AC_THREADS, n_rows - 1)];
-    } else {
-      __shared__ int l_acc[GR_LDS_ROWS];
-      cur = chase(chain.accepted, o, n, max_depth, l_acc, &len, path);
-    }
+    __shared__ int l_acc[GR_LDS_ROWS];
+    cur = chase(chain.accepted, o, n, max_depth, l_acc, &len, path);
   }
   for (;;) {
-    const int nk = gather_children(parent, o, n, cur, len < max_depth, kids, kids_sorted, &n_kids);
+    const int nk = gather_children<AC_THREADS>(parent, o, n, cur, len < max_depth, kids, kids_sorted, &n_kids);
 
     const float* p_row = target + (int64_t)(o + cur) * row_stride;
     const RowView p(p_row, p_row[t_arg[o + cur]], t_lz[o + cur], inv_t);
@@ -1192,90 +1322,8 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_walk(
     const bool sub_q = use_q && n_rej > 0;
     const double total = ratio_mode ? Z : rem;
     const double goal = (double)uniforms[NN + s] * total;
-    if (chain.bonus_rows != nullptr) {  // summed ahead of the walk (k_bonus_rows)
-#pragma unroll
-      for (int k = 0; k < PRE; ++k)
-        if (tid + k * AC_THREADS < n_rows) rowsum[tid + k * AC_THREADS] = pre[k];
-    } else {
-      bonus_row_sums(p, q, sub_q, beta, V, 0, n_rows, rowsum);
-    }
-    // (every rejected token's correction by a thread of its own: one trip to memory for all of them)
-    if (tid < n_rej) rej_fix[tid] = rej_w[tid] - token_weight(p, q, sub_q, beta, rej_tok[tid]);
-    __syncthreads();
-    if (tid == 0)
-      for (int i = 0; i < n_rej; ++i) rowsum[rej_tok[i] >> 6] += rej_fix[i];
-    __syncthreads();
-    // two levels: the sixteen waves sum chunks of 64 rows side by side, one wave then looks for the
-    // chunk, the row inside it and the token inside the row
-    const int n_chunks = (n_rows + 63) >> 6;
-    for (int c = wave; c < n_chunks; c += AC_WAVES) {
-      const int r = c * 64 + lane;
-      const double val = r < n_rows ? rowsum[r] : 0.0;
-      const double tot = wave_sum_dpp(val);
-      const unsigned long long pos = __ballot(r < n_rows && val > 0.0);
-      if (lane == 0) {
-        chunk_tot[c] = tot;
-        chunk_last[c] = pos != 0ull ? c * 64 + 63 - __clzll((long long)pos) : -1;  // its last row with mass
-      }
-    }
-    __syncthreads();
-    if (wave == 0) {
-      double carry = 0.0, chunk_excl = 0.0;
-      int chunk = -1, last_pos = -1;
-      for (int cb = 0; cb < n_chunks && chunk < 0; cb += 64) {
-        const int c = cb + lane;
-        const double val = c < n_chunks ? chunk_tot[c] : 0.0;
-        const int lp = c < n_chunks ? chunk_last[c] : -1;
-        const double incl = wave_incl_scan(val, lane) + carry;
-        const unsigned long long hit = __ballot(c < n_chunks && incl > goal);
-        if (hit != 0ull) {
-          const int l = __ffsll((long long)hit) - 1;
-          chunk = cb + l;
-          chunk_excl = __shfl(incl - val, l);
-        } else {
-          const unsigned long long pos = __ballot(lp >= 0);
-          if (pos != 0ull) last_pos = __shfl(lp, 63 - __clzll((long long)pos));
-          carry = __shfl(incl, 63);
-        }
-      }
-      int row = -1;
-      double excl = 0.0;
-      if (chunk >= 0) {
-        const int r = chunk * 64 + lane;
-        const double val = r < n_rows ? rowsum[r] : 0.0;
-        const double incl = wave_incl_scan(val, lane) + chunk_excl;
-        const unsigned long long hit = __ballot(r < n_rows && incl > goal);
-        if (hit != 0ull) {
-          const int l = __ffsll((long long)hit) - 1;
-          row = chunk * 64 + l;
-          excl = __shfl(incl - val, l);
-        } else {
-          last_pos = chunk_last[chunk];  // (the two orders of summation differ by a rounding: the chunk's last row with mass)
-        }
-      }
-      double row_goal = goal - excl;
-      if (row < 0) {  // rounding left the goal at or above the total: take the last token with mass
-        row = last_pos < 0 ? 0 : last_pos;
-        row_goal = HS_INF;
-      }
-      const int v = row * 64 + lane;
-      double w = v < V ? token_weight(p, q, sub_q, beta, v) : 0.0;
-      for (int i = 0; i < n_rej; ++i)
-        if (rej_tok[i] == v) w = rej_w[i];
-      const double incl = wave_incl_scan(w, lane);
-      const unsigned long long hit = __ballot(incl > row_goal);
-      const unsigned long long pos = __ballot(w > 0.0);
-      int l;
-      if (hit != 0ull)
-        l = __ffsll((long long)hit) - 1;
-      else
-        l = pos != 0ull ? 63 - __clzll((long long)pos) : 0;
-      if (lane == 0) {
-        accept_len[s] = len;
-        int tok = row * 64 + l;
-        bonus_token[s] = tok < V ? tok : V - 1;
-      }
-    }
+    bonus_row_sums<false>(p, q, sub_q, beta, V, 0, n_rows, rowsum);
+    draw_bonus<AC_THREADS>(p, q, sub_q, beta, goal, V, n_rej, rej_tok, rej_w, rowsum, s, len, accept_len, bonus_token);
     return;
   }
 }
@@ -1294,7 +1342,7 @@ static size_t bucket_workspace(int NN, int V, Carver* c, BucketWs* ws) {
   return align_up(n_st * 4, 256) + 2 * align_up(n_sb * 8, 256) + align_up((size_t)NN * V * sizeof(float2), 256);
 }
 
-// Bytes of the row sums k_bonus_rows leaves for the walk (0 beyond BK_NODES rows: the walk then sums
+// Bytes of the row sums of k_bonus_rows (0 beyond BK_NODES rows: the walk then sums
 // the rows of its stop node itself).
 static size_t bonus_rows_bytes(int NN, int V) {
   return NN <= BK_NODES ? align_up((size_t)NN * ((V + 63) / 64) * sizeof(double), 256) : 0;
@@ -1369,6 +1417,7 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
   slices.pairs_only = true;  // (the greedy walk needs the rows' argmax and nothing else)
   hs::ChainOut chain{};
   hs::BucketWs bk{};  // (all NULL: no sorted residual)
+  unsigned* tickets = nullptr;  // the scan's counters
   if (NN > 0) {
     hs::Carver c(workspace);
     t_arg = c.take<int32_t>(2 * (size_t)NN);
@@ -1390,6 +1439,7 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
       if (hs::bonus_rows_bytes(NN, V) > 0) chain.bonus_rows = c.take<double>((size_t)NN * ((V + 63) / 64));
     }
     void* scan_ws = c.take<char>(0);
+    tickets = static_cast<unsigned*>(scan_ws);
     const float T = stochastic ? temperature : 1.0f;
     hs_status r;
     if (!stochastic && hs::greedy_by_path(B, NN, V, max_depth)) {
@@ -1402,7 +1452,7 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
       // one scan over [target rows ; draft rows]; draft rows are read where a row has children, and
       // nowhere else
       hipLaunchKernelGGL(hs::k_tree_rows, dim3(B), dim3(hs::GR_THREADS), 0, st, parent, node_offsets, token, uniforms, NN,
-                         max_depth, wanted, chain, static_cast<unsigned*>(scan_ws));
+                         max_depth, wanted, chain, tickets);
       r = hs::launch_status("accept (tree rows)");
       if (r != HS_OK) return r;
       // (the rows' counters are clear: the scan merges its slices itself)
@@ -1438,10 +1488,15 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     if (r != HS_OK) return r;
     if (chain.bonus_rows != nullptr) {
       const unsigned slices = (unsigned)std::max(1, std::min(hs::BR_SLICES, hs::BR_WGS / B));
-      hipLaunchKernelGGL(hs::k_bonus_rows, dim3(B, slices), dim3(hs::BR_THREADS), 0, st, target_logits, draft_logits,
-                         row_stride, V, 1.0f / temperature, node_offsets, max_depth, t_arg, t_lz, d_arg, d_lz, chain, accept_path);
-      r = hs::launch_status("accept (bonus rows)");
-      if (r != HS_OK) return r;
+#define BR_LAUNCH(ROWS)                                                                                                    \
+  hipLaunchKernelGGL(hs::k_bonus_rows<ROWS>, dim3(B, slices), dim3(hs::BR_THREADS), 0, st, target_logits, draft_logits, row_stride, \
+                     token, parent, node_offsets, NN, V, 1.0f / temperature, uniforms, max_depth, (int)slices, t_arg, t_lz,  \
+                     d_arg, d_lz, chain, tickets, accept_len, accept_path, bonus_token)
+      // (16 KB of sums leave room for four workgroups to a compute unit, 64 KB for two)
+      if ((V + 63) / 64 <= hs::BR_FEW_ROWS) BR_LAUNCH(hs::BR_FEW_ROWS);
+      else BR_LAUNCH(hs::AC_MAX_ROWS);
+#undef BR_LAUNCH
+      return hs::launch_status("accept (bonus rows)");
     }
   }
   hipLaunchKernelGGL(hs::k_accept_walk, dim3(B), dim3(hs::AC_THREADS), 0, st, target_logits, draft_logits, row_stride,

@@ -403,6 +403,41 @@ def test_chains_end_with_their_first_accepted_child(G, V, n_kids, k):
             assert np.array_equal(G.host(out[key]), want[key]), (key, depth)
 
 
+@pytest.mark.parametrize("V,n_kids", [(1, 0), (63, 2), (4097, 0), (131072, 2), (131073, 2), (524288, 0), (524288, 2)])
+def test_bonus_draws_by_the_last_workgroup(G, V, n_kids):
+    """Ratio rule: two sequences with an empty one between them and a spare row behind, whose bonus tokens are drawn by the workgroup
+    that finishes the row, from fewer rows of 64 tokens than there are workgroups up to as many as LDS holds; from p itself and,
+    with all children rejected, from the residual."""
+    import paper_2505_13254_amd as hs
+    from oracle import verify_accept
+    rs = np.random.RandomState(V % 1000)
+    n = 1 + n_kids
+    parent = np.asarray(([-1] + [0] * n_kids) * 2 + [0], np.int32)
+    draft = rs.randn(2 * n + 1, V).astype(np.float32)
+    target = (draft + 0.5 * rs.randn(*draft.shape)).astype(np.float32)
+    token = np.zeros(2 * n + 1, np.int32)
+    for i in range(n_kids):                       # children that stand far below their draft probability
+        for g in (0, n):
+            token[g + 1 + i] = (i * (V // 2) + g) % V
+            draft[g, token[g + 1 + i]], target[g, token[g + 1 + i]] = 5.0, -2.0
+    offs = np.asarray([0, n, n, 2 * n], np.int32)
+    args = [G.dev(target), G.dev(draft), G.dev(token, torch.int32), G.dev(parent, torch.int32), G.dev(offs, torch.int32), 1, 1.0]
+    checked = 0
+    for draw in (0.013, 0.3, 0.5, 0.77, 0.98):
+        u = lambda e: np.concatenate([np.full(2 * n + 1, 0.9999), [draw + e, 0.5, 0.9 * draw + e]]).astype(np.float32)
+        # (the checker knows no spare row, and no uniform of one)
+        want, lo, hi = (verify_accept(target, draft, token, parent, offs, 1, 1.0, np.delete(u(e), 2 * n), 2) for e in (0.0, -1e-6, 1e-6))
+        out = hs.hs_verify_accept(*args, G.dev(u(0.0), torch.float32), 2)
+        assert G.host(out["accept_len"]).tolist() == want["accept_len"].tolist() == [0, 0, 0]
+        assert np.array_equal(G.host(out["accept_path"]), want["accept_path"])
+        got = G.host(out["bonus_token"])
+        assert got[1] == want["bonus_token"][1] == -1
+        for s_ in (0, 2):                         # (float32 probabilities move a token's interval by less than 1e-6 of the mass)
+            assert lo["bonus_token"][s_] <= got[s_] <= hi["bonus_token"][s_], (draw, s_)
+            checked += lo["bonus_token"][s_] == hi["bonus_token"][s_]
+    assert checked > 0 or V > 4097
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 @pytest.mark.parametrize("n_kids", [1, 63, 65, 250])
 def test_bonus_draws_after_many_rejections(G, mode, n_kids):
