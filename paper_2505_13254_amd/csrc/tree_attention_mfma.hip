@@ -206,6 +206,8 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // part of the kernel arguments, so entry `lane` exists whatever the launch), and every scalar
   // argument the kernel needs is fetched in one batch right behind: left to itself the compiler
   // fetches each argument where it is first used, one scalar-cache round trip after another.
+  // (h_half is not looked at: it comes with its neighbours, and its register, free otherwise, would be given to a later load of the
+  // batch, which then waits for this one: 0.2 us of 16.6 where that happened)
   uintx4 t0_lo = *reinterpret_cast<const uintx4*>(&a.tbl[lane]);
   uintx4 t0_hi = *(reinterpret_cast<const uintx4*>(&a.tbl[lane]) + 1);
   const void* const h_q = a.q;
@@ -219,11 +221,11 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   float* const h_part = a.part;
   const float h_scale = a.scale;
   const int h_sp_max = a.sp_max, h_n_tbl = a.n_tbl, h_tree_shared = a.tree_shared, h_narrow = a.narrow, h_share = a.share;
-  const int G = a.G, Hkv = a.Hkv, Hq = a.Hq;
+  const int G = a.G, Hkv = a.Hkv, Hq = a.Hq, h_half = a.half;
   asm volatile("" : "+v"(t0_lo), "+v"(t0_hi));  // (keeps the request here instead of inside the branch that uses it)
   asm volatile("" ::"s"(h_q), "s"(h_k_prefix), "s"(h_v_prefix), "s"(h_k_tree), "s"(h_v_tree), "s"(h_parent), "s"(h_o),
                "s"(h_lse), "s"(h_part), "s"(h_scale), "s"(h_sp_max), "s"(h_n_tbl), "s"(G), "s"(Hkv), "s"(Hq),
-               "s"(n_rg_max), "s"(h_tree_shared), "s"(h_narrow), "s"(h_share));
+               "s"(n_rg_max), "s"(h_tree_shared), "s"(h_narrow), "s"(h_share), "s"(h_half));
   int n0, M, g, rg, sp, n_sp, tiles_per_split;
   int64_t p0, L;
   if (h_n_tbl > 0) {
