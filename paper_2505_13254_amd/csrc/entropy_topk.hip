@@ -39,6 +39,7 @@ constexpr int SCAN_VPT = 16;                        // values per thread per til
 constexpr int scan_tile(int threads) { return threads * SCAN_VPT; }  // logits per workgroup tile
 constexpr int FIN_THREADS = 256;
 constexpr int FIN_CAP = HS_MAX_TOPK * HS_MAX_TOPK;  // candidates the merge of 64 slices can face
+constexpr int SCAN_NBUF = 3;                         // register buffers: tiles that a workgroup has in hand or in flight
 constexpr int MAX_SPLITS = 64;                       // slices per row (one list head per lane)
 constexpr int SCAN_BIG_WGS = 256;                    // rows are sliced until about so many sixteen-wave workgroups exist ...
 constexpr int SCAN_FINE_WGS = 600;                   // ... or four-wave ones (where they are: see plan_scan)
@@ -429,7 +430,11 @@ static_assert(ROW_SCAN_MAX * sizeof(unsigned) <= TICKET_BYTES, "every row has it
 // STATS false: only the K best pairs are wanted (the greedy accept walk's argmax scan); the softmax
 // statistics, most of the arithmetic of a tile, are left out and part_stats is not written.
 // STREAM: the whole tiles' loads carry the non-temporal hint (see row_topk_launch).
-template <int SCAN_THREADS, bool FUSED, int NBUF, bool STATS, bool STREAM>
+// SHORT: a workgroup has at most NBUF tiles, and the loops for more are left out: such launches wait for their instructions, and
+// the fewer lie between those they need the better (the loops in all launches: 10 rows of 128256 logits 10.98 us, now 10.74, 61 rows 17.3 and
+// 16.8, one of 8000 7.7 and 7.2; the 8B drafting half 91.9 and 90.0.  The second and third tile by one copy of the code, moved to its registers:
+// 10.9 and 17.3, as the copy waits for the third tile's loads).
+template <int SCAN_THREADS, bool FUSED, int NBUF, bool STATS, bool STREAM, bool SHORT>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restrict__ logits, int64_t row_stride,
                                                             int V, int K, float inv_t, int tiles_per_wg,
                                                             float4* __restrict__ part_stats,
@@ -672,7 +677,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
   const std::true_type YES{};
   const std::false_type NO{};
   int tile = 1;
-  if (n_full >= 2 * NBUF) {
+  if (!SHORT && n_full >= 2 * NBUF) {
     // (requested without a condition as well: a wait counts only loads that are pending on every path to it)
 #pragma unroll
     for (int b = 0; b < NBUF; ++b) load_full_tile(b, buf[b]);
@@ -693,7 +698,12 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_rows(const float* __restr
     }
     if (n_my > 0) process(buf[0], 0, YES);
   }
-  for (; tile < n_my; tile += NBUF) {
+  if constexpr (SHORT) {
+#pragma unroll
+    for (int b = 1; b < NBUF; ++b)
+      if (b < n_my) process(buf[b], b, NO);
+  }
+  for (; !SHORT && tile < n_my; tile += NBUF) {
 #pragma unroll
     for (int b = 0; b < NBUF; ++b) {
       if (tile + b < n_my) {
@@ -887,15 +897,18 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
   // logits 93.4 us without it, 84.5 with it; 2000 of 32000 56.1, 51.5 and (held) 50.4, 51.5; 200 of 128256 28.1, 26.0 and 26.0, 25.9;
   // 97 of 128256 24.0, 22.6 and 22.5, 21.3; 600 of 32000 25.5, 24.0 and 24.0, 23.1; but 1000 of 8192, which the L2 caches hold, 15.7, 15.5 and 12.9, 14.3.
   const bool stream_in = !rows.sparse && (int64_t)R * V >= SCAN_STREAM;
-#define HS_SCAN_LAUNCH_AS(T, F, ST, NT)                                                                                       \
-  hipLaunchKernelGGL((k_scan_rows<T, F, 3, ST, NT>), grid, dim3(T), 0, stream, logits, row_stride, V, K, inv_t, p.tiles_per_wg, \
+  const bool few_tiles = p.tiles_per_wg <= SCAN_NBUF && !stream_in;
+#define HS_SCAN_LAUNCH_AS(T, F, ST, NT, SH)                                                                                   \
+  hipLaunchKernelGGL((k_scan_rows<T, F, SCAN_NBUF, ST, NT, SH>), grid, dim3(T), 0, stream, logits, row_stride, V, K, inv_t, p.tiles_per_wg, \
                      part_stats, part_key, topk_idx, topk_logp, ent_topk, ent_full, lse, row_active, row_index, logits2, rows1, tickets)
-#define HS_SCAN_LAUNCH(F, ST)                                                            \
-  do {                                                                                   \
-    if (p.threads == SCAN_BIG && stream_in) HS_SCAN_LAUNCH_AS(SCAN_BIG, F, ST, true);      \
-    else if (p.threads == SCAN_BIG) HS_SCAN_LAUNCH_AS(SCAN_BIG, F, ST, false);             \
-    else if (stream_in) HS_SCAN_LAUNCH_AS(SCAN_SMALL, F, ST, true);                        \
-    else HS_SCAN_LAUNCH_AS(SCAN_SMALL, F, ST, false);                                      \
+#define HS_SCAN_LAUNCH(F, ST)                                                                        \
+  do {                                                                                               \
+    if (p.threads == SCAN_BIG && stream_in) HS_SCAN_LAUNCH_AS(SCAN_BIG, F, ST, true, false);           \
+    else if (p.threads == SCAN_BIG && few_tiles) HS_SCAN_LAUNCH_AS(SCAN_BIG, F, ST, false, true);      \
+    else if (p.threads == SCAN_BIG) HS_SCAN_LAUNCH_AS(SCAN_BIG, F, ST, false, false);                  \
+    else if (stream_in) HS_SCAN_LAUNCH_AS(SCAN_SMALL, F, ST, true, false);                             \
+    else if (few_tiles) HS_SCAN_LAUNCH_AS(SCAN_SMALL, F, ST, false, true);                             \
+    else HS_SCAN_LAUNCH_AS(SCAN_SMALL, F, ST, false, false);                                           \
   } while (0)
   if (slices != nullptr && slices->pairs_only) HS_SCAN_LAUNCH(false, false);
   else if (fused) HS_SCAN_LAUNCH(true, true);

@@ -35,6 +35,23 @@ def test_short_rows(G, R, V, K):
         assert G.entropy_err(got[k], want[k]) <= 1.0, k
 
 
+@pytest.mark.parametrize("R,V", [(1, 12288), (3, 12289), (2, 4 * 64 * 4096), (16, 12287), (16, 12288), (16, 16385), (129, 49151), (129, 49152), (129, 49153),
+                                 (129, 65536), (129, 65537), (40, 3 * 6 * 16384), (40, 3 * 6 * 16384 + 1), (300, 12288), (300, 12289)])
+def test_rows_around_three_tiles_to_a_workgroup(G, R, V):
+    """Workgroups of either size with one to three tiles, the last one whole, of one value or one value short, and with four: the
+    five best stand in the first and the last tile, with ties and masked logits between them."""
+    rs = np.random.RandomState(R + V % 1000)
+    x = rs.randn(R, V).astype(np.float32)
+    x[:, V // 2:V // 2 + 40] = -np.inf
+    x[:, [1, V - 1]] = 7.0
+    x[:, [V - 2, 3, V // 3]] = 6.0
+    want = draft_entropy_topk(x, 5, 1.0)
+    got = G.run_entropy(x, 5, 1.0)
+    assert np.array_equal(got["topk_idx"], want["topk_idx"])
+    for k in ("ent_topk", "ent_full"):
+        assert G.entropy_err(got[k], want[k]) <= 1.0, k
+
+
 @pytest.mark.parametrize("hq,hkv", [(4, 4), (8, 4), (6, 2)])
 @pytest.mark.parametrize("M", [1, 31, 32, 33, 128, 129, 257])
 def test_head_dimension_64_row_blocks(G, hq, hkv, M):
