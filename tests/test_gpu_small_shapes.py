@@ -442,7 +442,7 @@ def test_bonus_draws_by_the_last_workgroup(G, V, n_kids):
     checked = 0
     for draw in (0.013, 0.3, 0.5, 0.77, 0.98):
         u = lambda e: np.concatenate([np.full(2 * n + 1, 0.9999), [draw + e, 0.5, 0.9 * draw + e]]).astype(np.float32)
-        # (the checker knows no spare row, and no uniform of one)
+        # (the oracle knows no spare row, and no uniform of one)
         want, lo, hi = (verify_accept(target, draft, token, parent, offs, 1, 1.0, np.delete(u(e), 2 * n), 2) for e in (0.0, -1e-6, 1e-6))
         out = hs.hs_verify_accept(*args, G.dev(u(0.0), torch.float32), 2)
         assert G.host(out["accept_len"]).tolist() == want["accept_len"].tolist() == [0, 0, 0]
