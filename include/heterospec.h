@@ -484,8 +484,7 @@ int32_t hs_tree_attention_last_kernel(void);
  *   workgroups that a work item gets, 1, 2 or 4 (several: waves share row blocks, each with every second
  *   or fourth 32 keys of the item), plus
  *   16 or 32 where some row group shares: of five or six blocks (equal groups only) the last four waves share what is
- *   behind the fourth, two to a block; 16 = of sequences with several row groups, 32 = of all; plus
- *   64 where a KV head's last rows, at most 16 behind full row groups, go with the last of these.
+ *   behind the fourth, two to a block; 16 = of sequences with several row groups, 32 = of all.
  * 0: the any-shape kernel, or nothing planned. */
 int32_t hs_tree_attention_last_form(void);
 

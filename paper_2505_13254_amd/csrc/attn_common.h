@@ -106,8 +106,6 @@ struct AttnArgs {
   int narrow;      // work-list launches: 1 = two workgroups to an item, one for each 128 of its up to 256 rows; 2 = four
   int share;       // matrix-core kernel: equal row groups of five or six blocks share what is behind the fourth, 1 = of
                    // sequences with several groups, 2 = of all; 0 also where no group of the launch would
-  int ride;        // matrix-core kernel: 1 = of every sequence the last block, of at most ATTN_RIDE_ROWS rows behind full row
-                   // groups, has no group of its own: its rows ride along with the last full one
   int cmb_row0;    // first tree row that the merge of the splits looks at
   alignas(16) SeqEntry tbl[ATTN_TBL];  // (lanes fetch their entry with 16-byte loads)
 };
@@ -143,10 +141,6 @@ __host__ __device__ __forceinline__ void row_group(int n_blk, int rg, int* first
   *first = rg * each + (rg < more ? rg : more);
   *count = rg >= n_rg ? 0 : each + (rg < more ? 1 : 0);
 }
-
-// Rows of a KV head behind its last full row group that can ride along with it: AttnArgs::ride.
-constexpr int ATTN_RIDE_ROWS = 16;
-__host__ __device__ __forceinline__ bool rows_can_ride(int rows) { return rows > 256 && (rows - 1) % 256 < ATTN_RIDE_ROWS; }
 
 // Prefix length of sequence s (plain launches read it on the device).
 __device__ __forceinline__ int64_t prefix_len_of(const AttnArgs& a, int s) {

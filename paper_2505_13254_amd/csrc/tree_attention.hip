@@ -5,7 +5,6 @@
 // (k_attn_generic: float32 matrix instructions, 16 rows per workgroup, keys shared out to its waves)
 // and the split combine (k_attn_combine).  bfloat16 with head dimension 128, or 64 and an even number of
 // KV heads, goes to the kernel in tree_attention_mfma.hip (16-byte aligned tensors, G * rows < 65536).
-#include <math.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -529,22 +528,6 @@ static inline float plan_own_cu_us(int narrow, bool half, int waves, int tiles, 
 // 395 with the sharing of several groups alone, 381 with both).
 constexpr int PLAN_SHARE_ITEMS = 5 * PLAN_CUS;
 constexpr int PLAN_SHARE_LONG_ITEMS = 3 * PLAN_CUS / 2, PLAN_SHARE_LONG = 24;  // (from so many tiles to an item)
-// Whether up to 16 rows behind `groups` full row groups of a KV head ride along with the last of them (AttnArgs::ride),
-// in launches of more than one round of `heads` (entries times KV heads) equal ones: work per tile, and a fifth of what the last round leaves idle.
-// Against the groups that there would be otherwise: five and four blocks, 6 + 6 + 5, full ones and the rest alone.  Measured, whole
-// launches, 4000 tokens unless said otherwise, groups of their own and riding: 65 rows of 4 query heads, 33 / 64 layers 204 / 365 us and 171 / 306, 64 on 500 80 and
-// 64; 65 of 8, 80 on 8192 1411, 1371; 97 of 8, 20 / 32 layers 273 / 420, 254 / 396, 80 on 8192 1998, 1921; but 129 of 4, 20 / 32 / 40 layers 186 /
-// 289 / 365, 196 / 279 / 370, and 97 of 8, 12 / 16 layers (288 / 384 items) 165 / 203, 171 / 218.
-constexpr int PLAN_RIDE_M = 256;  // (the ancestor table of larger trees comes tile by tile)
-static inline bool plan_ride_pays(int groups, int64_t heads) {
-  if (heads * groups <= PLAN_CUS) return false;
-  auto us = [&](float work, int items) {  // of a head's groups in all, a tile
-    const float rounds = (float)(heads * items) / PLAN_CUS;
-    return rounds * work / (float)items + 0.2f * (ceilf(rounds) - rounds) * work / (float)items;
-  };
-  const float own = groups == 1 ? us(2.36f, 2) : groups == 2 ? us(3.95f, 3) : us(1.8f * groups + 0.53f, groups + 1);
-  return us(1.8f * groups + 0.2f, groups) < 0.97f * own;
-}
 constexpr int PLAN_MIN_SPLIT_TOKENS = PLAN_MIN_SPLIT_TILES * 64;
 static inline float plan_tile_us(int waves) { return 1.25f + 0.04f * (float)waves; }
 
@@ -632,13 +615,6 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   const int n_targets = (int)(sizeof(targets) / sizeof(targets[0])) - (coarse_items < PLAN_CUS ? 0 : 3);
   bool equal = true;  // entries of one size
   for (int i = 1; i < n; ++i) equal = equal && seqs[i].M == seqs[0].M && seqs[i].tiles == seqs[0].tiles;
-  const int rows = a.G * seqs[0].M;
-  a.ride = equal && !a.half && !lean && seqs[0].M <= PLAN_RIDE_M && rows_can_ride(rows) && plan_ride_pays(rows / 256, (int64_t)n * a.Hkv) ? 1 : 0;
-  if (a.ride != 0)
-    for (int i = 0; i < n; ++i) {
-      seqs[i].rg = rows / 256;
-      seqs[i].waves0 = seqs[i].waves_last = 8;
-    }
   ListPlan best{0.f, 0, 0, 1, 0};
   static thread_local std::vector<float> item_cost, cu_free;  // (kept between calls: no allocation in the steady state)
   for (int ti = 0; ti < n_targets; ++ti) {
@@ -799,7 +775,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
   a.n_tbl = n;
   a.n_items = (int)first;
   a.narrow = best.narrow;
-  a.share = first <= PLAN_CUS || a.ride != 0 ? 0 : !equal || first > (per_of[0] >= PLAN_SHARE_LONG ? PLAN_SHARE_LONG_ITEMS : PLAN_SHARE_ITEMS) ? 2 : 1;
+  a.share = first <= PLAN_CUS ? 0 : !equal || first > (per_of[0] >= PLAN_SHARE_LONG ? PLAN_SHARE_LONG_ITEMS : PLAN_SHARE_ITEMS) ? 2 : 1;
   a.sp_max = sp_max;
   return true;
 }
@@ -811,7 +787,7 @@ static bool plan_worklist(AttnArgs& a, const int32_t* hno, const int64_t* hpo, c
 struct PlanMemo {
   std::vector<int64_t> key;  // everything the plan is a function of; empty: unused slot
   bool ok;
-  int n_tbl, n_items, narrow, share, ride, sp_max, cmb_row0;
+  int n_tbl, n_items, narrow, share, sp_max, cmb_row0;
   SeqEntry tbl[ATTN_TBL];
 };
 constexpr int PLAN_MEMO_SLOTS = 4;
@@ -844,7 +820,6 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
         a.n_items = m.n_items;
         a.narrow = m.narrow;
         a.share = m.share;
-        a.ride = m.ride;
         a.sp_max = m.sp_max;
         a.cmb_row0 = m.cmb_row0;
         memcpy(a.tbl, m.tbl, sizeof(SeqEntry) * (size_t)m.n_tbl);
@@ -859,7 +834,6 @@ static bool plan_worklist_memo(AttnArgs& a, const int32_t* hno, const int64_t* h
     m.n_items = a.n_items;
     m.narrow = a.narrow;
     m.share = a.share;
-    m.ride = a.ride;
     m.sp_max = a.sp_max;
     m.cmb_row0 = a.cmb_row0;
     memcpy(m.tbl, a.tbl, sizeof(SeqEntry) * (size_t)a.n_tbl);
@@ -1012,7 +986,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   a.block_table = block_table; a.max_blocks = max_blocks;
   a.B = B; a.Hq = Hq; a.Hkv = mfma ? kv_units : Hkv; a.G = mfma ? g_unit : Hq / Hkv; a.half = mfma && pairs ? 1 : 0; a.scale = scale;
   a.o = o; a.lse = lse; a.part = static_cast<float*>(workspace);
-  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.share = 0; a.ride = 0; a.cmb_row0 = 0;
+  a.n_tbl = 0; a.n_items = 0; a.narrow = 0; a.share = 0; a.cmb_row0 = 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // the workspace query bounds the splits of a sequence the same way
   const int64_t sp_bound = total_prefix / PLAN_MIN_SPLIT_TOKENS + 1;
@@ -1034,7 +1008,6 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
   if (!(mfma && plan_worklist_memo(a, host_node_offsets, host_prefix_offsets, host_prefix_lens, B, sp_cap, false))) {
     a.n_tbl = 0;
     a.cmb_row0 = 0;
-    a.ride = 0;
     a.share = (int64_t)B * a.Hkv > PLAN_SHARE_ITEMS ? 2 : 1;  // (more than 96 sequences, or not for the matrix-core kernel)
     plan_plain(false);
   } else {
@@ -1054,7 +1027,7 @@ static hs_status attention_impl(const void* q, const void* k_prefix, const void*
       any = groups_share(row_blocks(a.G, a.half, host_node_offsets[s + 1] - host_node_offsets[s]), a.share);
     if (!any) a.share = 0;
   }
-  last_form = mfma ? (1 << a.narrow) + 16 * a.share + 64 * a.ride : 0;
+  last_form = mfma ? (1 << a.narrow) + 16 * a.share : 0;
   if (plan_only) {
     const int n_rg_max = mfma ? (a.G * max_M + 255) / 256 : plan.n_rb_max;
     report->totals[0] = mfma ? 1 : 2;

@@ -173,8 +173,7 @@ __device__ __forceinline__ void wait_lds(int n) {  // n is a constant once the w
 // SHARE: waves share row blocks behind the fourth, or four of them a block (a.share, a.narrow == 2).  The code for it is kept
 // out of the other launches: with it in all of them, 8 KB of 47, launches of short items lost up to 1 us (one row, 40 heads on 1056
 // tokens, 9 / 20 layers 42.4 / 85.7 us before there was sharing, 43.3 / 86.2 with its code in every launch, 42.1 / 85.0 now).
-// RIDE: up to 16 rows behind the last full row group of a KV head go with that group (a.ride): see ride_scores.
-template <bool PAGED, bool ONCE, bool BIG, bool HALF, bool SHARE, bool RIDE>
+template <bool PAGED, bool ONCE, bool BIG, bool HALF, bool SHARE>
 __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_max) {
   constexpr int Q_ROW_BYTES = HALF ? MF_ROW_BYTES / 2 : MF_ROW_BYTES;  // a row of Q and of O
   constexpr int NK = HALF ? 4 : 8;  // matrix instructions (and K fragments) of a 32-key score block
@@ -182,7 +181,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   constexpr int STEPS = NK / 2;     // steps of two matrix instructions in a window
   constexpr int EPS = 4 / STEPS;    // pairs of exponentials a step takes along
   static_assert(!(BIG && ONCE), "more than 256 tree rows are several row groups");
-  static_assert(!RIDE || (!BIG && !HALF && !SHARE), "riding rows: launches of one workgroup to an item, trees of up to 256 rows");
   __shared__ __attribute__((aligned(16))) char lds_k[MF_NBUF][MF_TILE_BYTES];
   __shared__ __attribute__((aligned(16))) char lds_v[MF_NBUF][MF_TILE_BYTES];
   __shared__ unsigned anc[BIG ? MF_BIG_WORDS : MF_MAX_M * MF_ANC_STRIDE];
@@ -191,13 +189,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   int* const par_lds = BIG ? reinterpret_cast<int*>(lds_v[MF_NBUF - 1]) : par_small;
   __shared__ int exact_flag;
   __shared__ int page_lds[PAGED ? 256 : 1];
-  constexpr int RIDE_P_ROW = 144;  // bytes from one riding row's weights of a tile to the next one's (64 bf16, and 16 so that rows lie in different banks)
-  __shared__ __attribute__((aligned(16))) char ride_q[RIDE ? ATTN_RIDE_ROWS * MF_ROW_BYTES : 16];
-  __shared__ __attribute__((aligned(16))) char ride_p[2][RIDE ? ATTN_RIDE_ROWS * RIDE_P_ROW : 16];
-  __shared__ float ride_l[4][ATTN_RIDE_ROWS], ride_m[ATTN_RIDE_ROWS];
-  __shared__ int ride_flag;
-  __shared__ __attribute__((aligned(16))) float4 ride_state[RIDE ? 512 : 1];
-  __shared__ float2 ride_ml[RIDE ? 256 : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (uniform for the compiler too: scalar branches)
@@ -291,9 +282,9 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const int Gh = HALF ? G >> 1 : G;      // query heads per KV head
   const int Rh = Gh * M;                  // rows of a KV head
   const int nbh = (Rh + 31) >> 5;
-  const int n_blk = HALF ? 2 * nbh : RIDE ? nbh - 1 : nbh;  // (row_blocks; RIDE: the last one has no place of its own)
+  const int n_blk = HALF ? 2 * nbh : nbh;  // (row_blocks)
   int blk0, blk_n;  // first block of this group, and how many
-  if (!RIDE && h_narrow != 0) {
+  if (h_narrow != 0) {
     const int most = 8 >> h_narrow;
     blk0 = rg * most;
     blk_n = n_blk - blk0 < most ? n_blk - blk0 : most;
@@ -308,7 +299,7 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // parity, `pair_shift` tells how far apart the two waves are.  (Groups of at most four blocks in
   // launches that fill the chip are bound by HBM at 1.25 us a tile either way, and sharing made them
   // run ahead of the other row groups of their keys, out of reach of the L2 copies: 0.8 % slower.)
-  const bool ksplit = !RIDE && h_narrow != 0;
+  const bool ksplit = h_narrow != 0;
   const int pair_shift = !ksplit ? 3 : blk_n <= 1 ? 0 : blk_n == 2 ? 1 : 2;
   // With four workgroups to an item there are at most two blocks for the eight waves: four waves share one, each with
   // every fourth 32 keys (`quarter`).  (61 rows on 2048 tokens, 8 KV heads, 32 layers one by one: 589 -> 535 us.)
@@ -324,9 +315,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const int my_blk = blk0 + (shared_tail && wave >= 4 ? 4 + (blk_n == 6 ? wave & 1 : 0) : wave & ((1 << pair_shift) - 1));
   const int kpar = shared_tail ? (wave < 4 ? 0 : blk_n == 6 ? (wave - 4) >> 1 : wave - 4) : wave >> pair_shift;  // (without sharing: 0)
   const bool wave_active = my_blk < blk0 + blk_n && kpar < ways;
-  const bool carry = RIDE && blk0 + blk_n == n_blk;  // the riding rows are this group's
-  const int ride_r0 = 32 * n_blk;                    // the first of them, and how many
-  const int ride_n = Rh - ride_r0;
   const int hb = HALF && my_blk >= nbh ? 1 : 0;          // head of the pair
   const int row_base = (my_blk - hb * nbh) * 32;          // of the head's rows
 
@@ -447,13 +435,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // behind it.  Here the waits count the younger loads (wait_vm), and an empty asm statement that
   // "writes" the registers keeps their uses behind the wait.  Lanes without a row of their own load
   // a valid row (the last one; tree row 0) and zero it afterwards.
-  uintx4 ride_raw;  // thread 16 i + c (and 256 more): chunk c of riding row i
-  if constexpr (RIDE) {
-    const int r = ride_r0 + ((tid >> 4) & 15), rc = r < Rh ? r : Rh - 1;
-    const int i = div_G(rc), gi = rc - i * Gh;
-    const char* src = static_cast<const char*>(h_q) + ((int64_t)(n0 + i) * Hq + g * G + gi) * MF_ROW_BYTES + (tid & 15) * 16;
-    asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(ride_raw) : "v"(src) : "memory");
-  }
   int my_parent = 0, far_parent = 0;  // (far: of tree row 512 + tid)
   {
     const int32_t* src = h_parent + (h_tree_shared ? 0 : n0) + (tid < M ? tid : 0);  // (one tree for all entries, or each its own)
@@ -490,7 +471,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   }
   wait_vm(NK + first_tile_loads);  // the parent pointers are there (the Q loads and the tiles are younger)
   asm volatile("" : "+v"(my_parent), "+v"(far_parent));
-  if constexpr (RIDE) asm volatile("" : "+v"(ride_raw));  // (older than the parent pointers)
   const int blk_node = div_G(row_base < Rh ? row_base : Rh - 1);  // first tree row of the block
   if (BIG && last_split) {
     // A lane walks one tree row's path.  (Two waves that share a block write the same bits: they are cleared before the
@@ -528,17 +508,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
     }
   }
   if (tid == 0) exact_flag = 0;
-  if constexpr (RIDE) {
-    if (tid == 0) ride_flag = 0;
-    if (tid < 256) {  // as the wave's own rows below; rows past the end are zeros
-      const bf16x8 raw = __builtin_bit_cast(bf16x8, ride_raw);
-      const float c2 = (tid >> 4) < ride_n ? h_scale * MF_LOG2E : 0.f;
-      bf16x8 q8;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) q8[e] = (__bf16)((float)raw[e] * c2);
-      *reinterpret_cast<bf16x8*>(ride_q + swz(tid >> 4, tid & 15)) = q8;
-    }
-  }
 
   // ---- Q fragments (B operand of the first product), pre-multiplied by scale * log2(e) so that
   // the scores come out of the MFMA in the log2 domain
@@ -779,110 +748,8 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   const std::true_type YES{};
   const std::false_type NO{};
 
-  // ---- Riding rows: up to 16 rows behind the last full row group, such as the G rows that the root adds to a tree of 32 nodes or a
-  // multiple (97 rows of 8 query heads are three groups and 8 rows).  As a group of their own they stream K and V once more, and
-  // launches of full groups are bound by the power that matrix cores, LDS and HBM take together: 80 layers on 8192 tokens, 96 rows 1.71 ms,
-  // 97 rows 2.00, riding 1.92; 64 layers of the 8B layout, 65 rows on 4000 tokens, 0.365 and 0.306.
-  // They are multiplied with 16 x 16 x 32 instructions: a tile's four 16-key groups by the first four waves at the start of its
-  // trip, the product by the other four behind the barrier in its middle, a quarter of the columns each; the weights go through LDS, in two buffers.
-  // ride_state, ride_ml (no register is free across the loops): of the last four waves O^T, lane (i, h) = (l % 16, l / 16) holds
-  // columns 4 h + v of row i, of two blocks of 16 columns; of the first four minus the reference maximum (of the first 16 keys, then fixed, as for
-  // the other rows) and the lane's denominator.  (The step's reads requested a window ahead, in three or five pieces: 16 to 24 registers
-  // across the windows, spilled, 1.95 ms.)
-  const int ri = lane & 15, rh = lane >> 4;
-  // (the lane number is found again in every step, as in tree_row: addresses kept across the loops would be spilled)
-  auto ride_lane = [&]() {
-    unsigned l = ~0u;
-    asm volatile("" : "+s"(l));
-    return (int)__builtin_amdgcn_mbcnt_hi(l, __builtin_amdgcn_mbcnt_lo(l, 0));
-  };
-  auto ride_kq = [&](int off, int ri, int rh) {  // scores of the 16 keys at byte `off` of the K ring
-    floatx4 S = {0.f, 0.f, 0.f, 0.f};
-    const int at = swz(ri, rh);  // (chunk 4 kk + rh: the swizzle's upper bits)
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-      S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(&lds_k[0][0] + ((at ^ (kk << 6)) + off)),
-                                                  *reinterpret_cast<const bf16x8*>(ride_q + (at ^ (kk << 6))), S, 0, 0, 0);
-    return S;
-  };
-  // masks of 16 keys of tile t, from key0 of the tile on
-  auto ride_mask = [&](int t, int key0, floatx4& S, int ri, int rh) {
-    if (t >= n_ptiles) {
-      const int j = (t - n_ptiles) * MF_TILE + key0 + 4 * rh;
-      const int r = ride_r0 + ri;
-      const unsigned bits = anc[div_G(r < Rh ? r : Rh - 1) * MF_ANC_STRIDE + (j >> 5)] >> (j & 31);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) S[v] = ((bits >> v) & 1u) ? S[v] : -HS_INF;
-    } else {
-      const int left = (int)(k_hi - k_lo) - t * MF_TILE - key0 - 4 * rh;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) S[v] = v < left ? S[v] : -HS_INF;
-    }
-  };
-  auto ride_scores = [&](int t, int slot, auto masked) {
-    asm volatile("" : "+v"(l0), "+v"(l1));  // (the additions stay ahead of the branch: put off behind it they kept all their terms alive)
-    if (!carry || wave >= 4) return;
-    const int lane = ride_lane(), ri = lane & 15, rh = lane >> 4;
-    floatx4 S = ride_kq(slot * MF_TILE_BYTES + wave * 16 * MF_ROW_BYTES, ri, rh);
-    if (decltype(masked)::value && t >= n_full) ride_mask(t, wave * 16, S, ri, rh);
-    float2* const st = &ride_ml[wave * 64 + lane];
-    const float2 ml = *st;
-    floatx2 p01 = {exp2_fast(S[0] + ml.x), exp2_fast(S[1] + ml.x)};
-    floatx2 p23 = {exp2_fast(S[2] + ml.x), exp2_fast(S[3] + ml.x)};
-    st->y = ml.y + ((p01[0] + p01[1]) + (p23[0] + p23[1]));
-    uint2 pk;
-    pk.x = __builtin_bit_cast(unsigned, __builtin_convertvector(p01, bf16x2));
-    pk.y = __builtin_bit_cast(unsigned, __builtin_convertvector(p23, bf16x2));
-    *reinterpret_cast<uint2*>(ride_p[t & 1] + ri * RIDE_P_ROW + wave * 32 + rh * 8) = pk;
-    // (there before the barrier that comes next: LDS keeps a wave's order, and the window in between waits for younger reads)
-  };
-  auto ride_product = [&](int t, int slot) {
-    asm volatile("" : "+v"(l0), "+v"(l1));
-    if (!carry || wave < 4) return;
-    const int lane = ride_lane(), ri = lane & 15, rh = lane >> 4;
-    const char* const p = ride_p[t & 1] + ri * RIDE_P_ROW + rh * 8;
-    const int vrow = 4 * rh + ((lane >> 2) & 3), a4 = lane & 3;
-    const int at = swz(vrow, 4 * (wave - 4) + (a4 >> 1)) + (a4 & 1) * 8;  // (rows 16 apart have the same swizzle)
-    float4* const st = &ride_state[(wave - 4) * 128 + lane];
-    floatx4 ride_acc[2];
-#pragma unroll
-    for (int d = 0; d < 2; ++d) ride_acc[d] = __builtin_bit_cast(floatx4, st[d * 64]);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const uint2 p0 = *reinterpret_cast<const uint2*>(p + kb * 64), p1 = *reinterpret_cast<const uint2*>(p + kb * 64 + 32);
-      const bf16x8 b = __builtin_bit_cast(bf16x8, uintx4{p0.x, p0.y, p1.x, p1.y});
-#pragma unroll
-      for (int d = 0; d < 2; ++d) {
-        bf16x8 v8;
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          const shortx4 got = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_s4_ptr)(&lds_v[0][0] + ((at ^ (d << 5)) + slot * MF_TILE_BYTES + (32 * kb + 16 * r) * MF_ROW_BYTES)));
-          const bf16x4 gb = __builtin_bit_cast(bf16x4, got);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v8[4 * r + e] = gb[e];
-        }
-        ride_acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v8, b, ride_acc[d], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < 2; ++d) st[d * 64] = __builtin_bit_cast(float4, ride_acc[d]);
-  };
-
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // the ancestor table is complete
   first_arrival();
-  if (RIDE && carry && wave < 4) {
-    floatx4 S = ride_kq(0, ri, rh);
-    if (n_full < 1) ride_mask(0, 0, S, ri, rh);
-    float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3]));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    ride_ml[wave * 64 + lane] = make_float2(-mx, 0.f);
-  }
-  if (RIDE && carry && wave >= 4) {
-#pragma unroll
-    for (int d = 0; d < 2; ++d) ride_state[(wave - 4) * 128 + d * 64 + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
   const int n_blocks = 2 * n_tiles;
 
   if (wave_active) {
@@ -984,7 +851,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       auto trip = [&](int t, int s, auto masked) {
         constexpr bool MASKED = decltype(masked)::value;
         const int s1 = (s + 1) % MF_NBUF;
-        if (RIDE) ride_scores(t, s, masked);
         win_qk(blk_off(s, 1), blk_off(s, 0), sB, sA, 1, pb);
         if (MASKED && 2 * t + 1 >= n_plain) mask_block(2 * t + 1, sB);
         if (MASKED) {
@@ -993,7 +859,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
           asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * MF_LOADS) : "memory");
           issue_full(t + 3, (s + 3) % MF_NBUF);
         }
-        if (RIDE) ride_product(t, s);
         win_pv(blk_off(s, 0), blk_off(s1, 0), pa, pb, sB, 0, pc, YES, YES);
         win_qk(blk_off(s1, 0), blk_off(s, 1), sA, sB, 1, pb);
         if (MASKED && 2 * t + 2 >= n_plain) mask_block(2 * t + 2, sA);
@@ -1011,7 +876,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
       for (; t + 1 < n_tiles; ++t) trip(t, t % MF_NBUF, YES);
       {  // last tile: nothing follows its odd block
         const int s = t % MF_NBUF;
-        if (RIDE) ride_scores(t, s, YES);
         win_qk(blk_off(s, 1), blk_off(s, 0), sB, sA, 1, pb);
         if (2 * t + 1 >= n_plain) mask_block(2 * t + 1, sB);
         win_pv(blk_off(s, 0), 0, pa, pb, sB, 0, pc, YES, NO);
@@ -1019,10 +883,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
 #pragma unroll
         for (int f = 0; f < 2 * MF_AHEAD; ++f) vf[f] = ldv(blk_off(s, 1), f);
         win_pv(blk_off(s, 1), 0, pc, pb, sB, 0, pa, NO, NO);
-        if (RIDE && carry) {  // (every wave of the group has rows)
-          asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-          ride_product(t, s);
-        }
       }
     }
     l_sum = l0 + l1;
@@ -1034,17 +894,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // ---- did the fixed reference hold?  (denominator of both half-waves; NaN counts as no)
   float l_tot = l_sum + __shfl_xor(l_sum, 32);
   if (wave_active && __ballot(!(l_tot < MF_SUM_LIMIT)) != 0ull && lane == 0) exact_flag = 1;
-  if (RIDE && carry && wave < 4) {
-    const float2 ml = ride_ml[wave * 64 + lane];
-    float l = ml.y;
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
-    if (__ballot(!(l < MF_SUM_LIMIT)) != 0ull && lane == 0) ride_flag = 1;
-    if (rh == 0) {
-      ride_l[wave][ri] = l;
-      if (wave == 0) ride_m[ri] = -ml.x;
-    }
-  }
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // also: every LDS read of the pass is done
   if (exact_flag != 0) {
     // ---- exact path (rare): the pass again, one block at a time, the reference following the
@@ -1189,64 +1038,6 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   }
   if (!wave_active) return;
 
-  // ---- results of a riding row (tree row i, query head `head`): four neighbouring columns from d0 on
-  auto ride_out = [&](int r, int d0, const floatx4& o, float m, float l) {
-    const int i = div_G(r), head = g * G + r - i * Gh;
-    const int64_t row = (int64_t)(n0 + i) * Hq + head;
-    if (n_sp == 1) {
-      const float inv = 1.f / l;
-      floatx2 f01 = {o[0] * inv, o[1] * inv}, f23 = {o[2] * inv, o[3] * inv};
-      uint2 pk;
-      pk.x = __builtin_bit_cast(unsigned, __builtin_convertvector(f01, bf16x2));
-      pk.y = __builtin_bit_cast(unsigned, __builtin_convertvector(f23, bf16x2));
-      *reinterpret_cast<uint2*>(static_cast<char*>(h_o) + row * MF_ROW_BYTES + d0 * 2) = pk;
-      if (h_lse && d0 == 0) h_lse[row] = (m + __log2f(l)) * MF_LN2;
-    } else {
-      float* rec = h_part + (row * h_sp_max + sp) * (32 * NT + ATTN_REC_PAD);
-      *reinterpret_cast<float4*>(rec + d0) = make_float4(o[0], o[1], o[2], o[3]);
-      if (d0 == 0) {
-        rec[32 * NT] = m * MF_LN2;
-        rec[32 * NT + 1] = l;
-      }
-    }
-  };
-  if (RIDE && carry && ride_flag == 0) {
-    if (wave >= 4 && ri < ride_n) {
-      const float l = (ride_l[0][ri] + ride_l[1][ri]) + (ride_l[2][ri] + ride_l[3][ri]), m = ride_m[ri];
-#pragma unroll
-      for (int d = 0; d < 2; ++d) 
-        ride_out(ride_r0 + ri, 32 * (wave - 4) + 16 * d + 4 * rh, __builtin_bit_cast(floatx4, ride_state[(wave - 4) * 128 + d * 64 + lane]), m, l);
-    }
-  } else if (RIDE && carry) {
-    // ---- the fixed reference did not hold: a row to a wave, key by key from memory, the reference following the running maximum
-    // (rare and slow; a lane has two columns)
-    for (int i = wave; i < ride_n; i += MF_THREADS / 64) {
-      const int r = ride_r0 + i, node = div_G(r);
-      const bf16x2 q2 = *reinterpret_cast<const bf16x2*>(ride_q + swz(i, lane >> 2) + (lane & 3) * 4);
-      float m = -HS_INF, l = 0.f, o0 = 0.f, o1 = 0.f;
-      for (int t = 0; t < n_tiles; ++t) {
-        const bool tree = t >= n_ptiles;
-        const int base = tree ? (t - n_ptiles) * MF_TILE : 0;
-        const int keys = tree ? min(MF_TILE, M - base) : (int)min((int64_t)MF_TILE, k_hi - k_lo - (int64_t)t * MF_TILE);
-        const int64_t off = tree ? base * tok_stride : prefix_tile(t);
-        for (int j = 0; j < keys; ++j) {
-          if (tree && ((anc[node * MF_ANC_STRIDE + ((base + j) >> 5)] >> ((base + j) & 31)) & 1u) == 0u) continue;
-          const bf16x2 k2 = *reinterpret_cast<const bf16x2*>((tree ? kt : kp) + off + j * tok_stride + lane * 4);
-          const bf16x2 v2 = *reinterpret_cast<const bf16x2*>((tree ? vt : vp) + off + j * tok_stride + lane * 4);
-          const float x = wave_sum(fmaf((float)q2[0], (float)k2[0], (float)q2[1] * (float)k2[1]));
-          if (x == -HS_INF) continue;  // (a masked key: no weight, and no reference either)
-          const float top = fmaxf(m, x), alpha = exp2_fast(m - top), w = exp2_fast(x - top);
-          m = top;
-          l = fmaf(l, alpha, w);
-          o0 = fmaf(o0, alpha, w * (float)v2[0]);
-          o1 = fmaf(o1, alpha, w * (float)v2[1]);
-        }
-      }
-      const floatx4 o = {o0, o1, __shfl_xor(o0, 1), __shfl_xor(o1, 1)};
-      if ((lane & 1) == 0) ride_out(r, 2 * lane, o, m, l);
-    }
-  }
-
   // `NB` column blocks (acc[0 .. NB)) of this wave's 32 rows, from column col0 of the head's row on
   auto write_out = [&](auto nb, int col0) {
     constexpr int NB = decltype(nb)::value;
@@ -1324,28 +1115,23 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
 // when the kernel begins and ends, so their elapsed time is the kernel's own duration.
 hs_status attn_mfma_launch(const AttnArgs& a, int max_tree_rows, hipStream_t stream, hipEvent_t ev_start,
                            hipEvent_t ev_stop) {
-  const int n_rg_max = (a.G * max_tree_rows + MF_ROWS - 1) / MF_ROWS - a.ride;
+  const int n_rg_max = (a.G * max_tree_rows + MF_ROWS - 1) / MF_ROWS;
   dim3 grid((unsigned)(a.Hkv * n_rg_max * a.sp_max), (unsigned)a.B);
   if (a.n_tbl > 0) grid = dim3((unsigned)a.n_items << a.narrow, 1u);
   const bool once = n_rg_max == 1 && a.narrow == 0;  // every (sequence, head) is one row group: its keys have one reader
   const bool big = max_tree_rows > MF_MAX_M;
   const dim3 block(MF_THREADS);
   const bool share = a.share != 0 || a.narrow == 2;
-#define MF_LAUNCH_AS(PAGED, ONCE, BIG, HALF, SHARE, RIDE) \
-  hipExtLaunchKernelGGL((k_attn_mfma<PAGED, ONCE, BIG, HALF, SHARE, RIDE>), grid, block, 0, stream, ev_start, ev_stop, 0, a, n_rg_max)
+#define MF_LAUNCH_AS(PAGED, ONCE, BIG, HALF, SHARE) \
+  hipExtLaunchKernelGGL((k_attn_mfma<PAGED, ONCE, BIG, HALF, SHARE>), grid, block, 0, stream, ev_start, ev_stop, 0, a, n_rg_max)
 #define MF_LAUNCH(PAGED, ONCE, BIG)                                 \
   do {                                                              \
-    if (a.half && share) MF_LAUNCH_AS(PAGED, ONCE, BIG, true, true, false);   \
-    else if (a.half) MF_LAUNCH_AS(PAGED, ONCE, BIG, true, false, false);      \
-    else if (share) MF_LAUNCH_AS(PAGED, ONCE, BIG, false, true, false);       \
-    else MF_LAUNCH_AS(PAGED, ONCE, BIG, false, false, false);                 \
+    if (a.half && share) MF_LAUNCH_AS(PAGED, ONCE, BIG, true, true);   \
+    else if (a.half) MF_LAUNCH_AS(PAGED, ONCE, BIG, true, false);      \
+    else if (share) MF_LAUNCH_AS(PAGED, ONCE, BIG, false, true);       \
+    else MF_LAUNCH_AS(PAGED, ONCE, BIG, false, false);                 \
   } while (0)
-  if (a.ride != 0) {
-    if (a.block_table != nullptr && once) MF_LAUNCH_AS(true, true, false, false, false, true);
-    else if (a.block_table != nullptr) MF_LAUNCH_AS(true, false, false, false, false, true);
-    else if (once) MF_LAUNCH_AS(false, true, false, false, false, true);
-    else MF_LAUNCH_AS(false, false, false, false, false, true);
-  } else if (a.block_table != nullptr) {
+  if (a.block_table != nullptr) {
     if (big) MF_LAUNCH(true, false, true);
     else if (once) MF_LAUNCH(true, true, false);
     else MF_LAUNCH(true, false, false);

@@ -219,21 +219,15 @@ def test_single_groups_share_earlier_where_items_are_long(B, L, form):
     assert hs.hs_tree_attention_last_form() == form
 
 
-@pytest.mark.parametrize("B,M,L,Hq,Hkv,n_rg,ride", [
-    (33, 65, 2000, 32, 8, 1, True), (64, 68, 500, 32, 8, 1, True), (64, 69, 500, 32, 8, 2, False), (64, 64, 500, 32, 8, 1, False),
-    (32, 65, 2000, 32, 8, 2, False),                                                     # no more than a round
-    (80, 65, 4000, 64, 8, 2, True), (80, 66, 4000, 64, 8, 2, True), (20, 129, 4000, 32, 8, 3, False),  # two groups: nearly whole rounds
-    (80, 97, 8192, 64, 8, 3, True), (80, 98, 8192, 64, 8, 3, True), (80, 99, 8192, 64, 8, 4, False), (16, 97, 4000, 64, 8, 4, False),
-    (80, 257, 300, 8, 8, 2, False)])                                                     # a tree beyond 256 rows
-def test_rows_that_ride_along(B, M, L, Hq, Hkv, n_rg, ride):
-    """Up to 16 rows of a KV head behind full row groups get no group of their own in launches of several rounds of equal
-    entries, in ragged ones they do."""
+@pytest.mark.parametrize("B,M,L,Hq,Hkv,n_rg", [
+    (33, 65, 2000, 32, 8, 2), (64, 68, 500, 32, 8, 2), (64, 64, 500, 32, 8, 1), (32, 65, 2000, 32, 8, 2), (80, 65, 4000, 64, 8, 3),
+    (20, 129, 4000, 32, 8, 3), (80, 97, 8192, 64, 8, 4), (80, 98, 8192, 64, 8, 4), (16, 97, 4000, 64, 8, 4), (80, 257, 300, 8, 8, 2)])
+def test_row_groups_hold_all_rows(B, M, L, Hq, Hkv, n_rg):
+    """A few rows behind what full row groups hold make one group more, whose blocks are dealt out equally: every row keeps a place
+    of its own in its group's pass, the one that follows the running maximum included, however many sequences there are."""
     totals, per = _plan([M] * B, [L] * B, Hq, Hkv)
-    assert (hs.hs_tree_attention_last_form() & 64 != 0) == ride
     assert all(int(r[2]) == n_rg for r in per)
     assert int(totals[1]) == sum(int(r[0]) * n_rg * Hkv for r in per)
-    _plan([M] * B, [L] * (B - 1) + [L + 640], Hq, Hkv)
-    assert hs.hs_tree_attention_last_form() & 64 == 0
 
 
 @pytest.mark.parametrize("Ms,Ls,Hkv,D,splits", [

@@ -126,14 +126,14 @@ def test_row_blocks_shared_by_waves(G, D, hq, hkv, M, L, B, shared, variant):
 
 
 @pytest.mark.parametrize("variant", ["unit", "hot", "last"])
-@pytest.mark.parametrize("hq,hkv,M,L,B,ride", [
-    (32, 8, 65, 100, 33, True), (32, 8, 68, 64, 40, True), (64, 8, 33, 0, 33, True), (8, 8, 65, 31, 40, False),  # one group: 4, 16, 8 rows; four blocks
-    (64, 4, 17, 1000, 66, True), (64, 4, 16, 200, 70, False),                                     # the last entries in splits; full groups alone
-    (64, 8, 65, 130, 32, True), (64, 8, 66, 65, 32, True), (64, 8, 67, 65, 32, False),            # two
-    (64, 8, 97, 129, 20, True), (64, 8, 98, 1, 32, True)])                                        # three
-def test_rows_that_ride_along_with_full_groups(G, hq, hkv, M, L, B, ride, variant):
-    """Up to 16 rows of a KV head behind its full row groups: one tile and many, a partial one, the tree's tiles alone, one node's
-    rows and two, splits; scores that leave the fixed reference, of any rows and ("last") of riding rows alone."""
+@pytest.mark.parametrize("hq,hkv,M,L,B", [
+    (32, 8, 65, 100, 33), (32, 8, 68, 64, 40), (64, 8, 33, 0, 33), (8, 8, 65, 31, 40),   # one group: 4, 16, 8 rows; four blocks
+    (64, 4, 17, 1000, 66), (64, 4, 16, 200, 70),                             # the last entries in splits; full groups alone
+    (64, 8, 65, 130, 32), (64, 8, 66, 65, 32), (64, 8, 67, 65, 32),                  # two
+    (64, 8, 97, 129, 20), (64, 8, 98, 1, 32)])                              # three
+def test_a_few_rows_behind_full_row_groups(G, hq, hkv, M, L, B, variant):
+    """A few rows of a KV head behind what full row groups hold: one tile and many, a partial one, the tree's tiles alone, one node's
+    rows and two, splits; scores that leave the fixed reference, of any rows and ("last") of the last row alone."""
     import paper_2505_13254_amd as hs
     from test_gpu_attention import _case, _compare, _random_parents
     w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv, D=128)
@@ -148,7 +148,7 @@ def test_rows_that_ride_along_with_full_groups(G, hq, hkv, M, L, B, ride, varian
             keys, at = (step["k_prefix"], (s + 1) * L - 1 - s % min(L, 40)) if L > 0 and s % 3 else (step["k_tree"], row)
             keys[at, h // (hq // hkv)] = torch.from_numpy(key).bfloat16().view(torch.int16).numpy().view(np.uint16)
     _compare(G, step, "bf16", big_scores=variant != "unit")
-    assert (hs.hs_tree_attention_last_form() & 64 != 0) == ride
+    assert hs.hs_tree_attention_last_kernel() == 1
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
