@@ -483,7 +483,7 @@ __device__ __forceinline__ bool ratio_accepts(double pc, double qc, float u) { r
 // Along a node's chain of rejections only beta changes: F(beta) = sum_v max(p(v) - beta q(v), 0),
 // taken at an increasing sequence of beta >= 1 that is not known in advance, but for the first:
 // 1.  A token contributes p - beta q while its ratio p / q exceeds beta and nothing afterwards.  So, for
-// every node with at least two children, a kernel that runs on the whole chip sorts the tokens with p > q of each
+// every node with at least two children (of long rows: with one), a kernel that runs on the whole chip sorts the tokens with p > q of each
 // vocabulary slice by their ratio into BK_N buckets (a counting sort inside a workgroup: count, then place) and keeps,
 // per bucket, the sums of p and of q.  F(1) is the sum of all of them, F(beta)
 //     sum over the buckets well above beta of (P_b - beta Q_b)      two suffix sums, read once
@@ -498,6 +498,14 @@ __device__ __forceinline__ bool ratio_accepts(double pc, double qc, float u) { r
 // integers in units of 2^-62 (LDS and per-slice partial sums), so neither the order in which the
 // lanes' atomic additions arrive nor the order of the tokens inside a bucket changes a result.
 // (A chain of one rejection needs the sums alone: no pairs are written for it.)
+// Nodes with one child are sorted where rows are long.  Their own workgroup of k_accept_chain makes the one sum
+// in a pass over both rows as well, 3 us of 32000 tokens and 10 of 128256, all nodes side by side, while the sort reads the rows of every
+// node with the whole chip before it knows that a first child is accepted.  Whole calls, chains of single children all rejected, without the sort and
+// with it: one tree of 9 rows of 128256 tokens 41.6 us and 35.2, of 31 47.4 and 40.8, 4 trees of 9 48.8 and 47.1, 16 of 9 84.9 and 90.0; one
+// of 9 of 65536 tokens 34.2 and 31.8, of 50257 33.0 and 31.8, of 32000 29.2 and 29.7; but 16 of 9 of 50257 tokens 51.0 and 59.1, of 32000 41.9 and 50.2, of 8192 31.7 and
+// 36.8, of 4096 28.1 and 34.5.  Trees that branch, 33 to 640 rows: within 2 % of each other on 32000 tokens, on 128256 up to 6 % faster with the sort.
+constexpr int BK_SINGLE_V = 65536;
+__device__ __forceinline__ int sorted_from(int V) { return V >= BK_SINGLE_V ? 1 : 2; }  // children of a node that is sorted
 struct BucketWs {
   uint32_t* start;            // [NN][BK_SLICES][BK_N + 1] first position in `pairs` of a slice's buckets (ascending ratio)
   unsigned long long* psum;   // [NN][BK_SLICES][BK_N] sum of p over a slice's bucket
@@ -524,7 +532,7 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
   // (one trip for what the row's statistics say, one for the slice and the two maxima)
   const int nk = chain.n_tried[g], p_arg = t_arg[g], q_arg = d_arg[g], x0 = chain.kid_tok[g];
   const float p_lz = t_lz[g], q_lz = d_lz[g], u0 = chain.kid_u[g];
-  if (nk < 1) return;
+  if (nk < sorted_from(V)) return;
   cnt[tid] = 0u;
   ps[tid] = 0ull;
   qs[tid] = 0ull;
@@ -919,7 +927,7 @@ __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
     if (tid == 0) out.accepted[g] = first;
     return;
   }
-  const bool sorted = bk.pairs != nullptr;  // there is a sorted residual
+  const bool sorted = bk.pairs != nullptr && nk >= sorted_from(V);  // there is a sorted residual
   // Everything is requested side by side: the tables, the children and their tokens, then the tokens' logits; the chain
   // below is serial, and a round trip to memory per step would dominate it.
   BucketLoads loads;

@@ -420,6 +420,13 @@ def test_chains_end_with_their_first_accepted_child(G, V, n_kids, k):
             assert np.array_equal(G.host(out[key]), want[key]), (key, depth)
 
 
+@pytest.mark.parametrize("k", [0, None])
+@pytest.mark.parametrize("V", [65535, 65536, 65537])
+def test_single_children_around_the_length_from_which_they_are_sorted(G, V, k):
+    """One child to a node, accepted or rejected, in rows that its own workgroup passes over and in rows that are sorted."""
+    test_chains_end_with_their_first_accepted_child(G, V, 1, k)
+
+
 @pytest.mark.parametrize("V,n_kids", [(1, 0), (63, 2), (4097, 0), (131072, 2), (131073, 2), (524288, 0), (524288, 2)])
 def test_bonus_draws_by_the_last_workgroup(G, V, n_kids):
     """Ratio rule: two sequences with an empty one between them and a spare row behind, whose bonus tokens are drawn by the workgroup
