@@ -217,7 +217,8 @@ hs_status hs_tree_prune_static(const int32_t* parent, const float* logc, const i
  * Requires Hq % Hkv == 0, D in {64, 128}, at most 1024 tree rows per sequence.
  * bfloat16 runs on the matrix cores (D = 64: with an even number of KV heads, which the kernel takes in
  * pairs); calls with a sequence of more than 256 tree rows ask for 128 bytes of workspace per tree row
- * besides (included in the workspace query).
+ * besides (included in the workspace query).  These are reserved: no kernel uses them at present, but a call without room
+ * for them is refused, or planned with fewer key splits.
  * Workspace: one partial record of D + 4 floats per (tree row, query head, key split); the query
  * returns the bound for min(64, total_prefix / 128 + 1) splits, more than any plan of that batch
  * uses (a batch whose keys are not cut needs none; hs_tree_attention_plan tells what a given batch needs).  The host keeps the last few plans per calling thread (a model's layers share theirs); the

@@ -70,7 +70,8 @@ struct ScanPlan {
 // 69.7 by the rule for full scans).
 // Rows that are not 16-byte aligned were read a value at a time when these rules were made, which only more workgroups made up
 // for; read 16 bytes at a time like the others they lose nothing by the finer slices (301 of 132058: 43.9 us, by the rule for aligned
-// rows 52.2; 330 of 50257 23.4 both, 7 of 137847 11.8 and 12.2).  Slices whose
+// rows 52.2; 330 of 50257 23.4 both, 7 of 137847 11.8 and 12.2).  Aligned rows keep the coarser slices that they had; the finer ones have not been
+// measured for them.  Slices whose
 // merge is the caller's (rows.pairs_only) cost no launch.  So the argmax scan takes 257 rows and more in three slices,
 // or two, as long as 1024 workgroups allow (277 rows of 50257: 1 slice 31.2, 2 28.7, 3 26.0; 305 of 187620, aligned: 57.1,
 // 50.5, 48.9; aligned rows from about 360 on gain nothing, 421 to 520 of 32000 or 50256 would lose 3 %), three-tile
@@ -893,6 +894,9 @@ hs_status row_topk_launch(const float* logits, int64_t row_stride, int R, int V,
   // one launch: the rows' last slices merge (needs the zeroed counters of a prepared workspace)
   const bool fused = prepared && slices == nullptr && p.splits > 1 && p.splits * K <= FUSED_CAP;
   // (the ratio rule reads its rows again, and not all of those that are counted here)
+  // Argmax scans gain either way: 97 rows of 128256 17.7, 16.3 and (held) 14.1, 13.1; 896 84.8, 74.5; 2000 of 32000 51.8, 45.0 and 44.0, 43.6.  Full scans
+  // of logits that the kernel before has just written, both together: 97 of 128256 37.8, 38.2, 400 of 32000 35.4, 35.9, 200 of 128256 55.0, 54.9, 2000 of 32000 144.8,
+  // 132.1, 896 of 128256 256.8, 238.0.
   // The hint leaves the caches to what is read again.  Cold inputs and ones that the last-level cache holds, K = 10: 896 rows of 128256
   // logits 93.4 us without it, 84.5 with it; 2000 of 32000 56.1, 51.5 and (held) 50.4, 51.5; 200 of 128256 28.1, 26.0 and 26.0, 25.9;
   // 97 of 128256 24.0, 22.6 and 22.5, 21.3; 600 of 32000 25.5, 24.0 and 24.0, 23.1; but 1000 of 8192, which the L2 caches hold, 15.7, 15.5 and 12.9, 14.3.

@@ -498,8 +498,9 @@ constexpr int PLAN_MIN_SPLIT_TILES = 2;
 // 1000 / 2048 / 4096 tokens 14.6 / 16.0 / 18.3 / 20.3 us and 13.9 / 15.1 / 16.7 / 19.5, D = 64 on 2048 13.3 and 12.9; 40
 // heads, 129 rows on 400 tokens 18.3 and 16.4.  None gained by items of at most 128 rows (20 on 2048 14.9 and 15.3), nor by long
 // prefixes, which want more splits than that leaves room for (9000 tokens 27.1 and 29.5).  Nor, with D = 128, by trees
-// beyond 256 rows, whose table comes tile by tile: 16 heads, 300 rows on 500 / 2000 tokens 21.5 / 35.9 us with two, 23.8 / 45.3 with four;
-// 1024 on 2000 51.8 and 59.8; D = 64, 300 on 1000 20.4 and 21.5, but 1024 on 200 28.0 and 26.6.
+// beyond 256 rows: 300 rows on 500 tokens, 16 heads one row each, 18.6 us with two and 21.4 with four, on 2000 25.2 and 25.1; 8 heads on 2, 260 rows
+// on 400 18.4 and 19.8, 300 on 1000 21.1 and 22.3, 1024 on 2000 40.7 and 48.9.  With D = 64 they do: 8 heads on 4, 300 on 1000 17.7 and 16.8, 1024 on 200 24.4 and
+// 23.9, 8 on 8, 300 on 2000 18.2 and 17.6; but 16 on 16, 300 on 1000 18.0 and 19.4.
 constexpr int PLAN_NARROW_ITEMS = PLAN_CUS / 2, PLAN_QUARTER_ITEMS = PLAN_CUS / 4, PLAN_QUARTER_ROWS = 256;
 // Launches that give every item a compute unit of its own, either way: the longest item decides.  A tile costs
 // the more the more K/V streams are read at a time, and above 128 rows, where two waves share a SIMD, the matrix

@@ -490,7 +490,7 @@ __device__ __forceinline__ bool ratio_accepts(double pc, double qc, float u) { r
 //   + sum over the tokens of beta's bucket (and of the next one where beta is near its edge) of max(p - beta q, 0)
 // which is what k_accept_chain evaluates per rejection: about a thousand pairs instead of two
 // vocabulary rows.  (Sorted across slices, with a scan and a second pass over the rows in launches of
-// their own: 23.6 us for a 61-row tree; slice by slice, read twice, 15.7; kept in registers for the second pass, now, 12.1.)
+// their own: 23.6 us for a 61-row tree; slice by slice, read twice, 15.7; kept in registers for the second pass, now, 11.7.)
 // A token's bucket is floor(BK_PER_OCTAVE * log2(p / q)), taken from the two
 // exponent arguments (p = exp2(a_p)): the rounding of that difference is many orders below a
 // bucket's width, and where beta lies near the edge of a bucket the next one is treated token by token as well, so
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_sort(const float* __restr
   auto px = [&](int i) { return load_float4(p_row + 4 * i); };
   auto qx = [&](int i) { return load_float4(q_row + 4 * i); };
   // A thread's tokens stay in its registers for both passes where they fit, requested all at once.  (Read twice, two at a
-  // time: 61 rows of 128256 tokens 15.7 us, now 12.1; 97 rows 28.7 and 19.8.)
+  // time: 61 rows of 128256 tokens 15.7 us, 12.1 so; 97 rows 28.7 and 19.8.)
   constexpr int KEEP = 8;
   const bool kept = i1 - i0 <= KEEP * BK_THREADS;
   float4 fp[KEEP], fq[KEEP];
@@ -887,7 +887,7 @@ __device__ __forceinline__ void bonus_row_sums(const RowView& p, const RowView& 
 // ratio rule.  Whether a child is accepted when its turn comes depends on the node, its uniform and the rejections before it, so the
 // chain ends with the first accepted child, usually the first child, before anything but its two probabilities has
 // been looked at.  (With every child rejected in turn, whatever the uniforms, and the rows of p summed here for every row
-// without children: 21.8 us for 61 rows of 128256 tokens, now 10.2; with all chains run to their ends the same as before.)
+// without children: 22.4 us for the 61 rows of 128256 tokens of the 8B step, now 14.1; with all chains run to their ends the same as before.)
 __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
     const float* __restrict__ target, const float* __restrict__ draft, int64_t row_stride,
     const int32_t* __restrict__ token, const int32_t* __restrict__ parent, const int32_t* __restrict__ node_offsets,
@@ -1149,7 +1149,7 @@ __device__ __forceinline__ void draw_bonus(const RowView& p, const RowView& q, b
 // tried; the rejected tokens' frozen weights are the draw's corrections.  The first slice's workgroup writes the path, and the one that
 // draws the last ticket of its sequence (a counter of the scan's, zero before and cleared by each call's k_tree_rows) draws the bonus token.
 // ROWS: rows of 64 tokens that LDS has room for.  (The draw by a launch of its own: 4.9 and 6.1 us for 61 rows
-// of 128256 tokens, 9.1 in one now; the whole step 151.1 us, now 149.1, on 32000 tokens 133.7 and 131.0.)
+// of 128256 tokens, 8.4 in one now; the whole step 151.1 us, now 149.1, on 32000 tokens 133.7 and 131.0.)
 template <int ROWS>
 __global__ __launch_bounds__(BR_THREADS) void k_bonus_rows(const float* __restrict__ target,
                                                            const float* __restrict__ draft, int64_t row_stride,
@@ -1350,7 +1350,7 @@ static size_t bucket_workspace(int NN, int V, Carver* c, BucketWs* ws) {
   return align_up(n_st * 4, 256) + 2 * align_up(n_sb * 8, 256) + align_up((size_t)NN * V * sizeof(float2), 256);
 }
 
-// Bytes of the row sums of k_bonus_rows (0 beyond BK_NODES rows: the walk then sums
+// Bytes of the row sums of k_bonus_rows, which has a place for every tree row and uses one a sequence (0 beyond BK_NODES rows: the walk then sums
 // the rows of its stop node itself).
 static size_t bonus_rows_bytes(int NN, int V) {
   return NN <= BK_NODES ? align_up((size_t)NN * ((V + 63) / 64) * sizeof(double), 256) : 0;
