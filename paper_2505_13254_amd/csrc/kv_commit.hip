@@ -11,12 +11,19 @@
 
 namespace hs {
 
-constexpr int KC_THREADS = 1024;
+// Workgroups of 1024 threads for up to one sequence to a compute unit, of 256 beyond that, where most of the threads of those of 1024 have no
+// piece and only take their time to start.  1024 and 256 threads, us a call: 64 sequences, 4 rows of 2 KB 3.9 and 4.1, 6 of 10 KB 6.6 and 8.8; 256, 4 of
+// 2 KB 4.4 and 4.7, 1 of 2 KB 4.1 and 3.8; 512, 2 of 1 KB 4.7 and 4.0; 1024, 2 of 1 KB 6.1 and 4.4; 4096, 1 of 2 KB 14.1 and 7.7, 6 of 256 bytes 13.8 and
+// 7.2; but 512, 9 of 10 KB 33.1 and 37.4.  (A thread's later pieces found by 64-bit divisions, the page requested behind the row: 256 threads, paged, 600
+// sequences, 61 rows of 2 KB 89 us, now 68.)
+constexpr int KC_THREADS = 1024, KC_THREADS_MANY = 256;
+constexpr int KC_MANY = 256;  // sequences
 
 // block_table == NULL: sequence s owns tokens cache_offsets[s] .. cache_offsets[s+1] of the caches.
 // Otherwise the caches are pools of pages of `page_tokens` tokens and token t of sequence s lives in
 // page block_table[s * max_blocks + t / page_tokens].
-__global__ __launch_bounds__(KC_THREADS) void k_kv_commit(const char* __restrict__ k_tree,
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_kv_commit(const char* __restrict__ k_tree,
                                                           const char* __restrict__ v_tree,
                                                           const int32_t* __restrict__ node_offsets,
                                                           const int32_t* __restrict__ accept_path,
@@ -49,25 +56,36 @@ __global__ __launch_bounds__(KC_THREADS) void k_kv_commit(const char* __restrict
   n_acc = n_acc < 0 ? 0 : (n_acc > max_depth ? max_depth : n_acc);
   int64_t rows = 1 + n_acc;  // the root, then the accepted rows
   rows = rows > room ? (room > 0 ? room : 0) : rows;
-  auto copy = [&](int t, unsigned c, int r) {
-    r = r < 0 ? 0 : (r >= M ? M - 1 : r);  // (a path entry outside the tree would be a caller's error)
-    const int64_t src = ((int64_t)(n0 + r)) * row_bytes + c * 16;
+  const bool small = (used + rows) >> 32 == 0;  // (a 64-bit division is a long sequence of instructions)
+  const int32_t* const table = block_table + (int64_t)s * max_blocks;
+  auto copy = [&](unsigned t, unsigned c, int r) {
     int64_t pos = c0 + used + t;  // token position in the caches
     if (paged) {
       const int64_t tok = used + t;
-      // (a 64-bit division is a long sequence of instructions)
-      const int64_t blk = tok >> 32 == 0 ? (int64_t)((unsigned)tok / (unsigned)page_tokens) : tok / page_tokens;
-      pos = (int64_t)block_table[(int64_t)s * max_blocks + blk] * page_tokens + (tok - blk * page_tokens);
+      const int64_t blk = small ? (int64_t)((unsigned)tok / (unsigned)page_tokens) : tok / page_tokens;
+      pos = (int64_t)table[blk] * page_tokens + (tok - blk * page_tokens);
     }
-    const int64_t dst = pos * row_bytes + c * 16;
+    r = t == 0 || r < 0 ? 0 : (r >= M ? M - 1 : r);  // (a path entry outside the tree would be a caller's error)
+    const int64_t src = ((int64_t)(n0 + r)) * row_bytes + c * 16, dst = pos * row_bytes + c * 16;
     const uint4 k = *reinterpret_cast<const uint4*>(k_tree + src), v = *reinterpret_cast<const uint4*>(v_tree + src);
     *reinterpret_cast<uint4*>(k_cache + dst) = k;
     *reinterpret_cast<uint4*>(v_cache + dst) = v;
   };
-  if (t0 < rows) copy((int)t0, tid - t0 * chunks, r0);
-  for (int64_t e = (int64_t)tid + KC_THREADS; e < rows * chunks; e += KC_THREADS) {
-    const int t = (int)(e / chunks);
-    copy(t, (unsigned)(e - (int64_t)t * chunks), t == 0 ? 0 : path[t - 1]);
+  unsigned t = t0, c = tid - t0 * chunks;
+  if (t < rows) copy(t, c, r0);
+  if (rows * chunks > THREADS) {
+    // a thread's next pieces, THREADS apart each; the row and the page of a piece are requested together
+    const unsigned dt = THREADS / chunks, dc = THREADS % chunks;
+    for (;;) {
+      t += dt;
+      c += dc;
+      if (c >= chunks) {
+        c -= chunks;
+        ++t;
+      }
+      if (t >= rows) break;
+      copy(t, c, path[t > 0 ? t - 1 : 0]);
+    }
   }
   __syncthreads();  // every thread has read the old length
   if (tid == 0) cache_lens[s] = used + rows;
@@ -95,10 +113,14 @@ static hs_status kv_commit_impl(const void* k_tree, const void* v_tree, const in
   auto aligned16 = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
   HS_REQUIRE(aligned16(k_tree) && aligned16(v_tree) && aligned16(k_cache) && aligned16(v_cache), HS_ERR_UNSUPPORTED,
              "hs_kv_commit: tensors must be 16-byte aligned");
-  hipLaunchKernelGGL(k_kv_commit, dim3((unsigned)B), dim3(KC_THREADS), 0, static_cast<hipStream_t>(stream),
-                     static_cast<const char*>(k_tree), static_cast<const char*>(v_tree), node_offsets, accept_path,
-                     accept_len, max_depth, static_cast<char*>(k_cache), static_cast<char*>(v_cache), cache_offsets,
-                     block_table, max_blocks, page_tokens, cache_lens, (int)row_bytes);
+#define KC_LAUNCH(T)                                                                                              \
+  hipLaunchKernelGGL(k_kv_commit<T>, dim3((unsigned)B), dim3(T), 0, static_cast<hipStream_t>(stream),               \
+                     static_cast<const char*>(k_tree), static_cast<const char*>(v_tree), node_offsets, accept_path, \
+                     accept_len, max_depth, static_cast<char*>(k_cache), static_cast<char*>(v_cache), cache_offsets, \
+                     block_table, max_blocks, page_tokens, cache_lens, (int)row_bytes)
+  if (B <= KC_MANY) KC_LAUNCH(KC_THREADS);
+  else KC_LAUNCH(KC_THREADS_MANY);
+#undef KC_LAUNCH
   return launch_status("kv commit");
 }
 

@@ -104,6 +104,43 @@ def test_commits_around_the_size_of_a_workgroup(G, hkv, D, depth, page_tokens):
         assert np.array_equal(_bits(got), exp)
 
 
+@pytest.mark.parametrize("page_tokens", [0, 5, 64])
+@pytest.mark.parametrize("hkv,D", [(1, 4), (8, 64), (3, 172)])
+@pytest.mark.parametrize("B", [256, 257])
+def test_commits_around_the_number_of_sequences_for_large_workgroups(G, B, hkv, D, page_tokens):
+    """Either size of a workgroup: chains of up to 40 rows, none accepted to all, rows of one piece to 129, in caches of different used
+    lengths, the last ones of which have no room for the whole path."""
+    import paper_2505_13254_amd as hs
+    from oracle.kv_commit import kv_commit_paged
+    rs = np.random.RandomState(B + D)
+    sizes = rs.randint(1, 42, B)
+    no = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    alen = np.asarray([rs.randint(0, m) for m in sizes], np.int32)
+    path = np.full((B, 41), -1, np.int32)
+    for s in range(B):
+        path[s, :alen[s]] = np.arange(1, alen[s] + 1)
+    lens = rs.randint(0, 70, B).astype(np.int64)
+    kt, vt = (rs.randn(int(no[-1]), hkv, D).astype(np.float32) for _ in range(2))
+    if page_tokens:
+        blocks = 112 // page_tokens  # (so that the longest have too few tokens)
+        table = rs.permutation(B * blocks).astype(np.int32).reshape(B, blocks)
+        lens = np.minimum(lens, blocks * page_tokens)
+        kc, vc = (rs.randn(B * blocks, page_tokens, hkv, D).astype(np.float32) for _ in range(2))
+        want = kv_commit_paged(kt, vt, no, path, alen, kc, vc, table, lens)
+    else:
+        co = np.concatenate([[0], np.cumsum(lens + rs.randint(0, 42, B))]).astype(np.int64)
+        kc, vc = (rs.randn(int(co[-1]), hkv, D).astype(np.float32) for _ in range(2))
+        want = kv_commit(kt, vt, no, path, alen, kc, vc, co, lens)
+    dk, dv, dl = G.dev(kc), G.dev(vc), G.dev(lens)
+    args = [G.dev(kt), G.dev(vt), G.dev(no), G.dev(path), G.dev(alen), dk, dv]
+    if page_tokens:
+        hs.hs_kv_commit_paged(*args, G.dev(table), dl)
+    else:
+        hs.hs_kv_commit(*args, G.dev(co), dl)
+    for got, exp in zip((dk, dv, dl), want):
+        assert np.array_equal(_bits(got), exp)
+
+
 @pytest.mark.parametrize("wid,B", [(1, 3), (2, 4), (5, 100)])
 def test_decoding_loop_on_caches_with_spare_capacity(G, wid, B):
     """Three verify / commit rounds: attention over the used part of each cache region, a random
