@@ -91,6 +91,17 @@ size_t attn_mfma_table_bytes(int max_tree_rows, int64_t NN) {
   return max_tree_rows > MF_MAX_M ? (size_t)NN * (MF_BIG_M / MF_TILE) * 8 : 0;
 }
 
+// The part of tree row i's root path inside its own word of 32 tree rows, as bits, and the first row of the path outside of
+// it (negative: none).  par: the tree's parent pointers in LDS, up: that of row i.
+__device__ __forceinline__ int2 anc_hop(const int* par, int i, int up) {
+  unsigned bits = 1u << (i & 31);
+  for (int j = i;; up = par[j]) {
+    j = up < j ? up : -1;  // (a malformed tree cannot keep the walk from ending)
+    if (j < (i & ~31)) return make_int2((int)bits, j);
+    bits |= 1u << (j & 31);
+  }
+}
+
 // Where a workgroup of a launch with large trees keeps the ancestor bits of its rows: an area for each of its blocks
 // (b: 0 .. 7, by their order in the row group), in it a row of words for each tree row of the block, word q for the tree
 // rows 32 q ..  .  With one query head to a KV head a block is 32 tree rows and eight blocks reach 1024 rows of up to 32
@@ -436,6 +447,9 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // behind it.  Here the waits count the younger loads (wait_vm), and an empty asm statement that
   // "writes" the registers keeps their uses behind the wait.  Lanes without a row of their own load
   // a valid row (the last one; tree row 0) and zero it afterwards.
+  // (first tree row of the block, and how many it has: the same for all lanes)
+  const int blk_node = __builtin_amdgcn_readfirstlane(div_G(row_base < Rh ? row_base : Rh - 1));
+  const int nodes = !wave_active ? 0 : __builtin_amdgcn_readfirstlane(div_G(row_base + 31 < Rh ? row_base + 31 : Rh - 1)) - blk_node + 1;
   int my_parent = 0, far_parent = 0;  // (far: of tree row 512 + tid)
   {
     const int32_t* src = h_parent + (h_tree_shared ? 0 : n0) + (tid < M ? tid : 0);  // (one tree for all entries, or each its own)
@@ -472,25 +486,27 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   }
   wait_vm(NK + first_tile_loads);  // the parent pointers are there (the Q loads and the tiles are younger)
   asm volatile("" : "+v"(my_parent), "+v"(far_parent));
-  const int blk_node = div_G(row_base < Rh ? row_base : Rh - 1);  // first tree row of the block
   if (BIG && last_split) {
-    // A lane walks one tree row's path.  (Two waves that share a block write the same bits: they are cleared before the
-    // barrier and only set behind it.)
+    // A lane walks one tree row's path, a word of 32 tree rows at a time: first every tree row of the entry finds the part of its
+    // path inside its own word.  No walk is longer than 32 steps, twice.  (Row by row up to the root: 8 chains of 1024 rows on 500 tokens, 32
+    // heads on 8, 341 us, now 192; 96 chains of 300 rows on 100 tokens 445, now 295.  With the words read by every workgroup from a table that
+    // a launch ahead makes with the same steps: 187 and 281, but 300 rows on 300 tokens 20.6 us, so 18.1, and 96 trees of 12 levels no less.)
+    // (Two waves that share a block write the same bits: they are cleared before the barrier and only set behind it.)
     unsigned* const area = &anc[anc_at.base];
-    const int last = row_base + 31 < Rh ? row_base + 31 : Rh - 1;
-    const int nodes = wave_active ? div_G(last) - blk_node + 1 : 0;
     for (int i = lane; i < nodes * anc_at.stride; i += 64) area[i] = 0u;
     par_lds[tid] = my_parent;
-    par_lds[tid + MF_THREADS] = far_parent;
+    if (M > MF_THREADS) par_lds[tid + MF_THREADS] = far_parent;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    int2* const hops = reinterpret_cast<int2*>(par_lds + MF_BIG_M);
+    hops[tid] = anc_hop(par_lds, tid, my_parent);
+    if (M > MF_THREADS) hops[tid + MF_THREADS] = anc_hop(par_lds, tid + MF_THREADS, far_parent);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (lane < nodes) {
       unsigned* const row = area + lane * anc_at.stride;
-      const int i = blk_node + lane;
-      atomicOr(row + (i >> 5), 1u << (i & 31));
-      for (int j = i, up = par_lds[i]; up >= 0 && up < j;) {  // (a malformed tree cannot keep the walk from ending)
-        j = up;
-        up = par_lds[j];
-        atomicOr(row + (j >> 5), 1u << (j & 31));
+      for (int j = blk_node + lane; j >= 0;) {
+        const int2 hop = hops[j];
+        row[j >> 5] = (unsigned)hop.x;
+        j = hop.y;
       }
     }
   }
@@ -584,19 +600,23 @@ __global__ __launch_bounds__(MF_THREADS) void k_attn_mfma(AttnArgs a, int n_rg_m
   // split.  Only the blocks from n_plain on need it (the partial prefix tail and the tree part).
   // (the lane's tree row is found again where a tree tile is masked, which the empty statements keep the compiler
   // from doing ahead of the loops: registers for it would be spilled, and read back behind a wait for the tiles)
+  // (large trees: where the words of tree row 0 would be; in a scalar register, as a vector one would be spilled likewise: 200 trees of 260 rows without a
+  // prefix, 8 heads, 212 us, now 180)
+  const int anc_row0 = BIG ? __builtin_amdgcn_readfirstlane(anc_at.base - blk_node * anc_at.stride) : 0;
+  const float inv_G_scalar = BIG ? __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, inv_G))) : 0.f;
   auto tree_row = [&]() {
     unsigned l = ~0u;
     int g = Gh;
     asm volatile("" : "+s"(l), "+s"(g));
     const int r = row_base + (int)(__builtin_amdgcn_mbcnt_hi(l, __builtin_amdgcn_mbcnt_lo(l, 0)) & 31);
-    return (int)(((float)(r < Rh ? r : Rh - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)g));  // (as div_G)
+    return (int)(((float)(r < Rh ? r : Rh - 1) + 0.5f) * (BIG ? inv_G_scalar : __builtin_amdgcn_rcpf((float)g)));  // (as div_G)
   };
   auto mask_block = [&](int blk, floatx16& S) {
     const int t = blk >> 1;
     if (t >= n_ptiles) {
       const int bbase = (t - n_ptiles) * MF_TILE + (blk & 1) * 32;
       unsigned word;
-      if constexpr (BIG) word = (bbase >> 5) < anc_at.stride ? anc[anc_at.base + (tree_row() - blk_node) * anc_at.stride + (bbase >> 5)] : 0u;
+      if constexpr (BIG) word = (bbase >> 5) < anc_at.stride ? anc[anc_row0 + (int)__umul24((unsigned)tree_row(), (unsigned)anc_at.stride) + (bbase >> 5)] : 0u;
       else word = bbase < M ? anc[tree_row() * MF_ANC_STRIDE + (bbase >> 5)] : 0u;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {

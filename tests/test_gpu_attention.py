@@ -236,6 +236,19 @@ def test_large_trees_of_extreme_shape(G, shape):
     assert hs.hs_tree_attention_last_kernel() == 1
 
 
+@pytest.mark.parametrize("shape", ["chain", "one_a_word", "word_fans", "two_chains"])
+@pytest.mark.parametrize("M,hq,hkv", [(257, 4, 4), (512, 8, 2), (513, 8, 2), (1024, 4, 4)])
+def test_root_paths_word_by_word(G, M, hq, hkv, shape):
+    """Trees beyond 256 rows have their paths walked in words of 32 rows: paths through every row, through one row of every word, from
+    a word's first row to the last of the word before, and every other row, with as many rows as threads, one more and the most there can be."""
+    import paper_2505_13254_amd as hs
+    up = {"chain": lambda i: i - 1, "one_a_word": lambda i: max(i - 32, 0), "word_fans": lambda i: i & ~31 if i & 31 else i - 1,
+          "two_chains": lambda i: max(i - 2, 0)}[shape]
+    w = W.small(W.WORKLOADS[2], Hq=hq, Hkv=hkv)
+    _compare(G, _case(w, 15, [[-1] + [up(i) for i in range(1, M)]], [70], "peaky"), "bf16")
+    assert hs.hs_tree_attention_last_kernel() == 1
+
+
 @pytest.mark.parametrize("heads", [4, 48])
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("M", [928, 929, 1023])
