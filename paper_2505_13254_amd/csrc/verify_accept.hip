@@ -37,6 +37,7 @@ constexpr int AC_MAX_KIDS = 256;    // children tried per node
 constexpr int AC_MAX_ROWS = 8192;   // 64-token rows of the CDF search held in LDS (V <= 524288)
 constexpr int BR_SLICES = 64, BR_WGS = 1024;  // workgroups per sequence, and in all, that sum the row a bonus token is drawn from
 constexpr int BR_THREADS = 512;
+constexpr int BR_TRIP_ROWS = BR_THREADS / 64 * 4;  // 64-token rows that such a workgroup sums in a trip
 constexpr int BR_FEW_ROWS = 2048;    // 64-token rows that most vocabularies have (V <= 131072)
 constexpr int BK_NODES = 4096;      // calls with up to this many tree rows get the sorted residual (below)
 constexpr int BK_SLICES = 16;       // vocabulary slices per row, each sorted by itself
@@ -1495,7 +1496,10 @@ extern "C" hs_status hs_verify_accept(const float* target_logits, const float* d
     hs_status r = hs::launch_status("accept (rejection chains)");
     if (r != HS_OK) return r;
     if (chain.bonus_rows != nullptr) {
-      const unsigned slices = (unsigned)std::max(1, std::min(hs::BR_SLICES, hs::BR_WGS / B));
+      // (no fewer rows to a workgroup than its waves take in a trip: more would only queue for the counters, which of short trees share a
+      // cache line.  Trees of the root alone, 64 workgroups each and so: 16 of 32000 tokens 32.4 us, now 23.9, 8 of 8000 22.1 and 17.0; one of 61 rows 34.7 and 34.6)
+      const int trips = ((V + 63) / 64 + hs::BR_TRIP_ROWS - 1) / hs::BR_TRIP_ROWS;
+      const unsigned slices = (unsigned)std::max(1, std::min({hs::BR_SLICES, hs::BR_WGS / B, trips}));
 #define BR_LAUNCH(ROWS)                                                                                                    \
   hipLaunchKernelGGL(hs::k_bonus_rows<ROWS>, dim3(B, slices), dim3(hs::BR_THREADS), 0, st, target_logits, draft_logits, row_stride, \
                      token, parent, node_offsets, NN, V, 1.0f / temperature, uniforms, max_depth, (int)slices, t_arg, t_lz,  \

@@ -427,7 +427,7 @@ def test_single_children_around_the_length_from_which_they_are_sorted(G, V, k):
     test_chains_end_with_their_first_accepted_child(G, V, 1, k)
 
 
-@pytest.mark.parametrize("V,n_kids", [(1, 0), (63, 2), (4097, 0), (131072, 2), (131073, 2), (524288, 0), (524288, 2)])
+@pytest.mark.parametrize("V,n_kids", [(1, 0), (63, 2), (2048, 0), (2049, 2), (4097, 0), (131072, 2), (131073, 2), (524288, 0), (524288, 2)])
 def test_bonus_draws_by_the_last_workgroup(G, V, n_kids):
     """Ratio rule: two sequences with an empty one between them and a spare row behind, whose bonus tokens are drawn by the workgroup
     that finishes the row, from fewer rows of 64 tokens than there are workgroups up to as many as LDS holds; from p itself and,
