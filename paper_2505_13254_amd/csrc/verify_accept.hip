@@ -888,7 +888,7 @@ __device__ __forceinline__ void bonus_row_sums(const RowView& p, const RowView& 
 // ratio rule.  Whether a child is accepted when its turn comes depends on the node, its uniform and the rejections before it, so the
 // chain ends with the first accepted child, usually the first child, before anything but its two probabilities has
 // been looked at.  (With every child rejected in turn, whatever the uniforms, and the rows of p summed here for every row
-// without children: 22.4 us for the 61 rows of 128256 tokens of the 8B step, now 14.1; with all chains run to their ends the same as before.)
+// without children: 22.4 us for the 61 rows of 128256 tokens of the 8B step, now 14.4; with all chains run to their ends the same as before.)
 __global__ __launch_bounds__(AC_THREADS) void k_accept_chain(
     const float* __restrict__ target, const float* __restrict__ draft, int64_t row_stride,
     const int32_t* __restrict__ token, const int32_t* __restrict__ parent, const int32_t* __restrict__ node_offsets,
